@@ -262,7 +262,7 @@ template <int SCHEME, int STAGE, class P, class MU>
 __host__ __device__ inline bool tri_adjoint(const D4 Zc[3], const double nxd[3], const double nyd[3], double gamma,
                                             double igamma, const MU& mu, P kN0, P kN1, P kT,
                                             const Stage2In<P>* s2, Stage2Bar* s2b, double Zb[3][4]) {
-  // ---------------- forward (recomputed, as in tri_compute) ----------------
+  // ---------------- forward (recomputed) ----------------
   Roe<double> q;
   q.g1 = gamma - 1.0;
   const double third = 1.0 / 3.0, igam = igamma;
@@ -329,7 +329,7 @@ __host__ __device__ inline bool tri_adjoint(const D4 Zc[3], const double nxd[3],
         for (int c = 0; c < 4; ++c) Aw[r][c] = A[r][c];
       }
       bool skipped;
-      solve2<double, false>(Aw, e0, e1, x0, x1, skipped);  // IEEE division: the fast one spills here
+      solve2(Aw, e0, e1, x0, x1, skipped);
       singular = singular || skipped;
       for (int r = 0; r < 4; ++r) {
         Ai[r][c2] = x0[r];
@@ -823,7 +823,7 @@ __host__ __device__ inline void adj_star_body(int64_t v, const Dev& d, const Adj
   double acc[4];
   const int32_t deg = d.row[v + 1] - d.row[v];
   const int64_t s0 = vslot(d, v);
-  sum_parts<double>(deg, [&](int32_t j) { return part_load<double>(d, s0 + 64 * (int64_t)j); }, acc);
+  sum_parts(deg, [&](int32_t j) { return part_load<double>(d, s0 + 64 * (int64_t)j); }, acc);
   if (b >= 0) {
     const D4 wn = d.WCn[b];
     for (int k = 0; k < 4; ++k) acc[k] = acc[k] + wn.v[k];

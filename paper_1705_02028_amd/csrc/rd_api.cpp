@@ -8,14 +8,18 @@
 #include <cstring>
 #include <memory>
 #include <string>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
 #include "rd.h"
 #include "rd3_launch.h"
 #include "rd_delaunay.h"
+#include "rd_fp32_launch.h"
 #include "rd_launch.h"
 #include "rd_noalloc.h"
+#include "rd_patch_launch.h"
+#include "rd_patching.h"
 #include "rd_tiling.h"
 
 #define RD_API extern "C" __attribute__((visibility("default")))
@@ -107,12 +111,27 @@ rd_status check_desc(const rd_mesh_desc* d, HostGeom* out) {
 }  // namespace
 
 struct rd_mesh {
-  rd::Dev d;
+  rd::Patches p;             // the step's view, vertices in internal order (patch by patch)
+  rd::Dev d;                 // the second view (the caller's order): residual, adjoint
+  rd::CflPlan cfl;           // its vertex reductions
+  // the FP32 step: buffers allocated on first use, tiles built when first
+  // needed after a tile size was set
+  rd::Dev32 d32;
+  rd::D4* W32 = nullptr;     // its state
+  rd::Tiles tiles;
+  int tiles_of = 0;          // the tile size they are for (0: none)
+  std::vector<void*> tile_allocs;
+  // Where the state is by the host's account: in the FP32 form after FP32
+  // steps (d32.Zf and d.sig belong to it then), else in a patch buffer. Once a
+  // call of this mesh was captured only the device's word (p.cur[0]) counts,
+  // since a replay moves the state without the host's knowledge.
+  bool form32 = false;
+  bool captured = false;
   hipStream_t stream = nullptr;
   int device = 0;
   int ncu = 0;      // compute units of the device
   int lds_max = 0;  // bytes of LDS one workgroup may use on the device
-  // host copies, kept for batches
+  // host copies, kept for batches, for other patches and for the second view
   std::vector<double> x, y, V;
   std::vector<int32_t> tri, wall, row, slot, bc, wv, wptr;
   std::vector<uint8_t> ghost;
@@ -121,13 +140,8 @@ struct rd_mesh {
   double Ldom = 0.0;  // domain size of the Bx sensor
   // device buffers
   std::vector<void*> allocs;
-  rd::CflPlan cfl;
-  void* C[2] = {nullptr, nullptr};
-  void* keepN[2] = {nullptr, nullptr};
-  void* keepT[2] = {nullptr, nullptr};
-  void* dW[2] = {nullptr, nullptr};
-  double* scratch = nullptr;  // [4 * max(nv, nt)]
-  int zprec = -1;             // precision the parameter vectors are valid for
+  double* scratch = nullptr;      // [4 nv] host states pass through it
+  double* phi_scratch = nullptr;  // [4 nt] triangle residuals to a host caller
   // adjoint buffers, allocated on first use
   rd::AdjDev adj;
   rd::D4* adjW = nullptr;     // W^n of the step being reversed
@@ -135,11 +149,13 @@ struct rd_mesh {
   double* adjIn = nullptr;    // [4 nv] host staging: W^n in, then dL/dW^n out
   double* adjOut = nullptr;   // [4 nv] host staging: dL/dW^{n+1} in
   hipEvent_t events[RD_NKERNELS + 1] = {};
-  // tiled form
-  int tile = 0;                     // triangles per tile, 0: two-pass form
-  rd::Tiles tiles;
+  // patches
+  int tile = 0;                     // triangles per tile as set by the caller, 0: the library's choice
+  int32_t max_mesh_patches = 0;     // patches of the mesh (of a batch: the member) that has most
   int64_t tile_info[4] = {0, 0, 0, 0};
-  std::vector<void*> tile_allocs;
+  std::vector<void*> patch_allocs;
+  const int32_t* inv = nullptr;     // [nv] device: internal vertex of each of the caller's
+  int version = 0;                  // counts the changes of what state_of() gives (a batch holds it)
   std::vector<int64_t> voff, toff;  // vertex / triangle ranges of the meshes laid end to end
 };
 
@@ -183,55 +199,11 @@ void free_list(std::vector<void*>& list) {
 }
 
 void free_all(rd_mesh* m) {
+  free_list(m->patch_allocs);
   free_list(m->tile_allocs);
   free_list(m->allocs);
 }
 
-// Buffers of one arithmetic precision, allocated on first use.
-rd_status ensure_prec(rd_mesh* m, int fp32) {
-  if (m->C[fp32]) return RD_OK;
-  const size_t q = fp32 ? sizeof(rd::F4) : sizeof(rd::D4);
-  const int64_t nt = m->d.nt, nv = m->d.nv;
-  char* p = nullptr;
-  rd_status st;
-  if ((st = dalloc(m, &p, q * m->d.ns)) != RD_OK) return st;
-  m->C[fp32] = p;
-  if ((st = dalloc(m, &p, q * 2 * nt)) != RD_OK) return st;
-  m->keepN[fp32] = p;
-  if ((st = dalloc(m, &p, q * nt)) != RD_OK) return st;
-  m->keepT[fp32] = p;
-  if ((st = dalloc(m, &p, q * nv)) != RD_OK) return st;
-  m->dW[fp32] = p;
-  if (fp32 && !m->d.Zf) {
-    rd::F4* z = nullptr;
-    if ((st = dalloc(m, &z, nv)) != RD_OK) return st;
-    m->d.Zf = z;
-  }
-  return RD_OK;
-}
-
-rd::Dev dev_for(const rd_mesh* m, int fp32) {
-  rd::Dev d = m->d;
-  d.C = m->C[fp32];
-  d.keepN = m->keepN[fp32];
-  d.keepT = m->keepT[fp32];
-  d.dW = m->dW[fp32];
-  return d;
-}
-
-// The parameter vectors must be valid for the arithmetic about to run.
-rd_status ensure_z(rd_mesh* m, int fp32) {
-  if (m->zprec == fp32) return RD_OK;
-  HIPCHK(rd::launch_refresh(dev_for(m, fp32), fp32, m->stream));
-  m->zprec = fp32;
-  return RD_OK;
-}
-
-// One step of Sections 3.2-3.4. With cfl > 0 the time step is computed on
-// the device from the state at the start of the step (the stage-1 triangle
-// pass writes l_max lambda_max per corner, two small passes reduce it);
-// otherwise it is already in d.dt. With `ev` (RD_NKERNELS + 1 events) an
-// event is recorded before every kernel slot and after the last.
 struct DeviceGuard {
   int prev = -1;
   explicit DeviceGuard(int dev) {
@@ -244,98 +216,277 @@ struct DeviceGuard {
   }
 };
 
-rd_status run_step_tiled(rd_mesh* m, int scheme, int time, int fp32, double cfl, hipEvent_t* ev);
+// One step of Sections 3.2-3.4. With cfl > 0 the time step is computed on
+// the device from the state at the start of the step: the stage-1 pass leaves
+// every patch's smallest bound, and the pass that needs dt takes their
+// minimum itself where no mesh has more than kDirectPatches patches (one load
+// per thread of the workgroup), else one workgroup per mesh reduces them
+// first (one more launch, against more than kDirectPatches loads by every
+// workgroup). Otherwise dt is given. With `ev` (RD_NKERNELS + 1 events) an
+// event is recorded before every kernel slot and after the last.
+constexpr int32_t kDirectPatches = rd::kPatchThreads;
 
-rd_status run_step(rd_mesh* m, int scheme, int time, int fp32, double cfl, hipEvent_t* ev = nullptr) {
-  if (m->tile > 0) return run_step_tiled(m, scheme, time, fp32, cfl, ev);
-  const rd::Dev d = dev_for(m, fp32);
+rd_status run_step32(rd_mesh* m, int scheme, int time, double cfl, double dt, hipEvent_t* ev);
+
+rd_status run_step(rd_mesh* m, int scheme, int time, int fp32, double cfl, double dt, hipEvent_t* ev = nullptr) {
+  if (fp32) return run_step32(m, scheme, time, cfl, dt, ev);
+  rd::Patches p = m->p;
   hipStream_t s = m->stream;
   auto mark = [&](int k) -> hipError_t { return ev ? hipEventRecord(ev[k], s) : hipSuccess; };
   const bool with_cfl = cfl > 0.0, bx = scheme == RD_BX;
+  p.dt_val = with_cfl ? 0.0 : dt;
   HIPCHK(mark(RD_K_WALL1));
-  HIPCHK(rd::launch_wall(d, false, s));
   HIPCHK(mark(RD_K_TRI1));
-  if (bx) HIPCHK(rd::launch_vrange(d, m->cfl, 0, s));
-  HIPCHK(rd::launch_tri(d, fp32, scheme, 1, time == RD_RK2, with_cfl, s));
+  if (bx) HIPCHK(rd::launch_patch_vrange(p, false, s));
+  HIPCHK(rd::launch_patch(p, scheme, 1, with_cfl, s));
   HIPCHK(mark(RD_K_SHARED1));
   HIPCHK(mark(RD_K_CFL));
   if (with_cfl) {
-    HIPCHK(rd::launch_cfl_part(d, m->cfl, cfl, 1, s, fp32));
-    HIPCHK(rd::launch_cfl_part(d, m->cfl, cfl, 2, s));
+    if (m->max_mesh_patches <= kDirectPatches && !bx) p.cfl = cfl;
+    else HIPCHK(rd::launch_patch_dt(p, cfl, s));
   }
   HIPCHK(mark(RD_K_GATHER1));
-  HIPCHK(rd::launch_gather(d, fp32, time == RD_RK2 ? rd::G_STAGE1 : rd::G_EULER, nullptr, s));
+  if (time != RD_RK2) HIPCHK(rd::launch_patch_euler(p, s));
   HIPCHK(mark(RD_K_WALL2));
+  HIPCHK(mark(RD_K_TRI2));
   if (time == RD_RK2) {
-    HIPCHK(rd::launch_wall(d, true, s));
-    HIPCHK(mark(RD_K_TRI2));
-    if (bx) HIPCHK(rd::launch_vrange(d, m->cfl, 1, s));
-    HIPCHK(rd::launch_tri(d, fp32, scheme, 2, false, false, s));
-    HIPCHK(mark(RD_K_GATHER2));
-    HIPCHK(rd::launch_gather(d, fp32, rd::G_STAGE2, nullptr, s));
-  } else {
-    HIPCHK(mark(RD_K_TRI2));
-    HIPCHK(mark(RD_K_GATHER2));
+    if (bx) HIPCHK(rd::launch_patch_vrange(p, true, s));
+    HIPCHK(rd::launch_patch(p, scheme, 2, false, s));
   }
+  HIPCHK(mark(RD_K_GATHER2));
   HIPCHK(mark(RD_NKERNELS));
-  m->zprec = fp32;
   return RD_OK;
 }
 
-// The tiled form of the same step: the tile pass finishes interior vertices
+rd::Dev view32(const rd_mesh* m) {
+  rd::Dev d = m->d;
+  d.W = m->W32;
+  return d;
+}
+
+// The tiled form of the FP32 step: the tile pass finishes interior vertices
 // (stage 1: their residual R1 and CFL bound; stage 2: their new state), the
 // shared pass the rest. Stage 1 stores R1 only; W* is rebuilt from it where
 // needed, after dt is known.
-rd_status run_step_tiled(rd_mesh* m, int scheme, int time, int fp32, double cfl, hipEvent_t* ev) {
-  const rd::Dev d = dev_for(m, fp32);
+rd_status run_step32_tiled(rd_mesh* m, int scheme, int time, double cfl, double dt, hipEvent_t* ev) {
+  const rd::Dev d = view32(m);
   const rd::Tiles& tl = m->tiles;
+  rd::Dev32 h = m->d32;
+  h.slump = m->p.slump;
   hipStream_t s = m->stream;
   auto mark = [&](int k) -> hipError_t { return ev ? hipEventRecord(ev[k], s) : hipSuccess; };
   const bool with_cfl = cfl > 0.0, rk2 = time == RD_RK2, bx = scheme == RD_BX;
   HIPCHK(mark(RD_K_WALL1));
+  if (!with_cfl) HIPCHK(rd::launch_set_scalar(d.dt, dt, s));
   HIPCHK(rd::launch_wall(d, false, s));
   HIPCHK(mark(RD_K_TRI1));
-  if (bx) HIPCHK(rd::launch_vrange(d, m->cfl, 0, s));
-  HIPCHK(rd::launch_tile(d, tl, fp32, scheme, 1, rk2, with_cfl, s));
+  if (bx) HIPCHK(rd::launch_vrange32(d, m->cfl, false, s));
+  HIPCHK(rd::launch_tile(d, h, tl, scheme, 1, rk2, with_cfl, s));
   HIPCHK(mark(RD_K_SHARED1));
-  HIPCHK(rd::launch_shared(d, tl, fp32, 1, with_cfl, s));
+  HIPCHK(rd::launch_shared(d, h, tl, 1, with_cfl, s));
   HIPCHK(mark(RD_K_CFL));
-  if (with_cfl) {
-    HIPCHK(rd::launch_cfl_part(d, m->cfl, cfl, 3, s));
-    HIPCHK(rd::launch_cfl_part(d, m->cfl, cfl, 2, s));
-  }
+  if (with_cfl) HIPCHK(rd::launch_tile_cfl(d, h, m->cfl, cfl, s));
   HIPCHK(mark(RD_K_GATHER1));
-  if (!rk2) HIPCHK(rd::launch_euler_apply(d, fp32, s));
+  if (!rk2) HIPCHK(rd::launch_euler_apply(d, h, s));
   HIPCHK(mark(RD_K_WALL2));
-  if (rk2) HIPCHK(rd::launch_wall(d, true, s, true));
+  if (rk2) HIPCHK(rd::launch_tile_wall2(d, h, s));
   HIPCHK(mark(RD_K_TRI2));
-  if (rk2 && bx) HIPCHK(rd::launch_vrange(d, m->cfl, 2, s));
-  if (rk2) HIPCHK(rd::launch_tile(d, tl, fp32, scheme, 2, false, false, s));
+  if (rk2 && bx) HIPCHK(rd::launch_tile_vrange(d, h, m->cfl, s));
+  if (rk2) HIPCHK(rd::launch_tile(d, h, tl, scheme, 2, false, false, s));
   HIPCHK(mark(RD_K_GATHER2));
-  if (rk2) HIPCHK(rd::launch_shared(d, tl, fp32, 2, false, s));
+  if (rk2) HIPCHK(rd::launch_shared(d, h, tl, 2, false, s));
   HIPCHK(mark(RD_NKERNELS));
-  m->zprec = fp32;
   return RD_OK;
 }
 
-// Builds (or drops, tt = 0) the tiles of a mesh.
-rd_status set_tile(rd_mesh* m, int tt) {
-  if (tt == m->tile) return RD_OK;
-  if (tt != 0 && (tt < 32 || tt > 1024)) return fail(RD_EINVAL, "tile size must be 0 or in [32, 1024]");
-  DeviceGuard g(m->device);
-  HIPCHK(hipStreamSynchronize(m->stream));
-  if (tt == 0) {
-    free_list(m->tile_allocs);
-    m->tiles = rd::Tiles();
-    m->tile = 0;
-    for (int64_t& x : m->tile_info) x = 0;
-    return RD_OK;
+// The step with FP32 distribution, two passes over the second view.
+rd_status run_step32(rd_mesh* m, int scheme, int time, double cfl, double dt, hipEvent_t* ev) {
+  if (m->tiles.ntiles > 0) return run_step32_tiled(m, scheme, time, cfl, dt, ev);
+  const rd::Dev d = view32(m);
+  rd::Dev32 h = m->d32;
+  h.slump = m->p.slump;
+  hipStream_t s = m->stream;
+  auto mark = [&](int k) -> hipError_t { return ev ? hipEventRecord(ev[k], s) : hipSuccess; };
+  const bool with_cfl = cfl > 0.0, bx = scheme == RD_BX, rk2 = time == RD_RK2;
+  HIPCHK(mark(RD_K_WALL1));
+  if (!with_cfl) HIPCHK(rd::launch_set_scalar(d.dt, dt, s));
+  HIPCHK(rd::launch_wall(d, false, s));
+  HIPCHK(mark(RD_K_TRI1));
+  if (bx) HIPCHK(rd::launch_vrange32(d, m->cfl, false, s));
+  HIPCHK(rd::launch_tri32(d, h, scheme, 1, rk2, with_cfl, s));
+  HIPCHK(mark(RD_K_SHARED1));
+  HIPCHK(mark(RD_K_CFL));
+  if (with_cfl) HIPCHK(rd::launch_cfl32(d, m->cfl, cfl, s));
+  HIPCHK(mark(RD_K_GATHER1));
+  HIPCHK(rd::launch_gather32(d, h, rk2 ? rd::G_STAGE1 : rd::G_EULER, s));
+  HIPCHK(mark(RD_K_WALL2));
+  if (rk2) HIPCHK(rd::launch_wall(d, true, s));
+  HIPCHK(mark(RD_K_TRI2));
+  if (rk2) {
+    if (bx) HIPCHK(rd::launch_vrange32(d, m->cfl, true, s));
+    HIPCHK(rd::launch_tri32(d, h, scheme, 2, false, false, s));
   }
+  HIPCHK(mark(RD_K_GATHER2));
+  if (rk2) HIPCHK(rd::launch_gather32(d, h, rd::G_STAGE2, s));
+  HIPCHK(mark(RD_NKERNELS));
+  return RD_OK;
+}
+
+// The host side of a call may run out of memory (or of threads): no C++
+// exception crosses the ABI.
+template <class F>
+rd_status guarded(F f) {
+  try {
+    return f();
+  } catch (const std::bad_alloc&) {
+    return fail(RD_ENOMEM, "host allocation failed");
+  } catch (const std::exception& e) {
+    return fail(RD_ENOMEM, std::string("host: ") + e.what());
+  }
+}
+
+rd::State state_of(const rd_mesh* m) {
+  return rd::State{{m->p.W[0], m->p.W[1]}, m->p.cur, m->inv, m->W32};
+}
+
+int host_threads() {
+  const unsigned n = std::thread::hardware_concurrency();
+  return (int)std::min(8u, std::max(1u, n));
+}
+
+// f(i) for i = 0 .. n - 1, on a few threads when there is enough to do.
+template <class F>
+void parallel_for(int64_t n, const F& f) {
+  const int w = n < 100000 ? 1 : host_threads();
+  rd::run_workers(w, [&](int q) {
+    for (int64_t i = n * q / w; i < n * (q + 1) / w; ++i) f(i);
+  });
+}
+
+// The tables of the second view of the mesh and the blocks of its vertex
+// reductions.
+rd_status build_view(rd_mesh* m) {
+  rd::Dev& d = m->d;
+  rd::CflPlan& c = m->cfl;
+  std::vector<void*>& list = m->allocs;
+  const int64_t nv = m->d.nv, nt = m->d.nt;
+  d.flag = m->p.flag;
+  d.dt = m->p.dt;
+  d.vr = m->p.vr;
+  d.gamma = m->gamma;
+  d.igamma = 1.0 / m->gamma;
+  d.gas = m->p.gas;
+  d.px = m->px;
+  d.py = m->py;
+  d.hpx = m->p.hpx;
+  d.hpy = m->p.hpy;
+  d.nwv = (int32_t)m->wv.size();
+  // sliced part layout: 64-vertex slices, each as wide as its largest
+  // degree; the j-th part of vertex v sits at sbase[v / 64] + v % 64 + 64 j
+  std::vector<int32_t> sbase((nv + 63) / 64);
+  int64_t base = 0;
+  for (int64_t g0 = 0; g0 < nv; g0 += 64) {
+    int32_t width = 0;
+    for (int64_t v = g0; v < std::min<int64_t>(g0 + 64, nv); ++v) width = std::max(width, m->row[v + 1] - m->row[v]);
+    sbase[g0 / 64] = (int32_t)base;
+    base += 64 * (int64_t)width;
+    if (base >= (int64_t(1) << 31)) return fail(RD_EINVAL, "mesh too large for 32-bit part slots");
+  }
+  d.ns = base;
+  std::vector<double2> xy(nv);
+  std::vector<int32_t> tv(3 * nt), vtri(base, -1), vmesh, tmesh;
+  std::vector<uint32_t> rk(nt);
+  // the triangle of every part slot
+  parallel_for(nv, [&](int64_t v) {
+    xy[v] = make_double2(m->x[v], m->y[v]);
+    for (int32_t j = 0; j < m->row[v + 1] - m->row[v]; ++j)
+      vtri[sbase[v / 64] + v % 64 + 64 * (int64_t)j] = m->slot[m->row[v] + j] / 3;
+  });
+  // corners, and the rank of each triangle among the triangles of each of its
+  // corner vertices (10 bits per corner)
+  parallel_for(nt, [&](int64_t t) {
+    uint32_t r = 0;
+    for (int k = 0; k < 3; ++k) {
+      const int32_t v = m->tri[3 * t + k];
+      tv[k * nt + t] = v;
+      const int32_t* b = &m->slot[m->row[v]];
+      uint32_t j = 0;
+      while (b[j] != 3 * t + k) ++j;
+      r |= j << (10 * k);
+    }
+    rk[t] = r;
+  });
+  const size_t nmesh = m->voff.size() - 1;
+  if (nmesh > 1) {
+    vmesh.resize(nv);
+    tmesh.resize(nt);
+    for (size_t k = 0; k < nmesh; ++k) {
+      std::fill(vmesh.begin() + m->voff[k], vmesh.begin() + m->voff[k + 1], (int32_t)k);
+      std::fill(tmesh.begin() + m->toff[k], tmesh.begin() + m->toff[k + 1], (int32_t)k);
+    }
+  }
+  // blocks of the CFL reduction, none straddling two meshes
+  std::vector<int32_t> v0, v1, b0{0};
+  for (size_t k = 0; k < nmesh; ++k) {
+    for (int64_t v = m->voff[k]; v < m->voff[k + 1]; v += rd::kCflSpan) {
+      v0.push_back((int32_t)v);
+      v1.push_back((int32_t)std::min<int64_t>(v + rd::kCflSpan, m->voff[k + 1]));
+    }
+    b0.push_back((int32_t)v0.size());
+  }
+  double2* pxy;
+  double *pV, *part, *vpart;
+  int32_t *prow, *ptv, *psbase, *pvtri, *pbc, *pwv, *pwptr, *pvm, *ptm, *pv0, *pv1, *pb0;
+  uint32_t* prk;
+  rd::WallEnt* pwent;
+  rd_status st;
+  if ((st = upload_in(list, &pxy, xy)) || (st = upload_in(list, &pV, m->V)) || (st = upload_in(list, &prow, m->row)) ||
+      (st = upload_in(list, &ptv, tv)) || (st = upload_in(list, &prk, rk)) || (st = upload_in(list, &psbase, sbase)) ||
+      (st = upload_in(list, &pvtri, vtri)) || (st = upload_in(list, &pbc, m->bc)) || (st = upload_in(list, &pwv, m->wv)) ||
+      (st = upload_in(list, &pwptr, m->wptr)) || (st = upload_in(list, &pwent, m->went)) ||
+      (st = upload_in(list, &pvm, vmesh)) || (st = upload_in(list, &ptm, tmesh)) || (st = upload_in(list, &pv0, v0)) ||
+      (st = upload_in(list, &pv1, v1)) || (st = upload_in(list, &pb0, b0)) ||
+      (st = dalloc_in(list, &part, v0.size())) || (st = dalloc_in(list, &vpart, 2 * v0.size())))
+    return st;
+  d.xy = pxy;
+  d.V = pV;
+  d.row = prow;
+  d.tv = ptv;
+  d.rk = prk;
+  d.sbase = psbase;
+  d.vtri = pvtri;
+  d.bc = m->bc.empty() ? nullptr : pbc;
+  d.wv = pwv;
+  d.wptr = pwptr;
+  d.went = pwent;
+  d.vmesh = vmesh.empty() ? nullptr : pvm;
+  d.tmesh = tmesh.empty() ? nullptr : ptm;
+  c.nblocks = (int32_t)v0.size();
+  c.nmesh = (int32_t)nmesh;
+  c.blk_v0 = pv0;
+  c.blk_v1 = pv1;
+  c.mesh_b0 = pb0;
+  c.part = part;
+  c.vpart = vpart;
+  return RD_OK;
+}
+
+void note_capture(rd_mesh* m) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(m->stream, &c) != hipSuccess) (void)hipGetLastError();
+  else m->captured = m->captured || c != hipStreamCaptureStatusNone;
+}
+
+// The tiles of the tile size in use; none where no tiles of that size can be
+// built or they need more LDS than a workgroup may use (the two passes serve).
+rd_status build_tiles(rd_mesh* m) {
   const rd::Dev& d = m->d;
   rd::TilePlan P;
   const std::string why = rd::build_tile_plan(d.nv, d.nt, m->tri.data(), m->x.data(), m->y.data(), m->px, m->py,
-                                              m->row.data(), m->slot.data(), m->voff, m->toff, tt, P);
-  if (!why.empty()) return fail(RD_EINVAL, why);
+                                              m->row.data(), m->slot.data(), m->voff, m->toff, m->tile, P);
+  m->tiles_of = m->tile;
+  m->tiles = rd::Tiles();
+  if (!why.empty()) return RD_OK;
   rd::Tiles tl;
   tl.ntiles = P.ntiles;
   tl.tt = P.tt;
@@ -344,14 +495,13 @@ rd_status set_tile(rd_mesh* m, int tt) {
   tl.max_slots = P.max_slots;
   tl.nsv = (int64_t)P.sv.size();
   tl.nss = P.nss;
-  const size_t need = std::max(rd::tile_lds_bytes(tl, 0, 1, true), rd::tile_lds_bytes(tl, 0, 2, false));
-  if (need > (size_t)m->lds_max)
-    return fail(RD_EUNSUPPORTED, "tiles of " + std::to_string(tt) + " triangles need " + std::to_string(need) +
-                                     " bytes of LDS");
+  const size_t need = std::max(rd::tile_lds_bytes(tl, 1, true), rd::tile_lds_bytes(tl, 2, false));
+  if (need > (size_t)m->lds_max) return RD_OK;
+  m->tiles_of = 0;  // until they are there
   std::vector<void*> list;
   int32_t *tbeg, *vbeg, *nvi, *lpb, *lp, *tvl, *dst, *tm, *sv, *ssbeg;
   uint16_t* lv;
-  rd::D4* cs;
+  rd::F4* cs;
   double* lams;
   rd_status st;
   if ((st = upload_in(list, &tbeg, P.tbeg)) || (st = upload_in(list, &vbeg, P.vbeg)) ||
@@ -364,15 +514,15 @@ rd_status set_tile(rd_mesh* m, int tt) {
     free_list(list);
     return st;
   }
-  if (!m->d.R1) {
+  if (!m->d32.R1) {
     rd::D4* r1;
     double* cv;
     if ((st = dalloc(m, &r1, d.nv)) || (st = dalloc(m, &cv, d.nv))) {
       free_list(list);
       return st;
     }
-    m->d.R1 = r1;
-    m->d.cflv = cv;
+    m->d32.R1 = r1;
+    m->d32.cflv = cv;
   }
   tl.tbeg = tbeg;
   tl.vbeg = vbeg;
@@ -387,17 +537,221 @@ rd_status set_tile(rd_mesh* m, int tt) {
   tl.ssbeg = ssbeg;
   tl.Cs = cs;
   tl.lams = lams;
-  free_list(m->tile_allocs);
   m->tile_allocs.swap(list);
   m->tiles = tl;
-  m->tile = tt;
-  int64_t nsc = 0;
-  for (int32_t v : P.sv) nsc += m->row[v + 1] - m->row[v];
-  m->tile_info[0] = P.ntiles;
-  m->tile_info[1] = (int64_t)P.tvl.size();
-  m->tile_info[2] = (int64_t)P.sv.size();
-  m->tile_info[3] = nsc;
+  m->tiles_of = m->tile;
   return RD_OK;
+}
+
+// The FP32 step's buffers and tiles, on first use.
+rd_status buffers32(rd_mesh* m) {
+  rd::Dev32& h = m->d32;
+  const int64_t nv = m->d.nv, nt = m->d.nt;
+  rd_status st;
+  if (!h.Zf) {
+    rd::Dev32 n;
+    rd::F4 *c, *kn, *kt;
+    rd::D4* W;
+    float* lam;
+    double* sig;
+    if ((st = dalloc(m, &n.Zf, nv)) || (st = dalloc(m, &n.dW, nv)) || (st = dalloc(m, &kn, 2 * nt)) ||
+        (st = dalloc(m, &kt, nt)) || (st = dalloc(m, &lam, nt)) || (st = dalloc(m, &sig, nv)) ||
+        (st = dalloc(m, &W, nv)) || (st = dalloc(m, &c, m->d.ns)))
+      return st;
+    n.C = c;
+    n.keepN = kn;
+    n.keepT = kt;
+    m->d.lam = lam;
+    m->d.sig = sig;
+    m->W32 = W;
+    h = n;
+    ++m->version;
+  }
+  return m->tile > 0 && m->tiles_of != m->tile ? build_tiles(m) : RD_OK;
+}
+
+// The state into the form the steps about to run use: the FP32 form with its
+// parameter vectors, or a patch buffer. One pass, where the last
+// steps were of the other precision; after a capture the device decides.
+rd_status enter(rd_mesh* m, int fp32) {
+  rd_status st;
+  note_capture(m);
+  if (fp32 && (st = guarded([&] { return buffers32(m); })) != RD_OK) return st;
+  if (!m->captured && (fp32 != 0) == m->form32) return RD_OK;
+  hipStream_t s = m->stream;
+  if (fp32) {
+    HIPCHK(rd::launch_enter32(view32(m), m->d32, state_of(m), s));
+    HIPCHK(rd::launch_set_int(m->p.cur, rd::kForm32, s));
+  } else {
+    HIPCHK(rd::launch_patch_enter(m->p, state_of(m), s));
+  }
+  m->form32 = fp32 != 0;
+  return RD_OK;
+}
+
+// Owned vertices per patch the library asks for: 215 (about 490 triangles, the
+// 512 threads of a workgroup nearly full) on meshes with enough vertices to
+// give every compute unit a patch, fewer on smaller ones so that the step is
+// spread over the device, down to 32 (below, the triangles shared with
+// neighbouring patches outnumber the patch's own).
+int patch_own(int64_t nv, int ncu) {
+  return (int)std::min<int64_t>(215, std::max<int64_t>(32, nv / std::max(1, ncu)));
+}
+
+// Builds the patches for tile size tt (0: the library's choice) and moves the
+// state to the new order.
+rd_status build_patches(rd_mesh* m, int tt) {
+  rd::Patches& q = m->p;
+  const int64_t nv = q.nv, nt = m->d.nt;
+  rd::PatchPlan P;
+  rd::PatchInput in;
+  in.nv = nv;
+  in.nt = nt;
+  in.tri = m->tri.data();
+  in.x = m->x.data();
+  in.y = m->y.data();
+  in.hpx = q.hpx;
+  in.hpy = q.hpy;
+  in.row = m->row.data();
+  in.slot = m->slot.data();
+  in.voff = &m->voff;
+  in.toff = &m->toff;
+  in.tile_tri = tt;
+  in.own = patch_own(nv, m->ncu);
+  in.threads = host_threads();
+  std::string why = rd::build_patch_plan(in, P);
+  // a vertex in more triangles than a workgroup has threads: its patch keeps
+  // vertex records and parts apart in LDS, so the other patches are kept small
+  if (why.empty() && P.max_tri > rd::kPatchThreads) {
+    in.max_tri = rd::kPatchThreads / 2;
+    why = rd::build_patch_plan(in, P);
+  }
+  if (!why.empty()) return fail(RD_EINVAL, why);
+  rd::Patches p = q;
+  p.ptn = (int64_t)P.tid.size();
+  p.npatch = P.npatch;
+  p.max_lv = P.max_lv;
+  p.max_slots = P.max_slots;
+  p.max_tri = P.max_tri;
+  p.threads = std::min(rd::kPatchThreads, (P.max_tri + 63) / 64 * 64);
+  const size_t need = std::max(rd::patch_lds_bytes(p, 1, true), rd::patch_lds_bytes(p, 2, false));
+  if (need > (size_t)m->lds_max)
+    return fail(RD_EUNSUPPORTED, "patches of this mesh need " + std::to_string(need) + " bytes of LDS");
+  // descriptors, geometry and boundary lists in internal order
+  std::vector<int32_t> inv(nv);
+  for (int64_t i = 0; i < nv; ++i) inv[P.order[i]] = (int32_t)i;
+  std::vector<rd::PatchDesc> desc(P.npatch);
+  std::vector<double2> xy(nv + P.halo.size());
+  std::vector<double> V(nv);
+  size_t at = 0;
+  for (int32_t k = 0; k < P.npatch; ++k) {
+    rd::PatchDesc& d = desc[k];
+    d = rd::PatchDesc();
+    d.v0 = P.vbeg[k];
+    d.own = P.vbeg[k + 1] - d.v0;
+    d.h0 = P.hbeg[k];
+    d.nlv = d.own + P.hbeg[k + 1] - d.h0;
+    d.t0 = P.tbeg[k];
+    d.nt = P.tbeg[k + 1] - d.t0;
+    d.xy0 = (int32_t)at;
+    d.mesh = P.pmesh[k];
+    d.seam = P.seam[k];
+    d.jb = P.jbeg[k];
+    for (int j = 0; j < 8; ++j) d.jb8[j] = (uint16_t)(j < P.jbeg[k + 1] - P.jbeg[k] ? P.jb[P.jbeg[k] + j] : 0);
+    for (int32_t l = 0; l < d.nlv; ++l) {
+      const int32_t v = P.order[l < d.own ? d.v0 + l : P.halo[d.h0 + l - d.own]];
+      xy[at++] = make_double2(m->x[v], m->y[v]);
+    }
+  }
+  for (int64_t i = 0; i < nv; ++i) V[i] = m->ghost[P.order[i]] ? -m->V[P.order[i]] : m->V[P.order[i]];
+  std::vector<int32_t> wb;
+  std::vector<rd::WallEnt> went = m->went;
+  if (!m->wv.empty()) {
+    wb.assign(nv, -1);
+    for (size_t b = 0; b < m->wv.size(); ++b)
+      if (!m->ghost[m->wv[b]]) wb[inv[m->wv[b]]] = (int32_t)b;
+    for (auto& e : went) e.other = inv[e.other];
+  }
+  std::vector<void*> list;
+  rd_status st;
+  int32_t *halo, *mbeg, *dinv, *dwb, *dwptr, *jb;
+  rd::PatchDesc* ddesc;
+  uint32_t* tri;
+  uint16_t* deg;
+  double2* dxy;
+  double *dV, *pmin, *vpart;
+  rd::WallEnt* dwent;
+  if ((st = upload_in(list, &ddesc, desc)) || (st = upload_in(list, &halo, P.halo)) ||
+      (st = upload_in(list, &mbeg, P.mbeg)) ||
+      (st = upload_in(list, &dinv, inv)) || (st = upload_in(list, &tri, P.tri)) ||
+      (st = upload_in(list, &deg, P.deg)) || (st = upload_in(list, &jb, P.jb)) || (st = upload_in(list, &dxy, xy)) ||
+      (st = upload_in(list, &dV, V)) || (st = dalloc_in(list, &pmin, P.npatch)) ||
+      (st = dalloc_in(list, &vpart, 2 * (size_t)P.npatch)) || (st = upload_in(list, &dwb, wb)) ||
+      (st = upload_in(list, &dwptr, m->wptr)) || (st = upload_in(list, &dwent, went))) {
+    free_list(list);
+    return st;
+  }
+  p.desc = ddesc;
+  p.halo = halo;
+  p.mbeg = mbeg;
+  p.nmesh = (int32_t)m->voff.size() - 1;
+  p.tri = tri;
+  p.deg = deg;
+  p.jb = jb;
+  p.xy = dxy;
+  p.V = dV;
+  p.wb = wb.empty() ? nullptr : dwb;
+  p.wptr = dwptr;
+  p.went = dwent;
+  p.pmin = pmin;
+  p.vpart = vpart;
+  if (m->inv) {  // the state moves through the caller's order
+    hipError_t e = rd::launch_state_get4(state_of(m), nv, m->d.W, m->stream);
+    if (e == hipSuccess) e = rd::launch_patch_set4(p, dinv, m->d.W, m->stream);
+    if (e == hipSuccess) e = rd::launch_set_int(p.cur, 0, m->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
+    if (e != hipSuccess) {
+      free_list(list);
+      return fail(RD_EDEVICE, std::string("moving the state: ") + hipGetErrorString(e));
+    }
+    m->form32 = false;
+  }
+  if (m->captured) {  // a captured graph may still read the old tables
+    m->allocs.insert(m->allocs.end(), m->patch_allocs.begin(), m->patch_allocs.end());
+    m->allocs.insert(m->allocs.end(), m->tile_allocs.begin(), m->tile_allocs.end());
+    m->patch_allocs.clear();
+    m->tile_allocs.clear();
+  }
+  free_list(m->patch_allocs);
+  m->patch_allocs.swap(list);
+  m->p = p;
+  m->inv = dinv;
+  ++m->version;
+  m->tile = tt;
+  // the FP32 step's tiles are built when it next runs, or now where it has run
+  // (a capture may record the next one)
+  free_list(m->tile_allocs);
+  m->tiles = rd::Tiles();
+  m->tiles_of = 0;
+  m->max_mesh_patches = 0;
+  for (size_t k = 0; k + 1 < P.mbeg.size(); ++k)
+    m->max_mesh_patches = std::max(m->max_mesh_patches, P.mbeg[k + 1] - P.mbeg[k]);
+  m->tile_info[0] = tt > 0 ? P.ntiles : 0;
+  m->tile_info[1] = tt > 0 ? nv + (int64_t)P.halo.size() : 0;
+  m->tile_info[2] = tt > 0 ? P.shared_vertices : 0;
+  m->tile_info[3] = tt > 0 ? P.shared_parts : 0;
+  return RD_OK;
+}
+
+rd_status set_tile(rd_mesh* m, int tt) {
+  if (tt == m->tile) return RD_OK;
+  if (tt != 0 && (tt < 32 || tt > 1024)) return fail(RD_EINVAL, "tile size must be 0 or in [32, 1024]");
+  DeviceGuard g(m->device);
+  HIPCHK(hipStreamSynchronize(m->stream));
+  return guarded([&] {
+    const rd_status st = build_patches(m, tt);
+    return st == RD_OK && m->d32.Zf ? buffers32(m) : st;
+  });
 }
 
 rd_status check_step_args(int scheme, int time, int precision) {
@@ -419,21 +773,30 @@ bool physical(const double* W, int64_t nv, int64_t i, double gamma) {
 
 RD_API rd_status rd_mesh_validate(const rd_mesh_desc* desc) { return check_desc(desc, nullptr); }
 
-RD_API rd_status rd_mesh_create(const rd_mesh_desc* desc, void* stream, rd_mesh** out) {
-  if (!out) return fail(RD_EINVAL, "null output pointer");
-  *out = nullptr;
+namespace {
+
+// A mesh of `voff.size() - 1` meshes laid end to end (vertex and triangle
+// ranges voff, toff; empty: one mesh), with the domain size of each for the
+// Bx sensor (empty: from the description).
+rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::vector<int64_t>& voff,
+                      const std::vector<int64_t>& toff, const std::vector<double>& Ldom, rd_mesh** out) {
   HostGeom geo;
   rd_status st = check_desc(desc, &geo);
   if (st != RD_OK) return st;
-  rd_mesh* m = new rd_mesh();
-  m->stream = static_cast<hipStream_t>(stream);
+  struct Drop {
+    void operator()(rd_mesh* m) const {
+      free_all(m);
+      delete m;
+    }
+  };
+  std::unique_ptr<rd_mesh, Drop> owner(new rd_mesh());
+  rd_mesh* m = owner.get();
+  m->stream = stream;
   if (hipGetDevice(&m->device) != hipSuccess ||
       hipDeviceGetAttribute(&m->ncu, hipDeviceAttributeMultiprocessorCount, m->device) != hipSuccess ||
       hipDeviceGetAttribute(&m->lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, m->device) != hipSuccess ||
-      m->ncu <= 0 || m->lds_max <= 0) {
-    delete m;
+      m->ncu <= 0 || m->lds_max <= 0)
     return fail(RD_EDEVICE, "no HIP device");
-  }
   const int64_t nv = desc->n_vertices, nt = desc->n_triangles;
   m->x.assign(desc->x, desc->x + nv);
   m->y.assign(desc->y, desc->y + nv);
@@ -446,8 +809,8 @@ RD_API rd_status rd_mesh_create(const rd_mesh_desc* desc, void* stream, rd_mesh*
   m->py = desc->period_y;
   m->gamma = desc->gamma;
   m->V.swap(geo.V);
-  m->voff = {0, nv};
-  m->toff = {0, nt};
+  m->voff = voff.empty() ? std::vector<int64_t>{0, nv} : voff;
+  m->toff = toff.empty() ? std::vector<int64_t>{0, nt} : toff;
 
   // vertex -> (triangle, corner) CSR, ascending triangle order in every row
   m->row.assign(nv + 1, 0);
@@ -464,24 +827,29 @@ RD_API rd_status rd_mesh_create(const rd_mesh_desc* desc, void* stream, rd_mesh*
   has_bc |= !m->wall.empty();
   if (has_bc) {
     m->bc.assign(nv, -1);
-    std::vector<std::vector<rd::WallEnt>> per(nv);
+    // incidences per vertex, ascending edge id
     const int64_t nw = (int64_t)m->wall.size() / 2;
-    for (int64_t e = 0; e < nw; ++e) {
-      const int32_t a = m->wall[2 * e], b = m->wall[2 * e + 1];
-      const double dx = unwrap_h(m->x[b] - m->x[a], m->px), dy = unwrap_h(m->y[b] - m->y[a], m->py);
-      const double len = std::sqrt(dx * dx + dy * dy);
-      rd::WallEnt ea{b, 0, len / 2.0, dy / len, -dx / len};
-      rd::WallEnt eb{a, 1, len / 2.0, dy / len, -dx / len};
-      per[a].push_back(ea);
-      per[b].push_back(eb);
+    std::vector<int32_t> wrow(nv + 1, 0);
+    for (int32_t v : m->wall) wrow[v + 1]++;
+    for (int64_t i = 0; i < nv; ++i) wrow[i + 1] += wrow[i];
+    std::vector<rd::WallEnt> ents(2 * nw);
+    {
+      std::vector<int32_t> fill(wrow.begin(), wrow.end() - 1);
+      for (int64_t e = 0; e < nw; ++e) {
+        const int32_t a = m->wall[2 * e], b = m->wall[2 * e + 1];
+        const double dx = unwrap_h(m->x[b] - m->x[a], m->px), dy = unwrap_h(m->y[b] - m->y[a], m->py);
+        const double len = std::sqrt(dx * dx + dy * dy);
+        ents[fill[a]++] = rd::WallEnt{b, 0, len / 2.0, dy / len, -dx / len};
+        ents[fill[b]++] = rd::WallEnt{a, 1, len / 2.0, dy / len, -dx / len};
+      }
     }
     m->wptr.push_back(0);
     for (int64_t i = 0; i < nv; ++i) {
       int32_t b = -1;
-      if (!per[i].empty()) {
+      if (wrow[i + 1] > wrow[i]) {
         b = (int32_t)m->wv.size();
         m->wv.push_back((int32_t)i);
-        for (const auto& e : per[i]) m->went.push_back(e);
+        m->went.insert(m->went.end(), ents.begin() + wrow[i], ents.begin() + wrow[i + 1]);
         m->wptr.push_back((int32_t)m->went.size());
       }
       if (m->ghost[i]) m->bc[i] = b >= 0 ? -3 - b : -2;
@@ -489,165 +857,96 @@ RD_API rd_status rd_mesh_create(const rd_mesh_desc* desc, void* stream, rd_mesh*
     }
   }
 
-  rd::Dev& d = m->d;
-  d.nv = nv;
-  d.nt = nt;
-  d.nwv = (int32_t)m->wv.size();
-  d.gamma = m->gamma;
-  d.igamma = 1.0 / m->gamma;
-  d.px = m->px;
-  d.py = m->py;
-  d.hpx = m->px > 0.0 ? 0.5 * m->px : HUGE_VAL;
-  d.hpy = m->py > 0.0 ? 0.5 * m->py : HUGE_VAL;
+  rd::Patches& p = m->p;
+  p.nv = nv;
+  m->d.nv = nv;
+  m->d.nt = nt;
+  p.gamma = m->gamma;
+  p.gas = rd::SymGas(m->gamma);
+  p.px = m->px;
+  p.py = m->py;
+  p.hpx = m->px > 0.0 ? 0.5 * m->px : HUGE_VAL;
+  p.hpy = m->py > 0.0 ? 0.5 * m->py : HUGE_VAL;
+  // domain size L of the Bx sensor: the period on a periodic axis, else the coordinate extent
   {
-    DeviceGuard g(m->device);
-    std::vector<double2> xy(nv);
-    for (int64_t i = 0; i < nv; ++i) xy[i] = make_double2(m->x[i], m->y[i]);
-    std::vector<int32_t> tv(3 * nt);
-    std::vector<uint32_t> rk(nt, 0u);
-    for (int64_t t = 0; t < nt; ++t)
-      for (int k = 0; k < 3; ++k) tv[k * nt + t] = m->tri[3 * t + k];
-    // sliced part layout: 64-vertex slices, each as wide as its largest
-    // degree; the j-th part of vertex v sits at sbase[v / 64] + v % 64 + 64 j
-    const int64_t nsl = (nv + 63) / 64;
-    std::vector<int32_t> sbase(nsl);
-    int64_t base = 0;
-    int32_t maxdeg = 0;
-    for (int64_t g0 = 0; g0 < nv; g0 += 64) {
-      const int64_t g1 = std::min<int64_t>(g0 + 64, nv);
-      int32_t width = 0;
-      for (int64_t v = g0; v < g1; ++v) width = std::max(width, m->row[v + 1] - m->row[v]);
-      sbase[g0 / 64] = (int32_t)std::min<int64_t>(base, INT32_MAX);
-      base += 64 * (int64_t)width;
-      maxdeg = std::max(maxdeg, width);
-    }
-    if (base >= (int64_t(1) << 31)) {
-      free_all(m);
-      delete m;
-      return fail(RD_EINVAL, "mesh too large for 32-bit part slots");
-    }
-    if (maxdeg > kMaxDegree) {  // rd_mesh_validate's check has run; kept as a guard
-      free_all(m);
-      delete m;
-      return fail(RD_EINVAL, "a vertex belongs to " + std::to_string(maxdeg) + " triangles; at most " +
-                                 std::to_string(kMaxDegree) + " are supported");
-    }
-    d.ns = base;
-    // rank of each triangle among the triangles of each of its corner vertices
-    // (10 bits per corner), and the triangle of every part slot
-    std::vector<int32_t> vtri(std::max<int64_t>(base, 1), -1);
-    for (int64_t v = 0; v < nv; ++v)
-      for (int32_t j = 0; j < m->row[v + 1] - m->row[v]; ++j) {
-        const int32_t cs = m->slot[m->row[v] + j];  // corner 3 t + k is the j-th part of v
-        rk[cs / 3] |= (uint32_t)j << (10 * (cs % 3));
-        vtri[sbase[v / 64] + v % 64 + 64 * (int64_t)j] = cs / 3;
-      }
-    double2* pxy;
-    double* pV;
-    int32_t *prow, *ptv, *psbase, *pvtri;
-    uint32_t* prk;
-    if ((st = upload(m, &pxy, xy)) || (st = upload(m, &pV, m->V)) || (st = upload(m, &prow, m->row)) ||
-        (st = upload(m, &ptv, tv)) || (st = upload(m, &prk, rk)) || (st = upload(m, &psbase, sbase)) ||
-        (st = upload(m, &pvtri, vtri))) {
-      free_all(m);
-      delete m;
-      return st;
-    }
-    d.xy = pxy;
-    d.V = pV;
-    d.row = prow;
-    d.tv = ptv;
-    d.rk = prk;
-    d.sbase = psbase;
-    d.vtri = pvtri;
-    if (has_bc) {
-      int32_t *pbc, *pwv, *pwptr;
-      rd::WallEnt* pwent;
-      if ((st = upload(m, &pbc, m->bc)) || (st = upload(m, &pwv, m->wv)) || (st = upload(m, &pwptr, m->wptr)) ||
-          (st = upload(m, &pwent, m->went))) {
-        free_all(m);
-        delete m;
-        return st;
-      }
-      d.bc = pbc;
-      d.wv = pwv;
-      d.wptr = pwptr;
-      d.went = pwent;
-      rd::D4 *wcn, *wcs;
-      if ((st = dalloc(m, &wcn, d.nwv)) || (st = dalloc(m, &wcs, d.nwv))) {
-        free_all(m);
-        delete m;
-        return st;
-      }
-      d.WCn = wcn;
-      d.WCs = wcs;
-    }
-    rd::D4 *W, *Ws, *Z;
-    double *sig, *lam, *dt, *scratch;
-    int* flag;
-    if ((st = dalloc(m, &W, nv)) || (st = dalloc(m, &Ws, nv)) || (st = dalloc(m, &Z, nv)) ||
-        (st = dalloc(m, &sig, nv)) || (st = dalloc(m, &lam, nt)) || (st = dalloc(m, &dt, 1)) ||
-        (st = dalloc(m, &flag, 1)) || (st = dalloc(m, &scratch, 4 * std::max(nv, nt)))) {
-      free_all(m);
-      delete m;
-      return st;
-    }
-    d.W = W;
-    d.Ws = Ws;
-    d.Z = Z;
-    d.sig = sig;
-    d.lam = lam;
-    d.dt = dt;
-    d.flag = flag;
-    m->scratch = scratch;
-    // CFL reduction plan: vertex blocks of kBlock, one segment
-    const int32_t nb = (int32_t)((nv + rd::kCflSpan - 1) / rd::kCflSpan);
-    std::vector<int32_t> v0(nb), v1(nb), b0 = {0, nb};
-    for (int32_t b = 0; b < nb; ++b) {
-      v0[b] = b * rd::kCflSpan;
-      v1[b] = (int32_t)std::min<int64_t>(nv, (int64_t)(b + 1) * rd::kCflSpan);
-    }
-    int32_t *pv0, *pv1, *pb0;
-    double *part, *vpart, *vr;
-    // domain size L of the Bx sensor: the period on a periodic axis, else the coordinate extent
-    {
-      const auto xr = std::minmax_element(m->x.begin(), m->x.end());
-      const auto yr = std::minmax_element(m->y.begin(), m->y.end());
-      const double lx = m->px > 0.0 ? m->px : *xr.second - *xr.first;
-      const double ly = m->py > 0.0 ? m->py : *yr.second - *yr.first;
-      m->Ldom = std::max(lx, ly);
-    }
-    const std::vector<double> vr0 = {0.0, 0.0, m->Ldom};
-    if ((st = upload(m, &pv0, v0)) || (st = upload(m, &pv1, v1)) || (st = upload(m, &pb0, b0)) ||
-        (st = dalloc(m, &part, nb)) || (st = dalloc(m, &vpart, 2 * nb)) || (st = upload(m, &vr, vr0))) {
-      free_all(m);
-      delete m;
-      return st;
-    }
-    d.vr = vr;
-    m->cfl.vpart = vpart;
-    m->cfl.nblocks = nb;
-    m->cfl.nmesh = 1;
-    m->cfl.blk_v0 = pv0;
-    m->cfl.blk_v1 = pv1;
-    m->cfl.mesh_b0 = pb0;
-    m->cfl.part = part;
-    if ((st = ensure_prec(m, 0)) != RD_OK) {
-      free_all(m);
-      delete m;
-      return st;
-    }
-    hipError_t e = hipMemset(W, 0, sizeof(rd::D4) * nv);
-    if (e == hipSuccess) e = hipMemset(flag, 0, sizeof(int));
-    if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e != hipSuccess) {
-      free_all(m);
-      delete m;
-      return fail(RD_EDEVICE, std::string("initialising buffers: ") + hipGetErrorString(e));
-    }
+    const auto xr = std::minmax_element(m->x.begin(), m->x.end());
+    const auto yr = std::minmax_element(m->y.begin(), m->y.end());
+    const double lx = m->px > 0.0 ? m->px : *xr.second - *xr.first;
+    const double ly = m->py > 0.0 ? m->py : *yr.second - *yr.first;
+    m->Ldom = std::max(lx, ly);
   }
-  *out = m;
+  const size_t nmesh = m->voff.size() - 1;
+  std::vector<double> vr0(3 * nmesh, 0.0);
+  for (size_t k = 0; k < nmesh; ++k) vr0[3 * k + 2] = Ldom.empty() ? m->Ldom : Ldom[k];
+  DeviceGuard g(m->device);
+  rd::Dev& d = m->d;
+  rd::D4 *W0, *W1, *D;
+  int *cur, *flag;
+  double *dt, *vr;
+  if ((st = dalloc(m, &W0, nv)) || (st = dalloc(m, &W1, nv)) || (st = dalloc(m, &D, nv)) ||
+      (st = upload(m, &cur, std::vector<int>{0, 0})) || (st = upload(m, &flag, std::vector<int>(nmesh, 0))) ||
+      (st = dalloc(m, &dt, nmesh)) || (st = upload(m, &vr, vr0)) || (st = dalloc(m, &m->scratch, 4 * nv)))
+    return st;
+  p.W[0] = W0;
+  p.W[1] = W1;
+  p.D = D;
+  p.cur = cur;
+  p.flag = d.flag = flag;
+  p.dt = d.dt = dt;
+  p.vr = d.vr = vr;
+  if ((st = build_view(m)) != RD_OK) return st;
+  rd::D4 *W, *Ws, *Z, *C, *kN, *kT, *wcn, *wcs;
+  if ((st = dalloc(m, &W, nv)) || (st = dalloc(m, &Ws, nv)) || (st = dalloc(m, &Z, nv)) ||
+      (st = dalloc(m, &C, d.ns)) || (st = dalloc(m, &kN, 2 * nt)) || (st = dalloc(m, &kT, nt)) ||
+      (st = dalloc(m, &wcn, m->wv.size())) || (st = dalloc(m, &wcs, m->wv.size())))
+    return st;
+  d.W = W;
+  d.Ws = Ws;
+  d.Z = Z;
+  d.C = C;
+  d.keepN = kN;
+  d.keepT = kT;
+  d.WCn = wcn;
+  d.WCs = wcs;
+  if ((st = build_patches(m, 0)) != RD_OK) return st;
+  hipError_t e = hipMemset(W0, 0, sizeof(rd::D4) * nv);
+  if (e == hipSuccess) e = hipDeviceSynchronize();
+  if (e != hipSuccess) return fail(RD_EDEVICE, std::string("initialising buffers: ") + hipGetErrorString(e));
+  *out = owner.release();
   return RD_OK;
+}
+
+// Workspace of the allocation-free adjoint: every buffer starts on a 256-byte
+// boundary.
+struct NoallocLayout {
+  size_t bytes = 0;
+  size_t R2, R1, LamS, LamN, Zn, Wa, Sig, CZ, CZW, KN, KT;
+  NoallocLayout(int64_t nv, int64_t nt, int64_t ns) {
+    auto take = [&](size_t n) {
+      const size_t at = bytes;
+      bytes += (n + 255) & ~size_t(255);
+      return at;
+    };
+    R2 = take(sizeof(rd::AdjRec2) * nv);
+    R1 = take(sizeof(rd::AdjRec1) * nv);
+    LamS = take(sizeof(rd::D4) * nv);
+    LamN = take(sizeof(rd::D4) * nv);
+    Zn = take(sizeof(rd::D4) * nv);
+    Wa = take(sizeof(rd::D4) * nv);
+    Sig = take(sizeof(double) * nv);
+    CZ = take(sizeof(rd::D4) * ns);
+    CZW = take(sizeof(rd::ZW) * ns);
+    KN = take(sizeof(rd::D4) * 2 * nt);
+    KT = take(sizeof(rd::D4) * nt);
+  }
+};
+
+}  // namespace
+
+RD_API rd_status rd_mesh_create(const rd_mesh_desc* desc, void* stream, rd_mesh** out) {
+  if (!out) return fail(RD_EINVAL, "null output pointer");
+  *out = nullptr;
+  return guarded([&] { return create_mesh(desc, static_cast<hipStream_t>(stream), {}, {}, {}, out); });
 }
 
 RD_API rd_status rd_mesh_destroy(rd_mesh* m) {
@@ -686,10 +985,11 @@ RD_API rd_status rd_set_state(rd_mesh* m, const double* W, int on_device) {
     HIPCHK(hipMemcpyAsync(m->scratch, W, sizeof(double) * 4 * nv, hipMemcpyHostToDevice, m->stream));
     src = m->scratch;
   }
-  rd::Dev d = dev_for(m, 0);
-  HIPCHK(rd::launch_set_int(d.flag, 0, m->stream));
-  HIPCHK(rd::launch_set_state(d, src, 0, m->stream));
-  m->zprec = 0;
+  HIPCHK(rd::launch_set_int(m->p.flag, 0, m->stream));
+  // into the form of the last steps
+  note_capture(m);
+  if (m->form32) HIPCHK(rd::launch_set32(view32(m), m->d32, m->p.cur, src, m->stream));
+  else HIPCHK(rd::launch_patch_set(m->p, m->inv, src, m->stream));
   if (!on_device) HIPCHK(hipStreamSynchronize(m->stream));
   return RD_OK;
 }
@@ -699,13 +999,13 @@ RD_API rd_status rd_get_state(rd_mesh* m, double* W, int on_device) {
   DeviceGuard g(m->device);
   const int64_t nv = m->d.nv;
   if (on_device) {
-    HIPCHK(rd::launch_get_state(m->d, m->d.W, W, m->stream));
+    HIPCHK(rd::launch_state_get(state_of(m), nv, W, m->stream));
     return RD_OK;
   }
-  HIPCHK(rd::launch_get_state(m->d, m->d.W, m->scratch, m->stream));
+  HIPCHK(rd::launch_state_get(state_of(m), nv, m->scratch, m->stream));
   HIPCHK(hipMemcpyAsync(W, m->scratch, sizeof(double) * 4 * nv, hipMemcpyDeviceToHost, m->stream));
   int flag = 0;
-  HIPCHK(hipMemcpyAsync(&flag, m->d.flag, sizeof(int), hipMemcpyDeviceToHost, m->stream));
+  HIPCHK(hipMemcpyAsync(&flag, m->p.flag, sizeof(int), hipMemcpyDeviceToHost, m->stream));
   HIPCHK(hipStreamSynchronize(m->stream));
   if (flag) return fail(RD_ENONPHYS, "a non-physical state was produced");
   return RD_OK;
@@ -715,14 +1015,15 @@ RD_API rd_status rd_max_dt(rd_mesh* m, double cfl, double* dt_out) {
   if (!m || !dt_out) return fail(RD_EINVAL, "null argument");
   if (!(cfl > 0.0)) return fail(RD_EINVAL, "cfl must be positive");
   DeviceGuard g(m->device);
-  // the signal speeds are valid for the state whenever the parameter vectors
-  // are; after a tune, a batch run or an adjoint step they are refreshed first
-  if (m->zprec < 0) {
-    rd_status st = ensure_z(m, 0);
+  if (m->form32 && !m->captured) {
+    HIPCHK(rd::launch_cfl32(view32(m), m->cfl, cfl, m->stream));
+  } else {
+    rd_status st = enter(m, 0);
     if (st != RD_OK) return st;
+    HIPCHK(rd::launch_patch_cfl(m->p, m->stream));
+    HIPCHK(rd::launch_patch_dt(m->p, cfl, m->stream));
   }
-  HIPCHK(rd::launch_cfl(m->d, m->cfl, cfl, m->stream));
-  HIPCHK(hipMemcpyAsync(dt_out, m->d.dt, sizeof(double), hipMemcpyDeviceToHost, m->stream));
+  HIPCHK(hipMemcpyAsync(dt_out, m->p.dt, sizeof(double), hipMemcpyDeviceToHost, m->stream));
   HIPCHK(hipStreamSynchronize(m->stream));
   return RD_OK;
 }
@@ -733,11 +1034,8 @@ RD_API rd_status rd_step(rd_mesh* m, double dt, int scheme, int time, int precis
   rd_status st = check_step_args(scheme, time, precision);
   if (st != RD_OK) return st;
   DeviceGuard g(m->device);
-  const int fp32 = precision == RD_FP32_ACC64;
-  if ((st = ensure_prec(m, fp32)) != RD_OK) return st;
-  if ((st = ensure_z(m, fp32)) != RD_OK) return st;
-  HIPCHK(rd::launch_set_scalar(m->d.dt, dt, m->stream));
-  return run_step(m, scheme, time, fp32, 0.0);
+  if ((st = enter(m, precision == RD_FP32_ACC64)) != RD_OK) return st;
+  return run_step(m, scheme, time, precision == RD_FP32_ACC64, 0.0, dt);
 }
 
 RD_API rd_status rd_step_cfl(rd_mesh* m, int n_steps, double cfl, int scheme, int time, int precision) {
@@ -747,11 +1045,9 @@ RD_API rd_status rd_step_cfl(rd_mesh* m, int n_steps, double cfl, int scheme, in
   rd_status st = check_step_args(scheme, time, precision);
   if (st != RD_OK) return st;
   DeviceGuard g(m->device);
-  const int fp32 = precision == RD_FP32_ACC64;
-  if ((st = ensure_prec(m, fp32)) != RD_OK) return st;
-  if ((st = ensure_z(m, fp32)) != RD_OK) return st;
+  if ((st = enter(m, precision == RD_FP32_ACC64)) != RD_OK) return st;
   for (int n = 0; n < n_steps; ++n)
-    if ((st = run_step(m, scheme, time, fp32, cfl)) != RD_OK) return st;
+    if ((st = run_step(m, scheme, time, precision == RD_FP32_ACC64, cfl, 0.0)) != RD_OK) return st;
   return RD_OK;
 }
 
@@ -762,12 +1058,11 @@ RD_API rd_status rd_step_timed(rd_mesh* m, double cfl, int scheme, int time, int
   if (st != RD_OK) return st;
   DeviceGuard g(m->device);
   const int fp32 = precision == RD_FP32_ACC64;
-  if ((st = ensure_prec(m, fp32)) != RD_OK) return st;
-  if ((st = ensure_z(m, fp32)) != RD_OK) return st;
+  if ((st = enter(m, fp32)) != RD_OK) return st;
   if (!m->events[0])
     for (int k = 0; k <= RD_NKERNELS; ++k) HIPCHK(hipEventCreate(&m->events[k]));
   hipEvent_t* ev = m->events;
-  if ((st = run_step(m, scheme, time, fp32, cfl, ev)) != RD_OK) return st;
+  if ((st = run_step(m, scheme, time, fp32, cfl, 0.0, ev)) != RD_OK) return st;
   HIPCHK(hipEventSynchronize(ev[RD_NKERNELS]));
   for (int k = 0; k < RD_NKERNELS; ++k) {
     float t = 0.0f;
@@ -791,13 +1086,13 @@ RD_API rd_status rd_mesh_get_tile(const rd_mesh* m, int* tile_triangles) {
 RD_API rd_status rd_mesh_set_lumping(rd_mesh* m, int lumping) {
   if (!m) return fail(RD_EINVAL, "null mesh");
   if (lumping != RD_LUMP_GLOBAL && lumping != RD_LUMP_SELECTIVE) return fail(RD_EINVAL, "unknown lumping");
-  m->d.slump = lumping == RD_LUMP_SELECTIVE;
+  m->p.slump = lumping == RD_LUMP_SELECTIVE;
   return RD_OK;
 }
 
 RD_API rd_status rd_mesh_get_lumping(const rd_mesh* m, int* lumping) {
   if (!m || !lumping) return fail(RD_EINVAL, "null argument");
-  *lumping = m->d.slump ? RD_LUMP_SELECTIVE : RD_LUMP_GLOBAL;
+  *lumping = m->p.slump ? RD_LUMP_SELECTIVE : RD_LUMP_GLOBAL;
   return RD_OK;
 }
 
@@ -859,18 +1154,18 @@ RD_API rd_status rd_tune(rd_mesh* m, double cfl, int scheme, int time, int preci
   if (st != RD_OK) return st;
   DeviceGuard g(m->device);
   const int fp32 = precision == RD_FP32_ACC64;
-  if ((st = ensure_prec(m, fp32)) != RD_OK) return st;
   hipStream_t s = m->stream;
-  // the state and the flag are saved in the scratch buffer (4 max(nv, nt) doubles)
+  // the state (in the caller's order) and the flag are saved
   rd::D4* saveW = reinterpret_cast<rd::D4*>(m->scratch);
-  HIPCHK(rd::launch_copy4(saveW, m->d.W, m->d.nv, s));
+  HIPCHK(rd::launch_state_get4(state_of(m), m->p.nv, saveW, s));
   int flag0 = 0;
-  HIPCHK(hipMemcpyAsync(&flag0, m->d.flag, sizeof(int), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(&flag0, m->p.flag, sizeof(int), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   auto restore = [&]() -> rd_status {
-    HIPCHK(rd::launch_copy4(m->d.W, saveW, m->d.nv, s));
-    HIPCHK(rd::launch_set_int(m->d.flag, flag0, s));
-    m->zprec = -1;
+    HIPCHK(rd::launch_patch_set4(m->p, m->inv, saveW, s));
+    HIPCHK(rd::launch_set_int(m->p.cur, 0, s));
+    HIPCHK(rd::launch_set_int(m->p.flag, flag0, s));
+    m->form32 = false;
     return RD_OK;
   };
   const int prev = m->tile;
@@ -881,11 +1176,11 @@ RD_API rd_status rd_tune(rd_mesh* m, double cfl, int scheme, int time, int preci
     st = set_tile(m, candidates[i]);
     if (st == RD_EUNSUPPORTED || st == RD_EINVAL) continue;
     if (st != RD_OK) break;
-    if ((st = ensure_z(m, fp32)) != RD_OK || (st = run_step(m, scheme, time, fp32, cfl)) != RD_OK) break;
+    if ((st = enter(m, fp32)) != RD_OK || (st = run_step(m, scheme, time, fp32, cfl, 0.0)) != RD_OK) break;
     float t = 0.0f;
     st = time_on(s, [&]() -> rd_status {
       for (int k = 0; k < n_steps; ++k) {
-        rd_status r = run_step(m, scheme, time, fp32, cfl);
+        rd_status r = run_step(m, scheme, time, fp32, cfl, 0.0);
         if (r != RD_OK) return r;
       }
       return RD_OK;
@@ -915,23 +1210,23 @@ RD_API rd_status rd_residual(rd_mesh* m, int scheme, double* R, double* phiT, in
   if (scheme < RD_N || scheme > RD_BX) return fail(RD_EINVAL, "unknown scheme");
   DeviceGuard g(m->device);
   rd_status st;
-  if ((st = ensure_z(m, 0)) != RD_OK) return st;
-  const rd::Dev d = dev_for(m, 0);
+  const rd::Dev& d = m->d;
   hipStream_t s = m->stream;
+  HIPCHK(rd::launch_view(d, state_of(m), s));
   const int64_t nv = d.nv, nt = d.nt;
-  HIPCHK(rd::launch_wall(d, false, s));
-  if (scheme == RD_BX) HIPCHK(rd::launch_vrange(d, m->cfl, 0, s));
-  HIPCHK(rd::launch_tri(d, 0, scheme, 1, true, false, s));
+  if (scheme == RD_BX) HIPCHK(rd::launch_vrange32(d, m->cfl, false, s));
+  HIPCHK(rd::launch_tri(d, scheme, s));
   if (on_device) {
-    HIPCHK(rd::launch_gather(d, 0, rd::G_RESIDUAL, R, s));
-    if (phiT) HIPCHK(rd::launch_keep_to_soa(d.keepT, phiT, nt, s));
+    HIPCHK(rd::launch_residual(d, R, s));
+    if (phiT) HIPCHK(rd::launch_keep_to_soa(d, phiT, s));
     return RD_OK;
   }
-  HIPCHK(rd::launch_gather(d, 0, rd::G_RESIDUAL, m->scratch, s));
+  if (phiT && !m->phi_scratch && (st = dalloc(m, &m->phi_scratch, 4 * nt)) != RD_OK) return st;
+  HIPCHK(rd::launch_residual(d, m->scratch, s));
   HIPCHK(hipMemcpyAsync(R, m->scratch, sizeof(double) * 4 * nv, hipMemcpyDeviceToHost, s));
   if (phiT) {
-    HIPCHK(rd::launch_keep_to_soa(d.keepT, m->scratch, nt, s));
-    HIPCHK(hipMemcpyAsync(phiT, m->scratch, sizeof(double) * 4 * nt, hipMemcpyDeviceToHost, s));
+    HIPCHK(rd::launch_keep_to_soa(d, m->phi_scratch, s));
+    HIPCHK(hipMemcpyAsync(phiT, m->phi_scratch, sizeof(double) * 4 * nt, hipMemcpyDeviceToHost, s));
   }
   HIPCHK(hipStreamSynchronize(s));
   return RD_OK;
@@ -964,7 +1259,7 @@ rd_status adjoint_args(rd_mesh* m, double dt, int scheme, int time) {
   rd_status st = check_step_args(scheme, time, RD_FP64);
   if (st != RD_OK) return st;
   if (scheme == RD_BX) return fail(RD_EUNSUPPORTED, "the adjoint does not cover the Bx scheme");
-  if (m->d.slump && time == RD_RK2)
+  if (m->p.slump && time == RD_RK2)
     return fail(RD_EUNSUPPORTED, "the adjoint does not cover selective lumping");
   return RD_OK;
 }
@@ -976,7 +1271,7 @@ rd_status adjoint_args(rd_mesh* m, double dt, int scheme, int time) {
 rd_status adjoint_enqueue(rd_mesh* m, const rd::AdjDev& a, rd::D4* Wa, double* sig, const double* W_n,
                           double dt, int scheme, int time, const double* lam_np1, double* lam_n) {
   hipStream_t s = m->stream;
-  rd::Dev d = dev_for(m, 0);
+  rd::Dev d = m->d;
   d.W = Wa;
   d.sig = sig;
   d.flag = a.flag;
@@ -989,16 +1284,15 @@ rd_status adjoint_enqueue(rd_mesh* m, const rd::AdjDev& a, rd::D4* Wa, double* s
   ad.lam = rd::LamSoA{lam_np1, m->d.nv};  // read in the caller's layout
   ad.idt = 1.0 / dt;
   ad.waves = rd::kAdjWavesPerCu * m->ncu;
-  HIPCHK(rd::launch_set_state(dn, W_n, 0, s));
+  HIPCHK(rd::launch_set_state(dn, W_n, s));
   HIPCHK(rd::launch_set_scalar(d.dt, dt, s));
   const bool rk2 = time == RD_RK2;
   if (rk2) {
     HIPCHK(rd::launch_wall(dn, false, s));
-    HIPCHK(rd::launch_tri(dn, 0, scheme, 1, true, false, s));
+    HIPCHK(rd::launch_tri(dn, scheme, s));
     HIPCHK(rd::launch_adj_star(d, ad, s));
   }
   HIPCHK(rd::launch_adjoint(d, ad, scheme, rk2 ? 1 : 0, lam_n, s));
-  m->zprec = -1;  // the parameter-vector buffer now holds the recomputation's values
   return RD_OK;
 }
 
@@ -1070,21 +1364,10 @@ RD_API rd_status rd_adjoint_step_noalloc(rd_mesh* m, const double* W_n, double d
   if (!m || !W_n || !lam_np1 || !lam_n || !flags) return fail(RD_EINVAL, "null argument");
   rd_status st = adjoint_args(m, dt, scheme, time);
   if (st != RD_OK) return st;
-  const int64_t nv = m->d.nv, nt = m->d.nt, ns = m->d.ns;
-  // workspace layout: every buffer starts on a 256-byte boundary
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    const size_t at = off;
-    off += (bytes + 255) & ~size_t(255);
-    return at;
-  };
-  const size_t oR2 = take(sizeof(rd::AdjRec2) * nv), oR1 = take(sizeof(rd::AdjRec1) * nv),
-               oLamS = take(sizeof(rd::D4) * nv),
-               oLamN = take(sizeof(rd::D4) * nv), oZn = take(sizeof(rd::D4) * nv), oWa = take(sizeof(rd::D4) * nv),
-               oSig = take(sizeof(double) * nv), oCZ = take(sizeof(rd::D4) * ns), oCZW = take(sizeof(rd::ZW) * ns),
-               oKN = take(sizeof(rd::D4) * 2 * nt), oKT = take(sizeof(rd::D4) * nt);
-  if (off > rd::kNoallocScratchBytes)
-    return fail(RD_EINVAL, "mesh too large for the allocation-free adjoint: it needs " + std::to_string(off) +
+  const int64_t nv = m->p.nv, nt = m->d.nt, ns = m->d.ns;
+  const NoallocLayout o(nv, nt, ns);
+  if (o.bytes > rd::kNoallocScratchBytes)
+    return fail(RD_EINVAL, "mesh too large for the allocation-free adjoint: it needs " + std::to_string(o.bytes) +
                                " bytes of workspace, the fixed workspace holds " +
                                std::to_string(rd::kNoallocScratchBytes));
   DeviceGuard g(m->device);
@@ -1092,19 +1375,19 @@ RD_API rd_status rd_adjoint_step_noalloc(rd_mesh* m, const double* W_n, double d
   HIPCHK(rd::noalloc_scratch(&base));
   char* p = static_cast<char*>(base);
   rd::AdjDev a;
-  a.r2 = reinterpret_cast<rd::AdjRec2*>(p + oR2);
-  a.r1 = reinterpret_cast<rd::AdjRec1*>(p + oR1);
-  a.lamS = reinterpret_cast<rd::D4*>(p + oLamS);
-  a.lamN = reinterpret_cast<rd::D4*>(p + oLamN);
-  a.Zn = reinterpret_cast<rd::D4*>(p + oZn);
-  a.cZ = reinterpret_cast<rd::D4*>(p + oCZ);
-  a.cZW = reinterpret_cast<rd::ZW*>(p + oCZW);
-  a.kN = reinterpret_cast<rd::D4*>(p + oKN);
-  a.kT = reinterpret_cast<rd::D4*>(p + oKT);
+  a.r2 = reinterpret_cast<rd::AdjRec2*>(p + o.R2);
+  a.r1 = reinterpret_cast<rd::AdjRec1*>(p + o.R1);
+  a.lamS = reinterpret_cast<rd::D4*>(p + o.LamS);
+  a.lamN = reinterpret_cast<rd::D4*>(p + o.LamN);
+  a.Zn = reinterpret_cast<rd::D4*>(p + o.Zn);
+  a.cZ = reinterpret_cast<rd::D4*>(p + o.CZ);
+  a.cZW = reinterpret_cast<rd::ZW*>(p + o.CZW);
+  a.kN = reinterpret_cast<rd::D4*>(p + o.KN);
+  a.kT = reinterpret_cast<rd::D4*>(p + o.KT);
   a.flag = flags;
   // the latches start cleared on every call (a fill kernel, so the call can be captured)
   HIPCHK(rd::launch_fill_int(flags, 0, 2, m->stream));
-  return adjoint_enqueue(m, a, reinterpret_cast<rd::D4*>(p + oWa), reinterpret_cast<double*>(p + oSig), W_n, dt,
+  return adjoint_enqueue(m, a, reinterpret_cast<rd::D4*>(p + o.Wa), reinterpret_cast<double*>(p + o.Sig), W_n, dt,
                          scheme, time, lam_np1, lam_n);
 }
 
@@ -1121,6 +1404,11 @@ struct rd_batch {
   rd_mesh* flat = nullptr;
   std::vector<rd_mesh*> members;
   std::vector<int64_t> voff, toff;
+  // the copy of the members' states in and out: one launch over blocks of one member's vertices
+  rd::PatchMember* mem = nullptr;
+  int32_t *mb = nullptr, *vb = nullptr;
+  int nblocks = 0;
+  std::vector<int> versions;     // of the members' internal orders, as in mem
   hipStream_t stream = nullptr;  // the caller's stream
   hipStream_t own = nullptr;     // the batch's own stream (a null stream cannot be captured)
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
@@ -1228,51 +1516,33 @@ RD_API rd_status rd_batch_create(rd_mesh* const* meshes, int n, void* stream, rd
     return fail(RD_EDEVICE, "hipEventCreate failed");
   }
   rd_mesh* flat = nullptr;
-  rd_status st = rd_mesh_create(&desc, own, &flat);
+  std::vector<double> Ldom(n);
+  for (int k = 0; k < n; ++k) Ldom[k] = meshes[k]->Ldom;  // each member's own domain size
+  rd_status st = create_mesh(&desc, own, voff, toff, Ldom, &flat);
   if (st != RD_OK) {
     (void)hipEventDestroy(ev_in);
     (void)hipEventDestroy(ev_out);
     (void)hipStreamDestroy(own);
     return st;
   }
-  // mesh ids, per-mesh time steps, per-mesh CFL segments
-  std::vector<int32_t> vm(voff.back()), tm(toff.back()), v0, v1, b0{0};
-  for (int k = 0; k < n; ++k) {
-    for (int64_t i = voff[k]; i < voff[k + 1]; ++i) vm[i] = k;
-    for (int64_t t = toff[k]; t < toff[k + 1]; ++t) tm[t] = k;
-    for (int64_t v = voff[k]; v < voff[k + 1]; v += rd::kCflSpan) {
-      v0.push_back((int32_t)v);
-      v1.push_back((int32_t)std::min<int64_t>(v + rd::kCflSpan, voff[k + 1]));
+  // blocks of the member copies
+  std::vector<int32_t> mb, vb;
+  for (int k = 0; k < n; ++k)
+    for (int64_t v = 0; v < meshes[k]->p.nv; v += rd::kBlock) {
+      mb.push_back(k);
+      vb.push_back((int32_t)v);
     }
-    b0.push_back((int32_t)v0.size());
-  }
-  int32_t *pvm, *ptm, *pv0, *pv1, *pb0;
-  double *dt, *part, *vpart, *vr;
-  int* mflag;  // one non-physical latch per member
-  std::vector<double> vr0(3 * n, 0.0);
-  for (int k = 0; k < n; ++k) vr0[3 * k + 2] = meshes[k]->Ldom;  // each member's own domain size
-  if ((st = upload(flat, &pvm, vm)) || (st = upload(flat, &ptm, tm)) || (st = upload(flat, &pv0, v0)) ||
-      (st = upload(flat, &pv1, v1)) || (st = upload(flat, &pb0, b0)) || (st = dalloc(flat, &dt, n)) ||
-      (st = dalloc(flat, &part, v0.size())) || (st = dalloc(flat, &vpart, 2 * v0.size())) ||
-      (st = upload(flat, &vr, vr0)) || (st = upload(flat, &mflag, std::vector<int>(n, 0)))) {
+  std::unique_ptr<rd_batch> owner(new rd_batch());
+  rd_batch* b = owner.get();
+  if ((st = dalloc(flat, &b->mem, n)) || (st = upload(flat, &b->mb, mb)) || (st = upload(flat, &b->vb, vb))) {
     rd_mesh_destroy(flat);
+    (void)hipEventDestroy(ev_in);
+    (void)hipEventDestroy(ev_out);
+    (void)hipStreamDestroy(own);
     return st;
   }
-  flat->d.flag = mflag;
-  flat->d.vr = vr;
-  flat->cfl.vpart = vpart;
-  flat->voff = voff;
-  flat->toff = toff;
-  flat->d.vmesh = pvm;
-  flat->d.tmesh = ptm;
-  flat->d.dt = dt;
-  flat->cfl.nblocks = (int32_t)v0.size();
-  flat->cfl.nmesh = n;
-  flat->cfl.blk_v0 = pv0;
-  flat->cfl.blk_v1 = pv1;
-  flat->cfl.mesh_b0 = pb0;
-  flat->cfl.part = part;
-  rd_batch* b = new rd_batch();
+  b->nblocks = (int)mb.size();
+  b->versions.assign(n, -1);
   b->flat = flat;
   b->members.assign(meshes, meshes + n);
   b->voff = voff;
@@ -1281,6 +1551,7 @@ RD_API rd_status rd_batch_create(rd_mesh* const* meshes, int n, void* stream, rd
   b->own = own;
   b->ev_in = ev_in;
   b->ev_out = ev_out;
+  (void)owner.release();
   *out = b;
   return RD_OK;
 }
@@ -1293,9 +1564,9 @@ rd_status batch_begin(rd_batch* b, int fp32, std::vector<hipStream_t>& outer) {
   rd_mesh* f = b->flat;
   // the members' lumping, which must agree
   for (rd_mesh* m : b->members)
-    if (m->d.slump != b->members[0]->d.slump)
+    if (m->p.slump != b->members[0]->p.slump)
       return fail(RD_EINVAL, "the meshes of a batch use different lumpings");
-  f->d.slump = b->members[0]->d.slump;
+  f->p.slump = b->members[0]->p.slump;
   hipStream_t s = f->stream;  // the batch's own stream
   outer.assign(1, b->stream);
   for (rd_mesh* m : b->members)
@@ -1304,13 +1575,23 @@ rd_status batch_begin(rd_batch* b, int fp32, std::vector<hipStream_t>& outer) {
     HIPCHK(hipEventRecord(b->ev_in, o));
     HIPCHK(hipStreamWaitEvent(s, b->ev_in, 0));
   }
-  for (size_t k = 0; k < b->members.size(); ++k) {
-    rd_mesh* m = b->members[k];
-    HIPCHK(rd::launch_copy4(f->d.W + b->voff[k], m->d.W, m->d.nv, s));
+  // a member whose state has moved to other buffers since the last run is described anew
+  bool same = true;
+  for (size_t k = 0; k < b->members.size(); ++k) same = same && b->versions[k] == b->members[k]->version;
+  if (!same) {
+    std::vector<rd::PatchMember> mem;
+    for (size_t k = 0; k < b->members.size(); ++k) {
+      const rd_mesh* m = b->members[k];
+      mem.push_back(rd::PatchMember{state_of(m), m->p.cur, m->p.flag, (int32_t)m->p.nv, (int32_t)b->voff[k]});
+      b->versions[k] = m->version;
+    }
+    HIPCHK(hipStreamSynchronize(s));
+    HIPCHK(hipMemcpy(b->mem, mem.data(), sizeof(rd::PatchMember) * mem.size(), hipMemcpyHostToDevice));
   }
-  HIPCHK(rd::launch_fill_int(f->d.flag, 0, (int64_t)b->members.size(), s));
-  f->zprec = -1;
-  return ensure_z(f, fp32);
+  HIPCHK(rd::launch_patch_members(state_of(f), f->p.cur, f->p.flag, f->p.nv, b->mem, b->mb, b->vb, b->nblocks, false,
+                                  s));
+  f->form32 = false;
+  return enter(f, fp32);
 }
 
 // The captured graph of n_steps steps (cached per configuration; the cache
@@ -1321,14 +1602,14 @@ rd_status batch_graph(rd_batch* b, int n_steps, double cfl, int scheme, int time
   hipStream_t s = f->stream;
   for (auto& c : b->graphs)
     if (c.n_steps == n_steps && c.scheme == scheme && c.time == time && c.fp32 == fp32 && c.cfl == cfl &&
-        c.slump == f->d.slump) {
+        c.slump == f->p.slump) {
       *exec = c.exec;
       return RD_OK;
     }
-  rd_batch::Graph c{n_steps, scheme, time, fp32, f->d.slump, cfl, nullptr, nullptr};
+  rd_batch::Graph c{n_steps, scheme, time, fp32, f->p.slump, cfl, nullptr, nullptr};
   HIPCHK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
   rd_status rs = RD_OK;
-  for (int k = 0; k < n_steps && rs == RD_OK; ++k) rs = run_step(f, scheme, time, fp32, cfl);
+  for (int k = 0; k < n_steps && rs == RD_OK; ++k) rs = run_step(f, scheme, time, fp32, cfl, 0.0);
   hipError_t ce = hipStreamEndCapture(s, &c.graph);
   if (rs != RD_OK) {
     if (ce == hipSuccess) (void)hipGraphDestroy(c.graph);
@@ -1364,7 +1645,6 @@ RD_API rd_status rd_batch_run(rd_batch* b, int n_steps, double cfl, int scheme, 
   rd_mesh* f = b->flat;
   DeviceGuard g(f->device);
   const int fp32 = precision == RD_FP32_ACC64;
-  if ((st = ensure_prec(f, fp32)) != RD_OK) return st;
   hipStream_t s = f->stream;
   std::vector<hipStream_t> outer;
   if ((st = batch_begin(b, fp32, outer)) != RD_OK) return st;
@@ -1373,12 +1653,12 @@ RD_API rd_status rd_batch_run(rd_batch* b, int n_steps, double cfl, int scheme, 
     if ((st = batch_graph(b, n_steps, cfl, scheme, time, fp32, &exec)) != RD_OK) return st;
     HIPCHK(hipGraphLaunch(exec, s));
   }
-  // states out; each member refreshes its parameter vectors before its next step
-  for (size_t k = 0; k < b->members.size(); ++k) {
-    rd_mesh* m = b->members[k];
-    HIPCHK(rd::launch_copy4(m->d.W, f->d.W + b->voff[k], m->d.nv, s));
-    HIPCHK(rd::launch_or_int(m->d.flag, f->d.flag + k, s));
-    m->zprec = -1;
+  // states and latches out
+  HIPCHK(rd::launch_patch_members(state_of(f), f->p.cur, f->p.flag, f->p.nv, b->mem, b->mb, b->vb, b->nblocks, true,
+                                  s));
+  for (rd_mesh* m : b->members) {
+    note_capture(m);
+    m->form32 = false;
   }
   HIPCHK(hipEventRecord(b->ev_out, s));
   for (hipStream_t o : outer) HIPCHK(hipStreamWaitEvent(o, b->ev_out, 0));
@@ -1398,7 +1678,6 @@ RD_API rd_status rd_batch_tune(rd_batch* b, double cfl, int scheme, int time, in
   rd_mesh* f = b->flat;
   DeviceGuard g(f->device);
   const int fp32 = precision == RD_FP32_ACC64;
-  if ((st = ensure_prec(f, fp32)) != RD_OK) return st;
   hipStream_t s = f->stream;
   const int prev = f->tile;
   int pick = -1;
@@ -1453,7 +1732,7 @@ RD_API rd_status rd_sync(rd_mesh* m) {
   if (!m) return fail(RD_EINVAL, "null mesh");
   DeviceGuard g(m->device);
   int flag = 0;
-  HIPCHK(hipMemcpyAsync(&flag, m->d.flag, sizeof(int), hipMemcpyDeviceToHost, m->stream));
+  HIPCHK(hipMemcpyAsync(&flag, m->p.flag, sizeof(int), hipMemcpyDeviceToHost, m->stream));
   HIPCHK(hipStreamSynchronize(m->stream));
   if (flag) return fail(RD_ENONPHYS, "a non-physical state was produced");
   return adjoint_status(m);

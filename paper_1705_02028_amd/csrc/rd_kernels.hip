@@ -1,145 +1,55 @@
-// gfx950 kernels of the two-pass residual-distribution step, the CFL
-// reduction, state conversion and the adjoint, with their launchers.
+// gfx950 kernels of the adjoint and of the spatial residual, with their
+// launchers.
 //
-// Launch shapes: one thread per triangle (triangle passes) or per vertex
-// (gather, CFL), 256-thread workgroups, block ids renumbered per XCD.
+// Launch shapes: one thread per triangle or per vertex, 256-thread
+// workgroups, block ids renumbered per XCD.
 #include "rd_adjoint.h"
 #include "rd_kcommon.h"
 #include "rd_launch.h"
 
 namespace rd {
 
-// One thread per triangle. (A persistent grid with the next triangle's loads
-// software-pipelined was measured slower: fewer waves in flight and, with
-// per-workgroup chunks, scattered working sets. So was the adjoint's staged
-// form below applied to the FP64 passes, persistent one-wavefront workgroups
-// with the next batch's gathered inputs loaded straight to LDS: 0.72-0.87 ms
-// against 0.545 ms for the stage-1 pass at 2048^2, 0.51 against 0.50 for
-// stage 2; two to three waves per SIMD already overlap these passes' gathers
-// with each other's arithmetic.)
-template <typename R, int SCHEME, int STAGE, bool SAVE, bool CFL, bool LUMP>
-__global__ __launch_bounds__(kBlock, (TriKernelWaves<R, SCHEME, STAGE, SAVE, CFL>::value)) void k_tri(Dev d) {
+// One thread per triangle: the scheme's parts of stage 1, the N parts and the
+// residual kept (for the adjoint's stage 2 and for the residual's caller).
+template <int SCHEME>
+__global__ __launch_bounds__(kBlock, 4) void k_tri(Dev d) {
   const int64_t t = xcd_block() * kBlock + threadIdx.x;
-  if (t < d.nt)
-    tri_body<R, SCHEME, STAGE, SAVE, CFL, LUMP, TriKernelWaves<R, SCHEME, STAGE, SAVE, CFL>::fast_div>(t, d);
+  if (t < d.nt) tri_body<SCHEME>(t, d);
 }
 
-template <typename R, int MODE>
-__global__ __launch_bounds__(kBlock) void k_gather(Dev d, double* out_soa) {
+__global__ __launch_bounds__(kBlock) void k_residual(Dev d, double* out_soa) {
   const int64_t v = xcd_block() * kBlock + threadIdx.x;
-  if (v < d.nv) gather_body<R, MODE>(v, d, out_soa);
+  if (v < d.nv) residual_body(v, d, out_soa);
 }
 
-template <bool STAGE2, bool TILED>
+template <bool STAGE2>
 __global__ __launch_bounds__(kBlock) void k_wall(Dev d) {
   const int64_t b = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (b < d.nwv) wall_body<STAGE2, TILED>(b, d);
+  if (b < d.nwv) wall_body<STAGE2>(b, d);
 }
 
-__global__ __launch_bounds__(kBlock) void k_cfl_tri(Dev d) {
-  const int64_t t = xcd_block() * kBlock + threadIdx.x;
-  if (t < d.nt) cfl_tri_body(t, d);
-}
-
-// Per-vertex CFL bounds 2 V_i / sum l_max lambda_max (summed over the terms of
-// the vertex's triangles, or read from the bounds the tiled passes store) and
-// their block minima.
-template <bool FROM_CFLV, typename R>
-__global__ __launch_bounds__(kBlock) void k_cfl_vertex(Dev d, CflPlan p) {
-  constexpr int U = kCflSpan / kBlock;
-  const int b = blockIdx.x;
-  double x = INFINITY;
-  int64_t v[U];
-  bool in[U];
-  for (int u = 0; u < U; ++u) {
-    v[u] = (int64_t)p.blk_v0[b] + u * kBlock + threadIdx.x;
-    in[u] = v[u] < p.blk_v1[b];
-  }
-  if (FROM_CFLV) {
-    for (int u = 0; u < U; ++u)
-      if (in[u]) x = rmin(x, d.cflv[v[u]]);
-  } else {
-    double bound[U];
-    cfl_vertex_bounds<R, U>(v, in, p.blk_v0[b], d, bound);
-    for (int u = 0; u < U; ++u)
-      if (in[u]) x = rmin(x, bound[u]);
-  }
-  const double m = block_min(x);
-  if (threadIdx.x == 0) p.part[b] = m;
-}
-
-// Per-mesh minimum over the mesh's blocks -> dt.
-__global__ __launch_bounds__(kBlock) void k_cfl_final(Dev d, CflPlan p, double cfl) {
-  const int m = blockIdx.x;
-  double x = INFINITY;
-  for (int b = p.mesh_b0[m] + threadIdx.x; b < p.mesh_b0[m + 1]; b += kBlock) x = rmin(x, p.part[b]);
-  x = block_min(x);
-  if (threadIdx.x == 0) d.dt[m] = cfl * x;
-}
-
-// Smallest and largest flow speed |v| over each CFL block's vertices (the Bx
-// sensor's range), at W^n (MODE 0), at W* held in Ws (MODE 1) or at W*
-// formed from the stage-1 residual (MODE 2, tiled form); then per mesh.
-template <int MODE>
-__global__ __launch_bounds__(kBlock) void k_vrange(Dev d, CflPlan p) {
-  const int b = blockIdx.x;
-  double lo = INFINITY, hi = 0.0;
-#pragma unroll
-  for (int u = 0; u < kCflSpan / kBlock; ++u) {
-    const int64_t v = (int64_t)p.blk_v0[b] + u * kBlock + threadIdx.x;
-    if (v < p.blk_v1[b]) {
-      const D4 w = MODE == 0 ? d.W[v] : (MODE == 1 ? d.Ws[v] : star_state(d, v, d.bc ? d.bc[v] : -1,
-                                                                            d.vmesh ? d.vmesh[v] : 0));
-      const double sp = flow_speed(w);
-      lo = rmin(lo, sp);
-      hi = rmax(hi, sp);
-    }
-  }
-  lo = block_min(lo);
-  __syncthreads();
-  hi = -block_min(-hi);
-  if (threadIdx.x == 0) {
-    p.vpart[2 * b] = lo;
-    p.vpart[2 * b + 1] = hi;
-  }
-}
-
-__global__ __launch_bounds__(kBlock) void k_vrange_final(Dev d, CflPlan p) {
-  const int m = blockIdx.x;
-  double lo = INFINITY, hi = 0.0;
-  for (int b = p.mesh_b0[m] + threadIdx.x; b < p.mesh_b0[m + 1]; b += kBlock) {
-    lo = rmin(lo, p.vpart[2 * b]);
-    hi = rmax(hi, p.vpart[2 * b + 1]);
-  }
-  lo = block_min(lo);
-  __syncthreads();
-  hi = -block_min(-hi);
-  if (threadIdx.x == 0) {
-    d.vr[3 * m] = lo;
-    d.vr[3 * m + 1] = hi;
-  }
-}
-
-__global__ __launch_bounds__(kBlock) void k_set_state(Dev d, const double* soa, int fp32) {
+__global__ __launch_bounds__(kBlock) void k_set_state(Dev d, const double* soa) {
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (v >= d.nv) return;
   const double w[4] = {soa[v], soa[d.nv + v], soa[2 * d.nv + v], soa[3 * d.nv + v]};
   st4<double>(d.W, v, w);
-  vertex_epilogue(d, v, w, fp32 != 0);
+  if (!vertex_z(d, v, w)) d.flag[0] = 1;
 }
 
-__global__ __launch_bounds__(kBlock) void k_refresh(Dev d, int fp32) {
+// The state, wherever it is, into d.W with its Z, and (thread b < nwv) the
+// wall term of wall vertex b: one launch instead of three, where a call on a
+// small mesh is little but its launches.
+__global__ __launch_bounds__(kBlock) void k_view(Dev d, State st) {
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (v < d.nwv) {
+    D4 acc;
+    wall_term(d.went, d.wptr[v], d.wptr[v + 1], d.wv[v], d.gamma, [&](int64_t i) { return *st.at(i); }, acc.v);
+    d.WCn[v] = acc;
+  }
   if (v >= d.nv) return;
-  const D4 w = d.W[v];
-  vertex_epilogue(d, v, w.v, fp32 != 0);
-}
-
-__global__ __launch_bounds__(kBlock) void k_aos_to_soa(const D4* src, double* soa, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  const D4 w = src[i];
-  for (int k = 0; k < 4; ++k) soa[k * n + i] = w.v[k];
+  const D4 w = *st.at(v);
+  d.W[v] = w;
+  vertex_z(d, v, w.v);
 }
 
 // FP64 kept triangle residuals (two 16-byte planes: components 0-1, then
@@ -156,17 +66,11 @@ __global__ __launch_bounds__(kBlock) void k_keep_to_soa(const double2* src, doub
 
 __global__ void k_set_scalar(double* p, double v) { p[0] = v; }
 __global__ void k_set_int(int* p, int v) { p[0] = v; }
-__global__ void k_or_int(int* dst, const int* src) { dst[0] = dst[0] | src[0]; }
 __global__ __launch_bounds__(kBlock) void k_fill_int(int* p, int v, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < n) p[i] = v;
 }
 
-
-__global__ __launch_bounds__(kBlock) void k_copy4(D4* dst, const D4* src, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) dst[i] = src[i];
-}
 
 // ------------------------------------------------------------- adjoint --
 
@@ -192,20 +96,6 @@ __global__ __launch_bounds__(kBlock) void k_adj_gather2(Dev d, AdjDev a) {
 __global__ __launch_bounds__(kBlock) void k_adj_gather1(Dev d, AdjDev a, int rk2, double* out) {
   const int64_t v = xcd_block() * kBlock + threadIdx.x;
   if (v < d.nv) adj_gather1_body(v, d, a, rk2 != 0, out);
-}
-
-__global__ __launch_bounds__(kBlock) void k_soa_to_aos(const double* soa, D4* dst, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  const double w[4] = {soa[i], soa[n + i], soa[2 * n + i], soa[3 * n + i]};
-  st4<double>(dst, i, w);
-}
-
-__global__ __launch_bounds__(kBlock) void k_zero4(D4* dst, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  const double z[4] = {0.0, 0.0, 0.0, 0.0};
-  st4<double>(dst, i, z);
 }
 
 // Staged reverse triangle passes. Each one-wavefront workgroup walks a
@@ -456,124 +346,46 @@ hipError_t launch_adj_star(const Dev& d, const AdjDev& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_soa_to_aos(const double* soa, D4* dst, int64_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_soa_to_aos, dim3(nblk(n)), dim3(kBlock), 0, s, soa, dst, n);
-  return hipGetLastError();
-}
-
-template <typename R, int SCHEME, int STAGE, bool SAVE, bool CFL, bool LUMP = false>
-static hipError_t tri_launch(const Dev& d, hipStream_t s) {
-  hipLaunchKernelGGL((k_tri<R, SCHEME, STAGE, SAVE, CFL, LUMP>), dim3(nblk(d.nt)), dim3(kBlock), 0, s, d);
-  return hipGetLastError();
-}
-
-template <typename R, int SCHEME>
-static hipError_t tri_dispatch(const Dev& d, int stage, bool save, bool cfl, hipStream_t s) {
-  if (stage == 1 && save && cfl) return tri_launch<R, SCHEME, 1, true, true>(d, s);
-  if (stage == 1 && save) return tri_launch<R, SCHEME, 1, true, false>(d, s);
-  if (stage == 1 && cfl) return tri_launch<R, SCHEME, 1, false, true>(d, s);
-  if (stage == 1) return tri_launch<R, SCHEME, 1, false, false>(d, s);
-  if (d.slump) return tri_launch<R, SCHEME, 2, false, false, true>(d, s);
-  return tri_launch<R, SCHEME, 2, false, false>(d, s);
-}
-
-template <typename R>
-static hipError_t tri_scheme(const Dev& d, int scheme, int stage, bool save, bool cfl, hipStream_t s) {
-  switch (scheme) {
-    case SCH_N: return tri_dispatch<R, SCH_N>(d, stage, save, cfl, s);
-    case SCH_LDA: return tri_dispatch<R, SCH_LDA>(d, stage, save, cfl, s);
-    case SCH_B: return tri_dispatch<R, SCH_B>(d, stage, save, cfl, s);
-    case SCH_BMAX: return tri_dispatch<R, SCH_BMAX>(d, stage, save, cfl, s);
-    case SCH_BMIN: return tri_dispatch<R, SCH_BMIN>(d, stage, save, cfl, s);
-    case SCH_BX: return tri_dispatch<R, SCH_BX>(d, stage, save, cfl, s);
-  }
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_tri(const Dev& d, int fp32, int scheme, int stage, bool save, bool cfl, hipStream_t s) {
+hipError_t launch_tri(const Dev& d, int scheme, hipStream_t s) {
   if (d.nt == 0) return hipSuccess;
-  return fp32 ? tri_scheme<float>(d, scheme, stage, save, cfl, s)
-              : tri_scheme<double>(d, scheme, stage, save, cfl, s);
-}
-
-template <typename R>
-static hipError_t gather_mode(const Dev& d, int mode, double* out, hipStream_t s) {
-  const dim3 g(nblk(d.nv)), b(kBlock);
-  switch (mode) {
-    case G_EULER: hipLaunchKernelGGL((k_gather<R, G_EULER>), g, b, 0, s, d, out); break;
-    case G_STAGE1: hipLaunchKernelGGL((k_gather<R, G_STAGE1>), g, b, 0, s, d, out); break;
-    case G_STAGE2: hipLaunchKernelGGL((k_gather<R, G_STAGE2>), g, b, 0, s, d, out); break;
-    case G_RESIDUAL: hipLaunchKernelGGL((k_gather<R, G_RESIDUAL>), g, b, 0, s, d, out); break;
+  const dim3 g(nblk(d.nt)), b(kBlock);
+  switch (scheme) {
+    case SCH_N: hipLaunchKernelGGL(k_tri<SCH_N>, g, b, 0, s, d); break;
+    case SCH_LDA: hipLaunchKernelGGL(k_tri<SCH_LDA>, g, b, 0, s, d); break;
+    case SCH_B: hipLaunchKernelGGL(k_tri<SCH_B>, g, b, 0, s, d); break;
+    case SCH_BMAX: hipLaunchKernelGGL(k_tri<SCH_BMAX>, g, b, 0, s, d); break;
+    case SCH_BMIN: hipLaunchKernelGGL(k_tri<SCH_BMIN>, g, b, 0, s, d); break;
+    case SCH_BX: hipLaunchKernelGGL(k_tri<SCH_BX>, g, b, 0, s, d); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_gather(const Dev& d, int fp32, int mode, double* out_soa, hipStream_t s) {
-  if (d.nv == 0) return hipSuccess;
-  return fp32 ? gather_mode<float>(d, mode, out_soa, s) : gather_mode<double>(d, mode, out_soa, s);
+hipError_t launch_residual(const Dev& d, double* out_soa, hipStream_t s) {
+  hipLaunchKernelGGL(k_residual, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, out_soa);
+  return hipGetLastError();
 }
 
-hipError_t launch_wall(const Dev& d, bool stage2, hipStream_t s, bool tiled) {
+hipError_t launch_wall(const Dev& d, bool stage2, hipStream_t s) {
   if (d.nwv == 0) return hipSuccess;
-  if (stage2 && tiled) hipLaunchKernelGGL((k_wall<true, true>), dim3(nblk(d.nwv)), dim3(kBlock), 0, s, d);
-  else if (stage2) hipLaunchKernelGGL((k_wall<true, false>), dim3(nblk(d.nwv)), dim3(kBlock), 0, s, d);
-  else hipLaunchKernelGGL((k_wall<false, false>), dim3(nblk(d.nwv)), dim3(kBlock), 0, s, d);
+  if (stage2) hipLaunchKernelGGL(k_wall<true>, dim3(nblk(d.nwv)), dim3(kBlock), 0, s, d);
+  else hipLaunchKernelGGL(k_wall<false>, dim3(nblk(d.nwv)), dim3(kBlock), 0, s, d);
   return hipGetLastError();
 }
 
-hipError_t launch_cfl_part(const Dev& d, const CflPlan& p, double cfl, int part, hipStream_t s, int fp32) {
-  if (part == 0) hipLaunchKernelGGL(k_cfl_tri, dim3(nblk(d.nt)), dim3(kBlock), 0, s, d);
-  else if (part == 1 && fp32) hipLaunchKernelGGL((k_cfl_vertex<false, float>), dim3(p.nblocks), dim3(kBlock), 0, s, d, p);
-  else if (part == 1) hipLaunchKernelGGL((k_cfl_vertex<false, double>), dim3(p.nblocks), dim3(kBlock), 0, s, d, p);
-  else if (part == 3) hipLaunchKernelGGL((k_cfl_vertex<true, double>), dim3(p.nblocks), dim3(kBlock), 0, s, d, p);
-  else hipLaunchKernelGGL(k_cfl_final, dim3(p.nmesh), dim3(kBlock), 0, s, d, p, cfl);
+hipError_t launch_set_state(const Dev& d, const double* soa, hipStream_t s) {
+  hipLaunchKernelGGL(k_set_state, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, soa);
   return hipGetLastError();
 }
 
-hipError_t launch_vrange(const Dev& d, const CflPlan& p, int mode, hipStream_t s) {
-  if (p.nblocks == 0) return hipSuccess;
-  if (mode == 0) hipLaunchKernelGGL(k_vrange<0>, dim3(p.nblocks), dim3(kBlock), 0, s, d, p);
-  else if (mode == 1) hipLaunchKernelGGL(k_vrange<1>, dim3(p.nblocks), dim3(kBlock), 0, s, d, p);
-  else if (mode == 2) hipLaunchKernelGGL(k_vrange<2>, dim3(p.nblocks), dim3(kBlock), 0, s, d, p);
-  else return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_vrange_final, dim3(p.nmesh), dim3(kBlock), 0, s, d, p);
+hipError_t launch_view(const Dev& d, const State& st, hipStream_t s) {
+  hipLaunchKernelGGL(k_view, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, st);
   return hipGetLastError();
 }
 
-hipError_t launch_cfl(const Dev& d, const CflPlan& p, double cfl, hipStream_t s) {
-  for (int part = 0; part < 3; ++part) {
-    hipError_t e = launch_cfl_part(d, p, cfl, part, s);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
-hipError_t launch_set_state(const Dev& d, const double* soa, int fp32, hipStream_t s) {
-  hipLaunchKernelGGL(k_set_state, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, soa, fp32);
-  return hipGetLastError();
-}
-
-hipError_t launch_refresh(const Dev& d, int fp32, hipStream_t s) {
-  hipLaunchKernelGGL(k_refresh, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, fp32);
-  return hipGetLastError();
-}
-
-hipError_t launch_get_state(const Dev& d, const D4* src, double* soa, hipStream_t s) {
-  hipLaunchKernelGGL(k_aos_to_soa, dim3(nblk(d.nv)), dim3(kBlock), 0, s, src, soa, d.nv);
-  return hipGetLastError();
-}
-
-hipError_t launch_aos_to_soa(const D4* src, double* soa, int64_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_aos_to_soa, dim3(nblk(n)), dim3(kBlock), 0, s, src, soa, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_keep_to_soa(const void* keep, double* soa, int64_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_keep_to_soa, dim3(nblk(n)), dim3(kBlock), 0, s, static_cast<const double2*>(keep), soa, n);
+hipError_t launch_keep_to_soa(const Dev& d, double* soa, hipStream_t s) {
+  hipLaunchKernelGGL(k_keep_to_soa, dim3(nblk(d.nt)), dim3(kBlock), 0, s, static_cast<const double2*>(d.keepT),
+                     soa, d.nt);
   return hipGetLastError();
 }
 
@@ -590,17 +402,6 @@ hipError_t launch_set_int(int* p, int v, hipStream_t s) {
 hipError_t launch_fill_int(int* p, int v, int64_t n, hipStream_t s) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_fill_int, dim3(nblk(n)), dim3(kBlock), 0, s, p, v, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_or_int(int* dst, const int* src, hipStream_t s) {
-  hipLaunchKernelGGL(k_or_int, dim3(1), dim3(1), 0, s, dst, src);
-  return hipGetLastError();
-}
-
-hipError_t launch_copy4(D4* dst, const D4* src, int64_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_copy4, dim3(nblk(n)), dim3(kBlock), 0, s, dst, src, n);
   return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-// Bodies of the tiled (fused) step.
+// Bodies of the tiled form of the FP32 step.
 //
 // One workgroup takes one tile of triangles (built on the host, see
 // rd_tiling.h) in three phases separated by workgroup barriers:
@@ -16,7 +16,7 @@
 // W^n - (dt/V) R1, by the arithmetic of the two-pass gather.
 #pragma once
 
-#include "rd_device.h"
+#include "rd_fp32.h"
 
 namespace rd {
 
@@ -35,45 +35,43 @@ struct Tiles {
   const int32_t* tmesh = nullptr; // [ntiles] mesh id (batches) or null
   const int32_t* sv = nullptr;    // [nsv] shared vertices
   const int32_t* ssbeg = nullptr; // [nsv] first shared part slot (stride 64)
-  void* Cs = nullptr;             // [nss] shared parts (D4 or F4)
+  F4* Cs = nullptr;               // [nss] shared parts
   double* lams = nullptr;         // [nss] shared CFL terms
 };
 
 // LDS carve-up of one tile workgroup.
-template <typename R>
 struct TileLds {
   double2* xy = nullptr;  // [max_lv]
-  Q4<R>* Z = nullptr;     // [max_lv] parameter vector (at W^n, or W* in stage 2)
-  Q4<R>* dW = nullptr;    // [max_lv] stage 2: W* - W^n
+  F4* Z = nullptr;     // [max_lv] parameter vector (at W^n, or W* in stage 2)
+  F4* dW = nullptr;    // [max_lv] stage 2: W* - W^n
   D4* Ws = nullptr;       // [max_lvi] stage 2: W* of interior vertices
   double* sig = nullptr;  // [max_lv] CFL: signal speed
   double* lam = nullptr;  // [max_slots] CFL: l_max lambda_max per interior corner
-  Q4<R>* P = nullptr;     // [max_slots] parts of interior corners
+  F4* P = nullptr;     // [max_slots] parts of interior corners
 };
 
 __host__ __device__ inline size_t lds_align(size_t x) { return (x + 31) & ~size_t(31); }
 
 // Bytes of LDS a tile workgroup needs; with base != null also sets out.
-template <typename R>
-__host__ __device__ inline size_t tile_lds(const Tiles& tl, int stage, bool cfl, char* base, TileLds<R>* out) {
+__host__ __device__ inline size_t tile_lds(const Tiles& tl, int stage, bool cfl, char* base, TileLds* out) {
   size_t o = 0;
   auto take = [&](size_t bytes) -> char* {
     char* p = base ? base + o : nullptr;
     o = lds_align(o + bytes);
     return p;
   };
-  TileLds<R> L;
+  TileLds L;
   L.xy = reinterpret_cast<double2*>(take(sizeof(double2) * tl.max_lv));
-  L.Z = reinterpret_cast<Q4<R>*>(take(sizeof(Q4<R>) * tl.max_lv));
+  L.Z = reinterpret_cast<F4*>(take(sizeof(F4) * tl.max_lv));
   if (stage == 2) {
-    L.dW = reinterpret_cast<Q4<R>*>(take(sizeof(Q4<R>) * tl.max_lv));
+    L.dW = reinterpret_cast<F4*>(take(sizeof(F4) * tl.max_lv));
     L.Ws = reinterpret_cast<D4*>(take(sizeof(D4) * tl.max_lvi));
   }
   if (cfl) {
     L.sig = reinterpret_cast<double*>(take(sizeof(double) * tl.max_lv));
     L.lam = reinterpret_cast<double*>(take(sizeof(double) * tl.max_slots));
   }
-  L.P = reinterpret_cast<Q4<R>*>(take(sizeof(Q4<R>) * tl.max_slots));
+  L.P = reinterpret_cast<F4*>(take(sizeof(F4) * tl.max_slots));
   if (out) *out = L;
   return o;
 }
@@ -81,25 +79,22 @@ __host__ __device__ inline size_t tile_lds(const Tiles& tl, int stage, bool cfl,
 __host__ __device__ inline int tile_mesh(const Tiles& tl, int64_t tile) { return tl.tmesh ? tl.tmesh[tile] : 0; }
 
 // Triangle IO of the tiled form.
-template <typename R>
 struct TileIO {
-  // fast FP64 reciprocals in the triangle body (see rcp)
-  static constexpr bool kFastDiv = true;
-  const TileLds<R>& L;
+  const TileLds& L;
   int lvi[3];
   int32_t dst[3];
-  void* Cs;
+  F4* Cs;
   double* lams;
-  R idt_;
+  float idt_;
   const double* vr_;
-  __host__ __device__ R idt(int64_t) const { return idt_; }
+  __host__ __device__ float idt(int64_t) const { return idt_; }
   __host__ __device__ const double* vr(int64_t) const { return vr_; }
-  __host__ __device__ Q4<R> dw(int i) const { return L.dW[lvi[i]]; }
-  __host__ __device__ void part(int i, const R out[4]) const {
-    Q4<R> q;
+  __host__ __device__ F4 dw(int i) const { return L.dW[lvi[i]]; }
+  __host__ __device__ void part(int i, const float out[4]) const {
+    F4 q;
     for (int k = 0; k < 4; ++k) q.v[k] = out[k];
     if (dst[i] < 0) L.P[-1 - dst[i]] = q;
-    else reinterpret_cast<Q4<R>*>(Cs)[dst[i]] = q;
+    else Cs[dst[i]] = q;
   }
   // the triangle's CFL term goes to each of its corners (interior corners in
   // LDS, shared ones to the shared-slot buffer)
@@ -111,47 +106,66 @@ struct TileIO {
   }
 };
 
+// The first-stage state W* = W^n - (dt / V) R1 of vertex v in the tiled form
+// (ghosts keep W^n), by the same arithmetic as the two-pass gather.
+__host__ __device__ inline D4 star_state(const Dev& d, const Dev32& h, int64_t v, int32_t code, int m) {
+  const D4 win = d.W[v];
+  if (is_ghost(code)) return win;
+  const double f = d.dt[m] / d.V[v];
+  const D4 r = h.R1[v];
+  D4 o;
+  vertex_update(win.v, f, r.v, o.v);
+  return o;
+}
+
+// The wall term of wall vertex b at W*.
+__host__ __device__ inline void tile_wall2(int64_t b, const Dev& d, const Dev32& h) {
+  D4 acc;
+  wall_term(d.went, d.wptr[b], d.wptr[b + 1], d.wv[b], d.gamma,
+            [&](int64_t i) { return star_state(d, h, i, d.bc[i], d.vmesh ? d.vmesh[i] : 0); }, acc.v);
+  d.WCs[b] = acc;
+}
+
 // ---- phase bodies (tile = workgroup id, l / j = local vertex / triangle) --
 
-template <typename R, bool CFL>
-__host__ __device__ inline void tile_load1(int64_t tile, int32_t l, const Dev& d, const Tiles& tl,
-                                           const TileLds<R>& L) {
+template <bool CFL>
+__host__ __device__ inline void tile_load1(int64_t tile, int32_t l, const Dev& d, const Dev32& h, const Tiles& tl,
+                                           const TileLds& L) {
   const int32_t v = tl.tvl[tl.vbeg[tile] + l];
   L.xy[l] = d.xy[v];
-  L.Z[l] = zbuf<R>(d)[v];
+  L.Z[l] = h.Zf[v];
   if (CFL) L.sig[l] = d.sig[v];
 }
 
-template <typename R>
-__host__ __device__ inline void tile_load2(int64_t tile, int32_t l, const Dev& d, const Tiles& tl,
-                                           const TileLds<R>& L) {
+__host__ __device__ inline void tile_load2(int64_t tile, int32_t l, const Dev& d, const Dev32& h, const Tiles& tl,
+                                           const TileLds& L) {
   const int32_t v = tl.tvl[tl.vbeg[tile] + l];
   L.xy[l] = d.xy[v];
   const int32_t code = d.bc ? d.bc[v] : -1;
-  Q4<R> dw;
+  F4 dw;
   if (is_ghost(code)) {
-    L.Z[l] = zbuf<R>(d)[v];
-    for (int k = 0; k < 4; ++k) dw.v[k] = R(0);
+    L.Z[l] = h.Zf[v];
+    for (int k = 0; k < 4; ++k) dw.v[k] = 0.0f;
     L.dW[l] = dw;
     return;
   }
   const D4 win = d.W[v];
-  const D4 ws = star_state(d, v, code, tile_mesh(tl, tile));
-  for (int k = 0; k < 4; ++k) dw.v[k] = (R)(ws.v[k] - win.v[k]);
+  const D4 ws = star_state(d, h, v, code, tile_mesh(tl, tile));
+  for (int k = 0; k < 4; ++k) dw.v[k] = (float)(ws.v[k] - win.v[k]);
   L.dW[l] = dw;
   const VertexDerived o = derive(d.gamma, ws.v);
-  L.Z[l] = zq<R>(o);
+  L.Z[l] = zf_of(o);
   if (!o.ok) d.flag[tile_mesh(tl, tile)] = 1;
   if (l < tl.nvi[tile]) L.Ws[l] = ws;
 }
 
-template <typename R, int SCHEME, int STAGE, bool SAVE, bool CFL, bool LUMP = false>
-__host__ __device__ inline void tile_tri(int64_t tile, int32_t j, const Dev& d, const Tiles& tl,
-                                         const TileLds<R>& L) {
+template <int SCHEME, int STAGE, bool SAVE, bool CFL, bool LUMP = false>
+__host__ __device__ inline void tile_tri(int64_t tile, int32_t j, const Dev& d, const Dev32& h, const Tiles& tl,
+                                         const TileLds& L) {
   const int64_t s = (int64_t)tl.tbeg[tile] + j;
   const int64_t nt = d.nt;
-  TileIO<R> io{L, {0, 0, 0}, {0, 0, 0}, tl.Cs, tl.lams, R(0), d.vr + 3 * tile_mesh(tl, tile)};
-  TriIn<R> in;
+  TileIO io{L, {0, 0, 0}, {0, 0, 0}, tl.Cs, tl.lams, 0.0f, d.vr + 3 * tile_mesh(tl, tile)};
+  TriIn32 in;
   for (int i = 0; i < 3; ++i) {
     const int q = tl.lv[i * nt + s];
     io.lvi[i] = q;
@@ -160,46 +174,45 @@ __host__ __device__ inline void tile_tri(int64_t tile, int32_t j, const Dev& d, 
     in.Z[i] = L.Z[q];
     if (CFL) in.sig[i] = L.sig[q];
   }
-  if (STAGE == 2) io.idt_ = (R)(1.0 / d.dt[tile_mesh(tl, tile)]);
-  tri_compute<R, SCHEME, STAGE, SAVE, CFL, LUMP>(s, in, d, io);
+  if (STAGE == 2) io.idt_ = (float)(1.0 / d.dt[tile_mesh(tl, tile)]);
+  tri32_compute<SCHEME, STAGE, SAVE, CFL, LUMP>(s, in, d, h, io);
 }
 
 // Stage-1 (or Euler) sum of interior vertex l: R1 = sum of parts + wall term,
 // and with CFL the vertex bound 2 V / sum l_max lambda_max.
-template <typename R, bool CFL>
-__host__ __device__ inline void tile_sum1(int64_t tile, int32_t l, const Dev& d, const Tiles& tl,
-                                          const TileLds<R>& L) {
+template <bool CFL>
+__host__ __device__ inline void tile_sum1(int64_t tile, int32_t l, const Dev& d, const Dev32& h, const Tiles& tl,
+                                          const TileLds& L) {
   const int32_t v = tl.tvl[tl.vbeg[tile] + l];
   const int32_t* lp = tl.lp + tl.lpb[tile];
   const int32_t a = lp[l], n = lp[l + 1] - a;
   if (CFL) {
     double acc = 0.0;
     for (int32_t j = 0; j < n; ++j) acc += L.lam[a + j];
-    d.cflv[v] = 2.0 * d.V[v] / acc;
+    h.cflv[v] = 2.0 * d.V[v] / acc;
   }
   const int32_t code = d.bc ? d.bc[v] : -1;
   if (is_ghost(code)) return;
   D4 acc;
-  sum_parts<R>(n, [&](int32_t j) { return L.P[a + j]; }, acc.v);
+  sum_parts32(n, [&](int32_t j) { return L.P[a + j]; }, acc.v);
   const int32_t b = wall_index(code);
   if (b >= 0) {
     const D4 wn = d.WCn[b];
     for (int k = 0; k < 4; ++k) acc.v[k] = acc.v[k] + wn.v[k];
   }
-  d.R1[v] = acc;
+  h.R1[v] = acc;
 }
 
 // Stage-2 sum and update of interior vertex l.
-template <typename R>
-__host__ __device__ inline void tile_sum2(int64_t tile, int32_t l, const Dev& d, const Tiles& tl,
-                                          const TileLds<R>& L) {
+__host__ __device__ inline void tile_sum2(int64_t tile, int32_t l, const Dev& d, const Dev32& h, const Tiles& tl,
+                                          const TileLds& L) {
   const int32_t v = tl.tvl[tl.vbeg[tile] + l];
   const int32_t code = d.bc ? d.bc[v] : -1;
   if (is_ghost(code)) return;
   const int32_t* lp = tl.lp + tl.lpb[tile];
   const int32_t a = lp[l], n = lp[l + 1] - a;
   double acc[4];
-  sum_parts<R>(n, [&](int32_t j) { return L.P[a + j]; }, acc);
+  sum_parts32(n, [&](int32_t j) { return L.P[a + j]; }, acc);
   const int32_t b = wall_index(code);
   if (b >= 0) {
     const D4 wn = d.WCn[b], ws = d.WCs[b];
@@ -210,44 +223,43 @@ __host__ __device__ inline void tile_sum2(int64_t tile, int32_t l, const Dev& d,
   double wo[4];
   vertex_update(win.v, f, acc, wo);
   st4<double>(d.W, v, wo);
-  vertex_epilogue(d, v, wo, sizeof(R) != sizeof(double));
+  vertex_epilogue32(d, h, v, wo, true);
 }
 
 // Shared vertex k, stage 1 (or Euler): as tile_sum1 over the shared buffer.
-template <typename R, bool CFL>
-__host__ __device__ inline void shared_sum1(int64_t k, const Dev& d, const Tiles& tl) {
+template <bool CFL>
+__host__ __device__ inline void shared_sum1(int64_t k, const Dev& d, const Dev32& h, const Tiles& tl) {
   const int32_t v = tl.sv[k];
   const int32_t n = d.row[v + 1] - d.row[v];
   const int64_t s0 = tl.ssbeg[k];
   if (CFL) {
     double acc = 0.0;
     for_loaded(n, [&](int32_t j) { return tl.lams[s0 + 64 * (int64_t)j]; }, [&](int32_t, double x) { acc += x; });
-    d.cflv[v] = 2.0 * d.V[v] / acc;
+    h.cflv[v] = 2.0 * d.V[v] / acc;
   }
   const int32_t code = d.bc ? d.bc[v] : -1;
   if (is_ghost(code)) return;
   D4 acc;
-  sum_parts<R>(n, [&](int32_t j) { return ld4<R>(tl.Cs, s0 + 64 * (int64_t)j); }, acc.v);
+  sum_parts32(n, [&](int32_t j) { return tl.Cs[s0 + 64 * (int64_t)j]; }, acc.v);
   const int32_t b = wall_index(code);
   if (b >= 0) {
     const D4 wn = d.WCn[b];
     for (int k = 0; k < 4; ++k) acc.v[k] = acc.v[k] + wn.v[k];
   }
-  d.R1[v] = acc;
+  h.R1[v] = acc;
 }
 
 // Shared vertex k, stage 2: rebuild W*, sum, update.
-template <typename R>
-__host__ __device__ inline void shared_sum2(int64_t k, const Dev& d, const Tiles& tl) {
+__host__ __device__ inline void shared_sum2(int64_t k, const Dev& d, const Dev32& h, const Tiles& tl) {
   const int32_t v = tl.sv[k];
   const int32_t code = d.bc ? d.bc[v] : -1;
   if (is_ghost(code)) return;
   const int m = d.vmesh ? d.vmesh[v] : 0;
-  const D4 ws = star_state(d, v, code, m);
+  const D4 ws = star_state(d, h, v, code, m);
   const int32_t n = d.row[v + 1] - d.row[v];
   const int64_t s0 = tl.ssbeg[k];
   double acc[4];
-  sum_parts<R>(n, [&](int32_t j) { return ld4<R>(tl.Cs, s0 + 64 * (int64_t)j); }, acc);
+  sum_parts32(n, [&](int32_t j) { return tl.Cs[s0 + 64 * (int64_t)j]; }, acc);
   const int32_t b = wall_index(code);
   if (b >= 0) {
     const D4 wn = d.WCn[b], wcs = d.WCs[b];
@@ -257,16 +269,16 @@ __host__ __device__ inline void shared_sum2(int64_t k, const Dev& d, const Tiles
   double wo[4];
   vertex_update(ws.v, f, acc, wo);
   st4<double>(d.W, v, wo);
-  vertex_epilogue(d, v, wo, sizeof(R) != sizeof(double));
+  vertex_epilogue32(d, h, v, wo, true);
 }
 
 // Forward-Euler update of vertex v from R1.
-__host__ __device__ inline void euler_apply(int64_t v, const Dev& d, bool fp32) {
+__host__ __device__ inline void euler_apply(int64_t v, const Dev& d, const Dev32& h) {
   const int32_t code = d.bc ? d.bc[v] : -1;
   if (is_ghost(code)) return;
-  const D4 wo = star_state(d, v, code, d.vmesh ? d.vmesh[v] : 0);
+  const D4 wo = star_state(d, h, v, code, d.vmesh ? d.vmesh[v] : 0);
   d.W[v] = wo;
-  vertex_epilogue(d, v, wo.v, fp32);
+  vertex_epilogue32(d, h, v, wo.v, true);
 }
 
 }  // namespace rd

@@ -1,0 +1,90 @@
+"""The state moves between the two forms of the step (FP64 patches, FP32 passes,
+each in its own vertex order) without a change: steps of both precisions
+interleaved, tile sizes changed between them, and captured steps replayed
+after the state has moved, bitwise equal to the same steps on fresh meshes."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_1705_02028_amd import inputs as I
+
+
+@pytest.fixture(scope="module")
+def rd():
+    from paper_1705_02028_amd import rd
+    return rd
+
+
+def problem(kind):
+    if kind == "box":
+        m = I.split_square(37, periodic=(False, False), bc=("ghost", "wall"), seed=2, jitter=0.1, renumber="random")
+    else:
+        m = I.split_square(24, seed=2, diagonal="random", renumber="random")
+    return m, I.ic_kelvin_helmholtz(m, seed=1)
+
+
+def fresh(rd, m, W, prec, tile, scheme, n=1):
+    g = rd.Mesh(m)
+    g.tile = tile
+    g.set_state(W)
+    g.step_cfl(n, 0.3, scheme, rd.RK2, prec)
+    out = g.get_state()
+    g.close()
+    return out
+
+
+@pytest.mark.parametrize("kind", ["box", "periodic"])
+@pytest.mark.parametrize("scheme", [2, 5])  # B, Bx
+def test_precisions_and_tiles_interleaved(rd, kind, scheme):
+    m, W = problem(kind)
+    g = rd.Mesh(m)
+    g.set_state(W)
+    seq = [(rd.FP64, 0), (rd.FP32_ACC64, 0), (rd.FP32_ACC64, 64), (rd.FP64, 64), (rd.FP32_ACC64, 64),
+           (rd.FP32_ACC64, 256), (rd.FP64, 256), (rd.FP32_ACC64, 0)]
+    ref = W
+    for prec, tile in seq:
+        g.tile = tile
+        g.step_cfl(1, 0.3, scheme, rd.RK2, prec)
+        ref = fresh(rd, m, ref, prec, tile, scheme)
+        if prec == rd.FP64:  # the CFL bounds of either form
+            h = rd.Mesh(m)
+            h.set_state(ref)
+            assert g.max_dt(0.3) == pytest.approx(h.max_dt(0.3), rel=1e-14)
+            h.close()
+        assert np.array_equal(g.get_state(), ref), (prec, tile)
+    g.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("tile", [0, 64])
+def test_captured_steps_replay_after_the_state_moved(rd, prec, tile):
+    m, W = problem("box")
+    s = torch.cuda.Stream()
+    g = rd.Mesh(m)
+    g.tile = tile
+    other = rd.FP32_ACC64 if prec == rd.FP64 else rd.FP64
+    for p in (other, prec):  # buffers of both forms
+        g.set_state(W)
+        g.step_cfl(1, 0.3, rd.B, rd.RK2, p)
+    torch.cuda.synchronize()
+    rd.rd_set_stream(g.h, s.cuda_stream)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s, capture_error_mode="thread_local"):
+        g.step_cfl(2, 0.3, rd.B, rd.RK2, prec)
+    g.set_state(W)
+    ref = W
+    for k in range(4):
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = fresh(rd, m, ref, prec, tile, rd.B, 2)
+        assert np.array_equal(g.get_state(), ref), k
+        if k % 2 == 0:  # the state leaves the captured form
+            g.step_cfl(1, 0.3, rd.B, rd.RK2, other)
+            g.sync()
+            ref = fresh(rd, m, ref, other, tile, rd.B)
+        else:
+            g.set_state(ref)
+    g.close()
