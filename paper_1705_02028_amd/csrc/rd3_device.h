@@ -1,59 +1,86 @@
 // Three-dimensional residual distribution on tetrahedra (the method of
 // Section 3 with a row and a column added to every matrix, as the paper's
-// closing discussion describes): per-tetrahedron and per-vertex bodies of the
-// gfx950 kernels in rd3_kernels.hip. FP64 throughout.
+// closing discussion describes): bodies of the gfx950 kernels in
+// rd3_kernels.hip. FP64 throughout.
 //
-// For a unit normal n the flux Jacobian K(n) = R diag(l) R^{-1} of the Euler
-// equations is applied in its rank-two form: with the pressure gradient
-// g = (g1 |u|^2 / 2, -g1 u, g1) (dp = g . dW), the normal-velocity row
-// m = (-u.n, n, 0) (rho du.n = m . dW), r0 = (1, u, H) and s = (0, n, u.n),
-// K x = l3 x + r0 ((l123 / c^2) g.x + (l12 / c) m.x) + s ((l12 / c) g.x + l123 m.x)
-// with l123 = (l1 + l2) / 2 - l3 and l12 = (l1 - l2) / 2 for the eigenvalues
-// l1 = u.n + c, l2 = u.n - c, l3 = u.n (or their positive or negative parts
-// for K^+ and K^-). This is the three-dimensional form of the entries of
-// Appendix A. K_i = (|n_i| / 3) K(n_i / |n_i|) with n_i the inward normal of
-// the face opposite corner i scaled by the face's area.
+// The algebra of a tetrahedron runs in symmetrising variables. At its Roe
+// state (u, H, c) a conserved perturbation x is held as y = (P, a, s),
+//   a = x_1..3 - u x_0,  P = dp / c,  s = x_0 - P / c,
+//   dp = (gamma - 1) (x_4 - (|u|^2 / 2) x_0 - u.a),
+// in which every K(n) is symmetric and the entropy component s decouples:
+// with N the inward normal of the face opposite a corner (twice its area
+// long), n = N / |N|, w = u.N and C = |N| c (up to the scale below),
+//   K y = (w P + C n.a, w a + n C P, w s),
+//   K^+ y = (p0 P + A P + B n.a, p0 a + n (B P + A n.a), p0 s)
+// with p0 = w^+, A = ((w + C)^+ + (w - C)^+) / 2 - p0, B = ((w + C)^+ -
+// (w - C)^+) / 2; K^- = K - K^+ has w - p0, -A and C - B. The distribution is
+// invariant under this change of variables; only the blends, whose
+// coefficients are per conserved component, need x itself. sum_i K_i^+ is a
+// symmetric 4x4 block, positive definite at every state (a null vector would
+// need P + n_i.a = 0 for four normals that span space), beside the scalar
+// sum_i p0_i: it is factored as L D L^T without pivoting, and a fluid at rest
+// is the scalar alone, whose unknown is 0 where the sum is at most 2^-45 of
+// the block's trace. A pivoted 5x5 elimination of the conserved matrix takes
+// more than twice the instructions.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
+#include "rd_math.h"
+
 namespace rd3 {
 
+using rd::len_rcp;
+using rd::rcp_normal;
+using rd::rmax;
+using rd::rmin;
+
 constexpr int kBlock = 256;
+constexpr int kTileTets = 256;    // most tetrahedra of a tile (one thread each)
+constexpr int kTileVerts = 256;   // most vertices
+// Doubles between two components' part planes in LDS: 4 parts of every
+// tetrahedron, and 13 more modulo 32, so that the sums of 13 neighbouring
+// vertices' five components fall on different banks.
+__host__ __device__ inline int part_plane(int tets) { return (4 * tets + 31) / 32 * 32 + 13; }
 
 enum { S_N = 0, S_LDA = 1, S_B = 2, S_BMAX = 3, S_BMIN = 4 };
 
-// Device view of a tetrahedral mesh and its state.
+// One tile: at most kTileTets tetrahedra, their vertices (by falling number of
+// the tile's tetrahedra at each), and the jagged diagonals their parts are
+// summed along.
+struct Tile3 {
+  int32_t t0, nt;    // tetrahedra
+  int32_t l0, nlv;   // local vertices
+  int32_t j0, nj;    // the tile's diagonals in jb
+};
+
+// Device view of a tetrahedral mesh and its state, vertices in internal order
+// (tile by tile).
 struct Dev3 {
-  int64_t nv = 0, nt = 0, ns = 0;  // vertices, tetrahedra, slots (4 nt plus slice padding)
-  double gamma = 1.4;
-  const int32_t* tet = nullptr;    // [4][nt] corners
-  const int32_t* slot = nullptr;   // [4][nt] slot of each corner's part
-  // Slots in sliced-ELL order: vertices in slices of 64; slice q owns
-  // [sbase[q], sbase[q] + 64 w_q) with w_q its largest degree; the j-th
-  // tetrahedron (ascending) of vertex v has slot sbase[v / 64] + 64 j + v % 64,
-  // so a wave summing its 64 vertices reads consecutive slots.
-  const int32_t* deg = nullptr;    // [nv] tetrahedra of vertex v
-  const int32_t* sbase = nullptr;  // [ceil(nv / 64)]
-  const double* nrm = nullptr;     // [12][nt] inward face normals scaled by area: component k of corner i at 3 i + k
-  const double* vol = nullptr;     // [nt] volume
-  const double* smax = nullptr;    // [nt] largest face area
-  const double* V = nullptr;       // [nv] vertex volume (sum of |T| / 4)
-  double* W = nullptr;             // [5][nv] state
-  double* Ws = nullptr;            // [5][nv] first-stage state
-  double* Z = nullptr;             // [5][nv] parameter vector of the state the next tetrahedron pass reads
-  double* rate = nullptr;          // [5][nv] (W* - W^n) / dt, written by the first vertex pass
-  double* sig = nullptr;           // [nv] |u| + c of W
-  double* part = nullptr;          // [5][ns] distributed parts by slot
-  double* keepN = nullptr;         // [15][nt] stage-1 N parts of corners 0-2 (component k of corner i at 5 i + k);
-                                   // corner 3's is the kept residual minus those three
-  double* keepT = nullptr;         // [5][nt] stage-1 residual
-  double* cpart = nullptr;         // [ns] CFL parts by slot
-  double* dt = nullptr;            // device scalar: the step's time step
-  double* bmin = nullptr;          // [blocks] partial minima of the CFL limit
-  int* flag = nullptr;             // non-physical state latch (rho <= 0, p <= 0 or not finite)
+  int64_t nv = 0;
+  int32_t ntiles = 0, threads = 0, max_lv = 0, max_tet = 0;
+  int32_t jb_at = 0, lds = 0;       // LDS of a tile workgroup: where its diagonals start, bytes
+  double gamma = 1.4, g1 = 0.4, ig1 = 2.5, gfac = 0.4 / 1.4;
+  double per[3] = {0, 0, 0}, half[3] = {0, 0, 0};  // periods, and half of each (infinite where not periodic)
+  const Tile3* tile = nullptr;      // [ntiles]
+  const uint4* tet = nullptr;       // [nt] of each corner its local vertex, and its part's slot << 16
+  const int32_t* lv = nullptr;      // vertex of each local vertex
+  const uint16_t* deg = nullptr;    // tile's tetrahedra at each local vertex
+  const int32_t* rpos = nullptr;    // record its sum goes to
+  const int32_t* jb = nullptr;      // first slot of each diagonal
+  const int32_t* rbeg = nullptr;    // [nv + 1] records of vertex v (ascending tile)
+  const int32_t* inv = nullptr;     // [nv] vertex of each of the caller's
+  const double* V = nullptr;        // [nv] vertex volume (sum of |T| / 4)
+  double* W = nullptr;              // [5][nv] state
+  double* Ws = nullptr;             // [5][nv] first-stage state
+  double2* r1 = nullptr;            // [nv][5] Z of W, |u| + c, position, unused
+  double2* r2 = nullptr;            // [nv][5] Z of W*, (W* - W^n) / dt
+  double* rec = nullptr;            // [records][6] a tile's sum of parts at a vertex, and of CFL terms
+  double* dt = nullptr;             // device scalar: the step's time step
+  double* bmin = nullptr;           // [blocks] partial minima of the CFL limit
+  int* flag = nullptr;              // non-physical state latch (rho <= 0, p <= 0 or not finite)
 };
 
 // Z and |u| + c of a state; returns whether it is physical (rho > 0, p > 0,
@@ -73,274 +100,217 @@ __device__ inline bool to_z(const double w[5], double gamma, double z[5], double
   return rho > 0.0 && p > 0.0 && isfinite(sig) && isfinite(z[4]) && isfinite(z[1] + z[2] + z[3]);
 }
 
-// Rank-two application y = scale * K(l1, l2, l3) x at one corner.
-struct Corner {
-  double n[3];   // unit normal
-  double un;     // u . n
-  double scale;  // |n_i| / 3
-};
+// Scale. The distribution is homogeneous in K and linear in the differences:
+// the code keeps K_i for 2 |N_i| where the scheme has |N_i| / 6 (the halves in
+// A and B are free then) and the differences from the sum of the corners'
+// parameter vectors where it has their mean, so residual and parts are 48
+// times the scheme's; stage 2 leaves out the halves of its means too (96).
+constexpr double kScale1 = 1.0 / 48.0, kScale2 = 1.0 / 96.0;
 
 struct Flow {
-  double u[3], H, c, g[5], r0[5];
+  double u[3], c, ic, hq, cg, gc;  // hq = |u|^2 / 2, cg = c / (gamma - 1), gc = (gamma - 1) / c
 };
 
-__device__ inline void kapply(const Flow& f, const Corner& q, double l1, double l2, double l3, const double x[5],
-                              double y[5]) {
-  const double l123 = 0.5 * (l1 + l2) - l3, l12 = 0.5 * (l1 - l2);
-  const double gx = f.g[0] * x[0] + f.g[1] * x[1] + f.g[2] * x[2] + f.g[3] * x[3] + f.g[4] * x[4];
-  const double mx = -q.un * x[0] + q.n[0] * x[1] + q.n[1] * x[2] + q.n[2] * x[3];
-  const double ic = 1.0 / f.c;
-  const double a = (l123 * ic * ic) * gx + (l12 * ic) * mx;
-  const double b = (l12 * ic) * gx + l123 * mx;
-  const double s[5] = {0.0, q.n[0], q.n[1], q.n[2], q.un};
-  for (int k = 0; k < 5; ++k) y[k] = q.scale * (l3 * x[k] + f.r0[k] * a + s[k] * b);
+// Unit normal of a corner and p0, A, B of its K^+.
+struct Corner {
+  double n[3], p0, A, B;
+};
+
+// L D L^T of the acoustic 4x4 block (reciprocal pivots) and the reciprocal of
+// the entropy sum (0 at rest).
+struct Factor {
+  double i[4], l10, l20, l30, l21, l31, l32, ia;
+};
+
+__device__ inline void to_conserved(const Flow& f, const double y[5], double x[5]) {
+  x[0] = y[4] + y[0] * f.ic;
+  for (int k = 0; k < 3; ++k) x[1 + k] = f.u[k] * x[0] + y[1 + k];
+  x[4] = f.cg * y[0] + f.hq * x[0] + f.u[0] * y[1] + f.u[1] * y[2] + f.u[2] * y[3];
 }
 
-__device__ inline double pos(double x) { return x > 0.0 ? x : 0.0; }
-__device__ inline double neg(double x) { return x < 0.0 ? x : 0.0; }
-
-// A x = b for two right-hand sides, Gaussian elimination with partial
-// pivoting (the largest magnitude among the rows not yet used, first such
-// row on ties); a column whose best pivot is at most 2^-45 max|A| is skipped
-// (its unknowns are 0). Every array index is a compile-time constant (the
-// pivot row is picked with selects and copied into U, its diagonal replaced
-// by the pivot's reciprocal), so nothing goes to scratch memory.
-__device__ inline void solve5x2(double A[5][5], double b1[5], double b2[5], double x1[5], double x2[5]) {
-  double amax = 0.0;
-#pragma unroll
-  for (int r = 0; r < 5; ++r)
-#pragma unroll
-    for (int q = 0; q < 5; ++q) amax = fmax(amax, fabs(A[r][q]));
-  const double tol = ldexp(amax, -45);
-  int used = 0;
-  bool skip[5];
-  double U[5][5], c1[5], c2[5];
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    int r = -1;
-    double best = -1.0;
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      const double a = fabs(A[i][k]);
-      if (!(used & (1 << i)) && a > best) {
-        best = a;
-        r = i;
-      }
-    }
-    skip[k] = r < 0 || !(best > tol);
-    double pr[5], pb1 = b1[0], pb2 = b2[0];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) pr[j] = A[0][j];
-#pragma unroll
-    for (int i = 1; i < 5; ++i) {
-      const bool sel = r == i;
-#pragma unroll
-      for (int j = 0; j < 5; ++j) pr[j] = sel ? A[i][j] : pr[j];
-      pb1 = sel ? b1[i] : pb1;
-      pb2 = sel ? b2[i] : pb2;
-    }
-#pragma unroll
-    for (int j = 0; j < 5; ++j) U[k][j] = pr[j];
-    c1[k] = pb1;
-    c2[k] = pb2;
-    if (skip[k]) continue;
-    used |= 1 << r;
-    const double ip = 1.0 / pr[k];
-    U[k][k] = ip;  // the back substitution multiplies by it
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      if (used & (1 << i)) continue;
-      const double fct = A[i][k] * ip;
-#pragma unroll
-      for (int j = k; j < 5; ++j) A[i][j] -= fct * pr[j];
-      b1[i] -= fct * pb1;
-      b2[i] -= fct * pb2;
-    }
-  }
-#pragma unroll
-  for (int k = 4; k >= 0; --k) {
-    double s1 = c1[k], s2 = c2[k];
-#pragma unroll
-    for (int j = k + 1; j < 5; ++j) {
-      s1 -= U[k][j] * x1[j];
-      s2 -= U[k][j] * x2[j];
-    }
-    x1[k] = skip[k] ? 0.0 : s1 * U[k][k];
-    x2[k] = skip[k] ? 0.0 : s2 * U[k][k];
-  }
+__device__ inline void from_conserved(const Flow& f, const double x[5], double y[5]) {
+  for (int k = 0; k < 3; ++k) y[1 + k] = x[1 + k] - f.u[k] * x[0];
+  y[0] = f.gc * (x[4] - f.hq * x[0] - f.u[0] * y[1] - f.u[1] * y[2] - f.u[2] * y[3]);
+  y[4] = x[0] - y[0] * f.ic;
 }
 
-// Blend coefficients of the B family from the residual `res` and the N
-// parts pn: Theta_k = min(1, |res_k| / sum_i |pn_ik|) (0 for a zero sum),
-// one common value for Bmax / Bmin; unused by N and LDA.
-__device__ inline void blend_theta(int scheme, const double res[5], const double pn[4][5], double th[5]) {
-  for (int k = 0; k < 5; ++k) {
-    const double den = fabs(pn[0][k]) + fabs(pn[1][k]) + fabs(pn[2][k]) + fabs(pn[3][k]);
-    const double q = den == 0.0 ? 0.0 : fabs(res[k]) / den;
-    th[k] = q > 1.0 ? 1.0 : q;
-  }
-  if (scheme == S_BMAX || scheme == S_BMIN) {
-    int pick = 0;
-    for (int k = 1; k < 5; ++k)
-      if (scheme == S_BMAX ? th[k] > th[pick] : th[k] < th[pick]) pick = k;
-    double t = th[0];
-    for (int k = 1; k < 5; ++k) t = pick == k ? th[k] : t;
-    for (int k = 0; k < 5; ++k) th[k] = t;
-  }
+// out = K^+ y
+__device__ inline void split(const double n[3], double p0, double A, double B, const double y[5], double out[5]) {
+  const double d = n[0] * y[1] + n[1] * y[2] + n[2] * y[3];
+  const double g = B * y[0] + A * d;
+  out[0] = (p0 + A) * y[0] + B * d;
+  for (int k = 0; k < 3; ++k) out[1 + k] = p0 * y[1 + k] + n[k] * g;
+  out[4] = p0 * y[4];
 }
 
-// One tetrahedron: stage 1 (or Euler) at the Z in d.Z; stage 2 adds the
-// mass term of the first-stage increment and the kept stage-1 parts.
-template <int STAGE, int SCHEME>
-__device__ inline void tet_body(const Dev3& d, int64_t t, bool keep) {
-  constexpr int scheme = SCHEME;
-  const int64_t nt = d.nt, nv = d.nv;
-  const double g1 = d.gamma - 1.0;
-  int32_t vid[4];
-  double Zc[4][5];
-  for (int i = 0; i < 4; ++i) {
-    vid[i] = d.tet[i * nt + t];
-    for (int k = 0; k < 5; ++k) Zc[i][k] = d.Z[k * nv + vid[i]];
+__device__ inline void solve(const Factor& q, const double b[5], double x[5]) {
+  const double y1 = b[1] - q.l10 * b[0];
+  const double y2 = b[2] - q.l20 * b[0] - q.l21 * y1;
+  const double y3 = b[3] - q.l30 * b[0] - q.l31 * y1 - q.l32 * y2;
+  x[3] = y3 * q.i[3];
+  x[2] = y2 * q.i[2] - q.l32 * x[3];
+  x[1] = y1 * q.i[1] - q.l21 * x[2] - q.l31 * x[3];
+  x[0] = b[0] * q.i[0] - q.l10 * x[1] - q.l20 * x[2] - q.l30 * x[3];
+  x[4] = b[4] * q.ia;
+}
+
+// sum_i K_i^+ as its corners are added.
+struct Matrix {
+  double al = 0.0, a = 0.0, m[3] = {0.0, 0.0, 0.0}, s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // 11 12 13 22 23 33
+  __device__ void add(const Corner& k) {
+    al += k.p0;
+    a += k.A;
+    for (int j = 0; j < 3; ++j) m[j] += k.B * k.n[j];
+    const double x = k.A * k.n[0], y = k.A * k.n[1], z = k.A * k.n[2];
+    s[0] += x * k.n[0];
+    s[1] += x * k.n[1];
+    s[2] += x * k.n[2];
+    s[3] += y * k.n[1];
+    s[4] += y * k.n[2];
+    s[5] += z * k.n[2];
   }
-  double zb[5];
-  for (int k = 0; k < 5; ++k) zb[k] = 0.25 * (Zc[0][k] + Zc[1][k] + Zc[2][k] + Zc[3][k]);
+};
+
+__device__ inline Factor factor(const Matrix& m) {
+  Factor q;
+  const double m00 = m.al + m.a, m11 = m.al + m.s[0], m22 = m.al + m.s[3], m33 = m.al + m.s[5];
+  q.i[0] = rcp_normal(m00);
+  q.l10 = m.m[0] * q.i[0];
+  q.l20 = m.m[1] * q.i[0];
+  q.l30 = m.m[2] * q.i[0];
+  q.i[1] = rcp_normal(m11 - q.l10 * m.m[0]);
+  const double t21 = m.s[1] - q.l20 * m.m[0], t31 = m.s[2] - q.l30 * m.m[0];
+  q.l21 = t21 * q.i[1];
+  q.l31 = t31 * q.i[1];
+  q.i[2] = rcp_normal(m22 - q.l20 * m.m[1] - q.l21 * t21);
+  const double t32 = m.s[4] - q.l30 * m.m[1] - q.l31 * t21;
+  q.l32 = t32 * q.i[2];
+  q.i[3] = rcp_normal(m33 - q.l30 * m.m[2] - q.l31 * t31 - q.l32 * t32);
+  const double tol = (m00 + m11 + m22 + m33) * 2.8421709430404007e-14;  // 2^-45
+  q.ia = m.al > tol ? rcp_normal(m.al) : 0.0;
+  return q;
+}
+
+// A tetrahedron at given corner parameter vectors: what its parts need.
+struct Tet {
   Flow f;
-  const double iz = 1.0 / zb[0];
-  f.u[0] = zb[1] * iz;
-  f.u[1] = zb[2] * iz;
-  f.u[2] = zb[3] * iz;
-  f.H = zb[4] * iz;
-  const double q2 = f.u[0] * f.u[0] + f.u[1] * f.u[1] + f.u[2] * f.u[2];
-  f.c = sqrt(g1 * (f.H - 0.5 * q2));
-  f.g[0] = 0.5 * g1 * q2;
-  f.g[1] = -g1 * f.u[0];
-  f.g[2] = -g1 * f.u[1];
-  f.g[3] = -g1 * f.u[2];
-  f.g[4] = g1;
-  f.r0[0] = 1.0;
-  f.r0[1] = f.u[0];
-  f.r0[2] = f.u[1];
-  f.r0[3] = f.u[2];
-  f.r0[4] = f.H;
-  // state differences M(zbar)(Z_i - Z_0)
-  double dW[4][5];
-  const double igam = 1.0 / d.gamma;
-  for (int k = 0; k < 5; ++k) dW[0][k] = 0.0;
-  for (int i = 1; i < 4; ++i) {
+  Corner k[3];          // corners 0, 1, 2 (the parts sum to the residual, which gives corner 3's)
+  double dy[2][5];      // differences of corners 1 and 2 from corner 0
+  double phi[5], xN[5]; // residual, sum_i K_i^- dW_i solved (symmetrising variables)
+  Factor q;
+};
+
+// Keeps the scheduler from interleaving what stands before and after it.
+__device__ inline void fence() { __builtin_amdgcn_sched_barrier(0); }
+
+// Corner from its face normal; adds K y to phi and K^- y to b where y is given.
+__device__ inline Corner corner(const Flow& f, const double N[3], const double* y, double phi[5], double b[5],
+                                bool needn) {
+  Corner k;
+  double L, iL;
+  len_rcp(N[0] * N[0] + N[1] * N[1] + N[2] * N[2], L, iL);
+  for (int j = 0; j < 3; ++j) k.n[j] = N[j] * iL;
+  const double hw = f.u[0] * N[0] + f.u[1] * N[1] + f.u[2] * N[2], hC = L * f.c;
+  const double p = rmax(hw + hC, 0.0), m = rmax(hw - hC, 0.0);
+  const double w = hw + hw, C = hC + hC;
+  k.p0 = rmax(w, 0.0);
+  k.A = (p + m) - k.p0;
+  k.B = p - m;
+  if (y) {
+    const double d = k.n[0] * y[1] + k.n[1] * y[2] + k.n[2] * y[3], cp = C * y[0];
+    phi[0] += w * y[0] + C * d;
+    for (int j = 0; j < 3; ++j) phi[1 + j] += w * y[1 + j] + k.n[j] * cp;
+    phi[4] += w * y[4];
+    if (needn) {
+      double t[5];
+      split(k.n, w - k.p0, -k.A, C - k.B, y, t);
+      for (int j = 0; j < 5; ++j) b[j] += t[j];
+    }
+  }
+  return k;
+}
+
+// z(i): parameter vector of corner i; N: face normals of corners 0..3.
+template <bool NEEDN, class Z>
+__device__ inline void tet_eval(const Dev3& d, const Z& z, const double N[4][3], Tet& s) {
+  double z0[5], z1[5], z2[5], z3[5], zs[5];
+  z(0, z0);
+  z(1, z1);
+  z(2, z2);
+  z(3, z3);
+  for (int k = 0; k < 5; ++k) zs[k] = z0[k] + z1[k] + z2[k] + z3[k];
+  Flow& f = s.f;
+  const double iz = rcp_normal(zs[0]);
+  for (int k = 0; k < 3; ++k) f.u[k] = zs[1 + k] * iz;
+  f.hq = 0.5 * (f.u[0] * f.u[0] + f.u[1] * f.u[1] + f.u[2] * f.u[2]);
+  len_rcp(d.g1 * (zs[4] * iz - f.hq), f.c, f.ic);
+  f.cg = f.c * d.ig1;
+  f.gc = f.ic * d.g1;
+  const double gf = d.gfac * f.ic;
+  auto diff = [&](const double zi[5], double y[5]) {
     double dz[5];
-    for (int k = 0; k < 5; ++k) dz[k] = Zc[i][k] - Zc[0][k];
-    dW[i][0] = 2.0 * zb[0] * dz[0];
-    for (int k = 1; k < 4; ++k) dW[i][k] = zb[k] * dz[0] + zb[0] * dz[k];
-    dW[i][4] = (zb[4] * dz[0] + g1 * (zb[1] * dz[1] + zb[2] * dz[2] + zb[3] * dz[3]) + zb[0] * dz[4]) * igam;
-  }
-  Corner cn[4];
-  for (int i = 0; i < 4; ++i) {
-    double n[3];
-    for (int k = 0; k < 3; ++k) n[k] = d.nrm[(3 * i + k) * nt + t];
-    const double area = sqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
-    const double ia = 1.0 / area;
-    for (int k = 0; k < 3; ++k) cn[i].n[k] = n[k] * ia;
-    cn[i].un = f.u[0] * cn[i].n[0] + f.u[1] * cn[i].n[1] + f.u[2] * cn[i].n[2];
-    cn[i].scale = area * (1.0 / 3.0);
-  }
-  // residual and the N right-hand side
-  double phiT[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, bN[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int i = 1; i < 4; ++i) {
-    const double un = cn[i].un;
-    double y[5];
-    kapply(f, cn[i], un + f.c, un - f.c, un, dW[i], y);
-    for (int k = 0; k < 5; ++k) phiT[k] += y[k];
-    kapply(f, cn[i], neg(un + f.c), neg(un - f.c), neg(un), dW[i], y);
-    for (int k = 0; k < 5; ++k) bN[k] += y[k];
-  }
-  // A = sum_i K_i^+ from the rank-two form: sum_i sc_i l3_i I + r0 (sum_i a_i)^T
-  // + sum_i s_i b_i^T, with s_i = (0, n_i, u.n_i) (its first entry is zero)
-  double A[5][5], abar[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, dsum = 0.0;
-  for (int r = 0; r < 5; ++r)
-    for (int q = 0; q < 5; ++q) A[r][q] = 0.0;
-  {
-    const double ic = 1.0 / f.c;
-    for (int i = 0; i < 4; ++i) {
-      const double un = cn[i].un;
-      const double l1 = pos(un + f.c), l2 = pos(un - f.c), l3 = pos(un);
-      const double sc = cn[i].scale;
-      const double l123 = sc * (0.5 * (l1 + l2) - l3), l12 = sc * (0.5 * (l1 - l2));
-      const double m[5] = {-un, cn[i].n[0], cn[i].n[1], cn[i].n[2], 0.0};
-      const double s[4] = {cn[i].n[0], cn[i].n[1], cn[i].n[2], un};
-      dsum += sc * l3;
-      for (int q = 0; q < 5; ++q) {
-        abar[q] += (l123 * ic * ic) * f.g[q] + (l12 * ic) * m[q];
-        const double b = (l12 * ic) * f.g[q] + l123 * m[q];
-        for (int r = 1; r < 5; ++r) A[r][q] += s[r - 1] * b;
-      }
+    for (int k = 0; k < 5; ++k) dz[k] = zi[k] - z0[k];
+    y[0] = gf * (zs[4] * dz[0] + zs[0] * dz[4] - zs[1] * dz[1] - zs[2] * dz[2] - zs[3] * dz[3]);
+    for (int k = 1; k < 4; ++k) y[k] = zs[0] * dz[k] - zs[k] * dz[0];
+    y[4] = 2.0 * zs[0] * dz[0] - y[0] * f.ic;
+  };
+  Matrix m;
+  double b[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, dy3[5];
+  for (int k = 0; k < 5; ++k) s.phi[k] = 0.0;
+  diff(z3, dy3);
+  diff(z2, s.dy[1]);
+  diff(z1, s.dy[0]);
+  m.add(corner(f, N[3], dy3, s.phi, b, NEEDN));
+  s.k[2] = corner(f, N[2], s.dy[1], s.phi, b, NEEDN);
+  m.add(s.k[2]);
+  s.k[1] = corner(f, N[1], s.dy[0], s.phi, b, NEEDN);
+  m.add(s.k[1]);
+  s.k[0] = corner(f, N[0], nullptr, s.phi, b, false);
+  m.add(s.k[0]);
+  s.q = factor(m);
+  if (NEEDN) solve(s.q, b, s.xN);
+}
+
+// N part of corner i < 3 in conserved variables.
+__device__ inline void n_part(const Tet& s, int i, double out[5]) {
+  double y[5], o[5];
+  for (int k = 0; k < 5; ++k) y[k] = i == 0 ? s.xN[k] : s.dy[i - 1][k] + s.xN[k];
+  split(s.k[i].n, s.k[i].p0, s.k[i].A, s.k[i].B, y, o);
+  to_conserved(s.f, o, out);
+}
+
+// The scheme's parts of the four corners from the residual being split, the N
+// parts of corners 0..2 and the unknown xT of the LDA parts. Blends: Theta_k =
+// min(1, |res_k| / sum_i |N_ik|), 0 for a zero sum (1e-300 added to the sum
+// changes no quotient whose sum is above 1e-284), one common value for Bmax
+// and Bmin.
+template <int SCHEME>
+__device__ inline void scheme_parts(const Tet& s, const double res[5], const double pn[3][5], const double xT[5],
+                                    double out[4][5]) {
+  double th[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  if (SCHEME >= S_B) {
+    for (int k = 0; k < 5; ++k) {
+      const double den = fabs(pn[0][k]) + fabs(pn[1][k]) + fabs(pn[2][k]) +
+                         fabs(res[k] - pn[0][k] - pn[1][k] - pn[2][k]);
+      th[k] = rmin(fabs(res[k]) * rcp_normal(den + 1e-300), 1.0);
+    }
+    if (SCHEME != S_B) {
+      double t = th[0];
+      for (int k = 1; k < 5; ++k) t = SCHEME == S_BMAX ? rmax(t, th[k]) : rmin(t, th[k]);
+      for (int k = 0; k < 5; ++k) th[k] = t;
     }
   }
-  for (int r = 0; r < 5; ++r) {
-    A[r][r] += dsum;
-    for (int q = 0; q < 5; ++q) A[r][q] += f.r0[r] * abar[q];
-  }
-  double PT[5];
-  if (STAGE == 1) {
-    for (int k = 0; k < 5; ++k) PT[k] = phiT[k];
-  } else {
-    // stage 2: the mass |T| / 4 times the first-stage rate, plus the mean of
-    // the kept and the current residual
-    const double mass = 0.25 * d.vol[t];
-    double rate_sum[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int i = 0; i < 4; ++i)
-      for (int k = 0; k < 5; ++k) rate_sum[k] += d.rate[k * nv + vid[i]];
-    for (int k = 0; k < 5; ++k) PT[k] = mass * rate_sum[k] + 0.5 * (d.keepT[k * nt + t] + phiT[k]);
-  }
-  double rhsT[5];
-  for (int k = 0; k < 5; ++k) rhsT[k] = PT[k];
-  double xN[5], xT[5];
-  solve5x2(A, bN, rhsT, xN, xT);
-  // N parts of every corner (the blend needs all of them), then each
-  // corner's LDA part and output. The parts of a distribution add up to the
-  // residual they split (sum_i K_i^+ (dW_i + xN) = phi^T, sum_i K_i^+ xT =
-  // PT), so corner 3's are that residual minus those of corners 0-2.
-  double pn[4][5];
+  for (int k = 0; k < 5; ++k) out[3][k] = res[k];
   for (int i = 0; i < 3; ++i) {
-    const double un = cn[i].un;
-    double y[5];
-    for (int k = 0; k < 5; ++k) y[k] = (i == 0 ? 0.0 : dW[i][k]) + xN[k];
-    kapply(f, cn[i], pos(un + f.c), pos(un - f.c), pos(un), y, pn[i]);
-  }
-  for (int k = 0; k < 5; ++k) pn[3][k] = phiT[k] - pn[0][k] - pn[1][k] - pn[2][k];
-  if (STAGE == 1 && keep) {
-    // read back only by the stage-2 pass after the gather: stored with the
-    // non-temporal hint so they do not evict what the gather reads next;
-    // corner 3's part is formed again from the residual in stage 2
-    for (int i = 0; i < 3; ++i)
-      for (int k = 0; k < 5; ++k) __builtin_nontemporal_store(pn[i][k], &d.keepN[(5 * i + k) * nt + t]);
-    for (int k = 0; k < 5; ++k) __builtin_nontemporal_store(phiT[k], &d.keepT[k * nt + t]);
-  }
-  if (STAGE == 2) {
-    const double mass = 0.25 * d.vol[t];
-    for (int k = 0; k < 5; ++k) {
-      double kn[4];
-      for (int i = 0; i < 3; ++i) kn[i] = d.keepN[(5 * i + k) * nt + t];
-      kn[3] = d.keepT[k * nt + t] - kn[0] - kn[1] - kn[2];
-      for (int i = 0; i < 4; ++i) pn[i][k] = mass * d.rate[k * nv + vid[i]] + 0.5 * (kn[i] + pn[i][k]);
-    }
-  }
-  double th[5];
-  blend_theta(scheme, PT, pn, th);
-  double lsum[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int i = 0; i < 4; ++i) {
-    double pl[5];
-    if (i < 3) {
-      const double un = cn[i].un;
-      kapply(f, cn[i], pos(un + f.c), pos(un - f.c), pos(un), xT, pl);
-      for (int k = 0; k < 5; ++k) lsum[k] += pl[k];
+    if (SCHEME == S_N) {
+      for (int k = 0; k < 5; ++k) out[i][k] = pn[i][k];
     } else {
-      for (int k = 0; k < 5; ++k) pl[k] = PT[k] - lsum[k];
+      double o[5], pl[5];
+      split(s.k[i].n, s.k[i].p0, s.k[i].A, s.k[i].B, xT, o);
+      to_conserved(s.f, o, pl);
+      for (int k = 0; k < 5; ++k) out[i][k] = SCHEME == S_LDA ? pl[k] : pl[k] + th[k] * (pn[i][k] - pl[k]);
     }
-    const int64_t sl = d.slot[i * nt + t];
-    for (int k = 0; k < 5; ++k) {
-      const double o = scheme == S_N ? pn[i][k] : scheme == S_LDA ? pl[k] : pl[k] + th[k] * (pn[i][k] - pl[k]);
-      d.part[k * d.ns + sl] = o;
-    }
+    for (int k = 0; k < 5; ++k) out[3][k] -= out[i][k];
   }
 }
 

@@ -7,16 +7,20 @@
 
 namespace rd3 {
 
-// Z and |u| + c of the state src ([5][nv]).
-hipError_t launch3_z(const Dev3& d, const double* src, hipStream_t s);
-// One tetrahedron pass: stage 1 (or Euler) reads d.Z of W (keep: store the
-// N parts and the residual for stage 2); stage 2 reads d.Z of Ws.
-hipError_t launch3_tet(const Dev3& d, int stage, int scheme, bool keep, hipStream_t s);
+// The state from / to the caller's [5][nv] arrays; set makes Z and |u| + c.
+hipError_t launch3_set(const Dev3& d, const double* src, hipStream_t s);
+hipError_t launch3_get(const Dev3& d, double* dst, hipStream_t s);
+// One tile pass: stage 1 (or Euler) at W, with the CFL terms where cfl, or
+// stage 2 at W*; stage 0: the CFL terms alone.
+hipError_t launch3_tile(const Dev3& d, int stage, int scheme, bool cfl, hipStream_t s);
 // Vertex sums and update: mode 0 Euler, 1 first stage, 2 second stage.
 hipError_t launch3_gather(const Dev3& d, int mode, hipStream_t s);
-// CFL limit of d.sig times cfl -> *d.dt (d.bmin holds cfl_blocks(nv) values).
+// CFL limit from the tiles' terms, times cfl -> *d.dt (d.bmin holds
+// cfl_blocks(nv) values).
 int cfl_blocks(int64_t nv);
 hipError_t launch3_cfl(const Dev3& d, double cfl, hipStream_t s);
 hipError_t launch3_set_dt(const Dev3& d, double dt, hipStream_t s);
+// Sets the layout of a tile workgroup's LDS (max_jd: most diagonals of a tile).
+void tile3_lds(Dev3& d, int32_t max_jd);
 
 }  // namespace rd3
