@@ -54,7 +54,7 @@ hipError_t launch_euler_apply(const Dev& d, const Dev32& h, hipStream_t s);
 hipError_t launch_tile_wall2(const Dev& d, const Dev32& h, hipStream_t s);
 hipError_t launch_tile_cfl(const Dev& d, const Dev32& h, const CflPlan& p, double cfl, hipStream_t s);
 hipError_t launch_tile_vrange(const Dev& d, const Dev32& h, const CflPlan& p, hipStream_t s);
-// Dynamic LDS bytes of a tile workgroup.
-size_t tile_lds_bytes(const Tiles& tl, int stage, bool cfl);
+// Dynamic LDS bytes of a tile workgroup with values of `size` bytes.
+size_t tile_lds_bytes(const Tiles& tl, int stage, bool cfl, size_t size);
 
 }  // namespace rd

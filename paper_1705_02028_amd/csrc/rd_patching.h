@@ -24,7 +24,7 @@
 namespace rd {
 
 struct PatchPlan {
-  int32_t npatch = 0, ntiles = 0;
+  int32_t npatch = 0;
   int32_t max_tri = 0;                 // triangles of the largest patch
   int32_t max_lv = 0, max_slots = 0;   // local vertices and part slots of the largest patches
   std::vector<int32_t> order;          // [nv] internal vertex -> caller's vertex
@@ -41,7 +41,6 @@ struct PatchPlan {
   std::vector<int32_t> pmesh;          // [npatch] mesh of each patch
   std::vector<uint8_t> seam;           // [npatch] 1: some triangle has a corner difference beyond half a period
   std::vector<int32_t> mbeg;           // [nmesh + 1] patches of each mesh
-  int64_t shared_vertices = 0, shared_parts = 0;
 };
 
 struct PatchInput {
@@ -52,8 +51,7 @@ struct PatchInput {
   const int32_t *row = nullptr, *slot = nullptr;  // vertex -> corner CSR (corner 3 t + i), ascending t in each row
   const std::vector<int64_t>*voff = nullptr, *toff = nullptr;
   int32_t max_tri = 512;  // a patch with more triangles is cut again (one vertex at least)
-  int32_t tile_tri = 0;   // > 0: ceil(triangles / tile_tri) groups per mesh, each one patch or more
-  int32_t own = 0;        // tile_tri = 0: wanted owned vertices per patch
+  int32_t own = 0;        // wanted owned vertices per patch
   int threads = 1;
 };
 
@@ -96,9 +94,7 @@ class PatchBuilder {
     std::vector<int64_t> cuts;  // group starts
     std::vector<int32_t> mesh_groups(nmesh + 1, 0);
     for (size_t k = 0; k < nmesh; ++k) {
-      const int64_t b = (*in_.voff)[k], e = (*in_.voff)[k + 1], ntk = (*in_.toff)[k + 1] - (*in_.toff)[k];
-      int64_t n = in_.tile_tri > 0 ? (ntk + in_.tile_tri - 1) / in_.tile_tri : (e - b + in_.own - 1) / in_.own;
-      n = std::max<int64_t>(1, std::min(n, e - b));
+      const int64_t n = std::max<int64_t>(1, ((*in_.voff)[k + 1] - (*in_.voff)[k] + in_.own - 1) / in_.own);
       mesh_groups[k + 1] = mesh_groups[k] + (int32_t)n;
     }
     const int64_t ngroups = mesh_groups[nmesh];
@@ -110,7 +106,6 @@ class PatchBuilder {
         bisect((*in_.voff)[k], (*in_.voff)[k + 1], mesh_groups[k], mesh_groups[k + 1], cuts, 1);
       });
     }
-    P_.ntiles = (int32_t)ngroups;
     // groups whose triangles exceed the limit are cut again; every piece is ordered by caller's id
     std::vector<std::vector<int64_t>> pieces(ngroups);
     parallel_stamped(ngroups, [&](int64_t g, std::vector<int32_t>& stamp, int32_t& mark) {
@@ -311,7 +306,6 @@ class PatchBuilder {
     P_.tid.resize(nt);
     P_.seam.assign(np, 0);
     P_.halo.resize(nh);
-    std::vector<uint8_t> shared(in_.nv, 0);
     parallel(np, [&](int64_t k) {
       const std::vector<int32_t>&T = tris[k], &H = halos[k];
       const int32_t v0 = P_.vbeg[k], v1 = P_.vbeg[k + 1], own = v1 - v0;
@@ -342,13 +336,6 @@ class PatchBuilder {
       }
       std::vector<int32_t>().swap(tris[k]);
     });
-    for (int32_t w : P_.halo) shared[w] = 1;
-    for (int64_t i = 0; i < in_.nv; ++i)
-      if (shared[i]) {
-        ++P_.shared_vertices;
-        const int32_t v = P_.order[i];
-        P_.shared_parts += in_.row[v + 1] - in_.row[v];
-      }
     return std::string();
   }
 };

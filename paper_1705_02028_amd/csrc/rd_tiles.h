@@ -52,8 +52,10 @@ struct TileLds {
 
 __host__ __device__ inline size_t lds_align(size_t x) { return (x + 31) & ~size_t(31); }
 
-// Bytes of LDS a tile workgroup needs; with base != null also sets out.
-__host__ __device__ inline size_t tile_lds(const Tiles& tl, int stage, bool cfl, char* base, TileLds* out) {
+// Bytes of LDS a tile workgroup needs when its values take `size` bytes; with
+// base != null also sets out (size = 4).
+__host__ __device__ inline size_t tile_lds(const Tiles& tl, int stage, bool cfl, char* base, TileLds* out,
+                                           size_t size = sizeof(float)) {
   size_t o = 0;
   auto take = [&](size_t bytes) -> char* {
     char* p = base ? base + o : nullptr;
@@ -62,16 +64,16 @@ __host__ __device__ inline size_t tile_lds(const Tiles& tl, int stage, bool cfl,
   };
   TileLds L;
   L.xy = reinterpret_cast<double2*>(take(sizeof(double2) * tl.max_lv));
-  L.Z = reinterpret_cast<F4*>(take(sizeof(F4) * tl.max_lv));
+  L.Z = reinterpret_cast<F4*>(take(4 * size * tl.max_lv));
   if (stage == 2) {
-    L.dW = reinterpret_cast<F4*>(take(sizeof(F4) * tl.max_lv));
+    L.dW = reinterpret_cast<F4*>(take(4 * size * tl.max_lv));
     L.Ws = reinterpret_cast<D4*>(take(sizeof(D4) * tl.max_lvi));
   }
   if (cfl) {
     L.sig = reinterpret_cast<double*>(take(sizeof(double) * tl.max_lv));
     L.lam = reinterpret_cast<double*>(take(sizeof(double) * tl.max_slots));
   }
-  L.P = reinterpret_cast<F4*>(take(sizeof(F4) * tl.max_slots));
+  L.P = reinterpret_cast<F4*>(take(4 * size * tl.max_slots));
   if (out) *out = L;
   return o;
 }

@@ -94,7 +94,9 @@ __global__ __launch_bounds__(kBlock) void k_tile_vrange(Dev d, Dev32 h, CflPlan 
   }
 }
 
-size_t tile_lds_bytes(const Tiles& tl, int stage, bool cfl) { return tile_lds(tl, stage, cfl, nullptr, nullptr); }
+size_t tile_lds_bytes(const Tiles& tl, int stage, bool cfl, size_t size) {
+  return tile_lds(tl, stage, cfl, nullptr, nullptr, size);
+}
 
 // Threads of a tile workgroup: one triangle each in stage 1, two in stage 2.
 static int tile_threads(const Tiles& tl, int stage) {

@@ -124,12 +124,12 @@ void run(int scheme, int st, bool lump, const std::vector<D4>& W, std::vector<D4
 
 extern "C" {
 
-// Builds the patches; info: patches, tiles, largest triangle count, shared
-// vertices, halo records, patch triangles, triangles listed as owned. Returns
-// 0, or 1 when the builder refuses or a triangle is not owned exactly once.
+// Builds the patches; info: patches, largest triangle count, halo records,
+// patch triangles, triangles listed as owned. Returns 0, or 1 when the builder
+// refuses or a triangle is not owned exactly once.
 int patch_build(int64_t nv, int64_t nt, const int32_t* tri, const double* x, const double* y, double px, double py,
                 const uint8_t* ghost, int64_t nw, const int32_t* wall, int nmesh, const int64_t* voff,
-                const int64_t* toff, int tile_tri, int own, int max_tri, int threads, int64_t* info) try {
+                const int64_t* toff, int own, int max_tri, int threads, int64_t* info) try {
   h = Host();
   h.nv = nv;
   h.nt = nt;
@@ -157,7 +157,6 @@ int patch_build(int64_t nv, int64_t nt, const int32_t* tri, const double* x, con
   in.voff = &h.voff;
   in.toff = &h.toff;
   in.max_tri = max_tri;
-  in.tile_tri = tile_tri;
   in.own = own;
   in.threads = threads;
   if (!rd::build_patch_plan(in, h.P).empty()) return 1;
@@ -206,9 +205,8 @@ int patch_build(int64_t nv, int64_t nt, const int32_t* tri, const double* x, con
         h.wptr.push_back((int32_t)h.went.size());
       }
   }
-  const int64_t a[7] = {P.npatch, P.ntiles, P.max_tri, P.shared_vertices, (int64_t)P.halo.size(),
-                        (int64_t)P.tid.size(), n};
-  for (int k = 0; k < 7; ++k) info[k] = a[k];
+  const int64_t a[5] = {P.npatch, P.max_tri, (int64_t)P.halo.size(), (int64_t)P.tid.size(), n};
+  for (int k = 0; k < 5; ++k) info[k] = a[k];
   return 0;
 } catch (const std::exception&) {
   return 1;

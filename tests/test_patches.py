@@ -33,20 +33,20 @@ def shim(tmp_path_factory):
     return lib
 
 
-def build(shim, m, tile=0, own=210, max_tri=512, voff=None, toff=None, threads=3):
+def build(shim, m, own=210, max_tri=512, voff=None, toff=None, threads=3):
     tri = np.ascontiguousarray(m["tri"], np.int32)
     wall = np.ascontiguousarray(m["wall"], np.int32).reshape(-1, 2)
     ghost = np.ascontiguousarray(m["ghost"], np.uint8)
     vo = np.array([0, m["nv"]] if voff is None else voff, np.int64)
     to = np.array([0, m["nt"]] if toff is None else toff, np.int64)
-    info = np.zeros(7, np.int64)
+    info = np.zeros(5, np.int64)
     p = lambda a: a.ctypes.data_as(C.c_void_p)  # noqa: E731
     x, y = np.ascontiguousarray(m["x"]), np.ascontiguousarray(m["y"])
     st = shim.patch_build(C.c_int64(m["nv"]), C.c_int64(m["nt"]), p(tri), p(x), p(y), C.c_double(m["px"]),
                           C.c_double(m["py"]), p(ghost), C.c_int64(len(wall)), p(wall), C.c_int(len(vo) - 1), p(vo),
-                          p(to), C.c_int(tile), C.c_int(own), C.c_int(max_tri), C.c_int(threads), p(info))
+                          p(to), C.c_int(own), C.c_int(max_tri), C.c_int(threads), p(info))
     assert st == 0
-    return dict(zip(("patches", "tiles", "max_tri", "shared", "halo", "listed", "owned"), info.tolist()))
+    return dict(zip(("patches", "max_tri", "halo", "listed", "owned"), info.tolist()))
 
 
 def err(a, b):
@@ -70,11 +70,9 @@ def test_patch_steps_match_the_oracle(orc, shim, case):
     for scheme in range(5):
         for time in (1, 2):
             ref = om.step(W, dt, scheme, time)
-            for kw in (dict(), dict(own=20), dict(tile=32), dict(own=40, max_tri=20)):
+            for kw in (dict(), dict(own=20), dict(own=40, max_tri=20)):
                 info = build(shim, m, **kw)
                 assert info["owned"] == m["nt"]
-                if kw.get("tile"):
-                    assert info["tiles"] == min(m["nv"], -(-m["nt"] // 32))
                 got = W.copy()
                 # the FP64 bar of one step: 1e-12 of each field's largest value
                 assert abs(shim.patch_step(got.ctypes.data, 0.4, scheme, time, 0) - dt) <= 1e-14 * dt
@@ -86,7 +84,7 @@ def test_results_do_not_depend_on_the_patches(shim):
                        renumber="random")
     W = I.random_smooth_state(m, seed=6, amp=0.2)
     outs = []
-    for kw in (dict(), dict(own=30), dict(tile=100), dict(own=5000, max_tri=100000), dict(own=1)):
+    for kw in (dict(), dict(own=30), dict(own=5000, max_tri=100000), dict(own=1)):
         build(shim, m, threads=1 + len(outs), **kw)
         for lump in (0, 1):
             got = W.copy()
