@@ -54,12 +54,43 @@ double unwrap_h(double d, double period) {
 // 10 bits.
 constexpr int32_t kMaxDegree = 1023;
 
-// Geometry the device does not recompute: vertex volumes (median dual).
-// Also the checks of rd_mesh_validate.
+int host_threads() {
+  const unsigned n = std::thread::hardware_concurrency();
+  return (int)std::min(8u, std::max(1u, n));
+}
+
+// f(i) for i = 0 .. n - 1, on a few threads when there is enough to do.
+template <class F>
+void parallel_for(int64_t n, const F& f, int64_t enough = 100000) {
+  const int w = n < enough ? 1 : host_threads();
+  rd::run_workers(w, [&](int q) {
+    for (int64_t i = n * q / w; i < n * (q + 1) / w; ++i) f(i);
+  });
+}
+
+// The host side of a call may run out of memory (or of threads): no C++
+// exception crosses the ABI.
+template <class F>
+rd_status guarded(F f) {
+  try {
+    return f();
+  } catch (const std::bad_alloc&) {
+    return fail(RD_ENOMEM, "host allocation failed");
+  } catch (const std::exception& e) {
+    return fail(RD_ENOMEM, std::string("host: ") + e.what());
+  }
+}
+
+// What check_desc works out: the vertex -> corner lists (corner 3 t + i,
+// ascending t in each row) and the vertex volumes (median dual).
 struct HostGeom {
-  std::vector<double> V;
+  rd::UVec<int32_t> row, slot;
+  rd::UVec<double> V;
 };
 
+// The checks of rd_mesh_validate. Several threads share large meshes: each
+// takes a range of triangles, then a range of vertices, whose corners it finds
+// by reading the whole triangle list.
 rd_status check_desc(const rd_mesh_desc* d, HostGeom* out) {
   if (!d) return fail(RD_EINVAL, "null mesh description");
   if (d->n_vertices <= 0 || d->n_triangles <= 0) return fail(RD_EINVAL, "empty mesh");
@@ -71,45 +102,78 @@ rd_status check_desc(const rd_mesh_desc* d, HostGeom* out) {
   if (d->n_wall_edges < 0 || (d->n_wall_edges > 0 && !d->wall_edges))
     return fail(RD_EINVAL, "bad wall edge list");
   const int64_t nv = d->n_vertices, nt = d->n_triangles;
-  std::vector<double> V(nv, 0.0), area(nt, 0.0);
-  for (int64_t t = 0; t < nt; ++t) {
-    int32_t v[3] = {d->tri[3 * t], d->tri[3 * t + 1], d->tri[3 * t + 2]};
-    for (int k = 0; k < 3; ++k)
-      if (v[k] < 0 || v[k] >= nv)
-        return fail(RD_EINVAL, "triangle " + std::to_string(t) + " has a vertex index out of range");
-    double px[3] = {0.0, 0.0, 0.0}, py[3] = {0.0, 0.0, 0.0};
-    for (int k = 1; k < 3; ++k) {
-      px[k] = unwrap_h(d->x[v[k]] - d->x[v[0]], d->period_x);
-      py[k] = unwrap_h(d->y[v[k]] - d->y[v[0]], d->period_y);
+  const int w = nt < 30000 ? 1 : host_threads();
+  rd::UVec<double> area(nt);
+  std::vector<int64_t> bad(w, nt);  // first bad triangle of each range
+  rd::run_workers(w, [&](int q) {
+    for (int64_t t = nt * q / w; t < nt * (q + 1) / w; ++t) {
+      const int32_t v[3] = {d->tri[3 * t], d->tri[3 * t + 1], d->tri[3 * t + 2]};
+      bool ok = true;
+      for (int k = 0; k < 3; ++k) ok = ok && v[k] >= 0 && v[k] < nv;
+      double px[3] = {0.0, 0.0, 0.0}, py[3] = {0.0, 0.0, 0.0};
+      for (int k = 1; ok && k < 3; ++k) {
+        px[k] = unwrap_h(d->x[v[k]] - d->x[v[0]], d->period_x);
+        py[k] = unwrap_h(d->y[v[k]] - d->y[v[0]], d->period_y);
+      }
+      area[t] = 0.5 * (px[1] * py[2] - py[1] * px[2]);
+      if (!ok || !(area[t] > 0.0)) {
+        bad[q] = t;
+        return;
+      }
     }
-    const double a = 0.5 * (px[1] * py[2] - py[1] * px[2]);
-    if (!(a > 0.0))
+  });
+  for (int64_t t : bad)
+    if (t < nt) {
+      for (int k = 0; k < 3; ++k)
+        if (d->tri[3 * t + k] < 0 || d->tri[3 * t + k] >= nv)
+          return fail(RD_EINVAL, "triangle " + std::to_string(t) + " has a vertex index out of range");
       return fail(RD_EINVAL, "triangle " + std::to_string(t) + " is not counter-clockwise with positive area");
-    area[t] = a;
-  }
-  std::vector<int32_t> deg(nv, 0);
-  for (int64_t t = 0; t < nt; ++t)
-    for (int k = 0; k < 3; ++k) {
-      V[d->tri[3 * t + k]] += area[t] / 3.0;
-      ++deg[d->tri[3 * t + k]];
     }
+  HostGeom geo;
+  rd::UVec<int32_t>&row = geo.row, &slot = geo.slot;
+  row.resize(nv + 1);
+  slot.resize(3 * nt);
+  geo.V.resize(nv);
+  auto share = [&](int q) { return nv * q / w; };
+  row[0] = 0;
+  rd::run_workers(w, [&](int q) {
+    const int64_t a = share(q), b = share(q + 1);
+    std::fill(row.begin() + a + 1, row.begin() + b + 1, 0);
+    for (int64_t s = 0; s < 3 * nt; ++s)
+      if (d->tri[s] >= a && d->tri[s] < b) ++row[d->tri[s] + 1];
+  });
   for (int64_t i = 0; i < nv; ++i) {
-    if (!(V[i] > 0.0)) return fail(RD_EINVAL, "vertex " + std::to_string(i) + " belongs to no triangle");
+    const int32_t deg = row[i + 1];
+    if (deg == 0) return fail(RD_EINVAL, "vertex " + std::to_string(i) + " belongs to no triangle");
     // a triangle's rank among the triangles of each corner vertex is packed in 10 bits
-    if (deg[i] > kMaxDegree)
-      return fail(RD_EINVAL, "vertex " + std::to_string(i) + " belongs to " + std::to_string(deg[i]) +
+    if (deg > kMaxDegree)
+      return fail(RD_EINVAL, "vertex " + std::to_string(i) + " belongs to " + std::to_string(deg) +
                                  " triangles; at most " + std::to_string(kMaxDegree) + " are supported");
+    row[i + 1] += row[i];
   }
+  rd::run_workers(w, [&](int q) {
+    const int64_t a = share(q), b = share(q + 1);
+    std::vector<int32_t> fill(row.begin() + a, row.begin() + b);
+    for (int64_t s = 0; s < 3 * nt; ++s)
+      if (d->tri[s] >= a && d->tri[s] < b) slot[fill[d->tri[s] - a]++] = (int32_t)s;
+    for (int64_t i = a; i < b; ++i) {
+      double V = 0.0;
+      for (int32_t j = row[i]; j < row[i + 1]; ++j) V += area[slot[j] / 3] / 3.0;
+      geo.V[i] = V;
+    }
+  });
   for (int64_t e = 0; e < d->n_wall_edges; ++e) {
     const int32_t a = d->wall_edges[2 * e], b = d->wall_edges[2 * e + 1];
     if (a < 0 || a >= nv || b < 0 || b >= nv || a == b)
       return fail(RD_EINVAL, "wall edge " + std::to_string(e) + " is invalid");
   }
-  if (out) out->V.swap(V);
+  if (out) *out = std::move(geo);
   return RD_OK;
 }
 
 }  // namespace
+
+constexpr size_t kSlab = size_t(1) << 19;
 
 struct rd_mesh {
   rd::Patches p;             // the step's view, vertices in internal order (patch by patch)
@@ -131,14 +195,17 @@ struct rd_mesh {
   int ncu = 0;      // compute units of the device
   int lds_max = 0;  // bytes of LDS one workgroup may use on the device
   // host copies, kept for batches, for other patches and for the second view
-  std::vector<double> x, y, V;
-  std::vector<int32_t> tri, wall, row, slot, bc, wv, wptr;
+  rd::UVec<double> x, y, V;
+  rd::UVec<int32_t> tri, row, slot;
+  std::vector<int32_t> wall, bc, wv, wptr;
   std::vector<uint8_t> ghost;
   std::vector<rd::WallEnt> went;
   double px = 0.0, py = 0.0, gamma = 1.4;
   double Ldom = 0.0;  // domain size of the Bx sensor
   // device buffers
   std::vector<void*> allocs;
+  char* slab = nullptr;  // the newest shared allocation, and its bytes that are free
+  size_t slab_left = 0;
   double* scratch = nullptr;      // [4 nv] host states pass through it
   double* phi_scratch = nullptr;  // [4 nt] triangle residuals to a host caller
   // adjoint buffers, allocated on first use
@@ -173,22 +240,36 @@ rd_status dalloc_in(std::vector<void*>& list, T** p, size_t n) {
   return RD_OK;
 }
 
+// Buffers that live as long as the mesh: small ones (a small mesh has some
+// sixty) share allocations of half a megabyte, at 256-byte boundaries.
 template <class T>
 rd_status dalloc(rd_mesh* m, T** p, size_t n) {
-  return dalloc_in(m->allocs, p, n);
+  const size_t bytes = (std::max<size_t>(n, 1) * sizeof(T) + 255) & ~size_t(255);
+  if (bytes > kSlab / 4) return dalloc_in(m->allocs, p, n);
+  if (bytes > m->slab_left) {
+    rd_status st = dalloc_in(m->allocs, &m->slab, kSlab);
+    if (st != RD_OK) return st;
+    m->slab_left = kSlab;
+  }
+  *p = reinterpret_cast<T*>(m->slab + (kSlab - m->slab_left));
+  m->slab_left -= bytes;
+  return RD_OK;
 }
 
-template <class T>
-rd_status upload_in(std::vector<void*>& list, T** p, const std::vector<T>& h) {
+template <class T, class A>
+rd_status upload_in(std::vector<void*>& list, T** p, const std::vector<T, A>& h) {
   rd_status st = dalloc_in(list, p, h.size());
   if (st != RD_OK) return st;
   if (!h.empty()) HIPCHK(hipMemcpy(*p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
   return RD_OK;
 }
 
-template <class T>
-rd_status upload(rd_mesh* m, T** p, const std::vector<T>& h) {
-  return upload_in(m->allocs, p, h);
+template <class T, class A>
+rd_status upload(rd_mesh* m, T** p, const std::vector<T, A>& h) {
+  rd_status st = dalloc(m, p, h.size());
+  if (st != RD_OK) return st;
+  if (!h.empty()) HIPCHK(hipMemcpy(*p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
+  return RD_OK;
 }
 
 void free_list(std::vector<void*>& list) {
@@ -329,35 +410,8 @@ rd_status run_step32(rd_mesh* m, int scheme, int time, double cfl, double dt, hi
   return RD_OK;
 }
 
-// The host side of a call may run out of memory (or of threads): no C++
-// exception crosses the ABI.
-template <class F>
-rd_status guarded(F f) {
-  try {
-    return f();
-  } catch (const std::bad_alloc&) {
-    return fail(RD_ENOMEM, "host allocation failed");
-  } catch (const std::exception& e) {
-    return fail(RD_ENOMEM, std::string("host: ") + e.what());
-  }
-}
-
 rd::State state_of(const rd_mesh* m) {
   return rd::State{{m->p.W[0], m->p.W[1]}, m->p.cur, m->inv, m->W32};
-}
-
-int host_threads() {
-  const unsigned n = std::thread::hardware_concurrency();
-  return (int)std::min(8u, std::max(1u, n));
-}
-
-// f(i) for i = 0 .. n - 1, on a few threads when there is enough to do.
-template <class F>
-void parallel_for(int64_t n, const F& f) {
-  const int w = n < 100000 ? 1 : host_threads();
-  rd::run_workers(w, [&](int q) {
-    for (int64_t i = n * q / w; i < n * (q + 1) / w; ++i) f(i);
-  });
 }
 
 // The tables of the second view of the mesh and the blocks of its vertex
@@ -365,7 +419,6 @@ void parallel_for(int64_t n, const F& f) {
 rd_status build_view(rd_mesh* m) {
   rd::Dev& d = m->d;
   rd::CflPlan& c = m->cfl;
-  std::vector<void*>& list = m->allocs;
   const int64_t nv = m->d.nv, nt = m->d.nt;
   d.flag = m->p.flag;
   d.dt = m->p.dt;
@@ -390,15 +443,21 @@ rd_status build_view(rd_mesh* m) {
     if (base >= (int64_t(1) << 31)) return fail(RD_EINVAL, "mesh too large for 32-bit part slots");
   }
   d.ns = base;
-  std::vector<double2> xy(nv);
-  std::vector<int32_t> tv(3 * nt), vtri(base, -1), vmesh, tmesh;
-  std::vector<uint32_t> rk(nt);
-  // the triangle of every part slot
-  parallel_for(nv, [&](int64_t v) {
-    xy[v] = make_double2(m->x[v], m->y[v]);
-    for (int32_t j = 0; j < m->row[v + 1] - m->row[v]; ++j)
-      vtri[sbase[v / 64] + v % 64 + 64 * (int64_t)j] = m->slot[m->row[v] + j] / 3;
-  });
+  rd::UVec<double2> xy(nv);
+  rd::UVec<int32_t> tv(3 * nt), vtri(base);
+  std::vector<int32_t> vmesh, tmesh;
+  rd::UVec<uint32_t> rk(nt);
+  // the triangle of every part slot (none: -1)
+  parallel_for((int64_t)sbase.size(), [&](int64_t g) {
+    const int64_t end = g + 1 < (int64_t)sbase.size() ? sbase[g + 1] : base;
+    for (int64_t l = 0; l < 64; ++l) {
+      const int64_t v = 64 * g + l;
+      const int32_t n = v < nv ? m->row[v + 1] - m->row[v] : 0;
+      if (v < nv) xy[v] = make_double2(m->x[v], m->y[v]);
+      for (int64_t j = 0; sbase[g] + 64 * j < end; ++j)
+        vtri[sbase[g] + l + 64 * j] = j < n ? m->slot[m->row[v] + j] / 3 : -1;
+    }
+  }, 2000);
   // corners, and the rank of each triangle among the triangles of each of its
   // corner vertices (10 bits per corner)
   parallel_for(nt, [&](int64_t t) {
@@ -437,13 +496,13 @@ rd_status build_view(rd_mesh* m) {
   uint32_t* prk;
   rd::WallEnt* pwent;
   rd_status st;
-  if ((st = upload_in(list, &pxy, xy)) || (st = upload_in(list, &pV, m->V)) || (st = upload_in(list, &prow, m->row)) ||
-      (st = upload_in(list, &ptv, tv)) || (st = upload_in(list, &prk, rk)) || (st = upload_in(list, &psbase, sbase)) ||
-      (st = upload_in(list, &pvtri, vtri)) || (st = upload_in(list, &pbc, m->bc)) || (st = upload_in(list, &pwv, m->wv)) ||
-      (st = upload_in(list, &pwptr, m->wptr)) || (st = upload_in(list, &pwent, m->went)) ||
-      (st = upload_in(list, &pvm, vmesh)) || (st = upload_in(list, &ptm, tmesh)) || (st = upload_in(list, &pv0, v0)) ||
-      (st = upload_in(list, &pv1, v1)) || (st = upload_in(list, &pb0, b0)) ||
-      (st = dalloc_in(list, &part, v0.size())) || (st = dalloc_in(list, &vpart, 2 * v0.size())))
+  if ((st = upload(m, &pxy, xy)) || (st = upload(m, &pV, m->V)) || (st = upload(m, &prow, m->row)) ||
+      (st = upload(m, &ptv, tv)) || (st = upload(m, &prk, rk)) || (st = upload(m, &psbase, sbase)) ||
+      (st = upload(m, &pvtri, vtri)) || (st = upload(m, &pbc, m->bc)) || (st = upload(m, &pwv, m->wv)) ||
+      (st = upload(m, &pwptr, m->wptr)) || (st = upload(m, &pwent, m->went)) ||
+      (st = upload(m, &pvm, vmesh)) || (st = upload(m, &ptm, tmesh)) || (st = upload(m, &pv0, v0)) ||
+      (st = upload(m, &pv1, v1)) || (st = upload(m, &pb0, b0)) ||
+      (st = dalloc(m, &part, v0.size())) || (st = dalloc(m, &vpart, 2 * v0.size())))
     return st;
   d.xy = pxy;
   d.V = pV;
@@ -625,7 +684,7 @@ rd_status build_patches(rd_mesh* m) {
   in.voff = &m->voff;
   in.toff = &m->toff;
   in.own = patch_own(nv, m->ncu);
-  in.threads = host_threads();
+  in.threads = nv < 15000 ? 1 : host_threads();  // a thread costs about 30 us
   std::string why = rd::build_patch_plan(in, P);
   // a vertex in more triangles than a workgroup has threads: its patch keeps
   // vertex records and parts apart in LDS, so the other patches are kept small
@@ -645,13 +704,13 @@ rd_status build_patches(rd_mesh* m) {
   if (need > (size_t)m->lds_max)
     return fail(RD_EUNSUPPORTED, "patches of this mesh need " + std::to_string(need) + " bytes of LDS");
   // descriptors, geometry and boundary lists in internal order
-  std::vector<int32_t> inv(nv);
-  for (int64_t i = 0; i < nv; ++i) inv[P.order[i]] = (int32_t)i;
+  rd::UVec<int32_t> inv(nv);
+  parallel_for(nv, [&](int64_t i) { inv[P.order[i]] = (int32_t)i; });
   std::vector<rd::PatchDesc> desc(P.npatch);
-  std::vector<double2> xy(nv + P.halo.size());
-  std::vector<double> V(nv);
-  size_t at = 0;
-  for (int32_t k = 0; k < P.npatch; ++k) {
+  rd::UVec<double2> xy(nv + P.halo.size());
+  rd::UVec<double> V(nv);
+  parallel_for(P.npatch, [&](int64_t k) {
+    int64_t at = (int64_t)P.vbeg[k] + P.hbeg[k];
     rd::PatchDesc& d = desc[k];
     d = rd::PatchDesc();
     d.v0 = P.vbeg[k];
@@ -669,8 +728,8 @@ rd_status build_patches(rd_mesh* m) {
       const int32_t v = P.order[l < d.own ? d.v0 + l : P.halo[d.h0 + l - d.own]];
       xy[at++] = make_double2(m->x[v], m->y[v]);
     }
-  }
-  for (int64_t i = 0; i < nv; ++i) V[i] = m->ghost[P.order[i]] ? -m->V[P.order[i]] : m->V[P.order[i]];
+  }, 400);
+  parallel_for(nv, [&](int64_t i) { V[i] = m->ghost[P.order[i]] ? -m->V[P.order[i]] : m->V[P.order[i]]; });
   std::vector<int32_t> wb;
   std::vector<rd::WallEnt> went = m->went;
   if (!m->wv.empty()) {
@@ -679,7 +738,6 @@ rd_status build_patches(rd_mesh* m) {
       if (!m->ghost[m->wv[b]]) wb[inv[m->wv[b]]] = (int32_t)b;
     for (auto& e : went) e.other = inv[e.other];
   }
-  std::vector<void*> list;
   rd_status st;
   int32_t *halo, *mbeg, *dinv, *dwb, *dwptr, *jb;
   rd::PatchDesc* ddesc;
@@ -688,16 +746,14 @@ rd_status build_patches(rd_mesh* m) {
   double2* dxy;
   double *dV, *pmin, *vpart;
   rd::WallEnt* dwent;
-  if ((st = upload_in(list, &ddesc, desc)) || (st = upload_in(list, &halo, P.halo)) ||
-      (st = upload_in(list, &mbeg, P.mbeg)) ||
-      (st = upload_in(list, &dinv, inv)) || (st = upload_in(list, &tri, P.tri)) ||
-      (st = upload_in(list, &deg, P.deg)) || (st = upload_in(list, &jb, P.jb)) || (st = upload_in(list, &dxy, xy)) ||
-      (st = upload_in(list, &dV, V)) || (st = dalloc_in(list, &pmin, P.npatch)) ||
-      (st = dalloc_in(list, &vpart, 2 * (size_t)P.npatch)) || (st = upload_in(list, &dwb, wb)) ||
-      (st = upload_in(list, &dwptr, m->wptr)) || (st = upload_in(list, &dwent, went))) {
-    free_list(list);
+  if ((st = upload(m, &ddesc, desc)) || (st = upload(m, &halo, P.halo)) ||
+      (st = upload(m, &mbeg, P.mbeg)) ||
+      (st = upload(m, &dinv, inv)) || (st = upload(m, &tri, P.tri)) ||
+      (st = upload(m, &deg, P.deg)) || (st = upload(m, &jb, P.jb)) || (st = upload(m, &dxy, xy)) ||
+      (st = upload(m, &dV, V)) || (st = dalloc(m, &pmin, P.npatch)) ||
+      (st = dalloc(m, &vpart, 2 * (size_t)P.npatch)) || (st = upload(m, &dwb, wb)) ||
+      (st = upload(m, &dwptr, m->wptr)) || (st = upload(m, &dwent, went)))
     return st;
-  }
   p.desc = ddesc;
   p.halo = halo;
   p.mbeg = mbeg;
@@ -712,7 +768,6 @@ rd_status build_patches(rd_mesh* m) {
   p.went = dwent;
   p.pmin = pmin;
   p.vpart = vpart;
-  m->allocs.insert(m->allocs.end(), list.begin(), list.end());
   m->p = p;
   m->inv = dinv;
   m->max_mesh_patches = 0;
@@ -750,7 +805,9 @@ bool physical(const double* W, int64_t nv, int64_t i, double gamma) {
 
 }  // namespace
 
-RD_API rd_status rd_mesh_validate(const rd_mesh_desc* desc) { return check_desc(desc, nullptr); }
+RD_API rd_status rd_mesh_validate(const rd_mesh_desc* desc) {
+  return guarded([&] { return check_desc(desc, nullptr); });
+}
 
 namespace {
 
@@ -777,9 +834,14 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
       m->ncu <= 0 || m->lds_max <= 0)
     return fail(RD_EDEVICE, "no HIP device");
   const int64_t nv = desc->n_vertices, nt = desc->n_triangles;
-  m->x.assign(desc->x, desc->x + nv);
-  m->y.assign(desc->y, desc->y + nv);
-  m->tri.assign(desc->tri, desc->tri + 3 * nt);
+  m->x.resize(nv);
+  m->y.resize(nv);
+  m->tri.resize(3 * nt);
+  parallel_for(nv, [&](int64_t i) {
+    m->x[i] = desc->x[i];
+    m->y[i] = desc->y[i];
+  });
+  parallel_for(3 * nt, [&](int64_t i) { m->tri[i] = desc->tri[i]; });
   m->ghost.assign(nv, 0);
   if (desc->ghost)
     for (int64_t i = 0; i < nv; ++i) m->ghost[i] = desc->ghost[i] ? 1 : 0;
@@ -791,15 +853,8 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   m->voff = voff.empty() ? std::vector<int64_t>{0, nv} : voff;
   m->toff = toff.empty() ? std::vector<int64_t>{0, nt} : toff;
 
-  // vertex -> (triangle, corner) CSR, ascending triangle order in every row
-  m->row.assign(nv + 1, 0);
-  for (int64_t s = 0; s < 3 * nt; ++s) m->row[m->tri[s] + 1]++;
-  for (int64_t i = 0; i < nv; ++i) m->row[i + 1] += m->row[i];
-  m->slot.assign(3 * nt, 0);
-  {
-    std::vector<int32_t> fill(m->row.begin(), m->row.end() - 1);
-    for (int64_t s = 0; s < 3 * nt; ++s) m->slot[fill[m->tri[s]]++] = (int32_t)s;
-  }
+  m->row.swap(geo.row);
+  m->slot.swap(geo.slot);
   // boundary kinds and wall incidences (ascending edge id per vertex)
   bool has_bc = false;
   for (int64_t i = 0; i < nv; ++i) has_bc |= m->ghost[i] != 0;
@@ -1439,10 +1494,10 @@ RD_API rd_status rd_batch_create(rd_mesh* const* meshes, int n, void* stream, rd
   for (int k = 0; k < n; ++k) {
     const rd_mesh* m = meshes[k];
     const double mp[2] = {m->px, m->py};
-    const std::vector<double>* c[2] = {&m->x, &m->y};
+    const rd::UVec<double>* c[2] = {&m->x, &m->y};
     for (int a = 0; a < 2; ++a) {
       if (bp[a] == 0.0 || mp[a] > 0.0) continue;
-      const std::vector<double>& q = *c[a];
+      const rd::UVec<double>& q = *c[a];
       const auto r = std::minmax_element(q.begin(), q.end());
       bool ok = *r.second - *r.first <= bp[a];
       for (size_t t = 0; ok && t < m->tri.size(); t += 3)

@@ -17,26 +17,46 @@
 #include <cmath>
 #include <cstdint>
 #include <new>
+#include <memory>
+#include <new>
 #include <string>
 #include <thread>
 #include <vector>
 
 namespace rd {
 
+// Vector whose new elements are left as they are: large tables that several
+// threads then fill (and so map into memory) together.
+template <class T>
+struct NoInit : std::allocator<T> {
+  template <class U>
+  struct rebind {
+    using other = NoInit<U>;
+  };
+  template <class U>
+  void construct(U*) noexcept {}
+  template <class U, class... A>
+  void construct(U* p, A&&... a) {
+    ::new (static_cast<void*>(p)) U(std::forward<A>(a)...);
+  }
+};
+template <class T>
+using UVec = std::vector<T, NoInit<T>>;
+
 struct PatchPlan {
   int32_t npatch = 0;
   int32_t max_tri = 0;                 // triangles of the largest patch
   int32_t max_lv = 0, max_slots = 0;   // local vertices and part slots of the largest patches
-  std::vector<int32_t> order;          // [nv] internal vertex -> caller's vertex
+  UVec<int32_t> order;                 // [nv] internal vertex -> caller's vertex
   std::vector<int32_t> vbeg;           // [npatch + 1] owned internal vertices of each patch
   std::vector<int32_t> hbeg, halo;     // halo (internal ids) of each patch, ascending
   std::vector<int32_t> tbeg;           // [npatch + 1] patch triangles
-  std::vector<uint32_t> tri;           // [3][patch triangle]: per corner its local id, and its part slot << 16 (0xffff: not owned)
-  std::vector<int32_t> tid;            // caller's triangle of each patch triangle, or -1 - t where another patch owns it
+  UVec<uint32_t> tri;                  // [3][patch triangle]: per corner its local id, and its part slot << 16 (0xffff: not owned)
+  UVec<int32_t> tid;                   // caller's triangle of each patch triangle, or -1 - t where another patch owns it
   // Part slots of a patch: its vertices stand in descending degree, and the
   // j-th parts (ascending triangle) of those that have one are consecutive:
   // slot = jb[jbeg[k] + j] + local vertex.
-  std::vector<uint16_t> deg;           // [nv] triangles of each owned vertex
+  UVec<uint16_t> deg;                  // [nv] triangles of each owned vertex
   std::vector<int32_t> jbeg, jb;
   std::vector<int32_t> pmesh;          // [npatch] mesh of each patch
   std::vector<uint8_t> seam;           // [npatch] 1: some triangle has a corner difference beyond half a period
@@ -89,7 +109,8 @@ class PatchBuilder {
     const size_t nmesh = in_.voff->size() - 1;
     P_ = PatchPlan();
     P_.order.resize(in_.nv);
-    for (int64_t i = 0; i < in_.nv; ++i) P_.order[i] = (int32_t)i;
+    pts_.resize(in_.nv);
+    parallel(in_.nv, [&](int64_t i) { pts_[i] = Point{in_.x[i], in_.y[i], (int32_t)i}; });
     // groups: per mesh a list of group bounds, found by bisection in parallel
     std::vector<int64_t> cuts;  // group starts
     std::vector<int32_t> mesh_groups(nmesh + 1, 0);
@@ -100,16 +121,30 @@ class PatchBuilder {
     const int64_t ngroups = mesh_groups[nmesh];
     cuts.assign(ngroups + 1, in_.nv);
     if (nmesh == 1) {
+      if (in_.threads > 1) swap_.resize(in_.nv);
       bisect(0, in_.nv, 0, ngroups, cuts, in_.threads);
+      UVec<Point>().swap(swap_);
     } else {
       parallel((int64_t)nmesh, [&](int64_t k) {
         bisect((*in_.voff)[k], (*in_.voff)[k + 1], mesh_groups[k], mesh_groups[k + 1], cuts, 1);
       });
     }
-    // groups whose triangles exceed the limit are cut again; every piece is ordered by caller's id
+    // groups whose triangles exceed the limit are cut again; every piece is ordered by degree and caller's id
+    gof_.resize(in_.nv);
+    parallel(ngroups, [&](int64_t g) {
+      for (int64_t i = cuts[g]; i < cuts[g + 1]; ++i) gof_[pts_[i].id] = (int32_t)g;
+    });
     std::vector<std::vector<int64_t>> pieces(ngroups);
-    parallel_stamped(ngroups, [&](int64_t g, std::vector<int32_t>& stamp, int32_t& mark) {
-      pieces[g] = split_to_fit(cuts[g], cuts[g + 1], stamp, mark);
+    std::vector<std::vector<int32_t>> tris(ngroups);  // of the groups left whole
+    parallel(ngroups, [&](int64_t g) {
+      group_triangles((int32_t)g, cuts[g], cuts[g + 1], tris[g]);
+      if ((int64_t)tris[g].size() <= in_.max_tri || cuts[g + 1] - cuts[g] == 1) {
+        pieces[g] = {cuts[g]};
+      } else {
+        pieces[g] = split_to_fit(cuts[g], cuts[g + 1]);
+        tris[g].clear();
+      }
+      for (int64_t i = cuts[g]; i < cuts[g + 1]; ++i) P_.order[i] = pts_[i].id;
       for (size_t q = 0; q < pieces[g].size(); ++q) {
         const int64_t b = pieces[g][q], e = q + 1 < pieces[g].size() ? pieces[g][q + 1] : cuts[g + 1];
         std::sort(P_.order.begin() + b, P_.order.begin() + e, [&](int32_t p, int32_t r) {
@@ -122,6 +157,8 @@ class PatchBuilder {
     for (size_t k = 0; k < nmesh; ++k) {
       for (int32_t g = mesh_groups[k]; g < mesh_groups[k + 1]; ++g)
         for (int64_t b : pieces[g]) {
+          tris_.emplace_back();
+          if (pieces[g].size() == 1) tris_.back().swap(tris[g]);
           P_.vbeg.push_back((int32_t)b);
           P_.pmesh.push_back((int32_t)k);
         }
@@ -129,12 +166,21 @@ class PatchBuilder {
     }
     P_.npatch = (int32_t)P_.vbeg.size();
     P_.vbeg.push_back((int32_t)in_.nv);
+    UVec<Point>().swap(pts_);
+    UVec<int32_t>().swap(gof_);
     return fill();
   }
 
  private:
   const PatchInput& in_;
   PatchPlan& P_;
+  struct Point {
+    double x, y;
+    int32_t id;
+  };
+  UVec<Point> pts_, swap_;  // vertices, partitioned as the order is found; room for parallel cuts
+  std::vector<std::vector<int32_t>> tris_;  // triangles of each patch (empty: still to be found)
+  UVec<int32_t> gof_;       // group of each of the caller's vertices
 
   template <class F>
   void parallel(int64_t n, const F& f) {
@@ -144,46 +190,98 @@ class PatchBuilder {
     });
   }
 
-  // Each worker has its own stamp array over the triangles.
-  template <class F>
-  void parallel_stamped(int64_t n, const F& f) {
-    const int w = (int)std::max<int64_t>(1, std::min<int64_t>(in_.threads, n));
-    run_workers(w, [&](int q) {
-      std::vector<int32_t> stamp(in_.nt, 0);
-      int32_t mark = 0;
-      for (int64_t i = n * q / w; i < n * (q + 1) / w; ++i) f(i, stamp, mark);
-    });
-  }
-
   // Position in [b, e) of the cut that leaves about `want` vertices before
-  // it, order[b, e) partitioned around it along the longer side.
-  int64_t cut(int64_t b, int64_t e, int64_t want, int64_t lo, int64_t hi) {
-    double x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
-    for (int64_t i = b; i < e; ++i) {
-      const int32_t v = P_.order[i];
-      x0 = std::min(x0, in_.x[v]);
-      x1 = std::max(x1, in_.x[v]);
-      y0 = std::min(y0, in_.y[v]);
-      y1 = std::max(y1, in_.y[v]);
+  // it, pts[b, e) partitioned around it along the longer side; on several
+  // threads by a histogram of the coordinate first.
+  int64_t cut(int64_t b, int64_t e, int64_t want, int64_t lo, int64_t hi, int threads = 1) {
+    struct Box {
+      double x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
+    };
+    const int w = threads > 1 && e - b > 100000 ? threads : 1;
+    std::vector<Box> box(w);
+    auto share = [&](int q) { return b + (e - b) * q / w; };
+    run_workers(w, [&](int q) {
+      Box B;
+      for (int64_t i = share(q); i < share(q + 1); ++i) {
+        B.x0 = std::min(B.x0, pts_[i].x);
+        B.x1 = std::max(B.x1, pts_[i].x);
+        B.y0 = std::min(B.y0, pts_[i].y);
+        B.y1 = std::max(B.y1, pts_[i].y);
+      }
+      box[q] = B;
+    });
+    Box B;
+    for (const Box& o : box) {
+      B.x0 = std::min(B.x0, o.x0);
+      B.x1 = std::max(B.x1, o.x1);
+      B.y0 = std::min(B.y0, o.y0);
+      B.y1 = std::max(B.y1, o.y1);
     }
-    const double* c = x1 - x0 >= y1 - y0 ? in_.x : in_.y;
-    auto less = [c](int32_t p, int32_t q) { return c[p] < c[q] || (c[p] == c[q] && p < q); };
-    int32_t* o = P_.order.data();
+    const bool ax = B.x1 - B.x0 >= B.y1 - B.y0;
+    auto co = [ax](const Point& p) { return ax ? p.x : p.y; };
+    auto less = [&](const Point& p, const Point& q) { return co(p) < co(q) || (co(p) == co(q) && p.id < q.id); };
+    int64_t u = b, v = e;  // the cut lies in [u, v), in place around it
     const int64_t m = b + want;
-    std::nth_element(o + b, o + m, o + e, less);
+    if (w > 1) {
+      constexpr int kBins = 4096;
+      const double c0 = ax ? B.x0 : B.y0, len = (ax ? B.x1 : B.y1) - c0, f = len > 0.0 ? kBins / len : 0.0;
+      auto bin = [&](const Point& p) { return std::min(kBins - 1, (int)((co(p) - c0) * f)); };
+      std::vector<std::vector<int64_t>> count(w);
+      run_workers(w, [&](int q) {
+        count[q].assign(kBins, 0);
+        for (int64_t i = share(q); i < share(q + 1); ++i) ++count[q][bin(pts_[i])];
+      });
+      int64_t before = b;
+      int at = 0;
+      for (;; ++at) {
+        int64_t n = 0;
+        for (int q = 0; q < w; ++q) n += count[q][at];
+        if (before + n > m) {
+          u = before;
+          v = before + n;
+          break;
+        }
+        before += n;
+      }
+      // three runs: bins below, the bin of the cut, bins above
+      std::vector<int64_t> p0(w), p1(w), p2(w);
+      int64_t a0 = b, a1 = u, a2 = v;
+      for (int q = 0; q < w; ++q) {
+        int64_t below = 0;
+        for (int k = 0; k < at; ++k) below += count[q][k];
+        p0[q] = a0;
+        p1[q] = a1;
+        p2[q] = a2;
+        a0 += below;
+        a1 += count[q][at];
+        a2 += share(q + 1) - share(q) - below - count[q][at];
+      }
+      run_workers(w, [&](int q) {
+        int64_t x = p0[q], y = p1[q], z = p2[q];
+        for (int64_t i = share(q); i < share(q + 1); ++i) {
+          const int k = bin(pts_[i]);
+          swap_[k < at ? x++ : (k == at ? y++ : z++)] = pts_[i];
+        }
+      });
+      run_workers(w, [&](int q) {
+        std::copy(swap_.begin() + share(q), swap_.begin() + share(q + 1), pts_.begin() + share(q));
+      });
+    }
+    auto o = pts_.begin();
+    std::nth_element(o + u, o + m, o + v, less);
     // the run of vertices with the coordinate of the cut: move the cut to its nearer end
-    const double at = c[o[m]];
-    int64_t below = 0, same = 0;
-    for (int64_t i = b; i < e; ++i) {
-      below += c[o[i]] < at;
-      same += c[o[i]] == at;
+    const double at = co(pts_[m]);
+    int64_t below = u - b, same = 0;
+    for (int64_t i = u; i < v; ++i) {
+      below += co(pts_[i]) < at;
+      same += co(pts_[i]) == at;
     }
     int64_t k = m;
     const int64_t k0 = b + below, k1 = k0 + same;
     if (m - k0 <= k1 - m && k0 >= b + lo && k0 <= b + hi) k = k0;
     else if (k1 >= b + lo && k1 <= b + hi) k = k1;
     else if (k0 >= b + lo && k0 <= b + hi) k = k0;
-    if (k != m) std::nth_element(o + b, o + k, o + e, less);
+    if (k != m && k > u && k < v) std::nth_element(o + u, o + k, o + v, less);
     return k;
   }
 
@@ -199,7 +297,7 @@ class PatchBuilder {
     const int64_t len = e - b, want = len * na / n;
     const int64_t slack = std::min(want, len - want) / 8;
     const int64_t lo = std::max(na, want - slack), hi = std::min(len - nb, want + slack);
-    const int64_t k = cut(b, e, std::min(std::max(want, na), len - nb), lo, hi);
+    const int64_t k = cut(b, e, std::min(std::max(want, na), len - nb), lo, hi, threads);
     run_workers(threads > 1 ? 2 : 1, [&](int q) {
       if (threads > 1) {
         if (q == 0) bisect(b, k, g0, g0 + na, cuts, threads / 2);
@@ -211,27 +309,32 @@ class PatchBuilder {
     });
   }
 
-  int64_t count_tri(int64_t b, int64_t e, std::vector<int32_t>& stamp, int32_t& mark) const {
-    ++mark;
-    int64_t n = 0;
+  // Triangles of a whole group: each taken at its corner of least id in it.
+  void group_triangles(int32_t g, int64_t b, int64_t e, std::vector<int32_t>& T) const {
+    T.reserve(2 * (e - b) + 2 * in_.own / 7 + 16);
     for (int64_t i = b; i < e; ++i) {
-      const int32_t v = P_.order[i];
+      const int32_t v = pts_[i].id;
       for (int32_t j = in_.row[v]; j < in_.row[v + 1]; ++j) {
         const int32_t t = in_.slot[j] / 3;
-        if (stamp[t] != mark) {
-          stamp[t] = mark;
-          ++n;
-        }
+        const int32_t* c = in_.tri + 3 * (int64_t)t;
+        bool first = true;
+        for (int q = 0; q < 3; ++q) first = first && !(c[q] < v && gof_[c[q]] == g);
+        if (first) T.push_back(t);
       }
     }
-    return n;
+    std::sort(T.begin(), T.end());
   }
 
-  std::vector<int64_t> split_to_fit(int64_t b, int64_t e, std::vector<int32_t>& stamp, int32_t& mark) {
-    if (e - b <= 1 || count_tri(b, e, stamp, mark) <= in_.max_tri) return {b};
+  std::vector<int64_t> split_to_fit(int64_t b, int64_t e) {
+    if (e - b <= 1) return {b};
+    std::vector<int32_t> t;
+    for (int64_t i = b; i < e; ++i)
+      for (int32_t j = in_.row[pts_[i].id]; j < in_.row[pts_[i].id + 1]; ++j) t.push_back(in_.slot[j] / 3);
+    std::sort(t.begin(), t.end());
+    if (std::unique(t.begin(), t.end()) - t.begin() <= in_.max_tri) return {b};
     const int64_t len = e - b, want = len / 2, slack = want / 8;
     const int64_t k = cut(b, e, want, std::max<int64_t>(1, want - slack), std::min(len - 1, want + slack));
-    std::vector<int64_t> out = split_to_fit(b, k, stamp, mark), more = split_to_fit(k, e, stamp, mark);
+    std::vector<int64_t> out = split_to_fit(b, k), more = split_to_fit(k, e);
     out.insert(out.end(), more.begin(), more.end());
     return out;
   }
@@ -239,11 +342,11 @@ class PatchBuilder {
   // Triangles, halo and part slots of every patch.
   std::string fill() {
     const int32_t np = P_.npatch;
-    std::vector<int32_t> inv(in_.nv);
+    UVec<int32_t> inv(in_.nv);
     parallel(in_.threads, [&](int64_t q) {
       for (int64_t i = in_.nv * q / in_.threads; i < in_.nv * (q + 1) / in_.threads; ++i) inv[P_.order[i]] = (int32_t)i;
     });
-    std::vector<int32_t> pof(in_.nv);  // patch of each internal vertex
+    UVec<int32_t> pof(in_.nv);  // patch of each internal vertex
     parallel(np, [&](int64_t k) {
       for (int32_t i = P_.vbeg[k]; i < P_.vbeg[k + 1]; ++i) pof[i] = (int32_t)k;
     });
@@ -251,30 +354,30 @@ class PatchBuilder {
     P_.tbeg.assign(np + 1, 0);
     P_.hbeg.assign(np + 1, 0);
     P_.deg.resize(in_.nv);
-    std::vector<std::vector<int32_t>> tris(np), halos(np);
+    std::vector<std::vector<int32_t>>&tris = tris_, halos(np);
     std::vector<int32_t> slots(np);
-    parallel_stamped(np, [&](int64_t k, std::vector<int32_t>& stamp, int32_t& mark) {
-      ++mark;
+    parallel(np, [&](int64_t k) {
       std::vector<int32_t>&T = tris[k], &H = halos[k];
       const int32_t v0 = P_.vbeg[k], v1 = P_.vbeg[k + 1];
       int32_t s = 0;
+      const bool known = !T.empty();
       for (int32_t i = v0; i < v1; ++i) {
         const int32_t v = P_.order[i];
         P_.deg[i] = (uint16_t)(in_.row[v + 1] - in_.row[v]);
         s += in_.row[v + 1] - in_.row[v];
-        for (int32_t j = in_.row[v]; j < in_.row[v + 1]; ++j) {
-          const int32_t t = in_.slot[j] / 3;
-          if (stamp[t] == mark) continue;
-          stamp[t] = mark;
-          T.push_back(t);
-          for (int c = 0; c < 3; ++c) {
-            const int32_t w = inv[in_.tri[3 * (int64_t)t + c]];
-            if (w < v0 || w >= v1) H.push_back(w);
-          }
-        }
+        if (!known)
+          for (int32_t j = in_.row[v]; j < in_.row[v + 1]; ++j) T.push_back(in_.slot[j] / 3);
       }
+      if (!known) {
+        std::sort(T.begin(), T.end());
+        T.erase(std::unique(T.begin(), T.end()), T.end());
+      }
+      for (int32_t t : T)
+        for (int c = 0; c < 3; ++c) {
+          const int32_t w = inv[in_.tri[3 * (int64_t)t + c]];
+          if (w < v0 || w >= v1) H.push_back(w);
+        }
       slots[k] = s;
-      std::sort(T.begin(), T.end());
       std::sort(H.begin(), H.end());
       H.erase(std::unique(H.begin(), H.end()), H.end());
     });
