@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -1784,90 +1785,115 @@ RD_API const char* rd_last_error(void) { return g_last_error.c_str(); }
 
 namespace {
 
-// Device buffers of one mesh-generation call, freed together.
+// Buffers of one mesh-generation call, freed together: device memory, cut
+// from few allocations, and the host's report, which the device writes.
 struct DlBuffers {
   std::vector<void*> p;
+  char* at = nullptr;
+  size_t left = 0;
+  rd::dl::Control* control = nullptr;
+  int exact_blocks = 0;  // workgroups the exact pass has scratch for
+  rd::dl::Report* report = nullptr;
   DlBuffers() = default;
   DlBuffers(const DlBuffers&) = delete;
   DlBuffers& operator=(const DlBuffers&) = delete;
   ~DlBuffers() {
     for (void* q : p) (void)hipFree(q);
+    if (report) (void)hipHostFree(report);
   }
   template <class T>
   bool get(T** out, size_t n) {
+    const size_t bytes = (std::max<size_t>(n, 1) * sizeof(T) + 255) & ~size_t(255);
+    if (bytes > left) {
+      void* q = nullptr;
+      const size_t take = std::max<size_t>(bytes, size_t(16) << 20);
+      if (hipMalloc(&q, take) != hipSuccess) return false;
+      p.push_back(q);
+      at = static_cast<char*>(q);
+      left = take;
+    }
+    *out = reinterpret_cast<T*>(at);
+    at += bytes;
+    left -= bytes;
+    return true;
+  }
+  bool get_control() {
     void* q = nullptr;
-    if (hipMalloc(&q, std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) return false;
-    p.push_back(q);
-    *out = static_cast<T*>(q);
+    if (!get(&control, 1) || hipHostMalloc(&q, sizeof(rd::dl::Report), hipHostMallocDefault) != hipSuccess) return false;
+    report = static_cast<rd::dl::Report*>(q);
     return true;
   }
 };
 
-// Corner and neighbour tables [3][ts] of nt triangles (tri: [nt][3]).
-rd_status dl_tables(int64_t nv, int64_t nt, int64_t ts, const int32_t* tri, std::vector<int32_t>& tsoa,
-                    std::vector<int32_t>& nbr) {
-  tsoa.assign(3 * ts, -1);
-  nbr.assign(3 * ts, -1);
-  struct Edge {
-    int64_t key;
-    int32_t t, i;
-  };
-  std::vector<Edge> edges(3 * nt);
-  for (int64_t t = 0; t < nt; ++t)
+// Corner and neighbour tables [3][nt] of nt triangles (tri: [nt][3]): the
+// triangle across an edge is the other one at its first vertex that has the
+// second.
+rd_status dl_tables(int64_t nt, const int32_t* tri, const HostGeom& geo, rd::UVec<int32_t>& tsoa,
+                    rd::UVec<int32_t>& nbr) {
+  tsoa.resize(3 * nt);
+  nbr.resize(3 * nt);
+  std::atomic<bool> many{false};
+  parallel_for(nt, [&](int64_t t) {
     for (int i = 0; i < 3; ++i) {
-      const int64_t b = tri[3 * t + (i + 1) % 3], c = tri[3 * t + (i + 2) % 3];
-      edges[3 * t + i] = {std::min(b, c) * nv + std::max(b, c), (int32_t)t, i};
-      tsoa[i * ts + t] = tri[3 * t + i];
+      const int32_t b = tri[3 * t + (i + 1) % 3], c = tri[3 * t + (i + 2) % 3];
+      int32_t u = -1;
+      for (int32_t j = geo.row[b]; j < geo.row[b + 1]; ++j) {
+        const int32_t w = geo.slot[j] / 3;
+        if (w == t || (tri[3 * (int64_t)w] != c && tri[3 * (int64_t)w + 1] != c && tri[3 * (int64_t)w + 2] != c)) continue;
+        if (u >= 0) many = true;
+        u = w;
+      }
+      tsoa[i * nt + t] = tri[3 * t + i];
+      nbr[i * nt + t] = u;
     }
-  std::sort(edges.begin(), edges.end(), [](const Edge& p, const Edge& q) { return p.key < q.key; });
-  for (size_t k = 0; k < edges.size();) {
-    size_t l = k + 1;
-    while (l < edges.size() && edges[l].key == edges[k].key) ++l;
-    if (l - k > 2) return fail(RD_EINVAL, "an edge belongs to more than two triangles");
-    if (l - k == 2) {
-      nbr[edges[k].i * ts + edges[k].t] = edges[k + 1].t;
-      nbr[edges[k + 1].i * ts + edges[k + 1].t] = edges[k].t;
-    }
-    k = l;
-  }
-  return RD_OK;
+  }, 20000);
+  return many ? fail(RD_EINVAL, "an edge belongs to more than two triangles") : RD_OK;
 }
 
 bool hip_ok(hipError_t e) { return e == hipSuccess; }
 
 // Flip rounds until no interior edge of m is illegal. Round and test-pass
 // numbers continue across calls (*round, *pass: the pass about to run, whose
-// marked triangles' edges are tested); m.work is allocated on first need.
-rd_status dl_flip_all(rd::dl::Mesh& m, DlBuffers& b, hipStream_t s, int64_t* flips, int32_t* round, int32_t* pass) {
-  const int64_t cap = 3 * m.ts / 2 + 1;  // interior edges at most
-  const int64_t chunk = std::min<int64_t>(cap, 4096);  // exact tests per launch
-  int32_t cnt[3] = {0, 0, 0};
-  auto read_counts = [&]() {
-    return hip_ok(hipMemcpyAsync(cnt, m.count, sizeof(cnt), hipMemcpyDeviceToHost, s)) &&
-           hip_ok(hipStreamSynchronize(s));
-  };
-  const int32_t kMaxRounds = 1000000;
-  for (int32_t n = 0;; ++n) {
-    const int32_t p = (*pass)++;
-    if (!hip_ok(rd::dl::launch_reset(m, s)) || !hip_ok(rd::dl::launch_mark(m, p, s)) || !read_counts())
-      return fail(RD_EDEVICE, "in-circle pass failed");
-    if (cnt[2] > 0) {
-      if (!m.work && !b.get(&m.work, chunk * rd::dl::exact_scratch()))
-        return fail(RD_ENOMEM, "device allocation failed");
-      for (int64_t f = 0; f < cnt[2]; f += chunk)
-        if (!hip_ok(rd::dl::launch_exact(m, f, std::min<int64_t>(cnt[2], f + chunk), s)))
-          return fail(RD_EDEVICE, "exact in-circle pass failed");
-      if (!read_counts()) return fail(RD_EDEVICE, "exact in-circle pass failed");
-    }
-    if (cnt[1] == 0) return RD_OK;
-    if (n >= kMaxRounds) return fail(RD_EDEVICE, "flipping did not finish");
-    ++*round;
-    if (!hip_ok(rd::dl::launch_flip(m, *round, p, s)) || !hip_ok(rd::dl::launch_fix(m, *round, s)) ||
-        !read_counts())
+// marked triangles' edges are tested). `ahead` rounds are enqueued at a time,
+// then what `more` enqueues (which takes effect only if the run is done by
+// then), and the host waits for the report: *ahead follows the number of
+// rounds that runs take.
+template <class More>
+rd_status dl_flip_all(rd::dl::Mesh& m, const rd::dl::Refine& r, DlBuffers& b, hipStream_t s, int64_t* flips,
+                      int32_t* round, int32_t* pass, int* ahead, const More& more) {
+  constexpr int32_t kMaxRounds = 1000000;
+  const int32_t round0 = *round, pass0 = *pass;
+  volatile rd::dl::Report* h = b.report;
+  int start = rd::dl::kFresh;
+  for (int32_t n = 0;;) {
+    for (int k = 0; k < *ahead; ++k, ++n, start = rd::dl::kGoOn)
+      if (!hip_ok(rd::dl::launch_round(m, b.control, start, round0 + 1 + n, pass0 + n, r.count, b.exact_blocks, s)))
+        return fail(RD_EDEVICE, "flip pass failed");
+    if (!more() || !hip_ok(rd::dl::launch_report(m, r, b.control, b.report, s)) || !hip_ok(hipStreamSynchronize(s)))
       return fail(RD_EDEVICE, "flip pass failed");
-    if (cnt[0] < 1) return fail(RD_EDEVICE, "a round flipped no edge");
-    *flips += cnt[0];
+    if (h->c.stuck) return fail(RD_EDEVICE, "a round flipped no edge");
+    // scratch for the exact pass: 41 KB a thread, a few times the edges seen at most
+    const int want = (int)std::min<int64_t>(16, (h->c.need + 63) / 64);
+    if (h->c.starved || want > 4 * b.exact_blocks) {
+      if (want > b.exact_blocks) {
+        if (!b.get(&m.work, rd::dl::exact_scratch(want))) return fail(RD_ENOMEM, "device allocation failed");
+        b.exact_blocks = want;
+      }
+      if (h->c.starved) {
+        n = h->c.rounds;
+        start = rd::dl::kResume;
+        continue;
+      }
+    }
+    if (h->c.done) break;
+    if (n >= kMaxRounds) return fail(RD_EDEVICE, "flipping did not finish");
+    *ahead = std::min(2 * *ahead, 32);
   }
+  *flips += h->c.flips;
+  *round = round0 + h->c.rounds;
+  *pass = pass0 + h->c.rounds + 1;  // the last pass found nothing illegal
+  *ahead = std::max(2, std::min(h->c.rounds + 2, 32));
+  return RD_OK;
 }
 
 // Device arrays of the flip passes for a capacity of ts triangles.
@@ -1918,11 +1944,12 @@ RD_API rd_status rd_delaunay_flip(int64_t n_vertices, const double* x, const dou
   desc.period_x = period_x;
   desc.period_y = period_y;
   desc.gamma = 1.4;  // not used; the check requires a valid value
-  rd_status st = check_desc(&desc, nullptr);
+  HostGeom geo;
+  rd_status st = check_desc(&desc, &geo);
   if (st != RD_OK) return st;
   const int64_t nt = n_triangles, nv = n_vertices;
-  std::vector<int32_t> nbr, tsoa;
-  if ((st = dl_tables(nv, nt, nt, tri, tsoa, nbr)) != RD_OK) return st;
+  rd::UVec<int32_t> nbr, tsoa;
+  if ((st = dl_tables(nt, tri, geo, tsoa, nbr)) != RD_OK) return st;
   DlBuffers b;
   StreamGuard g;  // declared after the buffers: the stream is drained before they are freed
   rd::dl::Mesh m;
@@ -1930,7 +1957,7 @@ RD_API rd_status rd_delaunay_flip(int64_t n_vertices, const double* x, const dou
   m.ts = nt;
   m.px = period_x;
   m.py = period_y;
-  if (!b.get(&m.x, nv) || !b.get(&m.y, nv) || !dl_flip_arrays(m, b, nt))
+  if (!b.get(&m.x, nv) || !b.get(&m.y, nv) || !dl_flip_arrays(m, b, nt) || !b.get_control())
     return fail(RD_ENOMEM, "device allocation failed");
   if (hipStreamCreate(&g.s) != hipSuccess) return fail(RD_EDEVICE, "hipStreamCreate failed");
   const hipStream_t s = g.s;
@@ -1943,7 +1970,9 @@ RD_API rd_status rd_delaunay_flip(int64_t n_vertices, const double* x, const dou
     return fail(RD_EDEVICE, "upload failed");
   int64_t flips = 0;
   int32_t round = 0, pass = 0;  // every mark is 0: the first pass tests every edge
-  if ((st = dl_flip_all(m, b, s, &flips, &round, &pass)) != RD_OK) return st;
+  int ahead = 6;
+  if ((st = dl_flip_all(m, rd::dl::Refine(), b, s, &flips, &round, &pass, &ahead, [] { return true; })) != RD_OK)
+    return st;
   if (!hip_ok(hipMemcpyAsync(tsoa.data(), m.tri, sizeof(int32_t) * 3 * nt, hipMemcpyDeviceToHost, s)) ||
       !hip_ok(hipStreamSynchronize(s)))
     return fail(RD_EDEVICE, "download failed");
@@ -1986,36 +2015,60 @@ RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, i
   desc.period_x = period_x;
   desc.period_y = period_y;
   desc.gamma = 1.4;  // not used; the check requires a valid value
-  rd_status st = check_desc(&desc, nullptr);
+  HostGeom geo;
+  rd_status st = check_desc(&desc, &geo);
   if (st != RD_OK) return st;
   for (int64_t v = 0; v < nv0; ++v)
     if ((period_x > 0.0 && !(x[v] >= 0.0 && x[v] < period_x)) || (period_y > 0.0 && !(y[v] >= 0.0 && y[v] < period_y)))
       return fail(RD_EINVAL, "a coordinate on a periodic axis is outside [0, period)");
-  const int64_t ts = max_triangles;
-  std::vector<int32_t> nbr, tsoa;
-  if ((st = dl_tables(nv0, nt0, ts, tri, tsoa, nbr)) != RD_OK) return st;
+  rd::UVec<int32_t> nbr, tsoa;
+  if ((st = dl_tables(nt0, tri, geo, tsoa, nbr)) != RD_OK) return st;
   for (int64_t t = 0; t < nt0; ++t)
     for (int i = 0; i < 3; ++i) {
-      if (nbr[i * ts + t] >= 0) continue;
-      const int32_t b = tsoa[((i + 1) % 3) * ts + t], c = tsoa[((i + 2) % 3) * ts + t];
+      if (nbr[i * nt0 + t] >= 0) continue;
+      const int32_t b = tsoa[((i + 1) % 3) * nt0 + t], c = tsoa[((i + 2) % 3) * nt0 + t];
       if (x[b] != x[c] && y[b] != y[c]) return fail(RD_EINVAL, "a boundary edge is not axis-aligned");
     }
+  // Arrays for `vs` vertices and `ts` triangles. The caller's limits are often
+  // far beyond what the mesh comes to need (mapping arrays of that size took
+  // longer than the refinement), so they grow with it: an iteration over nt
+  // triangles adds at most 2 nt, and no more vertices than triangles.
+  struct Arrays {
+    DlBuffers b;
+    rd::dl::Mesh m;
+    rd::dl::Refine r;
+    rd::dl::Order o;
+    char *scan_tmp = nullptr, *sort_tmp = nullptr;
+    size_t scan_bytes = 0, sort_bytes = 0;
+  };
   DlBuffers b;
-  StreamGuard g;
-  rd::dl::Mesh m;
-  rd::dl::Refine r;
-  m.nt = nt0;
-  m.ts = ts;
-  m.px = period_x;
-  m.py = period_y;
-  r.nv = nv0;
-  r.r2 = max_radius * max_radius;
-  r.b2 = max_ratio * max_ratio;
-  if (!b.get(&m.x, max_vertices) || !b.get(&m.y, max_vertices) || !dl_flip_arrays(m, b, ts) ||
-      !b.get(&r.prio, ts) || !b.get(&r.px, ts) || !b.get(&r.py, ts) || !b.get(&r.loc, ts) ||
-      !b.get(&r.where, ts) || !b.get(&r.lock, ts) || !b.get(&r.win, ts) || !b.get(&r.wpos, ts) ||
-      !b.get(&r.tnew, ts) || !b.get(&r.tpos, ts) || !b.get(&r.split, ts) || !b.get(&r.child, 2 * ts) ||
-      !b.get(&r.count, 3))
+  std::unique_ptr<Arrays> A(new Arrays());
+  StreamGuard g;  // declared after the buffers: the stream is drained before they are freed
+  auto allocate = [&](Arrays& a, int64_t vs, int64_t ts) {
+    a.m.ts = ts;
+    rd::dl::Refine& r = a.r;
+    a.scan_bytes = rd::dl::scan_tmp_bytes(ts);
+    if (!a.b.get(&a.m.x, vs) || !a.b.get(&a.m.y, vs) || !dl_flip_arrays(a.m, a.b, ts) || !a.b.get(&r.prio, ts) ||
+        !a.b.get(&r.px, ts) || !a.b.get(&r.py, ts) || !a.b.get(&r.loc, ts) || !a.b.get(&r.where, ts) ||
+        !a.b.get(&r.lock, ts) || !a.b.get(&r.win, ts) || !a.b.get(&r.wpos, ts) || !a.b.get(&r.tnew, ts) ||
+        !a.b.get(&r.tpos, ts) || !a.b.get(&r.split, ts) || !a.b.get(&r.child, 2 * ts) || !a.b.get(&r.count, 3) ||
+        !a.b.get(&a.scan_tmp, a.scan_bytes))
+      return false;
+    if (!morton) return true;
+    const int64_t n = std::max(vs, ts);
+    a.sort_bytes = rd::dl::sort_tmp_bytes(n);
+    return a.b.get(&a.o.key, n) && a.b.get(&a.o.skey, n) && a.b.get(&a.o.idx, n) && a.b.get(&a.o.perm, n) &&
+           a.b.get(&a.o.inv, n) && a.b.get(&a.o.xt, vs) && a.b.get(&a.o.yt, vs) && a.b.get(&a.o.tt, 3 * ts) &&
+           a.b.get(&a.o.nb, 3 * ts) && a.b.get(&a.sort_tmp, a.sort_bytes);
+  };
+  const int64_t ts0 = std::min<int64_t>(max_triangles, std::max<int64_t>(4 * nt0, 1 << 16));
+  A->m.nt = nt0;
+  A->m.px = period_x;
+  A->m.py = period_y;
+  A->r.nv = nv0;
+  A->r.r2 = max_radius * max_radius;
+  A->r.b2 = max_ratio * max_ratio;
+  if (!allocate(*A, std::min(max_vertices, nv0 + ts0 - nt0), ts0) || !b.get_control())
     return fail(RD_ENOMEM, "device allocation failed");
   if (size_grid) {
     // grid frame: the period on a periodic axis (nodes wrap), else the input's extent
@@ -2028,23 +2081,17 @@ RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, i
       g0 = period > 0.0 ? 0.0 : lo;
       gd = period > 0.0 ? period / n : (n > 1 ? (hi - lo) / (n - 1) : 1.0);
     };
-    frame(x, period_x, grid_nx, r.gx0, r.gdx);
-    frame(y, period_y, grid_ny, r.gy0, r.gdy);
+    frame(x, period_x, grid_nx, A->r.gx0, A->r.gdx);
+    frame(y, period_y, grid_ny, A->r.gy0, A->r.gdy);
     double* g = nullptr;
     const int64_t ng = (int64_t)grid_nx * grid_ny;
     if (!b.get(&g, ng)) return fail(RD_ENOMEM, "device allocation failed");
     if (hipMemcpy(g, size_grid, sizeof(double) * ng, hipMemcpyHostToDevice) != hipSuccess)
       return fail(RD_EDEVICE, "upload failed");
-    r.sgrid = g;
-    r.gnx = grid_nx;
-    r.gny = grid_ny;
+    A->r.sgrid = g;
+    A->r.gnx = grid_nx;
+    A->r.gny = grid_ny;
   }
-  const size_t scan_bytes = rd::dl::scan_tmp_bytes(ts);
-  char* scan_tmp = nullptr;
-  if (!b.get(&scan_tmp, scan_bytes)) return fail(RD_ENOMEM, "device allocation failed");
-  rd::dl::Order o;
-  size_t sort_bytes = 0;
-  char* sort_tmp = nullptr;
   if (morton) {
     // Morton frame: the period on a periodic axis, else the input's extent
     auto frame = [&](const double* c, double period, double& c0, double& sc) {
@@ -2056,76 +2103,103 @@ RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, i
       c0 = period > 0.0 ? 0.0 : lo;
       sc = 4294967296.0 / (period > 0.0 ? period : hi - lo);
     };
-    frame(x, period_x, o.x0, o.sx);
-    frame(y, period_y, o.y0, o.sy);
-    const int64_t n = std::max(max_vertices, ts);
-    sort_bytes = rd::dl::sort_tmp_bytes(n);
-    if (!b.get(&o.key, n) || !b.get(&o.skey, n) || !b.get(&o.idx, n) || !b.get(&o.perm, n) || !b.get(&o.inv, n) ||
-        !b.get(&o.xt, max_vertices) || !b.get(&o.yt, max_vertices) || !b.get(&o.tt, 3 * ts) ||
-        !b.get(&o.nb, 3 * ts) || !b.get(&sort_tmp, sort_bytes))
-      return fail(RD_ENOMEM, "device allocation failed");
+    frame(x, period_x, A->o.x0, A->o.sx);
+    frame(y, period_y, A->o.y0, A->o.sy);
   }
   if (hipStreamCreate(&g.s) != hipSuccess) return fail(RD_EDEVICE, "hipStreamCreate failed");
   const hipStream_t s = g.s;
-  if (!hip_ok(hipMemcpyAsync(m.x, x, sizeof(double) * nv0, hipMemcpyHostToDevice, s)) ||
-      !hip_ok(hipMemcpyAsync(m.y, y, sizeof(double) * nv0, hipMemcpyHostToDevice, s)) ||
-      !hip_ok(hipMemcpyAsync(m.tri, tsoa.data(), sizeof(int32_t) * 3 * ts, hipMemcpyHostToDevice, s)) ||
-      !hip_ok(hipMemcpyAsync(m.nbr, nbr.data(), sizeof(int32_t) * 3 * ts, hipMemcpyHostToDevice, s)) ||
-      !hip_ok(hipMemsetAsync(m.flipped, 0, sizeof(int32_t) * ts, s)) ||
-      !hip_ok(hipMemsetAsync(m.mark, 0, sizeof(int32_t) * ts, s)) ||
-      !hip_ok(hipMemsetAsync(r.split, 0, sizeof(int32_t) * ts, s)))
+  // a table of three rows of n entries, rows `to` and `from` entries apart
+  auto rows = [&](int32_t* dst, int64_t to, const int32_t* src, int64_t from, int64_t n, hipMemcpyKind k) {
+    return hip_ok(hipMemcpy2DAsync(dst, sizeof(int32_t) * to, src, sizeof(int32_t) * from, sizeof(int32_t) * n, 3, k, s));
+  };
+  auto clear = [&](Arrays& a) {
+    return hip_ok(hipMemsetAsync(a.m.flipped, 0, sizeof(int32_t) * a.m.ts, s)) &&
+           hip_ok(hipMemsetAsync(a.m.mark, 0, sizeof(int32_t) * a.m.ts, s)) &&
+           hip_ok(hipMemsetAsync(a.r.split, 0, sizeof(int32_t) * a.m.ts, s));
+  };
+  if (!hip_ok(hipMemcpyAsync(A->m.x, x, sizeof(double) * nv0, hipMemcpyHostToDevice, s)) ||
+      !hip_ok(hipMemcpyAsync(A->m.y, y, sizeof(double) * nv0, hipMemcpyHostToDevice, s)) ||
+      !rows(A->m.tri, ts0, tsoa.data(), nt0, nt0, hipMemcpyHostToDevice) ||
+      !rows(A->m.nbr, ts0, nbr.data(), nt0, nt0, hipMemcpyHostToDevice) || !clear(*A))
     return fail(RD_EDEVICE, "upload failed");
   int64_t flips = 0;
   int32_t round = 0, it = 0, pass = 0;  // every mark is 0: the first pass tests every edge
   int64_t nv = nv0, nt = nt0, nt_ordered = nt0;
   // the mesh reached so far goes back to the caller, also when a limit stops the loop
   auto download = [&](rd_status result) {
-    if (!hip_ok(hipMemcpyAsync(x, m.x, sizeof(double) * nv, hipMemcpyDeviceToHost, s)) ||
-        !hip_ok(hipMemcpyAsync(y, m.y, sizeof(double) * nv, hipMemcpyDeviceToHost, s)) ||
-        !hip_ok(hipMemcpyAsync(tsoa.data(), m.tri, sizeof(int32_t) * 3 * ts, hipMemcpyDeviceToHost, s)) ||
-        !hip_ok(hipStreamSynchronize(s)))
+    tsoa.resize(3 * nt);
+    if (!hip_ok(hipMemcpyAsync(x, A->m.x, sizeof(double) * nv, hipMemcpyDeviceToHost, s)) ||
+        !hip_ok(hipMemcpyAsync(y, A->m.y, sizeof(double) * nv, hipMemcpyDeviceToHost, s)) ||
+        !rows(tsoa.data(), nt, A->m.tri, A->m.ts, nt, hipMemcpyDeviceToHost) || !hip_ok(hipStreamSynchronize(s)))
       return fail(RD_EDEVICE, "download failed");
     for (int64_t t = 0; t < nt; ++t)
-      for (int i = 0; i < 3; ++i) tri[3 * t + i] = tsoa[i * ts + t];
+      for (int i = 0; i < 3; ++i) tri[3 * t + i] = tsoa[i * nt + t];
     *n_vertices = nv;
     *n_triangles = nt;
     if (n_iterations) *n_iterations = it;
     if (n_flips) *n_flips = flips;
     return result;
   };
-  if ((st = dl_flip_all(m, b, s, &flips, &round, &pass)) != RD_OK) return st;
-  int32_t cnt[3];
+  int ahead = 6;
+  // the same arrays with room for the next iteration
+  auto grow = [&]() -> rd_status {
+    const int64_t ts = std::min<int64_t>(max_triangles, std::max(4 * nt, 2 * A->m.ts));
+    std::unique_ptr<Arrays> n(new Arrays());
+    n->m.nt = nt;
+    n->m.px = period_x;
+    n->m.py = period_y;
+    n->m.work = A->m.work;
+    n->r = A->r;
+    n->o = A->o;
+    if (!allocate(*n, std::min(max_vertices, nv + ts - nt), ts)) return fail(RD_ENOMEM, "device allocation failed");
+    auto move = [&](void* dst, const void* src, size_t bytes) {
+      return hip_ok(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s));
+    };
+    if (!clear(*n) || !move(n->m.x, A->m.x, sizeof(double) * nv) || !move(n->m.y, A->m.y, sizeof(double) * nv) ||
+        !rows(n->m.tri, ts, A->m.tri, A->m.ts, nt, hipMemcpyDeviceToDevice) ||
+        !rows(n->m.nbr, ts, A->m.nbr, A->m.ts, nt, hipMemcpyDeviceToDevice) ||
+        !move(n->m.flipped, A->m.flipped, sizeof(int32_t) * nt) || !move(n->m.mark, A->m.mark, sizeof(int32_t) * nt) ||
+        !move(n->r.split, A->r.split, sizeof(int32_t) * nt) || !hip_ok(hipStreamSynchronize(s)))
+      return fail(RD_EDEVICE, "growing the mesh failed");
+    A.swap(n);
+    return RD_OK;
+  };
   for (;;) {
+    if (A->m.ts < std::min<int64_t>(max_triangles, 3 * nt) && (st = grow()) != RD_OK) return st;
+    rd::dl::Mesh& m = A->m;
+    rd::dl::Refine& r = A->r;
+    rd::dl::Order& o = A->o;
+    // the flips, then (unless a renumbering, which the host decides, comes in
+    // between) the candidates and the insertion set of the next iteration
     r.seed = 0x9e3779b9u * (uint32_t)(it + 1);
-    if (!hip_ok(hipMemsetAsync(r.count, 0, sizeof(cnt), s)) || !hip_ok(rd::dl::launch_quality(m, r, s)) ||
-        !hip_ok(hipMemcpyAsync(cnt, r.count, sizeof(cnt), hipMemcpyDeviceToHost, s)) ||
-        !hip_ok(hipStreamSynchronize(s)))
-      return fail(RD_EDEVICE, "quality pass failed");
-    if (cnt[0] == 0) {
-      if (cnt[1] > 0)
+    auto candidates = [&] {
+      return hip_ok(rd::dl::launch_candidates(m, r, b.control, s)) &&
+             hip_ok(rd::dl::launch_scan(r.win, r.wpos, nt, A->scan_tmp, A->scan_bytes, s)) &&
+             hip_ok(rd::dl::launch_scan(r.tnew, r.tpos, nt, A->scan_tmp, A->scan_bytes, s));
+    };
+    const bool renumber = it > 0 && morton && 4 * nt >= 5 * nt_ordered;  // after every 25 % of growth, and at the end
+    if ((st = dl_flip_all(m, r, b, s, &flips, &round, &pass, &ahead, [&] { return renumber || candidates(); })) != RD_OK)
+      return st;
+    if (renumber) {
+      if ((st = dl_reorder(m, o, nv, A->sort_tmp, A->sort_bytes, s)) != RD_OK) return st;
+      nt_ordered = nt;
+      if (!candidates() || !hip_ok(rd::dl::launch_report(m, r, b.control, b.report, s)) ||
+          !hip_ok(hipStreamSynchronize(s)))
+        return fail(RD_EDEVICE, "insertion-set passes failed");
+    }
+    const volatile rd::dl::Report* h = b.report;
+    if (h->count[0] == 0) {
+      if (h->count[1] > 0)
         return download(fail(RD_EUNSUPPORTED, "a circumcentre lies more than a quarter period from its triangle"));
-      if (morton && nt != nt_ordered && (st = dl_reorder(m, o, nv, sort_tmp, sort_bytes, s)) != RD_OK) return st;
+      if (morton && nt != nt_ordered && (st = dl_reorder(m, o, nv, A->sort_tmp, A->sort_bytes, s)) != RD_OK) return st;
       return download(RD_OK);
     }
     if (it >= max_iterations) return download(fail(RD_EINVAL, "refinement needs more than max_iterations iterations"));
     ++it;
-    if (!hip_ok(rd::dl::launch_locate(m, r, s)) || !hip_ok(rd::dl::launch_lock(m, r, s)) ||
-        !hip_ok(rd::dl::launch_check(m, r, s)) ||
-        !hip_ok(rd::dl::launch_scan(r.win, r.wpos, nt, scan_tmp, scan_bytes, s)) ||
-        !hip_ok(rd::dl::launch_scan(r.tnew, r.tpos, nt, scan_tmp, scan_bytes, s)))
-      return fail(RD_EDEVICE, "insertion-set passes failed");
-    int32_t last[4];
-    if (!hip_ok(hipMemcpyAsync(&last[0], r.win + nt - 1, sizeof(int32_t), hipMemcpyDeviceToHost, s)) ||
-        !hip_ok(hipMemcpyAsync(&last[1], r.wpos + nt - 1, sizeof(int32_t), hipMemcpyDeviceToHost, s)) ||
-        !hip_ok(hipMemcpyAsync(&last[2], r.tnew + nt - 1, sizeof(int32_t), hipMemcpyDeviceToHost, s)) ||
-        !hip_ok(hipMemcpyAsync(&last[3], r.tpos + nt - 1, sizeof(int32_t), hipMemcpyDeviceToHost, s)) ||
-        !hip_ok(hipMemcpyAsync(cnt, r.count, sizeof(cnt), hipMemcpyDeviceToHost, s)) ||
-        !hip_ok(hipStreamSynchronize(s)))
-      return fail(RD_EDEVICE, "insertion-set passes failed");
-    const int64_t nwin = (int64_t)last[0] + last[1], nadd = (int64_t)last[2] + last[3];
+    const int64_t nwin = h->nwin, nadd = h->nadd;
     if (nwin == 0)
-      return download(fail(RD_EUNSUPPORTED, "no candidate could be inserted (" + std::to_string(cnt[1]) +
-                                                " not located, " + std::to_string(cnt[2]) + " cavities too large)"));
+      return download(fail(RD_EUNSUPPORTED, "no candidate could be inserted (" + std::to_string(h->count[1]) +
+                                                " not located, " + std::to_string(h->count[2]) + " cavities too large)"));
     if (nv + nwin > max_vertices || nt + nadd > max_triangles)
       return download(fail(RD_ENOMEM, "the refined mesh needs more than max_vertices or max_triangles"));
     r.nv = nv;
@@ -2135,11 +2209,6 @@ RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, i
     nv += nwin;
     nt += nadd;
     m.nt = nt;
-    if ((st = dl_flip_all(m, b, s, &flips, &round, &pass)) != RD_OK) return st;
-    if (morton && 4 * nt >= 5 * nt_ordered) {  // renumber after every 25 % of growth, and at the end
-      if ((st = dl_reorder(m, o, nv, sort_tmp, sort_bytes, s)) != RD_OK) return st;
-      nt_ordered = nt;
-    }
   }
 }
 

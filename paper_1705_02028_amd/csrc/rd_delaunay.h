@@ -11,28 +11,44 @@
 namespace rd {
 namespace dl {
 
-// Scratch doubles per thread of the exact in-circle pass.
-int64_t exact_scratch();
+// Account of a run of flip rounds, kept on the device.
+struct Control {
+  int32_t done = 0;    // a round found no illegal edge
+  int32_t rounds = 0;  // rounds that flipped
+  int32_t stuck = 0;   // a round with illegal edges flipped none
+  int32_t starved = 0; // the exact pass had work and no scratch: done, but unfinished
+  int32_t need = 0;    // most edges the exact pass had to test in a round
+  int64_t flips = 0;
+};
 
-// One flip round: reset the claims; test in FP64 the interior edges of the
-// triangles marked for test pass `pass` (undecided ones go to m.undecided);
-// test undecided edges [first, last) exactly; flip the edges that hold both
-// claims (marking triangles with an illegal edge, and flipped ones, for
-// pass + 1); repoint neighbours at flipped pairs.
-hipError_t launch_reset(const Mesh& m, hipStream_t s);
-hipError_t launch_mark(const Mesh& m, int32_t pass, hipStream_t s);
-hipError_t launch_exact(const Mesh& m, int64_t first, int64_t last, hipStream_t s);
-hipError_t launch_flip(const Mesh& m, int32_t round, int32_t pass, hipStream_t s);
-hipError_t launch_fix(const Mesh& m, int32_t round, hipStream_t s);
+// What the host reads after a batch of launches.
+struct Report {
+  Control c;
+  int32_t count[3];  // candidates, not located, cavities too large
+  int32_t nwin, nadd;
+};
 
-// One refinement iteration over the m.nt triangles in use: candidates
-// (quality and encroachment), their location and encroachment test, cavity
-// locks, winners (win, tnew), then, after the host has taken the prefix sums,
-// the insertion and the neighbour repair over the nt_after triangles.
-hipError_t launch_quality(const Mesh& m, const Refine& r, hipStream_t s);
-hipError_t launch_locate(const Mesh& m, const Refine& r, hipStream_t s);
-hipError_t launch_lock(const Mesh& m, const Refine& r, hipStream_t s);
-hipError_t launch_check(const Mesh& m, const Refine& r, hipStream_t s);
+// Scratch doubles of the exact in-circle pass (m.work) on that many workgroups.
+int64_t exact_scratch(int blocks);
+
+// One flip round (start: the first of a run, or the one to try again after it
+// starved): reset the claims (and the three
+// ints at `also`, if any); test in FP64 the interior edges of the triangles
+// marked for test pass `pass`, and exactly those left undecided; flip the
+// edges that hold both claims (marking triangles with an illegal edge, and
+// flipped ones, for pass + 1); repoint neighbours at flipped pairs. Does
+// nothing once the run is done.
+enum { kGoOn = 0, kFresh = 1, kResume = 2 };
+hipError_t launch_round(const Mesh& m, Control* c, int start, int32_t round, int32_t pass, int* also, int exact_blocks,
+                        hipStream_t s);
+
+// One refinement iteration over the m.nt triangles in use, once the flips are
+// done (nothing before): candidates (quality and encroachment), their location
+// and encroachment test, cavity locks, winners (win, tnew); then, after the
+// prefix sums, the insertion and the neighbour repair over the nt_after
+// triangles.
+hipError_t launch_candidates(const Mesh& m, const Refine& r, const Control* c, hipStream_t s);
+hipError_t launch_report(const Mesh& m, const Refine& r, const Control* c, Report* h, hipStream_t s);
 hipError_t launch_insert(const Mesh& m, const Refine& r, int32_t it, int32_t pass, hipStream_t s);
 hipError_t launch_fixsplit(const Mesh& m, const Refine& r, int32_t it, int64_t nt_after, hipStream_t s);
 

@@ -33,12 +33,26 @@ namespace dl {
 
 constexpr int kBlock = 256;
 
-__global__ __launch_bounds__(kBlock) void k_reset(Mesh m) {
+// Rounds are enqueued several at a time without the host looking in between:
+// whether an edge was illegal, and what the round did, is kept on the device
+// (Control), and once a round found nothing illegal the kernels of the rounds
+// after it return at once. Waiting for the host after every kernel instead,
+// 285 times on a mesh refined to 47000 vertices, cost two thirds of its time.
+__global__ __launch_bounds__(kBlock) void k_reset(Mesh m, Control* c, int start, int* also) {
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (t < 3 && also) also[t] = 0;
+  if (start == kFresh) {
+    if (t == 0) *c = Control();
+  } else if (start == kResume) {
+    if (t == 0) c->done = c->starved = 0;
+  } else if (c->done) {
+    return;
+  }
   reset_body(m, t);
 }
 
-__global__ __launch_bounds__(kBlock) void k_mark(Mesh m, int32_t pass) {
+__global__ __launch_bounds__(kBlock) void k_mark(Mesh m, const Control* c, int32_t pass) {
+  if (c->done) return;
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   const int r = t < m.nt ? mark_body(m, t, pass) : 0;
   for (int i = 0; i < 3; ++i) {
@@ -48,40 +62,79 @@ __global__ __launch_bounds__(kBlock) void k_mark(Mesh m, int32_t pass) {
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_exact(Mesh m, int64_t first, int64_t last) {
-  const int64_t k = first + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const bool illegal = k < last && exact_body(m, k, m.work + (k - first) * pred::kIncircleScratch);
-  wave_add(&m.count[1], illegal);
+// Without scratch memory, and with something to do, ends the run unfinished.
+__global__ __launch_bounds__(kBlock) void k_exact(Mesh m, Control* c) {
+  const int64_t n = m.count[2], id = (int64_t)blockIdx.x * kBlock + threadIdx.x, all = (int64_t)gridDim.x * kBlock;
+  if (!m.work) {  // one workgroup
+    if (id == 0 && !c->done && n > 0) {
+      c->done = c->starved = 1;
+      c->need = (int32_t)n;
+    }
+    return;
+  }
+  if (c->done) return;
+  if (id == 0 && n > c->need) c->need = (int32_t)n;
+  for (int64_t first = 0; first < n; first += all) {
+    const int64_t k = first + id;
+    const bool illegal = k < n && exact_body(m, k, m.work + id * pred::kIncircleScratch);
+    wave_add(&m.count[1], illegal);
+  }
 }
 
-__global__ __launch_bounds__(kBlock) void k_flip(Mesh m, int32_t round, int32_t pass) {
+__global__ __launch_bounds__(kBlock) void k_flip(Mesh m, const Control* c, int32_t round, int32_t pass) {
+  if (c->done || m.count[1] == 0) return;
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   wave_add(&m.count[0], t < m.nt && flip_body(m, t, round, pass));
 }
 
-__global__ __launch_bounds__(kBlock) void k_fix(Mesh m, int32_t round) {
+// Also keeps the account (no thread of this launch reads it).
+__global__ __launch_bounds__(kBlock) void k_fix(Mesh m, Control* c, int32_t round) {
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (t < m.nt) fix_body(m, t, round);
+  const int illegal = m.count[1], flips = m.count[0];
+  if (c->starved) return;
+  if (t == 0) {
+    if (illegal == 0) {
+      c->done = 1;
+    } else {
+      c->rounds += 1;
+      c->flips += flips;
+      if (flips < 1) c->done = c->stuck = 1;
+    }
+  }
+  if (illegal != 0 && t < m.nt) fix_body(m, t, round);
 }
 
-__global__ __launch_bounds__(kBlock) void k_quality(Mesh m, Refine r) {
+__global__ __launch_bounds__(kBlock) void k_quality(Mesh m, Refine r, const Control* c) {
+  if (!c->done || c->starved) return;
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   const int q = t < m.nt ? quality_body(m, r, t) : kNone;
   wave_add(&r.count[0], q == kCandidate);
   wave_add(&r.count[1], q == kTooFar);
 }
 
-__global__ __launch_bounds__(kBlock) void k_locate(Mesh m, Refine r) {
+// What the host decides on, into its own (mapped) memory.
+__global__ void k_report(Mesh m, Refine r, const Control* c, Report* h) {
+  h->c = *c;
+  if (!r.count) return;
+  for (int k = 0; k < 3; ++k) h->count[k] = r.count[k];
+  h->nwin = r.win[m.nt - 1] + r.wpos[m.nt - 1];
+  h->nadd = r.tnew[m.nt - 1] + r.tpos[m.nt - 1];
+}
+
+__global__ __launch_bounds__(kBlock) void k_locate(Mesh m, Refine r, const Control* c) {
+  if (!c->done || c->starved || r.count[0] == 0) return;
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (t < m.nt) locate_body(m, r, t);
 }
 
-__global__ __launch_bounds__(kBlock) void k_lock(Mesh m, Refine r) {
+__global__ __launch_bounds__(kBlock) void k_lock(Mesh m, Refine r, const Control* c) {
+  if (!c->done || c->starved || r.count[0] == 0) return;
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (t < m.nt) lock_body(m, r, t);
 }
 
-__global__ __launch_bounds__(kBlock) void k_check(Mesh m, Refine r) {
+__global__ __launch_bounds__(kBlock) void k_check(Mesh m, Refine r, const Control* c) {
+  if (!c->done || c->starved || r.count[0] == 0) return;
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (t < m.nt) check_body(m, r, t);
 }
@@ -128,46 +181,33 @@ __global__ __launch_bounds__(kBlock) void k_tapply(Mesh m, Order o) {
 
 static unsigned nblocks(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-int64_t exact_scratch() { return pred::kIncircleScratch; }
+int64_t exact_scratch(int blocks) { return blocks * kBlock * (int64_t)pred::kIncircleScratch; }
 
-hipError_t launch_reset(const Mesh& m, hipStream_t s) {
-  hipLaunchKernelGGL(k_reset, dim3(nblocks(m.nt > 3 ? m.nt : 3)), dim3(kBlock), 0, s, m);
-  return hipGetLastError();
-}
-hipError_t launch_mark(const Mesh& m, int32_t pass, hipStream_t s) {
-  hipLaunchKernelGGL(k_mark, dim3(nblocks(m.nt)), dim3(kBlock), 0, s, m, pass);
-  return hipGetLastError();
-}
-hipError_t launch_exact(const Mesh& m, int64_t first, int64_t last, hipStream_t s) {
-  if (last <= first) return hipSuccess;
-  hipLaunchKernelGGL(k_exact, dim3(nblocks(last - first)), dim3(kBlock), 0, s, m, first, last);
-  return hipGetLastError();
-}
-hipError_t launch_flip(const Mesh& m, int32_t round, int32_t pass, hipStream_t s) {
-  hipLaunchKernelGGL(k_flip, dim3(nblocks(m.nt)), dim3(kBlock), 0, s, m, round, pass);
-  return hipGetLastError();
-}
-hipError_t launch_fix(const Mesh& m, int32_t round, hipStream_t s) {
-  hipLaunchKernelGGL(k_fix, dim3(nblocks(m.nt)), dim3(kBlock), 0, s, m, round);
+hipError_t launch_round(const Mesh& m, Control* c, int start, int32_t round, int32_t pass, int* also, int exact_blocks,
+                        hipStream_t s) {
+  const dim3 g(nblocks(m.nt)), b(kBlock);
+  hipLaunchKernelGGL(k_reset, dim3(nblocks(m.nt > 3 ? m.nt : 3)), b, 0, s, m, c, start, also);
+  hipLaunchKernelGGL(k_mark, g, b, 0, s, m, c, pass);
+  hipLaunchKernelGGL(k_exact, dim3(m.work ? exact_blocks : 1), b, 0, s, m, c);
+  hipLaunchKernelGGL(k_flip, g, b, 0, s, m, c, round, pass);
+  hipLaunchKernelGGL(k_fix, g, b, 0, s, m, c, round);
   return hipGetLastError();
 }
 
-hipError_t launch_quality(const Mesh& m, const Refine& r, hipStream_t s) {
-  hipLaunchKernelGGL(k_quality, dim3(nblocks(m.nt)), dim3(kBlock), 0, s, m, r);
+hipError_t launch_candidates(const Mesh& m, const Refine& r, const Control* c, hipStream_t s) {
+  const dim3 g(nblocks(m.nt)), b(kBlock);
+  hipLaunchKernelGGL(k_quality, g, b, 0, s, m, r, c);
+  hipLaunchKernelGGL(k_locate, g, b, 0, s, m, r, c);
+  hipLaunchKernelGGL(k_lock, g, b, 0, s, m, r, c);
+  hipLaunchKernelGGL(k_check, g, b, 0, s, m, r, c);
   return hipGetLastError();
 }
-hipError_t launch_locate(const Mesh& m, const Refine& r, hipStream_t s) {
-  hipLaunchKernelGGL(k_locate, dim3(nblocks(m.nt)), dim3(kBlock), 0, s, m, r);
+
+hipError_t launch_report(const Mesh& m, const Refine& r, const Control* c, Report* h, hipStream_t s) {
+  hipLaunchKernelGGL(k_report, dim3(1), dim3(1), 0, s, m, r, c, h);
   return hipGetLastError();
 }
-hipError_t launch_lock(const Mesh& m, const Refine& r, hipStream_t s) {
-  hipLaunchKernelGGL(k_lock, dim3(nblocks(m.nt)), dim3(kBlock), 0, s, m, r);
-  return hipGetLastError();
-}
-hipError_t launch_check(const Mesh& m, const Refine& r, hipStream_t s) {
-  hipLaunchKernelGGL(k_check, dim3(nblocks(m.nt)), dim3(kBlock), 0, s, m, r);
-  return hipGetLastError();
-}
+
 hipError_t launch_insert(const Mesh& m, const Refine& r, int32_t it, int32_t pass, hipStream_t s) {
   hipLaunchKernelGGL(k_insert, dim3(nblocks(m.nt)), dim3(kBlock), 0, s, m, r, it, pass);
   return hipGetLastError();
