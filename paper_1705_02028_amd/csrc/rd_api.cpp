@@ -337,6 +337,37 @@ rd_status run_step(rd_mesh* m, int scheme, int time, int fp32, double cfl, doubl
   return RD_OK;
 }
 
+// n CFL-limited steps. FP64 Euler steps of one call run into each other (a
+// pass brings the state forward by the step before it); D and the bounds
+// alternate between two buffers, the second lent by the second view and the
+// speed ranges.
+rd_status run_steps(rd_mesh* m, int n, int scheme, int time, int fp32, double cfl) {
+  rd_status st;
+  if (fp32 || time == RD_RK2 || scheme == RD_BX || n < 2) {
+    for (int k = 0; k < n; ++k)
+      if ((st = run_step(m, scheme, time, fp32, cfl, 0.0)) != RD_OK) return st;
+    return RD_OK;
+  }
+  rd::Patches p = m->p;
+  hipStream_t s = m->stream;
+  rd::D4* D[2] = {p.D, m->d.Ws};
+  double* pmin[2] = {p.pmin, p.vpart};
+  const bool direct = m->max_mesh_patches <= kDirectPatches;
+  for (int k = 0; k < n; ++k) {
+    p.ci = k & 1;
+    p.D = D[k & 1];
+    p.Dp = D[~k & 1];
+    p.pmin = pmin[k & 1];
+    p.pminp = pmin[~k & 1];
+    HIPCHK(k ? rd::launch_patch_after(p, scheme, s) : rd::launch_patch(p, scheme, 1, true, s));
+    if (direct) p.cfl = cfl;
+    else HIPCHK(rd::launch_patch_dt(p, cfl, s));
+  }
+  p.ci = n & 1;
+  HIPCHK(rd::launch_patch_euler(p, s));
+  return RD_OK;
+}
+
 rd::Dev view32(const rd_mesh* m) {
   rd::Dev d = m->d;
   d.W = m->W32;
@@ -1081,9 +1112,7 @@ RD_API rd_status rd_step_cfl(rd_mesh* m, int n_steps, double cfl, int scheme, in
   if (st != RD_OK) return st;
   DeviceGuard g(m->device);
   if ((st = enter(m, precision == RD_FP32_ACC64)) != RD_OK) return st;
-  for (int n = 0; n < n_steps; ++n)
-    if ((st = run_step(m, scheme, time, precision == RD_FP32_ACC64, cfl, 0.0)) != RD_OK) return st;
-  return RD_OK;
+  return run_steps(m, n_steps, scheme, time, precision == RD_FP32_ACC64, cfl);
 }
 
 RD_API rd_status rd_step_timed(rd_mesh* m, double cfl, int scheme, int time, int precision, double* ms) {
@@ -1644,7 +1673,7 @@ rd_status batch_graph(rd_batch* b, int n_steps, double cfl, int scheme, int time
   rd_batch::Graph c{n_steps, scheme, time, fp32, f->p.slump, cfl, nullptr, nullptr};
   HIPCHK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
   rd_status rs = RD_OK;
-  for (int k = 0; k < n_steps && rs == RD_OK; ++k) rs = run_step(f, scheme, time, fp32, cfl, 0.0);
+  rs = run_steps(f, n_steps, scheme, time, fp32, cfl);
   hipError_t ce = hipStreamEndCapture(s, &c.graph);
   if (rs != RD_OK) {
     if (ce == hipSuccess) (void)hipGraphDestroy(c.graph);

@@ -73,6 +73,10 @@ struct Patches {
   int* flag = nullptr;             // [nmesh] non-physical state latch
   double dt_val = 0.0;             // > 0: the step's dt
   double cfl = 0.0;                // > 0: the workgroup takes dt = cfl * min of its mesh's pmin itself
+  // a stage-1 pass that first takes the Euler step whose D the pass before it left
+  const D4* Dp = nullptr;
+  const double* pminp = nullptr;
+  int ci = 1;                      // where it (and the Euler update) finds the state's buffer: cur[ci]
   int32_t slump = 0;
 };
 

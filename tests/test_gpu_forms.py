@@ -88,3 +88,31 @@ def test_captured_steps_replay_after_the_state_moved(rd, prec, tile):
         else:
             g.set_state(ref)
     g.close()
+
+
+@pytest.mark.parametrize("kind", ["box", "periodic", "large"])
+@pytest.mark.parametrize("scheme", [0, 1, 2, 3, 5])
+def test_runs_of_euler_steps_equal_single_ones(rd, kind, scheme):
+    """n Euler steps of one call (whose updates run into the next step's pass)
+    and n calls of one are equal bit for bit, for odd and even n, and further
+    steps of either time integration go on from them; `large` has more patches
+    than a workgroup reduces by itself."""
+    if kind == "large":
+        m = I.split_square(400, seed=1)
+        W = I.ic_kelvin_helmholtz(m, seed=1)
+    else:
+        m, W = problem(kind)
+    for n in (2, 3, 5):
+        a, b = rd.Mesh(m), rd.Mesh(m)
+        for g in (a, b):
+            g.set_state(W)
+        a.step_cfl(n, 0.3, scheme, rd.EULER1, rd.FP64)
+        for _ in range(n):
+            b.step_cfl(1, 0.3, scheme, rd.EULER1, rd.FP64)
+        assert np.array_equal(a.get_state(), b.get_state()), n
+        for g in (a, b):
+            g.step_cfl(2, 0.3, scheme, rd.EULER1, rd.FP64)
+            g.step_cfl(1, 0.3, scheme, rd.RK2, rd.FP64)
+        assert np.array_equal(a.get_state(), b.get_state()), n
+        a.close()
+        b.close()
