@@ -208,6 +208,8 @@ struct rd_mesh {
   char* slab = nullptr;  // the newest shared allocation, and its bytes that are free
   size_t slab_left = 0;
   double* scratch = nullptr;      // [4 nv] host states pass through it
+  unsigned* done = nullptr;       // workgroups of the CFL pass that have finished
+  double* host_dt = nullptr;      // host memory it writes its result to, from the first rd_max_dt on
   double* phi_scratch = nullptr;  // [4 nt] triangle residuals to a host caller
   // adjoint buffers, allocated on first use
   rd::AdjDev adj;
@@ -279,6 +281,8 @@ void free_list(std::vector<void*>& list) {
 }
 
 void free_all(rd_mesh* m) {
+  if (m->host_dt) (void)hipHostFree(m->host_dt);
+  m->host_dt = nullptr;
   free_list(m->tile_allocs);
   free_list(m->allocs);
 }
@@ -950,7 +954,7 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   int *cur, *flag;
   double *dt, *vr;
   if ((st = dalloc(m, &W0, nv)) || (st = dalloc(m, &W1, nv)) || (st = dalloc(m, &D, nv)) ||
-      (st = upload(m, &cur, std::vector<int>{0, 0})) || (st = upload(m, &flag, std::vector<int>(nmesh, 0))) ||
+      (st = upload(m, &cur, std::vector<int>{0, 0})) || (st = upload(m, &m->done, std::vector<unsigned>{0})) || (st = upload(m, &flag, std::vector<int>(nmesh, 0))) ||
       (st = dalloc(m, &dt, nmesh)) || (st = upload(m, &vr, vr0)) || (st = dalloc(m, &m->scratch, 4 * nv)))
     return st;
   p.W[0] = W0;
@@ -1083,14 +1087,26 @@ RD_API rd_status rd_max_dt(rd_mesh* m, double cfl, double* dt_out) {
   DeviceGuard g(m->device);
   if (m->form32 && !m->captured) {
     HIPCHK(rd::launch_cfl32(view32(m), m->cfl, cfl, m->stream));
-  } else {
-    rd_status st = enter(m, 0);
-    if (st != RD_OK) return st;
-    HIPCHK(rd::launch_patch_cfl(m->p, m->stream));
-    HIPCHK(rd::launch_patch_dt(m->p, cfl, m->stream));
+    HIPCHK(hipMemcpyAsync(dt_out, m->p.dt, sizeof(double), hipMemcpyDeviceToHost, m->stream));
+    HIPCHK(hipStreamSynchronize(m->stream));
+    return RD_OK;
   }
-  HIPCHK(hipMemcpyAsync(dt_out, m->p.dt, sizeof(double), hipMemcpyDeviceToHost, m->stream));
+  rd_status st = enter(m, 0);
+  if (st != RD_OK) return st;
+  // The device writes the result into host memory: a wait then gives it, where
+  // a copy behind the kernels cost 10 us more at 49^2. Up to kDirectPatches
+  // patches the last workgroup takes the minimum itself (their count goes
+  // through one word, which many more would queue for).
+  if (!m->host_dt) {
+    void* q = nullptr;
+    HIPCHK(hipHostMalloc(&q, sizeof(double), hipHostMallocDefault));
+    m->host_dt = static_cast<double*>(q);
+  }
+  const bool one = m->p.npatch <= kDirectPatches;
+  HIPCHK(rd::launch_patch_cfl(m->p, cfl, one ? m->done : nullptr, m->host_dt, m->stream));
+  if (!one) HIPCHK(rd::launch_patch_dt(m->p, cfl, m->stream, m->host_dt));
   HIPCHK(hipStreamSynchronize(m->stream));
+  *dt_out = *const_cast<volatile double*>(m->host_dt);
   return RD_OK;
 }
 
@@ -1276,7 +1292,7 @@ RD_API rd_status rd_residual(rd_mesh* m, int scheme, double* R, double* phiT, in
   rd_status st;
   const rd::Dev& d = m->d;
   hipStream_t s = m->stream;
-  HIPCHK(rd::launch_view(d, state_of(m), s));
+  HIPCHK(rd::launch_view(d, state_of(m), scheme == RD_BX, s));
   const int64_t nv = d.nv, nt = d.nt;
   if (scheme == RD_BX) HIPCHK(rd::launch_vrange32(d, m->cfl, false, s));
   HIPCHK(rd::launch_tri(d, scheme, s));

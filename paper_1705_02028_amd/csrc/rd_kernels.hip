@@ -36,10 +36,10 @@ __global__ __launch_bounds__(kBlock) void k_set_state(Dev d, const double* soa) 
   if (!vertex_z(d, v, w)) d.flag[0] = 1;
 }
 
-// The state, wherever it is, into d.W with its Z, and (thread b < nwv) the
+// Z of the state, wherever it is (keep: the state into d.W too), and (thread b < nwv) the
 // wall term of wall vertex b: one launch instead of three, where a call on a
 // small mesh is little but its launches.
-__global__ __launch_bounds__(kBlock) void k_view(Dev d, State st) {
+__global__ __launch_bounds__(kBlock) void k_view(Dev d, State st, int keep) {
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (v < d.nwv) {
     D4 acc;
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kBlock) void k_view(Dev d, State st) {
   }
   if (v >= d.nv) return;
   const D4 w = *st.at(v);
-  d.W[v] = w;
+  if (keep) d.W[v] = w;
   vertex_z(d, v, w.v);
 }
 
@@ -378,8 +378,8 @@ hipError_t launch_set_state(const Dev& d, const double* soa, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_view(const Dev& d, const State& st, hipStream_t s) {
-  hipLaunchKernelGGL(k_view, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, st);
+hipError_t launch_view(const Dev& d, const State& st, bool keep, hipStream_t s) {
+  hipLaunchKernelGGL(k_view, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, st, keep ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -18,8 +18,8 @@ hipError_t launch_residual(const Dev& d, double* out_soa, hipStream_t s);
 hipError_t launch_wall(const Dev& d, bool stage2, hipStream_t s);
 // d.W and d.Z from the caller's [4][nv]; flag[0] where non-physical
 hipError_t launch_set_state(const Dev& d, const double* soa, hipStream_t s);
-// The state into d.W with d.Z, and the wall terms at it.
-hipError_t launch_view(const Dev& d, const State& st, hipStream_t s);
+// d.Z of the state (keep: and d.W), and the wall terms at it.
+hipError_t launch_view(const Dev& d, const State& st, bool keep, hipStream_t s);
 // FP64 kept triangle residuals (keepT) to component-major arrays
 hipError_t launch_keep_to_soa(const Dev& d, double* soa, hipStream_t s);
 hipError_t launch_set_scalar(double* p, double v, hipStream_t s);

@@ -316,8 +316,10 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch_euler(Patches p) {
   }
 }
 
-// The patch's smallest CFL bound alone (rd_max_dt).
-__global__ __launch_bounds__(kPatchThreads) void k_patch_cfl(Patches p) {
+// The smallest CFL bound alone (rd_max_dt): every patch its own and, with
+// `done` (a count of workgroups, 0 between launches), the workgroup that
+// finishes last the mesh's, into dt and straight into the host's memory.
+__global__ __launch_bounds__(kPatchThreads) void k_patch_cfl(Patches p, double cfl, unsigned* done, double* host) {
   extern __shared__ double2 lds[];
   const int32_t k = (int32_t)xcd_block();
   const PatchDesc q = p.desc[k];
@@ -350,17 +352,37 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch_cfl(Patches p) {
   }
   __shared__ double red[16];
   bound = patch_min(bound, red);
-  if (tid == 0) p.pmin[k] = bound;
+  __shared__ unsigned last;
+  if (tid == 0) {
+    p.pmin[k] = bound;
+    if (done) __threadfence();
+    last = done && atomicAdd(done, 1u) + 1u == gridDim.x;
+  }
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  double x = INFINITY;
+  for (int32_t b = tid; b < p.npatch; b += nthr) x = rmin(x, __hip_atomic_load(&p.pmin[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  __syncthreads();
+  x = patch_min(x, red);
+  if (tid == 0) {
+    p.dt[0] = cfl * x;
+    *host = cfl * x;
+    *done = 0;
+  }
 }
 
 // Per mesh: dt = cfl * the minimum of its patches' bounds.
-__global__ __launch_bounds__(1024) void k_patch_dt(Patches p, double cfl) {
+__global__ __launch_bounds__(1024) void k_patch_dt(Patches p, double cfl, double* host) {
   const int m = blockIdx.x;
   double x = INFINITY;
   for (int32_t b = p.mbeg[m] + threadIdx.x; b < p.mbeg[m + 1]; b += blockDim.x) x = rmin(x, p.pmin[b]);
   __shared__ double red[16];
   x = patch_min(x, red);
-  if (threadIdx.x == 0) p.dt[m] = cfl * x;
+  if (threadIdx.x == 0) {
+    p.dt[m] = cfl * x;
+    if (host) host[m] = cfl * x;
+  }
 }
 
 // Smallest and largest flow speed |v| over each patch's vertices (the Bx
@@ -513,14 +535,14 @@ hipError_t launch_patch_euler(const Patches& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_patch_cfl(const Patches& p, hipStream_t s) {
+hipError_t launch_patch_cfl(const Patches& p, double cfl, unsigned* done, double* host, hipStream_t s) {
   const size_t lds = (size_t)p.max_lv * 24 + (size_t)p.max_slots * 8;
-  hipLaunchKernelGGL(k_patch_cfl, dim3(p.npatch), dim3(p.threads), lds, s, p);
+  hipLaunchKernelGGL(k_patch_cfl, dim3(p.npatch), dim3(p.threads), lds, s, p, cfl, done, host);
   return hipGetLastError();
 }
 
-hipError_t launch_patch_dt(const Patches& p, double cfl, hipStream_t s) {
-  hipLaunchKernelGGL(k_patch_dt, dim3(p.nmesh), dim3(1024), 0, s, p, cfl);
+hipError_t launch_patch_dt(const Patches& p, double cfl, hipStream_t s, double* host) {
+  hipLaunchKernelGGL(k_patch_dt, dim3(p.nmesh), dim3(1024), 0, s, p, cfl, host);
   return hipGetLastError();
 }
 

@@ -25,8 +25,11 @@ hipError_t launch_patch(const Patches& p, int scheme, int stage, bool cfl, hipSt
 hipError_t launch_patch_after(const Patches& p, int scheme, hipStream_t s);
 // Forward Euler: the state in cur[p.ci]'s buffer by -dt p.D.
 hipError_t launch_patch_euler(const Patches& p, hipStream_t s);
-hipError_t launch_patch_cfl(const Patches& p, hipStream_t s);
-hipError_t launch_patch_dt(const Patches& p, double cfl, hipStream_t s);
+// The patch bounds alone, with `done` also their minimum times cfl -> p.dt[0]
+// and *host (one mesh).
+hipError_t launch_patch_cfl(const Patches& p, double cfl, unsigned* done, double* host, hipStream_t s);
+// Per mesh cfl times the minimum of its patches' bounds -> p.dt (and host).
+hipError_t launch_patch_dt(const Patches& p, double cfl, hipStream_t s, double* host = nullptr);
 // Bx sensor range at W^n, or at W* (after stage 1, with p.dt set) -> p.vr
 hipError_t launch_patch_vrange(const Patches& p, bool star, hipStream_t s);
 // The state from the caller's [4][nv] arrays into the first patch buffer
