@@ -1290,24 +1290,19 @@ RD_API rd_status rd_residual(rd_mesh* m, int scheme, double* R, double* phiT, in
   if (scheme < RD_N || scheme > RD_BX) return fail(RD_EINVAL, "unknown scheme");
   DeviceGuard g(m->device);
   rd_status st;
+  if ((st = enter(m, 0)) != RD_OK) return st;
   const rd::Dev& d = m->d;
   hipStream_t s = m->stream;
-  HIPCHK(rd::launch_view(d, state_of(m), scheme == RD_BX, s));
   const int64_t nv = d.nv, nt = d.nt;
-  if (scheme == RD_BX) HIPCHK(rd::launch_vrange32(d, m->cfl, false, s));
-  HIPCHK(rd::launch_tri(d, scheme, s));
-  if (on_device) {
-    HIPCHK(rd::launch_residual(d, R, s));
-    if (phiT) HIPCHK(rd::launch_keep_to_soa(d, phiT, s));
-    return RD_OK;
-  }
-  if (phiT && !m->phi_scratch && (st = dalloc(m, &m->phi_scratch, 4 * nt)) != RD_OK) return st;
-  HIPCHK(rd::launch_residual(d, m->scratch, s));
+  if (!on_device && phiT && !m->phi_scratch && (st = dalloc(m, &m->phi_scratch, 4 * nt)) != RD_OK) return st;
+  if (scheme == RD_BX) HIPCHK(rd::launch_patch_vrange(m->p, false, s));
+  HIPCHK(rd::launch_patch_residual(m->p, scheme, s));
+  const rd::State res{{m->p.D, m->p.D}, m->p.cur, m->inv, nullptr};
+  double* phi = !phiT || on_device ? phiT : m->phi_scratch;
+  HIPCHK(rd::launch_residual(d, res, on_device ? R : m->scratch, state_of(m), phi, s));
+  if (on_device) return RD_OK;
   HIPCHK(hipMemcpyAsync(R, m->scratch, sizeof(double) * 4 * nv, hipMemcpyDeviceToHost, s));
-  if (phiT) {
-    HIPCHK(rd::launch_keep_to_soa(d, m->phi_scratch, s));
-    HIPCHK(hipMemcpyAsync(phiT, m->phi_scratch, sizeof(double) * 4 * nt, hipMemcpyDeviceToHost, s));
-  }
+  if (phiT) HIPCHK(hipMemcpyAsync(phiT, m->phi_scratch, sizeof(double) * 4 * nt, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   return RD_OK;
 }

@@ -576,19 +576,24 @@ __host__ __device__ inline void vertex_update(const double in[4], double f, cons
   for (int k = 0; k < 4; ++k) out[k] = in[k] - f * acc[k];
 }
 
-// Residual of vertex v: the sum of its parts and the wall term.
-__host__ __device__ inline void residual_body(int64_t v, const Dev& d, double* out_soa) {
-  const int32_t code = d.bc ? d.bc[v] : -1;
-  const int32_t b = is_ghost(code) ? -1 : wall_index(code);
-  double acc[4];
-  const int32_t deg = d.row[v + 1] - d.row[v];
-  const int64_t s0 = vslot(d, v);
-  sum_parts(deg, [&](int32_t j) { return part_load<double>(d, s0 + 64 * (int64_t)j); }, acc);
-  if (b >= 0) {
-    const D4 wn = d.WCn[b];
-    for (int k = 0; k < 4; ++k) acc[k] = acc[k] + wn.v[k];
+// phi^T of triangle t at the state st, into component-major arrays.
+__host__ __device__ inline void phi_body(int64_t t, const Dev& d, const State& st, double* soa) {
+  D4 z[3];
+  double2 xy[3];
+  for (int i = 0; i < 3; ++i) {
+    const int32_t v = d.tv[i * d.nt + t];
+    const VertexDerived o = derive(d.gamma, st.at(v)->v);
+    for (int k = 0; k < 4; ++k) z[i].v[k] = o.z[k];
+    xy[i] = d.xy[v];
   }
-  for (int k = 0; k < 4; ++k) out_soa[k * d.nv + v] = acc[k];
+  const TriDiff g = tri_diff(d, xy[0], xy[1], xy[2]);
+  SymEdge<double> e[3];
+  sym_edges(g.d1x, g.d1y, g.d2x, g.d2y, e);
+  SymTri<double> s;
+  sym_triangle<double, false>(z[0].v, z[1].v, z[2].v, e, d.gas, s);
+  double phi[4];
+  sym_to_conserved(s.f, s.phi, phi);
+  for (int k = 0; k < 4; ++k) soa[k * d.nt + t] = phi[k] * kSymScale;
 }
 
 // Wall term (Section 3.5) of vertex v: the sum over its wall incidences

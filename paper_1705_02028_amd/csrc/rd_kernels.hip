@@ -17,11 +17,6 @@ __global__ __launch_bounds__(kBlock, 4) void k_tri(Dev d) {
   if (t < d.nt) tri_body<SCHEME>(t, d);
 }
 
-__global__ __launch_bounds__(kBlock) void k_residual(Dev d, double* out_soa) {
-  const int64_t v = xcd_block() * kBlock + threadIdx.x;
-  if (v < d.nv) residual_body(v, d, out_soa);
-}
-
 template <bool STAGE2>
 __global__ __launch_bounds__(kBlock) void k_wall(Dev d) {
   const int64_t b = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -36,32 +31,16 @@ __global__ __launch_bounds__(kBlock) void k_set_state(Dev d, const double* soa) 
   if (!vertex_z(d, v, w)) d.flag[0] = 1;
 }
 
-// Z of the state, wherever it is (keep: the state into d.W too), and (thread b < nwv) the
-// wall term of wall vertex b: one launch instead of three, where a call on a
-// small mesh is little but its launches.
-__global__ __launch_bounds__(kBlock) void k_view(Dev d, State st, int keep) {
-  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (v < d.nwv) {
-    D4 acc;
-    wall_term(d.went, d.wptr[v], d.wptr[v + 1], d.wv[v], d.gamma, [&](int64_t i) { return *st.at(i); }, acc.v);
-    d.WCn[v] = acc;
+// Residuals into the caller's arrays: thread v moves vertex v's (r) to R,
+// thread t works out triangle t's (phi^T) at the state st. One launch for
+// both: on a small mesh the launches are the time.
+__global__ __launch_bounds__(kBlock) void k_residual(Dev d, State r, double* R, State st, double* phi) {
+  const int64_t i = xcd_block() * kBlock + threadIdx.x;
+  if (i < d.nv) {
+    const D4 x = *r.at(i);
+    for (int k = 0; k < 4; ++k) R[k * d.nv + i] = x.v[k];
   }
-  if (v >= d.nv) return;
-  const D4 w = *st.at(v);
-  if (keep) d.W[v] = w;
-  vertex_z(d, v, w.v);
-}
-
-// FP64 kept triangle residuals (two 16-byte planes: components 0-1, then
-// 2-3) to component-major arrays.
-__global__ __launch_bounds__(kBlock) void k_keep_to_soa(const double2* src, double* soa, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  const double2 a = src[i], b = src[n + i];
-  soa[i] = a.x;
-  soa[n + i] = a.y;
-  soa[2 * n + i] = b.x;
-  soa[3 * n + i] = b.y;
+  if (phi && i < d.nt) phi_body(i, d, st, phi);
 }
 
 __global__ void k_set_scalar(double* p, double v) { p[0] = v; }
@@ -355,14 +334,8 @@ hipError_t launch_tri(const Dev& d, int scheme, hipStream_t s) {
     case SCH_B: hipLaunchKernelGGL(k_tri<SCH_B>, g, b, 0, s, d); break;
     case SCH_BMAX: hipLaunchKernelGGL(k_tri<SCH_BMAX>, g, b, 0, s, d); break;
     case SCH_BMIN: hipLaunchKernelGGL(k_tri<SCH_BMIN>, g, b, 0, s, d); break;
-    case SCH_BX: hipLaunchKernelGGL(k_tri<SCH_BX>, g, b, 0, s, d); break;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_residual(const Dev& d, double* out_soa, hipStream_t s) {
-  hipLaunchKernelGGL(k_residual, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, out_soa);
   return hipGetLastError();
 }
 
@@ -378,14 +351,9 @@ hipError_t launch_set_state(const Dev& d, const double* soa, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_view(const Dev& d, const State& st, bool keep, hipStream_t s) {
-  hipLaunchKernelGGL(k_view, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, st, keep ? 1 : 0);
-  return hipGetLastError();
-}
-
-hipError_t launch_keep_to_soa(const Dev& d, double* soa, hipStream_t s) {
-  hipLaunchKernelGGL(k_keep_to_soa, dim3(nblk(d.nt)), dim3(kBlock), 0, s, static_cast<const double2*>(d.keepT),
-                     soa, d.nt);
+hipError_t launch_residual(const Dev& d, const State& r, double* R, const State& st, double* phi, hipStream_t s) {
+  const int64_t n = phi && d.nt > d.nv ? d.nt : d.nv;
+  hipLaunchKernelGGL(k_residual, dim3(nblk(n)), dim3(kBlock), 0, s, d, r, R, st, phi);
   return hipGetLastError();
 }
 

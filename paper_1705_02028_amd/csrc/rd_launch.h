@@ -12,16 +12,13 @@ constexpr int kBlock = 256;
 
 // Stage-1 parts of every triangle, N parts and residual kept.
 hipError_t launch_tri(const Dev& d, int scheme, hipStream_t s);
-// Vertex sums of the parts and the wall term -> [4][nv].
-hipError_t launch_residual(const Dev& d, double* out_soa, hipStream_t s);
 // wall term at W, or (stage2) at Ws
 hipError_t launch_wall(const Dev& d, bool stage2, hipStream_t s);
 // d.W and d.Z from the caller's [4][nv]; flag[0] where non-physical
 hipError_t launch_set_state(const Dev& d, const double* soa, hipStream_t s);
-// d.Z of the state (keep: and d.W), and the wall terms at it.
-hipError_t launch_view(const Dev& d, const State& st, bool keep, hipStream_t s);
-// FP64 kept triangle residuals (keepT) to component-major arrays
-hipError_t launch_keep_to_soa(const Dev& d, double* soa, hipStream_t s);
+// Vertex residuals (r) -> R [4][nv]; phi^T of every triangle at the state st
+// -> phi [4][nt] (may be null).
+hipError_t launch_residual(const Dev& d, const State& r, double* R, const State& st, double* phi, hipStream_t s);
 hipError_t launch_set_scalar(double* p, double v, hipStream_t s);
 hipError_t launch_set_int(int* p, int v, hipStream_t s);
 // p[0..n) = v

@@ -127,7 +127,9 @@ __device__ __forceinline__ TriDiff patch_diff(const Patches& p, const PatchDesc&
 // the other buffer by their owner. A run of n Euler steps is then n passes and
 // one update instead of n of each: 20 steps of the N scheme take 7.0 us a step
 // against 9.9 at 64^2 and 308 against 406 at 2048^2.
-template <int SCHEME, bool CFL, bool AFTER>
+// RES: the residual itself (sum of parts and wall term, ghosts' sums of parts
+// too) in D's place.
+template <int SCHEME, bool CFL, bool AFTER, bool RES = false>
 __global__ __launch_bounds__(kPatchThreads, 4) void k_patch1(Patches p) {
   extern __shared__ double2 lds[];
   const int c0 = p.cur[AFTER ? p.ci : 0];
@@ -206,7 +208,7 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch1(Patches p) {
     }
     const double f = V > 0.0 ? rcp(V) : 0.0;
     D4 o;
-    for (int c = 0; c < 4; ++c) o.v[c] = V > 0.0 ? f * acc[c] : 0.0;
+    for (int c = 0; c < 4; ++c) o.v[c] = RES ? acc[c] : (V > 0.0 ? f * acc[c] : 0.0);
     p.D[v] = o;
   }
   if (CFL) {
@@ -501,6 +503,21 @@ static hipError_t patch_go(const Patches& p, int stage, bool cfl, hipStream_t s)
   else if (stage == 2) hipLaunchKernelGGL((k_patch2<SCHEME, false>), g, b, lds, s, p);
   else if (cfl) hipLaunchKernelGGL((k_patch1<SCHEME, true, false>), g, b, lds, s, p);
   else hipLaunchKernelGGL((k_patch1<SCHEME, false, false>), g, b, lds, s, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_patch_residual(const Patches& p, int scheme, hipStream_t s) {
+  const dim3 g(p.npatch), b(p.threads);
+  const size_t lds = patch_lds_bytes(p, 1, false);
+  switch (scheme) {
+    case SCH_N: hipLaunchKernelGGL((k_patch1<SCH_N, false, false, true>), g, b, lds, s, p); break;
+    case SCH_LDA: hipLaunchKernelGGL((k_patch1<SCH_LDA, false, false, true>), g, b, lds, s, p); break;
+    case SCH_B: hipLaunchKernelGGL((k_patch1<SCH_B, false, false, true>), g, b, lds, s, p); break;
+    case SCH_BMAX: hipLaunchKernelGGL((k_patch1<SCH_BMAX, false, false, true>), g, b, lds, s, p); break;
+    case SCH_BMIN: hipLaunchKernelGGL((k_patch1<SCH_BMIN, false, false, true>), g, b, lds, s, p); break;
+    case SCH_BX: hipLaunchKernelGGL((k_patch1<SCH_BX, false, false, true>), g, b, lds, s, p); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

@@ -20,6 +20,8 @@ size_t patch_lds_bytes(const Patches& p, int stage, bool cfl);
 // stage 1 (also Euler): p.D and, with cfl, the patch bounds p.pmin; stage 2:
 // the new state (in the other buffer).
 hipError_t launch_patch(const Patches& p, int scheme, int stage, bool cfl, hipStream_t s);
+// The residual of every vertex into p.D (p.vr set for Bx).
+hipError_t launch_patch_residual(const Patches& p, int scheme, hipStream_t s);
 // Stage 1 with CFL bounds of a state that is one Euler step back (p.Dp,
 // p.pminp of the pass before; not for Bx, whose sensor needs the state first).
 hipError_t launch_patch_after(const Patches& p, int scheme, hipStream_t s);
