@@ -80,8 +80,22 @@ def algorithmic_bytes(nt, nv, fp32):
     return k
 
 
+def patch_bytes(nt, nv):
+    """The same for the FP64 step, whose passes work patch by patch and keep
+    every part in LDS: per triangle its three packed words, per vertex state,
+    coordinates, volume and degree in (stage 2: D too), D or the new state out.
+    Vertices on a patch border are read by each of its patches and their
+    triangles are computed again; neither is counted (about a quarter and a
+    seventh more). method_bytes counts parts that never reach HBM here, so the
+    FP64 roofline is taken from these bytes; the passes are bound by FP64
+    instructions, not by them."""
+    vert = 32 + 16 + 8 + 2
+    return {"tri1": nt * 12 + nv * (vert + 32), "tri2": nt * 12 + nv * (vert + 32 + 32),
+            "cfl": 0, "shared1": 0, "gather1": 0, "gather2": 0, "wall1": 0, "wall2": 0}
+
+
 def algorithmic_bytes_tiled(nt, nv, fp32, info):
-    """The same for the tiled form. info = rd_mesh_tile_info: L local vertex
+    """The same for the tiled form of the FP32 step. info = rd_mesh_tile_info: L local vertex
     records over all tiles (a vertex on a tile border is loaded by each of its
     tiles), S shared vertices, P their parts; I = nv - S vertices are finished
     inside their tile. Parts of interior vertices never leave LDS."""
@@ -109,9 +123,10 @@ def algorithmic_bytes_tiled(nt, nv, fp32, info):
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_kh2048.txt")
 
 
-# The sources that define the triangle kernels of both forms (their bodies,
+# The sources that define the triangle kernels of all forms (their bodies,
 # launch shapes and the translation units they are compiled in).
-TRI_SOURCES = ("rd_device.h", "rd_kcommon.h", "rd_launch.h", "rd_kernels.hip", "rd_tiles.h", "rd_tiles.hip")
+TRI_SOURCES = ("rd_device.h", "rd_math.h", "rd_sym.h", "rd_kcommon.h", "rd_patch.h", "rd_patch.hip", "rd_fp32.h",
+               "rd_fp32.hip", "rd_tiles.h", "rd_tiles.hip")
 
 
 def source_hash():
@@ -155,10 +170,10 @@ def roofline_entry(name, mbytes, ibytes, ms, traffic_key=None):
                                "frac": round(impl / PEAK_HBM, 4)}}
 
 
-def step_roofline(nt, fp32, ms_step):
-    """The whole step against HBM: the method's bytes of all four passes over
-    the measured time per step."""
-    b = sum(method_bytes(nt, fp32).values())
+def step_roofline(nbytes, ms_step):
+    """The whole step against HBM: the bytes of all passes over the measured
+    time per step."""
+    b = sum(nbytes.values())
     return {"bytes": int(b), "achieved": round(b / (ms_step * 1e-3) / 1e9, 1),
             "frac": round(b / (ms_step * 1e-3) / PEAK_HBM, 4)}
 
@@ -467,13 +482,12 @@ def three_d(rd, inputs, N=128, steps=10, warmup=2):
     g.close()
     nt, nv = m["nt"], m["nv"]
     names = ["cfl", "tet1", "gather1", "tet2", "gather2"]
-    # algorithmic bytes per tetrahedron pass. First: corners and slots (32),
-    # normals (96), the parts (160), the kept N parts of three corners and the
-    # residual (160) per tetrahedron, Z once per vertex (40). Second: the same
-    # with the kept values read instead of written (160), the volume (8), and
-    # the first-stage rate besides Z per vertex (80).
-    b_tet1 = nt * (32 + 96 + 160 + 160) + nv * 40
-    b_tet2 = nt * (32 + 96 + 8 + 160 + 160) + nv * 80
+    # bytes per tetrahedron pass that no tiling avoids: the packed corners (16)
+    # per tetrahedron; per vertex Z, |u| + c and position in (72; the second
+    # pass Z at W* and the rate too, 80) and a sum of parts out (48). The
+    # passes are bound by FP64 instructions, not by these.
+    b_tet1 = nt * 16 + nv * (72 + 48)
+    b_tet2 = nt * 16 + nv * (72 + 80 + 48)
     dom = 1 if ms[1] >= ms[3] else 3
     b_dom = b_tet1 if dom == 1 else b_tet2
     ach = b_dom / (ms[dom] * 1e-3)
@@ -515,7 +529,7 @@ def main():
     ap.add_argument("--renumber", choices=["none", "random", "morton"], default="none",
                     help="vertex and triangle numbering of the mesh (default: the lattice order)")
     ap.add_argument("--tile", type=int, default=-1,
-                    help="triangles per tile of the fused step (0: two-pass form; -1: run the autotuner)")
+                    help="triangles per tile of the FP32 step (0: its two-pass form; -1: run the autotuner)")
     ap.add_argument("--no-adjoint", action="store_true")
     ap.add_argument("--batch", type=int, default=256, metavar="NMESH",
                     help="time NMESH four-quadrant meshes (32^2..512^2) per instance vs one batched graph (0: skip)")
@@ -593,7 +607,7 @@ def main():
         "roofline": roofline_entry(dom32, method_bytes(nt, True)[dom32], b32[dom32], per32[dom32],
                                    f"fp32/{form_name(form32['tile'])}/{dom32}"
                                    if args.renumber == "none" and args.N == 2048 else None),
-        "step_roofline": step_roofline(nt, True, ms32 / args.steps),
+        "step_roofline": step_roofline(method_bytes(nt, True), ms32 / args.steps),
         "vertex_updates_per_s": round(nv * args.steps / (ms32 * 1e-3), 1),
         "stages": stage_rates(per32, nt),
         "kernels_ms": {k: round(v, 5) for k, v in per32.items()},
@@ -605,39 +619,22 @@ def main():
         print(f"bench: fp64 {args.steps} steps", file=sys.stderr, flush=True)
         ms64, per64, form64 = time_variant(rd, torch, mesh, W0, rd.FP64, args.steps, args.warmup, args.cfl,
                                            args.timed_reps, args.tile)
-        b64 = (algorithmic_bytes_tiled(nt, nv, False, form64["tile_info"]) if form64["tile"]
-               else algorithmic_bytes(nt, nv, False))
+        b64 = patch_bytes(nt, nv)
         dom64 = max(per64, key=per64.get)
         result["fp64"] = {"value": round(nt * args.steps / (ms64 * 1e-3), 1), "unit": "triangle-updates/s",
                           "ms_per_step": round(ms64 / args.steps, 5),
                           "vertex_updates_per_s": round(nv * args.steps / (ms64 * 1e-3), 1),
                           "stages": stage_rates(per64, nt),
-                          "roofline": roofline_entry(dom64, method_bytes(nt, False)[dom64], b64[dom64], per64[dom64],
-                                                     f"fp64/{form_name(form64['tile'])}/{dom64}"
+                          "roofline": roofline_entry(dom64, b64[dom64], b64[dom64], per64[dom64],
+                                                     f"fp64/patches/{dom64}"
                                                      if args.renumber == "none" and args.N == 2048 else None),
-                          "step_roofline": step_roofline(nt, False, ms64 / args.steps),
+                          "step_roofline": step_roofline(b64, ms64 / args.steps),
                           "kernels_ms": {k: round(v, 5) for k, v in per64.items()},
                           "kernels_GBps": {k: round(b64[k] / (v * 1e-3) / 1e9, 1)
                                            for k, v in per64.items() if v > 0 and b64.get(k)},
                           "form": form64}
-        if form64["tile"]:
-            # the two-pass form beside the tuner's tiled pick: its triangle passes are the FP64
-            # kernels with a per-triangle roofline of their own
-            ms2, per2, _ = time_variant(rd, torch, mesh, W0, rd.FP64, args.steps, args.warmup, args.cfl,
-                                        args.timed_reps, 0)
-            b2 = algorithmic_bytes(nt, nv, False)
-            dom2 = max(per2, key=per2.get)
-            result["fp64"]["two_pass"] = {
-                "ms_per_step": round(ms2 / args.steps, 5),
-                "value": round(nt * args.steps / (ms2 * 1e-3), 1),
-                "roofline": roofline_entry(dom2, method_bytes(nt, False)[dom2], b2[dom2], per2[dom2],
-                                           f"fp64/two-pass/{dom2}"
-                                           if args.renumber == "none" and args.N == 2048 else None),
-                "kernels_ms": {k: round(v, 5) for k, v in per2.items()},
-                "kernels_GBps": {k: round(b2[k] / (v * 1e-3) / 1e9, 1) for k, v in per2.items()
-                                 if v > 0 and b2.get(k)}}
     if not args.no_variants:
-        # the other blends and lumpings of Sections 3.3.3 and 3.4 on the same workload (two-pass form)
+        # the other blends and lumpings of Sections 3.3.3 and 3.4 on the same workload
         print("bench: scheme variants", file=sys.stderr, flush=True)
         variants = {}
         for name, scheme, lump in (("Bx", rd.BX, 0), ("B, selective lumping", rd.B, 1)):

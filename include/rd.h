@@ -144,19 +144,19 @@ rd_status rd_step(rd_mesh* mesh, double dt, int scheme, int time, int precision)
 rd_status rd_step_cfl(rd_mesh* mesh, int n_steps, double cfl, int scheme, int time, int precision);
 
 /* Kernel slots of one step, in launch order, as reported by rd_step_timed.
- * Two-pass form: every part goes to HBM, a vertex gather sums it. Tiled
- * form: a tile pass sums the parts of tile-interior vertices in LDS and a
- * shared pass sums those of vertices on tile borders. */
+ * The FP64 step is two passes over patches of vertices, each of which finishes
+ * its own; the FP32 step's two-pass form sends every part to HBM, where a
+ * vertex gather sums it, and its tiled form sums the parts of tile-interior
+ * vertices in LDS and those of vertices on tile borders in a shared pass. */
 enum {
-  RD_K_WALL1 = 0,   /* wall term at W^n (meshes with walls) */
-  RD_K_TRI1 = 1,    /* stage-1 (or Euler) triangle pass; two-pass form: also l_max lambda_max per
-                       corner; tiled form: tile pass, also interior vertex residuals and CFL bounds */
+  RD_K_WALL1 = 0,   /* FP32: wall term at W^n (meshes with walls) */
+  RD_K_TRI1 = 1,    /* stage-1 (or Euler) pass over patches, triangles or tiles, with CFL terms */
   RD_K_SHARED1 = 2, /* tiled form: shared-vertex residuals and CFL bounds */
-  RD_K_CFL = 3,     /* CFL reduction: per-vertex bounds, block and per-mesh minima -> dt */
-  RD_K_GATHER1 = 4, /* two-pass form: stage-1 vertex sums and update; tiled form: Euler update */
-  RD_K_WALL2 = 5,   /* wall term at W* (RK2 with walls) */
-  RD_K_TRI2 = 6,    /* stage-2 triangle pass (RK2); tiled form: also the interior vertex update */
-  RD_K_GATHER2 = 7, /* stage-2 vertex sums and update (RK2); tiled form: shared vertices only */
+  RD_K_CFL = 3,     /* CFL reduction -> dt (FP64: of the patches' minima) */
+  RD_K_GATHER1 = 4, /* two-pass form: stage-1 vertex sums and update; else the Euler update */
+  RD_K_WALL2 = 5,   /* FP32: wall term at W* (RK2 with walls) */
+  RD_K_TRI2 = 6,    /* stage-2 pass (RK2) */
+  RD_K_GATHER2 = 7, /* two-pass form: stage-2 vertex sums and update (RK2); tiled form: shared vertices */
   RD_NKERNELS = 8
 };
 
@@ -166,16 +166,18 @@ enum {
  * kernels the step does not launch). For profiling. */
 rd_status rd_step_timed(rd_mesh* mesh, double cfl, int scheme, int time, int precision, double* ms);
 
-/* Form of the step (Sections 3.2-3.4 computed either way). tile_triangles
- * = 0 selects the two-pass form. A value in [32, 1024] selects the tiled
- * form: triangles are ordered along a Morton curve of their centroids and cut
- * into tiles of that many triangles; one workgroup per tile stages the
- * tile's vertex data in LDS and finishes the vertices all of whose
- * triangles are in the tile. Every vertex sums its parts in ascending
- * triangle order in both forms, so results are bitwise identical for every
- * tile size and equal to the two-pass form's up to rounding. RD_EUNSUPPORTED
- * if a tile would need more LDS than one workgroup may use on the device
- * (160 KiB on MI355X). Waits for the mesh's stream. The default is 0. */
+/* Form of the FP32 step (Sections 3.2-3.4 computed either way; the FP64 step
+ * has one form, whose patches the library sizes). tile_triangles = 0 selects
+ * the two-pass form. A value in [32, 1024] selects the tiled form: triangles
+ * are ordered along a Morton curve of their centroids and cut into tiles of
+ * that many triangles; one workgroup per tile stages the tile's vertex data in
+ * LDS and finishes the vertices all of whose triangles are in the tile. Every
+ * vertex sums its parts in ascending triangle order in every form, so results
+ * are bitwise identical for every tile size and equal to the two-pass form's
+ * up to rounding. RD_EUNSUPPORTED if a tile would need more LDS than one
+ * workgroup may use on the device (160 KiB on MI355X). Waits for the mesh's
+ * stream. The default is 0. A graph captured from FP32 steps of this mesh is
+ * no longer valid once its tile size has changed. */
 rd_status rd_mesh_set_tile(rd_mesh* mesh, int tile_triangles);
 rd_status rd_mesh_get_tile(const rd_mesh* mesh, int* tile_triangles);
 /* Lumping of the mesh's RK2 steps (rd_lumping; RD_EINVAL for other values).

@@ -1359,8 +1359,7 @@ rd_status adjoint_enqueue(rd_mesh* m, const rd::AdjDev& a, rd::D4* Wa, double* s
   ad.lam = rd::LamSoA{lam_np1, m->d.nv};  // read in the caller's layout
   ad.idt = 1.0 / dt;
   ad.waves = rd::kAdjWavesPerCu * m->ncu;
-  HIPCHK(rd::launch_set_state(dn, W_n, s));
-  HIPCHK(rd::launch_set_scalar(d.dt, dt, s));
+  HIPCHK(rd::launch_set_state(dn, W_n, dt, s));
   const bool rk2 = time == RD_RK2;
   if (rk2) {
     HIPCHK(rd::launch_wall(dn, false, s));

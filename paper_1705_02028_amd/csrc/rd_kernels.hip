@@ -23,8 +23,9 @@ __global__ __launch_bounds__(kBlock) void k_wall(Dev d) {
   if (b < d.nwv) wall_body<STAGE2>(b, d);
 }
 
-__global__ __launch_bounds__(kBlock) void k_set_state(Dev d, const double* soa) {
+__global__ __launch_bounds__(kBlock) void k_set_state(Dev d, const double* soa, double dt) {
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (v == 0) d.dt[0] = dt;
   if (v >= d.nv) return;
   const double w[4] = {soa[v], soa[d.nv + v], soa[2 * d.nv + v], soa[3 * d.nv + v]};
   st4<double>(d.W, v, w);
@@ -346,8 +347,8 @@ hipError_t launch_wall(const Dev& d, bool stage2, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_set_state(const Dev& d, const double* soa, hipStream_t s) {
-  hipLaunchKernelGGL(k_set_state, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, soa);
+hipError_t launch_set_state(const Dev& d, const double* soa, double dt, hipStream_t s) {
+  hipLaunchKernelGGL(k_set_state, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, soa, dt);
   return hipGetLastError();
 }
 

@@ -14,8 +14,8 @@ constexpr int kBlock = 256;
 hipError_t launch_tri(const Dev& d, int scheme, hipStream_t s);
 // wall term at W, or (stage2) at Ws
 hipError_t launch_wall(const Dev& d, bool stage2, hipStream_t s);
-// d.W and d.Z from the caller's [4][nv]; flag[0] where non-physical
-hipError_t launch_set_state(const Dev& d, const double* soa, hipStream_t s);
+// d.W and d.Z from the caller's [4][nv], and d.dt[0]; flag[0] where non-physical
+hipError_t launch_set_state(const Dev& d, const double* soa, double dt, hipStream_t s);
 // Vertex residuals (r) -> R [4][nv]; phi^T of every triangle at the state st
 // -> phi [4][nt] (may be null).
 hipError_t launch_residual(const Dev& d, const State& r, double* R, const State& st, double* phi, hipStream_t s);

@@ -1,4 +1,4 @@
-// Host-side construction of the triangle tiles of the fused step.
+// Host-side construction of the triangle tiles of the FP32 step's tiled form.
 //
 // Triangles are ordered along a Morton curve of their centroids (within each
 // mesh of a batch, on that mesh's own bounding box) and cut into tiles of
