@@ -208,6 +208,7 @@ struct rd_mesh {
   char* slab = nullptr;  // the newest shared allocation, and its bytes that are free
   size_t slab_left = 0;
   double* scratch = nullptr;      // [4 nv] host states pass through it
+  int* bad = nullptr;             // first vertex of a host state that is not physical
   unsigned* done = nullptr;       // workgroups of the CFL pass that have finished
   double* host_dt = nullptr;      // host memory it writes its result to, from the first rd_max_dt on
   double* phi_scratch = nullptr;  // [4 nt] triangle residuals to a host caller
@@ -831,14 +832,6 @@ rd_status check_step_args(int scheme, int time, int precision) {
   return RD_OK;
 }
 
-bool physical(const double* W, int64_t nv, int64_t i, double gamma) {
-  const double rho = W[i], mx = W[nv + i], my = W[2 * nv + i], e = W[3 * nv + i];
-  if (!std::isfinite(rho) || !std::isfinite(mx) || !std::isfinite(my) || !std::isfinite(e)) return false;
-  if (!(rho > 0.0)) return false;
-  const double p = (gamma - 1.0) * (e - 0.5 * (mx * mx + my * my) / rho);
-  return p > 0.0;
-}
-
 }  // namespace
 
 RD_API rd_status rd_mesh_validate(const rd_mesh_desc* desc) {
@@ -954,7 +947,7 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   int *cur, *flag;
   double *dt, *vr;
   if ((st = dalloc(m, &W0, nv)) || (st = dalloc(m, &W1, nv)) || (st = dalloc(m, &D, nv)) ||
-      (st = upload(m, &cur, std::vector<int>{0, 0})) || (st = upload(m, &m->done, std::vector<unsigned>{0})) || (st = upload(m, &flag, std::vector<int>(nmesh, 0))) ||
+      (st = upload(m, &cur, std::vector<int>{0, 0})) || (st = upload(m, &m->done, std::vector<unsigned>{0})) || (st = dalloc(m, &m->bad, 1)) || (st = upload(m, &flag, std::vector<int>(nmesh, 0))) ||
       (st = dalloc(m, &dt, nmesh)) || (st = upload(m, &vr, vr0)) || (st = dalloc(m, &m->scratch, 4 * nv)))
     return st;
   p.W[0] = W0;
@@ -1049,18 +1042,20 @@ RD_API rd_status rd_set_state(rd_mesh* m, const double* W, int on_device) {
   const int64_t nv = m->d.nv;
   const double* src = W;
   if (!on_device) {
-    for (int64_t i = 0; i < nv; ++i)
-      if (!physical(W, nv, i, m->gamma))
-        return fail(RD_ENONPHYS, "vertex " + std::to_string(i) + " has rho <= 0, p <= 0 or a non-finite value");
     HIPCHK(hipMemcpyAsync(m->scratch, W, sizeof(double) * 4 * nv, hipMemcpyHostToDevice, m->stream));
     src = m->scratch;
+    int bad = 0;
+    HIPCHK(rd::launch_check_state(src, nv, 2, m->gamma, m->bad, m->stream));
+    HIPCHK(hipMemcpyAsync(&bad, m->bad, sizeof(int), hipMemcpyDeviceToHost, m->stream));
+    HIPCHK(hipStreamSynchronize(m->stream));
+    if (bad < nv)
+      return fail(RD_ENONPHYS, "vertex " + std::to_string(bad) + " has rho <= 0, p <= 0 or a non-finite value");
   }
   HIPCHK(rd::launch_set_int(m->p.flag, 0, m->stream));
   // into the form of the last steps
   note_capture(m);
   if (m->form32) HIPCHK(rd::launch_set32(view32(m), m->d32, m->p.cur, src, m->stream));
   else HIPCHK(rd::launch_patch_set(m->p, m->inv, src, m->stream));
-  if (!on_device) HIPCHK(hipStreamSynchronize(m->stream));
   return RD_OK;
 }
 
@@ -2259,6 +2254,7 @@ RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, i
 
 struct rd3_mesh {
   rd3::Dev3 d;
+  int* bad = nullptr;  // first vertex of a host state that is not physical
   std::vector<void*> bufs;
   hipStream_t stream = nullptr;
   ~rd3_mesh() {
@@ -2406,7 +2402,7 @@ static rd_status rd3_create(const rd3_mesh_desc* desc, rd3_mesh** out) {
       !dev_put(m.get(), &drbeg, P.rbeg) || !dev_put(m.get(), &dinv, P.inv) || !dev_put(m.get(), &dV, Vi) ||
       !dev_put(m.get(), &d.r1, r1) || !dev_get(m.get(), &d.W, 5 * nv) || !dev_get(m.get(), &d.Ws, 5 * nv) ||
       !dev_get(m.get(), &d.r2, 5 * nv) || !dev_get(m.get(), &d.rec, 6 * P.lv.size()) || !dev_get(m.get(), &d.dt, 1) ||
-      !dev_get(m.get(), &d.bmin, nb) || !dev_get(m.get(), &d.flag, 1))
+      !dev_get(m.get(), &d.bmin, nb) || !dev_get(m.get(), &d.flag, 1) || !dev_get(m.get(), &m->bad, 1))
     return fail(RD_ENOMEM, "device allocation failed");
   HIPCHK(hipStreamCreate(&m->stream));
   HIPCHK(hipMemsetAsync(d.W, 0, sizeof(double) * 5 * nv, m->stream));
@@ -2437,19 +2433,17 @@ RD_API rd_status rd3_mesh_destroy(rd3_mesh* mesh) {
 RD_API rd_status rd3_set_state(rd3_mesh* m, const double* W, int on_device) {
   if (!m || !W) return fail(RD_EINVAL, "null argument");
   const int64_t nv = m->d.nv;
-  if (!on_device) {
-    for (int64_t i = 0; i < nv; ++i) {
-      const double rho = W[i], e = W[4 * nv + i];
-      const double q = W[nv + i] * W[nv + i] + W[2 * nv + i] * W[2 * nv + i] + W[3 * nv + i] * W[3 * nv + i];
-      if (!(rho > 0.0) || !std::isfinite(e) || !((m->d.gamma - 1.0) * (e - 0.5 * q / rho) > 0.0))
-        return fail(RD_ENONPHYS, "vertex " + std::to_string(i) + ": rho <= 0, p <= 0 or not finite");
-    }
+  if (!on_device) {  // through Ws, which holds nothing between steps
+    int bad = 0;
+    HIPCHK(hipMemcpyAsync(m->d.Ws, W, sizeof(double) * 5 * nv, hipMemcpyHostToDevice, m->stream));
+    HIPCHK(rd::launch_check_state(m->d.Ws, nv, 3, m->d.gamma, m->bad, m->stream));
+    HIPCHK(hipMemcpyAsync(&bad, m->bad, sizeof(int), hipMemcpyDeviceToHost, m->stream));
+    HIPCHK(hipStreamSynchronize(m->stream));
+    if (bad < nv)
+      return fail(RD_ENONPHYS, "vertex " + std::to_string(bad) + ": rho <= 0, p <= 0 or not finite");
   }
-  // host states pass through Ws, which holds nothing between steps
-  if (!on_device) HIPCHK(hipMemcpyAsync(m->d.Ws, W, sizeof(double) * 5 * nv, hipMemcpyHostToDevice, m->stream));
   HIPCHK(rd::launch_fill_int(m->d.flag, 0, 1, m->stream));
   HIPCHK(rd3::launch3_set(m->d, on_device ? W : m->d.Ws, m->stream));
-  if (!on_device) HIPCHK(hipStreamSynchronize(m->stream));
   return RD_OK;
 }
 

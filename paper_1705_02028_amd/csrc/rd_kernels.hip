@@ -3,6 +3,8 @@
 //
 // Launch shapes: one thread per triangle or per vertex, 256-thread
 // workgroups, block ids renumbered per XCD.
+#include <climits>
+
 #include "rd_adjoint.h"
 #include "rd_kcommon.h"
 #include "rd_launch.h"
@@ -42,6 +44,29 @@ __global__ __launch_bounds__(kBlock) void k_residual(Dev d, State r, double* R, 
     for (int k = 0; k < 4; ++k) R[k * d.nv + i] = x.v[k];
   }
   if (phi && i < d.nt) phi_body(i, d, st, phi);
+}
+
+// First vertex of a caller's state [2 + M][nv] that is not physical (rho > 0,
+// p > 0, finite; three-dimensional states with M = 3 momenta have always been
+// taken with an infinite density) -> *bad, which holds INT_MAX before. On the
+// device the check costs the copy's bytes once more; on the host it took
+// longer than the copy. Contraction off: the host's arithmetic.
+template <int M>
+__global__ __launch_bounds__(kBlock) void k_check_state(const double* W, int64_t nv, double gamma, int* bad) {
+#pragma clang fp contract(off)
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= nv) return;
+  const double rho = W[i], e = W[(1 + M) * nv + i];
+  bool ok = rho > 0.0 && isfinite(e);
+  double q = 0.0;
+  for (int k = 1; k <= M; ++k) {
+    const double m = W[k * nv + i];
+    q = k == 1 ? m * m : q + m * m;
+    if (M == 2) ok = ok && isfinite(m);
+  }
+  if (M == 2) ok = ok && isfinite(rho);
+  ok = ok && (gamma - 1.0) * (e - 0.5 * q / rho) > 0.0;
+  if (!ok) atomicMin(bad, (int)i);
 }
 
 __global__ void k_set_scalar(double* p, double v) { p[0] = v; }
@@ -355,6 +380,13 @@ hipError_t launch_set_state(const Dev& d, const double* soa, double dt, hipStrea
 hipError_t launch_residual(const Dev& d, const State& r, double* R, const State& st, double* phi, hipStream_t s) {
   const int64_t n = phi && d.nt > d.nv ? d.nt : d.nv;
   hipLaunchKernelGGL(k_residual, dim3(nblk(n)), dim3(kBlock), 0, s, d, r, R, st, phi);
+  return hipGetLastError();
+}
+
+hipError_t launch_check_state(const double* W, int64_t nv, int momenta, double gamma, int* bad, hipStream_t s) {
+  hipLaunchKernelGGL(k_set_int, dim3(1), dim3(1), 0, s, bad, INT_MAX);
+  if (momenta == 2) hipLaunchKernelGGL(k_check_state<2>, dim3(nblk(nv)), dim3(kBlock), 0, s, W, nv, gamma, bad);
+  else hipLaunchKernelGGL(k_check_state<3>, dim3(nblk(nv)), dim3(kBlock), 0, s, W, nv, gamma, bad);
   return hipGetLastError();
 }
 

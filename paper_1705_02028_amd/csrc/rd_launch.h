@@ -19,6 +19,9 @@ hipError_t launch_set_state(const Dev& d, const double* soa, double dt, hipStrea
 // Vertex residuals (r) -> R [4][nv]; phi^T of every triangle at the state st
 // -> phi [4][nt] (may be null).
 hipError_t launch_residual(const Dev& d, const State& r, double* R, const State& st, double* phi, hipStream_t s);
+// First vertex of a state [2 + momenta][nv] that is not physical -> *bad
+// (INT_MAX: none).
+hipError_t launch_check_state(const double* W, int64_t nv, int momenta, double gamma, int* bad, hipStream_t s);
 hipError_t launch_set_scalar(double* p, double v, hipStream_t s);
 hipError_t launch_set_int(int* p, int v, hipStream_t s);
 // p[0..n) = v

@@ -116,3 +116,33 @@ def test_runs_of_euler_steps_equal_single_ones(rd, kind, scheme):
         assert np.array_equal(a.get_state(), b.get_state()), n
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("where", [[0], [300, 77], [-1]])
+@pytest.mark.parametrize("what", ["rho", "pressure", "energy"])
+def test_host_states_are_checked_on_the_device(rd, dim, where, what):
+    """The first vertex that is not physical is named, and the state that was
+    there stays."""
+    if dim == 2:
+        m, W = problem("periodic")
+        g = rd.Mesh(m)
+    else:
+        m = I.cube_tets(8, seed=1)
+        W = I.ic3_kelvin_helmholtz(m, seed=1)
+        g = rd.Mesh3(m)
+    g.set_state(W)
+    bad = W.copy()
+    for v in where:
+        if what == "rho":
+            bad[0, v] = 0.0
+        elif what == "pressure":
+            bad[-1, v] = 0.0
+            bad[1, v] = 1.0
+        else:
+            bad[-1, v] = np.inf
+    with pytest.raises(rd.RDError, match=f"vertex {min(v % m['nv'] for v in where)}\\b") as e:
+        g.set_state(bad)
+    assert e.value.status == rd.RD_ENONPHYS
+    assert np.array_equal(g.get_state(), W)
+    g.close()
