@@ -698,10 +698,13 @@ rd_status enter(rd_mesh* m, int fp32) {
 // Owned vertices per patch the library asks for: 215 (about 490 triangles, the
 // 512 threads of a workgroup nearly full) on meshes with enough vertices to
 // give every compute unit a patch, fewer on smaller ones so that the step is
-// spread over the device, down to 32 (below, the triangles shared with
-// neighbouring patches outnumber the patch's own).
+// spread over the device, down to 48: below, the triangles shared with
+// neighbouring patches outnumber the patch's own, and a pass is the latency of
+// one patch anyway (RK2 step, us, with a least size of 16 / 32 / 48 / 64 / 128:
+// 14.0 / 13.4 / 13.5 / 13.5 / 16.5 at 64^2, 15.3 / 15.3 / 13.8 / 13.7 / 16.5 at
+// 100^2, 16.4 / 16.5 / 16.5 / 16.5 / 16.4 at 160^2).
 int patch_own(int64_t nv, int ncu) {
-  return (int)std::min<int64_t>(215, std::max<int64_t>(32, nv / std::max(1, ncu)));
+  return (int)std::min<int64_t>(215, std::max<int64_t>(48, nv / std::max(1, ncu)));
 }
 
 rd_status build_patches(rd_mesh* m) {
