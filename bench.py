@@ -170,6 +170,24 @@ def roofline_entry(name, mbytes, ibytes, ms, traffic_key=None):
                                "frac": round(impl / PEAK_HBM, 4)}}
 
 
+# VALU wavefront instructions per triangle of the FP64 passes on the 2048^2
+# mesh (border triangles counted once per patch; profiles/pmc_kh2048.md), and
+# the rate a device of 256 CUs issues them at: one per SIMD every 4 cycles.
+PATCH_VALU = {"tri1": 12.91, "tri2": 18.27}
+VALU_ISSUE = 256 * 4 * 2.4e9 / 4
+
+
+def valu_issue(entry, name, nt):
+    """Says what bounds an FP64 pass: the share of the issue peak its
+    instructions take."""
+    if name in PATCH_VALU:
+        rate = nt * PATCH_VALU[name] / (entry["avg_ms"] * 1e-3)
+        entry["valu_issue"] = {"achieved": round(rate / 1e9, 1), "peak": VALU_ISSUE / 1e9, "unit": "Ginstr/s",
+                               "frac": round(rate / VALU_ISSUE, 4)}
+        entry["bound"] = "valu"
+    return entry
+
+
 def step_roofline(nbytes, ms_step):
     """The whole step against HBM: the bytes of all passes over the measured
     time per step."""
@@ -625,9 +643,9 @@ def main():
                           "ms_per_step": round(ms64 / args.steps, 5),
                           "vertex_updates_per_s": round(nv * args.steps / (ms64 * 1e-3), 1),
                           "stages": stage_rates(per64, nt),
-                          "roofline": roofline_entry(dom64, b64[dom64], b64[dom64], per64[dom64],
-                                                     f"fp64/patches/{dom64}"
-                                                     if args.renumber == "none" and args.N == 2048 else None),
+                          "roofline": valu_issue(
+                              roofline_entry(dom64, b64[dom64], b64[dom64], per64[dom64], f"fp64/patches/{dom64}"
+                                             if args.renumber == "none" and args.N == 2048 else None), dom64, nt),
                           "step_roofline": step_roofline(b64, ms64 / args.steps),
                           "kernels_ms": {k: round(v, 5) for k, v in per64.items()},
                           "kernels_GBps": {k: round(b64[k] / (v * 1e-3) / 1e9, 1)
