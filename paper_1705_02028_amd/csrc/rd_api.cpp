@@ -1083,14 +1083,10 @@ RD_API rd_status rd_max_dt(rd_mesh* m, double cfl, double* dt_out) {
   if (!m || !dt_out) return fail(RD_EINVAL, "null argument");
   if (!(cfl > 0.0)) return fail(RD_EINVAL, "cfl must be positive");
   DeviceGuard g(m->device);
-  if (m->form32 && !m->captured) {
-    HIPCHK(rd::launch_cfl32(view32(m), m->cfl, cfl, m->stream));
-    HIPCHK(hipMemcpyAsync(dt_out, m->p.dt, sizeof(double), hipMemcpyDeviceToHost, m->stream));
-    HIPCHK(hipStreamSynchronize(m->stream));
-    return RD_OK;
-  }
-  rd_status st = enter(m, 0);
-  if (st != RD_OK) return st;
+  // The bounds are those of the FP64 passes whatever steps ran before. A state
+  // in the FP32 form stays there, for the steps that follow: a copy is read.
+  note_capture(m);
+  if (m->form32 || m->captured) HIPCHK(rd::launch_patch_copy(m->p, state_of(m), m->stream));
   // The device writes the result into host memory: a wait then gives it, where
   // a copy behind the kernels cost 10 us more at 49^2. Up to kDirectPatches
   // patches the last workgroup takes the minimum itself (their count goes

@@ -325,7 +325,8 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch_cfl(Patches p, double c
   extern __shared__ double2 lds[];
   const int32_t k = (int32_t)xcd_block();
   const PatchDesc q = p.desc[k];
-  const D4* W = p.W[p.cur[0]];
+  const int c0 = p.cur[0];
+  const D4* W = p.W[c0 == kForm32 ? 0 : c0];  // a state in the FP32 form: its copy (launch_patch_copy)
   const int32_t tid = threadIdx.x, nthr = blockDim.x;
   double2* xy = lds;
   double* sig = reinterpret_cast<double*>(xy + p.max_lv);
@@ -584,6 +585,10 @@ hipError_t launch_state_get4(const State& st, int64_t nv, D4* out, hipStream_t s
 }
 hipError_t launch_patch_set4(const Patches& p, const int32_t* inv, const D4* in, hipStream_t s) {
   hipLaunchKernelGGL(k_patch_set4, dim3(nblk(p.nv)), dim3(kBlock), 0, s, p, inv, in);
+  return hipGetLastError();
+}
+hipError_t launch_patch_copy(const Patches& p, const State& st, hipStream_t s) {
+  hipLaunchKernelGGL(k_patch_enter, dim3(nblk(p.nv)), dim3(kBlock), 0, s, st, p.nv);
   return hipGetLastError();
 }
 hipError_t launch_patch_enter(const Patches& p, const State& st, hipStream_t s) {

@@ -27,7 +27,8 @@ hipError_t launch_patch_residual(const Patches& p, int scheme, hipStream_t s);
 hipError_t launch_patch_after(const Patches& p, int scheme, hipStream_t s);
 // Forward Euler: the state in cur[p.ci]'s buffer by -dt p.D.
 hipError_t launch_patch_euler(const Patches& p, hipStream_t s);
-// The patch bounds alone, with `done` also their minimum times cfl -> p.dt[0]
+// The patch bounds alone (a state in the FP32 form is read from its copy in the
+// first patch buffer, see launch_patch_copy), with `done` also their minimum times cfl -> p.dt[0]
 // and *host (one mesh).
 hipError_t launch_patch_cfl(const Patches& p, double cfl, unsigned* done, double* host, hipStream_t s);
 // Per mesh cfl times the minimum of its patches' bounds -> p.dt (and host).
@@ -42,8 +43,10 @@ hipError_t launch_state_get4(const State& st, int64_t nv, D4* out, hipStream_t s
 // Records of the caller's order into the first patch buffer; the state is
 // there once p.cur[0] is set (launch_set_int).
 hipError_t launch_patch_set4(const Patches& p, const int32_t* inv, const D4* in, hipStream_t s);
-// A state in the FP32 form into the first patch buffer; nothing where it is in
-// a patch buffer already.
+// A copy of a state in the FP32 form in the first patch buffer, which holds
+// nothing then; nothing where the state is in a patch buffer.
+hipError_t launch_patch_copy(const Patches& p, const State& st, hipStream_t s);
+// The same, and the state is there from now on.
 hipError_t launch_patch_enter(const Patches& p, const State& st, hipStream_t s);
 // The members' states into the batch's first patch buffer (batch latches
 // cleared), or the batch's state and latches out into the members' first ones.
