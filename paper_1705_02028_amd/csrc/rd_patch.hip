@@ -239,15 +239,15 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch2(Patches p) {
   const PatchDesc q = p.desc[xcd_block()];
   PatchTri t;  // loaded ahead of the vertices it indexes
   if (tid < q.nt) t = patch_tri(p, q.t0 + tid);
-  const double dt = patch_dt(p, q.mesh, p.pmin);
+  const double dt = patch_dt(p, q.mesh, p.pmin), idt = rcp(dt);
   for (int32_t l = tid; l < q.nlv; l += nthr) {
     const int32_t v = patch_vertex(p, q, l);
     xy[l] = p.xy[q.xy0 + l];
-    const D4 w = W[v], dd = p.D[v];
+    const D4 w = W[v], ws = patch_star(w, p.D[v], dt);
     Zn.set(l, patch_z(p, w, nullptr, nullptr).v);
     bool ok;
-    Zs.set(l, patch_z(p, patch_star(w, dd, dt), nullptr, &ok).v);
-    D.set(l, dd.v);
+    Zs.set(l, patch_z(p, ws, nullptr, &ok).v);
+    D.set(l, patch_rate(w, ws, idt).v);
     if (!ok && l < q.own) p.flag[q.mesh] = 1;
   }
   __syncthreads();
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch2(Patches p) {
         if (t.owned(c)) P.set(t.dst(c), out[c]);
   }
   PatchOwn own = patch_own(p, q, tid);
-  D4 wo, so;  // W^n and D of the owned vertex
+  D4 wo, so;  // W^n and the stage-1 D of the owned vertex
   if (tid < q.own) {
     wo = W[q.v0 + tid];
     so = p.D[q.v0 + tid];
