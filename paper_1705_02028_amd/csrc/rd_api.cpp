@@ -707,6 +707,8 @@ int patch_own(int64_t nv, int ncu) {
   return (int)std::min<int64_t>(215, std::max<int64_t>(48, nv / std::max(1, ncu)));
 }
 
+constexpr int kPatchVertexBytes = 112;  // of LDS in the second stage
+
 rd_status build_patches(rd_mesh* m) {
   rd::Patches& q = m->p;
   const int64_t nv = q.nv, nt = m->d.nt;
@@ -740,6 +742,22 @@ rd_status build_patches(rd_mesh* m) {
   p.max_slots = P.max_slots;
   p.max_tri = P.max_tri;
   p.threads = std::min(rd::kPatchThreads, (P.max_tri + 63) / 64 * 64);
+  // wide patches: the kernels' own shared words take less than 512 bytes, the
+  // largest vertex's parts 32 bytes each
+  const int32_t room = (m->lds_max - 512 - 32 * (kMaxDegree + 1)) / kPatchVertexBytes;
+  p.all_lv = P.max_lv;
+  std::vector<int32_t> wide;
+  rd_status st;
+  if (P.max_lv > room) {
+    p.max_lv = 0;
+    for (int32_t k = 0; k < P.npatch; ++k) {
+      const int32_t lv = P.vbeg[k + 1] - P.vbeg[k] + P.hbeg[k + 1] - P.hbeg[k];
+      if (lv > room) wide.push_back(k);
+      else p.max_lv = std::max(p.max_lv, lv);
+    }
+    p.nloc = nv + (int64_t)P.halo.size();
+    if ((st = dalloc(m, &p.rec, 3 * p.nloc)) || (st = dalloc(m, &p.rsig, p.nloc))) return st;
+  }
   const size_t need = std::max(rd::patch_lds_bytes(p, 1, true), rd::patch_lds_bytes(p, 2, false));
   if (need > (size_t)m->lds_max)
     return fail(RD_EUNSUPPORTED, "patches of this mesh need " + std::to_string(need) + " bytes of LDS");
@@ -778,7 +796,6 @@ rd_status build_patches(rd_mesh* m) {
       if (!m->ghost[m->wv[b]]) wb[inv[m->wv[b]]] = (int32_t)b;
     for (auto& e : went) e.other = inv[e.other];
   }
-  rd_status st;
   int32_t *halo, *mbeg, *dinv, *dwb, *dwptr, *jb;
   rd::PatchDesc* ddesc;
   uint32_t* tri;
@@ -794,7 +811,16 @@ rd_status build_patches(rd_mesh* m) {
       (st = dalloc(m, &vpart, 2 * (size_t)P.npatch)) || (st = upload(m, &dwb, wb)) ||
       (st = upload(m, &dwptr, m->wptr)) || (st = upload(m, &dwent, went)))
     return st;
-  p.desc = ddesc;
+  p.desc = p.all = ddesc;
+  if (!wide.empty()) {
+    for (int32_t k : wide) desc[k].own = desc[k].nlv = desc[k].nt = 0;
+    int32_t* dwide;
+    rd::PatchDesc* rest;
+    if ((st = upload(m, &dwide, wide)) || (st = upload(m, &rest, desc))) return st;
+    p.nwide = (int32_t)wide.size();
+    p.wide = dwide;
+    p.desc = rest;
+  }
   p.halo = halo;
   p.mbeg = mbeg;
   p.nmesh = (int32_t)m->voff.size() - 1;

@@ -48,7 +48,7 @@ struct Patches {
   int64_t nv = 0, ptn = 0;  // vertices, patch triangles
   int32_t npatch = 0, threads = 0;
   int32_t max_lv = 0, max_slots = 0, max_tri = 0;
-  const PatchDesc* desc = nullptr; // [npatch]
+  const PatchDesc* desc = nullptr; // [npatch] wide patches (below) empty
   const int32_t* halo = nullptr;   // internal ids
   const uint32_t* tri = nullptr;   // [3][ptn] local corner id, part slot << 16 (0xffff: not owned)
   const uint16_t* deg = nullptr;   // [nv]
@@ -78,6 +78,19 @@ struct Patches {
   const double* pminp = nullptr;
   int ci = 1;                      // where it (and the Euler update) finds the state's buffer: cur[ci]
   int32_t slump = 0;
+  const PatchDesc* all = nullptr;  // [npatch] wide patches as they are
+  // Wide patches: those whose vertex records would not fit a workgroup's LDS
+  // beside the parts of any one vertex (1166 local vertices or more of 160 KiB:
+  // 583 triangles or more around a vertex that share no other corner). They keep
+  // them in memory ([3][nloc] records of all patches' local vertices, patch by
+  // patch, and in stage 1 |v| + c), and a launch of their own takes them after
+  // the others'; so a vertex's bits do not depend on the mesh or batch around
+  // it. max_lv does not count them, all_lv does.
+  int32_t nwide = 0, all_lv = 0;
+  const int32_t* wide = nullptr;   // [nwide] patches
+  D4* rec = nullptr;
+  double* rsig = nullptr;
+  int64_t nloc = 0;
 };
 
 
@@ -95,6 +108,15 @@ struct Lds4 {
   __host__ __device__ void set(int32_t i, const double v[4]) const {
     a[i] = make_double2(v[0], v[1]);
     a[n + i] = make_double2(v[2], v[3]);
+  }
+};
+
+// The same in memory.
+struct Mem4 {
+  D4* a;
+  __host__ __device__ D4 get(int32_t i) const { return a[i]; }
+  __host__ __device__ void set(int32_t i, const double v[4]) const {
+    for (int k = 0; k < 4; ++k) a[i].v[k] = v[k];
   }
 };
 

@@ -117,6 +117,13 @@ __device__ __forceinline__ TriDiff patch_diff(const Patches& p, const PatchDesc&
   return TriDiff{b.x - a.x, b.y - a.y, c.x - a.x, c.y - a.y};
 }
 
+// Records of a patch's local vertices: those in LDS, or the i-th in memory.
+template <bool MEM>
+__device__ __forceinline__ auto patch_rec(const Patches& p, const PatchDesc& q, const Lds4& lds, int i) {
+  if constexpr (MEM) return Mem4{p.rec + i * p.nloc + q.xy0};
+  else return lds;
+}
+
 // The two passes of a step: one workgroup per patch, four waves per SIMD. (A
 // grid of the workgroups the device holds at once, each walking a run of
 // patches with the next one's records loaded ahead, was measured slower:
@@ -129,30 +136,34 @@ __device__ __forceinline__ TriDiff patch_diff(const Patches& p, const PatchDesc&
 // against 9.9 at 64^2 and 308 against 406 at 2048^2.
 // RES: the residual itself (sum of parts and wall term, ghosts' sums of parts
 // too) in D's place.
-template <int SCHEME, bool CFL, bool AFTER, bool RES = false>
+// MEM: the wide patches (see Patches::wide) alone.
+template <int SCHEME, bool CFL, bool AFTER, bool RES = false, bool MEM = false>
 __global__ __launch_bounds__(kPatchThreads, 4) void k_patch1(Patches p) {
   extern __shared__ double2 lds[];
   const int c0 = p.cur[AFTER ? p.ci : 0];
   const D4* W = p.W[c0];
   const int32_t tid = threadIdx.x, nthr = blockDim.x;
-  const bool big = p.max_tri > nthr;
-  const Lds4 Z{lds, p.max_lv};
+  const bool big = !MEM && p.max_tri > nthr;
+  const Lds4 Zl{lds, p.max_lv};
   double2* xy = lds + 2 * p.max_lv;
-  double* sig = reinterpret_cast<double*>(xy + p.max_lv);
+  double* sl = reinterpret_cast<double*>(xy + p.max_lv);
   const Lds4 P{big ? lds + patch_vert_bytes<false, CFL>(p.max_lv + (p.max_lv & 1)) / 16 : lds, p.max_slots};
   double* lam = reinterpret_cast<double*>(P.a + 2 * p.max_slots);
   if (blockIdx.x == 0 && tid == 0) {
     if (AFTER) p.cur[p.ci ^ 1] = c0 ^ 1;
     else p.cur[1] = c0;
   }
-  const int32_t k = (int32_t)xcd_block();
-  const PatchDesc q = p.desc[k];
+  const int32_t k = MEM ? p.wide[blockIdx.x] : (int32_t)xcd_block();
+  const PatchDesc q = (MEM ? p.all : p.desc)[k];
+  const auto Z = patch_rec<MEM>(p, q, Zl, 0);
+  double* sig = MEM ? p.rsig + q.xy0 : sl;
+  const double2* at = MEM ? p.xy + q.xy0 : xy;
   PatchTri t;  // loaded ahead of the vertices it indexes
   if (tid < q.nt) t = patch_tri(p, q.t0 + tid);
   const double dt = AFTER ? patch_dt(p, q.mesh, p.pminp) : 0.0;
   for (int32_t l = tid; l < q.nlv; l += nthr) {
     const int32_t v = patch_vertex(p, q, l);
-    xy[l] = p.xy[q.xy0 + l];
+    if (!MEM) xy[l] = p.xy[q.xy0 + l];
     double s;
     bool ok;
     const D4 w = AFTER ? patch_star(W[v], p.Dp[v], dt) : W[v];
@@ -170,13 +181,13 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch1(Patches p) {
     if (j0 > 0 && j < q.nt) t = patch_tri(p, q.t0 + j);
     if (j < q.nt) {
       const D4 z[3] = {Z.get(t.lv(0)), Z.get(t.lv(1)), Z.get(t.lv(2))};
-      const TriDiff g = patch_diff(p, q, xy[t.lv(0)], xy[t.lv(1)], xy[t.lv(2)]);
+      const TriDiff g = patch_diff(p, q, at[t.lv(0)], at[t.lv(1)], at[t.lv(2)]);
       if (CFL) term = rmax(rmax(sig[t.lv(0)], sig[t.lv(1)]), sig[t.lv(2)]);
       double pN[2][4], phi[4];
       const double lmax = stage1_parts<SCHEME>(g, z, p.gas, p.vr + 3 * q.mesh, out, pN, phi);
       if (CFL) term = lmax * term;
     }
-    if (!big) __syncthreads();
+    if (!big && !MEM) __syncthreads();
     if (j < q.nt)
       for (int c = 0; c < 3; ++c)
         if (t.owned(c)) {
@@ -224,25 +235,27 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch1(Patches p) {
   }
 }
 
-template <int SCHEME, bool LUMP>
+template <int SCHEME, bool LUMP, bool MEM = false>
 __global__ __launch_bounds__(kPatchThreads, 4) void k_patch2(Patches p) {
   extern __shared__ double2 lds[];
   const int c0 = p.cur[1];
   const D4* W = p.W[c0];
   D4* Wn = p.W[c0 ^ 1];
   const int32_t tid = threadIdx.x, nthr = blockDim.x;
-  const bool big = p.max_tri > nthr;
-  const Lds4 Zn{lds, p.max_lv}, Zs{lds + 2 * p.max_lv, p.max_lv}, D{lds + 4 * p.max_lv, p.max_lv};
+  const bool big = !MEM && p.max_tri > nthr;
+  const Lds4 Znl{lds, p.max_lv}, Zsl{lds + 2 * p.max_lv, p.max_lv}, Dl{lds + 4 * p.max_lv, p.max_lv};
   double2* xy = lds + 6 * p.max_lv;
   const Lds4 P{big ? lds + patch_vert_bytes<true, false>(p.max_lv + (p.max_lv & 1)) / 16 : lds, p.max_slots};
   if (blockIdx.x == 0 && tid == 0) p.cur[0] = c0 ^ 1;
-  const PatchDesc q = p.desc[xcd_block()];
+  const PatchDesc q = MEM ? p.all[p.wide[blockIdx.x]] : p.desc[xcd_block()];
+  const auto Zn = patch_rec<MEM>(p, q, Znl, 0), Zs = patch_rec<MEM>(p, q, Zsl, 1), D = patch_rec<MEM>(p, q, Dl, 2);
+  const double2* at = MEM ? p.xy + q.xy0 : xy;
   PatchTri t;  // loaded ahead of the vertices it indexes
   if (tid < q.nt) t = patch_tri(p, q.t0 + tid);
   const double dt = patch_dt(p, q.mesh, p.pmin), idt = rcp(dt);
   for (int32_t l = tid; l < q.nlv; l += nthr) {
     const int32_t v = patch_vertex(p, q, l);
-    xy[l] = p.xy[q.xy0 + l];
+    if (!MEM) xy[l] = p.xy[q.xy0 + l];
     const D4 w = W[v], ws = patch_star(w, p.D[v], dt);
     Zn.set(l, patch_z(p, w, nullptr, nullptr).v);
     bool ok;
@@ -256,11 +269,11 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch2(Patches p) {
     double out[3][4];
     if (j0 > 0 && j < q.nt) t = patch_tri(p, q.t0 + j);
     if (j < q.nt) {
-      const TriDiff g = patch_diff(p, q, xy[t.lv(0)], xy[t.lv(1)], xy[t.lv(2)]);
+      const TriDiff g = patch_diff(p, q, at[t.lv(0)], at[t.lv(1)], at[t.lv(2)]);
       patch_tri2<SCHEME, LUMP>(p, g, [&](int i) { return Zn.get(t.lv(i)); }, [&](int i) { return Zs.get(t.lv(i)); },
                                [&](int i) { return D.get(t.lv(i)); }, p.vr + 3 * q.mesh, out);
     }
-    if (!big) __syncthreads();
+    if (!big && !MEM) __syncthreads();
     if (j < q.nt)
       for (int c = 0; c < 3; ++c)
         if (t.owned(c)) P.set(t.dst(c), out[c]);
@@ -305,7 +318,7 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch2(Patches p) {
 // Forward Euler: W <- W - dt D in place, and cur[0] its buffer.
 __global__ __launch_bounds__(kPatchThreads) void k_patch_euler(Patches p) {
   const int32_t k = (int32_t)xcd_block();
-  const PatchDesc q = p.desc[k];
+  const PatchDesc q = p.all[k];
   const int c0 = p.cur[p.ci];
   D4* W = p.W[c0];
   if (p.ci == 1 && blockIdx.x == 0 && threadIdx.x == 0) p.cur[0] = c0;
@@ -324,13 +337,13 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch_euler(Patches p) {
 __global__ __launch_bounds__(kPatchThreads) void k_patch_cfl(Patches p, double cfl, unsigned* done, double* host) {
   extern __shared__ double2 lds[];
   const int32_t k = (int32_t)xcd_block();
-  const PatchDesc q = p.desc[k];
+  const PatchDesc q = p.all[k];
   const int c0 = p.cur[0];
   const D4* W = p.W[c0 == kForm32 ? 0 : c0];  // a state in the FP32 form: its copy (launch_patch_copy)
   const int32_t tid = threadIdx.x, nthr = blockDim.x;
   double2* xy = lds;
-  double* sig = reinterpret_cast<double*>(xy + p.max_lv);
-  double* lam = sig + p.max_lv;
+  double* sig = reinterpret_cast<double*>(xy + p.all_lv);
+  double* lam = sig + p.all_lv;
   for (int32_t l = tid; l < q.nlv; l += nthr) {
     const int32_t v = patch_vertex(p, q, l);
     xy[l] = p.xy[q.xy0 + l];
@@ -393,7 +406,7 @@ __global__ __launch_bounds__(1024) void k_patch_dt(Patches p, double cfl, double
 template <bool STAR>
 __global__ __launch_bounds__(kPatchThreads) void k_patch_vrange(Patches p) {
   const int32_t k = (int32_t)xcd_block();
-  const PatchDesc q = p.desc[k];
+  const PatchDesc q = p.all[k];
   const D4* W = p.W[p.cur[STAR ? 1 : 0]];
   const double dt = !STAR || p.dt_val > 0.0 ? p.dt_val : p.dt[q.mesh];
   double lo = INFINITY, hi = 0.0;
@@ -488,64 +501,60 @@ __global__ __launch_bounds__(kBlock) void k_patch_members(State st, int* cur, in
 
 // ------------------------------------------------------------- launchers --
 
-size_t patch_lds_bytes(const Patches& p, int stage, bool cfl) {
+size_t patch_lds_bytes(const Patches& p, int stage, bool cfl, bool wide) {
   const int32_t lv = p.max_lv + (p.max_lv & 1);
   const size_t vert = stage == 2 ? patch_vert_bytes<true, false>(lv)
                                  : (cfl ? patch_vert_bytes<false, true>(lv) : patch_vert_bytes<false, false>(lv));
   const size_t parts = (size_t)p.max_slots * (stage == 1 && cfl ? 40 : 32);
+  if (wide) return parts;
   return p.max_tri > p.threads ? vert + parts : (vert > parts ? vert : parts);
 }
 
-template <int SCHEME>
-static hipError_t patch_go(const Patches& p, int stage, bool cfl, hipStream_t s) {
-  const dim3 g(p.npatch), b(p.threads);
-  const size_t lds = patch_lds_bytes(p, stage, cfl);
-  if (stage == 2 && p.slump) hipLaunchKernelGGL((k_patch2<SCHEME, true>), g, b, lds, s, p);
-  else if (stage == 2) hipLaunchKernelGGL((k_patch2<SCHEME, false>), g, b, lds, s, p);
-  else if (cfl) hipLaunchKernelGGL((k_patch1<SCHEME, true, false>), g, b, lds, s, p);
-  else hipLaunchKernelGGL((k_patch1<SCHEME, false, false>), g, b, lds, s, p);
+enum { kStep, kAfter, kResidual };
+
+template <int SCHEME, bool MEM>
+static hipError_t patch_go(const Patches& p, int what, int stage, bool cfl, hipStream_t s) {
+  const dim3 g(MEM ? p.nwide : p.npatch), b(p.threads);
+  const size_t lds = patch_lds_bytes(p, stage, cfl, MEM);
+  if (what == kResidual) hipLaunchKernelGGL((k_patch1<SCHEME, false, false, true, MEM>), g, b, lds, s, p);
+  else if (what == kAfter) {
+    if constexpr (SCHEME == SCH_BX) return hipErrorInvalidValue;
+    else hipLaunchKernelGGL((k_patch1<SCHEME, true, true, false, MEM>), g, b, lds, s, p);
+  } else if (stage == 2 && p.slump) hipLaunchKernelGGL((k_patch2<SCHEME, true, MEM>), g, b, lds, s, p);
+  else if (stage == 2) hipLaunchKernelGGL((k_patch2<SCHEME, false, MEM>), g, b, lds, s, p);
+  else if (cfl) hipLaunchKernelGGL((k_patch1<SCHEME, true, false, false, MEM>), g, b, lds, s, p);
+  else hipLaunchKernelGGL((k_patch1<SCHEME, false, false, false, MEM>), g, b, lds, s, p);
   return hipGetLastError();
+}
+
+template <int SCHEME>
+static hipError_t patch_go(const Patches& p, int what, int stage, bool cfl, hipStream_t s) {
+  const hipError_t e = patch_go<SCHEME, false>(p, what, stage, cfl, s);
+  return e == hipSuccess && p.nwide ? patch_go<SCHEME, true>(p, what, stage, cfl, s) : e;
+}
+
+static hipError_t patch_go(const Patches& p, int scheme, int what, int stage, bool cfl, hipStream_t s) {
+  switch (scheme) {
+    case SCH_N: return patch_go<SCH_N>(p, what, stage, cfl, s);
+    case SCH_LDA: return patch_go<SCH_LDA>(p, what, stage, cfl, s);
+    case SCH_B: return patch_go<SCH_B>(p, what, stage, cfl, s);
+    case SCH_BMAX: return patch_go<SCH_BMAX>(p, what, stage, cfl, s);
+    case SCH_BMIN: return patch_go<SCH_BMIN>(p, what, stage, cfl, s);
+    case SCH_BX: return patch_go<SCH_BX>(p, what, stage, cfl, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_patch_residual(const Patches& p, int scheme, hipStream_t s) {
-  const dim3 g(p.npatch), b(p.threads);
-  const size_t lds = patch_lds_bytes(p, 1, false);
-  switch (scheme) {
-    case SCH_N: hipLaunchKernelGGL((k_patch1<SCH_N, false, false, true>), g, b, lds, s, p); break;
-    case SCH_LDA: hipLaunchKernelGGL((k_patch1<SCH_LDA, false, false, true>), g, b, lds, s, p); break;
-    case SCH_B: hipLaunchKernelGGL((k_patch1<SCH_B, false, false, true>), g, b, lds, s, p); break;
-    case SCH_BMAX: hipLaunchKernelGGL((k_patch1<SCH_BMAX, false, false, true>), g, b, lds, s, p); break;
-    case SCH_BMIN: hipLaunchKernelGGL((k_patch1<SCH_BMIN, false, false, true>), g, b, lds, s, p); break;
-    case SCH_BX: hipLaunchKernelGGL((k_patch1<SCH_BX, false, false, true>), g, b, lds, s, p); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return patch_go(p, scheme, kResidual, 1, false, s);
 }
 
 hipError_t launch_patch_after(const Patches& p, int scheme, hipStream_t s) {
-  const dim3 g(p.npatch), b(p.threads);
-  const size_t lds = patch_lds_bytes(p, 1, true);
-  switch (scheme) {
-    case SCH_N: hipLaunchKernelGGL((k_patch1<SCH_N, true, true>), g, b, lds, s, p); break;
-    case SCH_LDA: hipLaunchKernelGGL((k_patch1<SCH_LDA, true, true>), g, b, lds, s, p); break;
-    case SCH_B: hipLaunchKernelGGL((k_patch1<SCH_B, true, true>), g, b, lds, s, p); break;
-    case SCH_BMAX: hipLaunchKernelGGL((k_patch1<SCH_BMAX, true, true>), g, b, lds, s, p); break;
-    case SCH_BMIN: hipLaunchKernelGGL((k_patch1<SCH_BMIN, true, true>), g, b, lds, s, p); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return patch_go(p, scheme, kAfter, 1, true, s);
 }
 
 hipError_t launch_patch(const Patches& p, int scheme, int stage, bool cfl, hipStream_t s) {
-  switch (scheme) {
-    case SCH_N: return patch_go<SCH_N>(p, stage, cfl, s);
-    case SCH_LDA: return patch_go<SCH_LDA>(p, stage, cfl, s);
-    case SCH_B: return patch_go<SCH_B>(p, stage, cfl, s);
-    case SCH_BMAX: return patch_go<SCH_BMAX>(p, stage, cfl, s);
-    case SCH_BMIN: return patch_go<SCH_BMIN>(p, stage, cfl, s);
-    case SCH_BX: return patch_go<SCH_BX>(p, stage, cfl, s);
-  }
-  return hipErrorInvalidValue;
+  return patch_go(p, scheme, kStep, stage, cfl, s);
 }
 
 hipError_t launch_patch_euler(const Patches& p, hipStream_t s) {
@@ -554,7 +563,7 @@ hipError_t launch_patch_euler(const Patches& p, hipStream_t s) {
 }
 
 hipError_t launch_patch_cfl(const Patches& p, double cfl, unsigned* done, double* host, hipStream_t s) {
-  const size_t lds = (size_t)p.max_lv * 24 + (size_t)p.max_slots * 8;
+  const size_t lds = (size_t)p.all_lv * 24 + (size_t)p.max_slots * 8;
   hipLaunchKernelGGL(k_patch_cfl, dim3(p.npatch), dim3(p.threads), lds, s, p, cfl, done, host);
   return hipGetLastError();
 }

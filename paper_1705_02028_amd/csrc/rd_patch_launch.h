@@ -16,7 +16,7 @@ struct PatchMember {
 };
 
 // Dynamic LDS bytes of a patch workgroup.
-size_t patch_lds_bytes(const Patches& p, int stage, bool cfl);
+size_t patch_lds_bytes(const Patches& p, int stage, bool cfl, bool wide = false);
 // stage 1 (also Euler): p.D and, with cfl, the patch bounds p.pmin; stage 2:
 // the new state (in the other buffer).
 hipError_t launch_patch(const Patches& p, int scheme, int stage, bool cfl, hipStream_t s);
