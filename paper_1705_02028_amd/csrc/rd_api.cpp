@@ -1069,22 +1069,29 @@ RD_API rd_status rd_set_state(rd_mesh* m, const double* W, int on_device) {
   if (!m || !W) return fail(RD_EINVAL, "null argument");
   DeviceGuard g(m->device);
   const int64_t nv = m->d.nv;
+  hipStream_t s = m->stream;
   const double* src = W;
+  const int* bad = nullptr;
   if (!on_device) {
-    HIPCHK(hipMemcpyAsync(m->scratch, W, sizeof(double) * 4 * nv, hipMemcpyHostToDevice, m->stream));
+    HIPCHK(hipMemcpyAsync(m->scratch, W, sizeof(double) * 4 * nv, hipMemcpyHostToDevice, s));
     src = m->scratch;
-    int bad = 0;
-    HIPCHK(rd::launch_check_state(src, nv, 2, m->gamma, m->bad, m->stream));
-    HIPCHK(hipMemcpyAsync(&bad, m->bad, sizeof(int), hipMemcpyDeviceToHost, m->stream));
-    HIPCHK(hipStreamSynchronize(m->stream));
-    if (bad < nv)
-      return fail(RD_ENONPHYS, "vertex " + std::to_string(bad) + " has rho <= 0, p <= 0 or a non-finite value");
+    bad = m->bad;
+    HIPCHK(rd::launch_check_state(src, nv, 2, m->gamma, m->bad, s));
+    HIPCHK(rd::launch_clear_unless(m->p.flag, bad, nv, s));
+  } else {
+    HIPCHK(rd::launch_set_int(m->p.flag, 0, s));
   }
-  HIPCHK(rd::launch_set_int(m->p.flag, 0, m->stream));
   // into the form of the last steps
   note_capture(m);
-  if (m->form32) HIPCHK(rd::launch_set32(view32(m), m->d32, m->p.cur, src, m->stream));
-  else HIPCHK(rd::launch_patch_set(m->p, m->inv, src, m->stream));
+  if (m->form32) HIPCHK(rd::launch_set32(view32(m), m->d32, m->p.cur, src, bad, s));
+  else HIPCHK(rd::launch_patch_set(m->p, m->inv, src, bad, s));
+  if (on_device) return RD_OK;
+  // a host state is in place when the call returns
+  int first = 0;
+  HIPCHK(hipMemcpyAsync(&first, bad, sizeof(int), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  if (first < nv)
+    return fail(RD_ENONPHYS, "vertex " + std::to_string(first) + " has rho <= 0, p <= 0 or a non-finite value");
   return RD_OK;
 }
 

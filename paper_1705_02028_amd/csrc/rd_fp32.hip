@@ -30,8 +30,9 @@ __global__ __launch_bounds__(kBlock) void k_enter32(Dev d, Dev32 h, State st) {
 }
 
 // The state from the caller's [4][nv] arrays, as k_patch_set, with its Zf and |v| + c.
-__global__ __launch_bounds__(kBlock) void k_set32(Dev d, Dev32 h, int* cur, const double* soa) {
+__global__ __launch_bounds__(kBlock) void k_set32(Dev d, Dev32 h, int* cur, const double* soa, const int* bad) {
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (bad && *bad < d.nv) return;
   if (v == 0) cur[0] = kForm32;
   if (v >= d.nv) return;
   const double w[4] = {soa[v], soa[d.nv + v], soa[2 * d.nv + v], soa[3 * d.nv + v]};
@@ -148,8 +149,8 @@ hipError_t launch_enter32(const Dev& d, const Dev32& h, const State& st, hipStre
   return hipGetLastError();
 }
 
-hipError_t launch_set32(const Dev& d, const Dev32& h, int* cur, const double* soa, hipStream_t s) {
-  hipLaunchKernelGGL(k_set32, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, h, cur, soa);
+hipError_t launch_set32(const Dev& d, const Dev32& h, int* cur, const double* soa, const int* bad, hipStream_t s) {
+  hipLaunchKernelGGL(k_set32, dim3(nblk(d.nv)), dim3(kBlock), 0, s, d, h, cur, soa, bad);
   return hipGetLastError();
 }
 

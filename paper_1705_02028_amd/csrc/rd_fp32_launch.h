@@ -31,8 +31,9 @@ hipError_t launch_gather32(const Dev& d, const Dev32& h, int mode, hipStream_t s
 // A state in a patch buffer into d.W, parameter vectors and signal speeds with
 // it; the caller marks where the state is now.
 hipError_t launch_enter32(const Dev& d, const Dev32& h, const State& st, hipStream_t s);
-// The same from the caller's arrays, and cur[0] set to the FP32 form.
-hipError_t launch_set32(const Dev& d, const Dev32& h, int* cur, const double* soa, hipStream_t s);
+// The same from the caller's arrays, and cur[0] set to the FP32 form; nothing
+// with a `bad` that names a vertex (launch_check_state).
+hipError_t launch_set32(const Dev& d, const Dev32& h, int* cur, const double* soa, const int* bad, hipStream_t s);
 // d.dt from the terms of the stage-1 pass.
 hipError_t launch_cfl32(const Dev& d, const CflPlan& p, double cfl, hipStream_t s);
 // Bx sensor range at W, or (star) at Ws -> d.vr

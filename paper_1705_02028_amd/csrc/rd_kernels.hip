@@ -71,6 +71,9 @@ __global__ __launch_bounds__(kBlock) void k_check_state(const double* W, int64_t
 
 __global__ void k_set_scalar(double* p, double v) { p[0] = v; }
 __global__ void k_set_int(int* p, int v) { p[0] = v; }
+__global__ void k_clear_unless(int* p, const int* bad, int64_t nv) {
+  if (*bad >= nv) p[0] = 0;
+}
 __global__ __launch_bounds__(kBlock) void k_fill_int(int* p, int v, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < n) p[i] = v;
@@ -397,6 +400,11 @@ hipError_t launch_set_scalar(double* p, double v, hipStream_t s) {
 
 hipError_t launch_set_int(int* p, int v, hipStream_t s) {
   hipLaunchKernelGGL(k_set_int, dim3(1), dim3(1), 0, s, p, v);
+  return hipGetLastError();
+}
+
+hipError_t launch_clear_unless(int* p, const int* bad, int64_t nv, hipStream_t s) {
+  hipLaunchKernelGGL(k_clear_unless, dim3(1), dim3(1), 0, s, p, bad, nv);
   return hipGetLastError();
 }
 

@@ -24,6 +24,8 @@ hipError_t launch_residual(const Dev& d, const State& r, double* R, const State&
 hipError_t launch_check_state(const double* W, int64_t nv, int momenta, double gamma, int* bad, hipStream_t s);
 hipError_t launch_set_scalar(double* p, double v, hipStream_t s);
 hipError_t launch_set_int(int* p, int v, hipStream_t s);
+// *p = 0 unless *bad names one of nv vertices
+hipError_t launch_clear_unless(int* p, const int* bad, int64_t nv, hipStream_t s);
 // p[0..n) = v
 hipError_t launch_fill_int(int* p, int v, int64_t n, hipStream_t s);
 

@@ -444,9 +444,11 @@ __global__ __launch_bounds__(1024) void k_patch_vrange_final(Patches p) {
 
 // The caller's [4][nv] arrays to the first state buffer and from the state,
 // one thread per caller's vertex v (inv[v] is its internal vertex): the arrays
-// are read and written in whole lines, the 32-byte records scattered.
-__global__ __launch_bounds__(kBlock) void k_patch_set(Patches p, const int32_t* inv, const double* soa) {
+// are read and written in whole lines, the 32-byte records scattered. With
+// `bad` nothing where it names a vertex.
+__global__ __launch_bounds__(kBlock) void k_patch_set(Patches p, const int32_t* inv, const double* soa, const int* bad) {
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (bad && *bad < p.nv) return;
   if (v == 0) p.cur[0] = 0;
   if (v >= p.nv) return;
   D4 w;
@@ -580,8 +582,8 @@ hipError_t launch_patch_vrange(const Patches& p, bool star, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_patch_set(const Patches& p, const int32_t* inv, const double* soa, hipStream_t s) {
-  hipLaunchKernelGGL(k_patch_set, dim3(nblk(p.nv)), dim3(kBlock), 0, s, p, inv, soa);
+hipError_t launch_patch_set(const Patches& p, const int32_t* inv, const double* soa, const int* bad, hipStream_t s) {
+  hipLaunchKernelGGL(k_patch_set, dim3(nblk(p.nv)), dim3(kBlock), 0, s, p, inv, soa, bad);
   return hipGetLastError();
 }
 hipError_t launch_state_get(const State& st, int64_t nv, double* soa, hipStream_t s) {

@@ -36,8 +36,9 @@ hipError_t launch_patch_dt(const Patches& p, double cfl, hipStream_t s, double* 
 // Bx sensor range at W^n, or at W* (after stage 1, with p.dt set) -> p.vr
 hipError_t launch_patch_vrange(const Patches& p, bool star, hipStream_t s);
 // The state from the caller's [4][nv] arrays into the first patch buffer
-// (p.cur[0] with it), and from where it is to the caller's arrays or records.
-hipError_t launch_patch_set(const Patches& p, const int32_t* inv, const double* soa, hipStream_t s);
+// (p.cur[0] with it; nothing with a `bad` that names a vertex, see
+// launch_check_state), and from where it is to the caller's arrays or records.
+hipError_t launch_patch_set(const Patches& p, const int32_t* inv, const double* soa, const int* bad, hipStream_t s);
 hipError_t launch_state_get(const State& st, int64_t nv, double* soa, hipStream_t s);
 hipError_t launch_state_get4(const State& st, int64_t nv, D4* out, hipStream_t s);
 // Records of the caller's order into the first patch buffer; the state is

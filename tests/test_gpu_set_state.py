@@ -1,0 +1,38 @@
+"""A state from host memory is in place when rd_set_state returns: nothing of it
+is pending on the stream, so the mesh may go on on another stream."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_1705_02028_amd import inputs as I
+
+
+@pytest.mark.parametrize("N", [24, 700])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_host_state_then_another_stream(N, prec):
+    from paper_1705_02028_amd import rd
+    m = I.split_square(N, seed=1)
+    W = [I.ic_kelvin_helmholtz(m, seed=k) * (1.0 + k) for k in range(2)]
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    g = rd.Mesh(m)
+    rd.rd_set_stream(g.h, a.cuda_stream)
+    g.set_state(W[0])
+    g.step_cfl(1, 0.3, rd.B, rd.RK2, prec)  # the form the state is set in
+    g.sync()
+    for k in range(4):
+        rd.rd_set_stream(g.h, (a, b)[k % 2].cuda_stream)
+        g.set_state(W[k % 2])
+        assert (a, b)[k % 2].query(), "work is pending on the stream"
+        rd.rd_set_stream(g.h, (b, a)[k % 2].cuda_stream)
+        assert np.array_equal(g.get_state(), W[k % 2])
+    bad = W[0].copy()
+    bad[0, 5] = 0.0
+    with pytest.raises(rd.RDError, match="vertex 5 "):
+        g.set_state(bad)
+    assert np.array_equal(g.get_state(), W[1])
+    g.step_cfl(1, 0.3, rd.B, rd.RK2, prec)
+    g.sync()
+    g.close()
