@@ -1686,8 +1686,7 @@ rd_status batch_begin(rd_batch* b, int fp32, std::vector<hipStream_t>& outer) {
       mem.push_back(rd::PatchMember{state_of(m), m->p.cur, m->p.flag, (int32_t)m->p.nv, (int32_t)b->voff[k]});
       b->versions[k] = m->version;
     }
-    HIPCHK(hipStreamSynchronize(s));
-    HIPCHK(hipMemcpy(b->mem, mem.data(), sizeof(rd::PatchMember) * mem.size(), hipMemcpyHostToDevice));
+    HIPCHK(rd::launch_put_members(b->mem, mem.data(), (int)mem.size(), s));
   }
   HIPCHK(rd::launch_patch_members(state_of(f), f->p.cur, f->p.flag, f->p.nv, b->mem, b->mb, b->vb, b->nblocks, false,
                                   s));
