@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -54,6 +55,30 @@ double unwrap_h(double d, double period) {
 // a triangle among the triangles of each of its corner vertices is packed in
 // 10 bits.
 constexpr int32_t kMaxDegree = 1023;
+
+// Host states of up to this many vertices are checked on the host, larger ones
+// on the device (launch_check_state), whose two launches and copy take 16 us
+// whatever the size (rd_set_state, us, host / device: 20 / 36 at 64 vertices,
+// 39 / 41 at 6400, 48 / 44 at 10000; rd3_set_state: 22 / 36 at 125, 40 / 51 at
+// 8000, 52 / 56 at 13824, 72 / 65 at 21952).
+constexpr int64_t kHostCheck2 = 8192, kHostCheck3 = 16384;
+
+// First vertex of a state [2 + momenta][nv] that is not physical, nv if none:
+// the check of launch_check_state.
+int64_t first_unphysical(const double* W, int64_t nv, int momenta, double gamma) {
+  for (int64_t i = 0; i < nv; ++i) {
+    const double rho = W[i], e = W[(1 + momenta) * nv + i];
+    bool ok = rho > 0.0 && std::isfinite(e) && (momenta == 3 || std::isfinite(rho));
+    double q = 0.0;
+    for (int k = 1; k <= momenta; ++k) {
+      const double m = W[k * nv + i];
+      q += m * m;
+      ok = ok && (momenta == 3 || std::isfinite(m));
+    }
+    if (!ok || !((gamma - 1.0) * (e - 0.5 * q / rho) > 0.0)) return i;
+  }
+  return nv;
+}
 
 int host_threads() {
   const unsigned n = std::thread::hardware_concurrency();
@@ -1072,9 +1097,18 @@ RD_API rd_status rd_set_state(rd_mesh* m, const double* W, int on_device) {
   hipStream_t s = m->stream;
   const double* src = W;
   const int* bad = nullptr;
+  int64_t first = nv;
+  auto status = [&] {
+    return first == nv ? RD_OK
+                       : fail(RD_ENONPHYS, "vertex " + std::to_string(first) +
+                                               " has rho <= 0, p <= 0 or a non-finite value");
+  };
   if (!on_device) {
+    if (nv <= kHostCheck2 && (first = first_unphysical(W, nv, 2, m->gamma)) < nv) return status();
     HIPCHK(hipMemcpyAsync(m->scratch, W, sizeof(double) * 4 * nv, hipMemcpyHostToDevice, s));
     src = m->scratch;
+  }
+  if (!on_device && nv > kHostCheck2) {
     bad = m->bad;
     HIPCHK(rd::launch_check_state(src, nv, 2, m->gamma, m->bad, s));
     HIPCHK(rd::launch_clear_unless(m->p.flag, bad, nv, s));
@@ -1087,12 +1121,11 @@ RD_API rd_status rd_set_state(rd_mesh* m, const double* W, int on_device) {
   else HIPCHK(rd::launch_patch_set(m->p, m->inv, src, bad, s));
   if (on_device) return RD_OK;
   // a host state is in place when the call returns
-  int first = 0;
-  HIPCHK(hipMemcpyAsync(&first, bad, sizeof(int), hipMemcpyDeviceToHost, s));
+  int named = INT_MAX;
+  if (bad) HIPCHK(hipMemcpyAsync(&named, bad, sizeof(int), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  if (first < nv)
-    return fail(RD_ENONPHYS, "vertex " + std::to_string(first) + " has rho <= 0, p <= 0 or a non-finite value");
-  return RD_OK;
+  first = std::min<int64_t>(named, nv);
+  return status();
 }
 
 RD_API rd_status rd_get_state(rd_mesh* m, double* W, int on_device) {
@@ -2464,17 +2497,23 @@ RD_API rd_status rd3_mesh_destroy(rd3_mesh* mesh) {
 RD_API rd_status rd3_set_state(rd3_mesh* m, const double* W, int on_device) {
   if (!m || !W) return fail(RD_EINVAL, "null argument");
   const int64_t nv = m->d.nv;
+  int64_t first = nv;
   if (!on_device) {  // through Ws, which holds nothing between steps
-    int bad = 0;
-    HIPCHK(hipMemcpyAsync(m->d.Ws, W, sizeof(double) * 5 * nv, hipMemcpyHostToDevice, m->stream));
-    HIPCHK(rd::launch_check_state(m->d.Ws, nv, 3, m->d.gamma, m->bad, m->stream));
-    HIPCHK(hipMemcpyAsync(&bad, m->bad, sizeof(int), hipMemcpyDeviceToHost, m->stream));
-    HIPCHK(hipStreamSynchronize(m->stream));
-    if (bad < nv)
-      return fail(RD_ENONPHYS, "vertex " + std::to_string(bad) + ": rho <= 0, p <= 0 or not finite");
+    if (nv <= kHostCheck3) first = first_unphysical(W, nv, 3, m->d.gamma);
+    if (first == nv) HIPCHK(hipMemcpyAsync(m->d.Ws, W, sizeof(double) * 5 * nv, hipMemcpyHostToDevice, m->stream));
+    if (nv > kHostCheck3) {
+      int named = 0;
+      HIPCHK(rd::launch_check_state(m->d.Ws, nv, 3, m->d.gamma, m->bad, m->stream));
+      HIPCHK(hipMemcpyAsync(&named, m->bad, sizeof(int), hipMemcpyDeviceToHost, m->stream));
+      HIPCHK(hipStreamSynchronize(m->stream));
+      first = std::min<int64_t>(named, nv);
+    }
+    if (first < nv)
+      return fail(RD_ENONPHYS, "vertex " + std::to_string(first) + ": rho <= 0, p <= 0 or not finite");
   }
   HIPCHK(rd::launch_fill_int(m->d.flag, 0, 1, m->stream));
   HIPCHK(rd3::launch3_set(m->d, on_device ? W : m->d.Ws, m->stream));
+  if (!on_device && nv <= kHostCheck3) HIPCHK(hipStreamSynchronize(m->stream));
   return RD_OK;
 }
 

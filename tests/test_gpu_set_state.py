@@ -36,3 +36,34 @@ def test_host_state_then_another_stream(N, prec):
     g.step_cfl(1, 0.3, rd.B, rd.RK2, prec)
     g.sync()
     g.close()
+
+
+@pytest.mark.parametrize("dim,N", [(2, 89), (2, 90), (3, 25), (3, 26)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_either_check_names_the_first_vertex(dim, N, prec):
+    """Small host states are checked on the host, those of more than 8192
+    vertices (16384 in three dimensions) on the device: the same vertex, and
+    the state that was there stays."""
+    from paper_1705_02028_amd import rd
+    if dim == 2:
+        m = I.split_square(N + 1, seed=1, periodic=(False, False), bc=("ghost", "ghost"))
+        W, g = I.ic_kelvin_helmholtz(m, seed=1), rd.Mesh(m)
+        g.set_state(W)
+        g.step_cfl(1, 0.3, rd.B, rd.RK2, prec)
+    else:
+        m = I.cube_tets(N, seed=1)
+        W, g = I.ic3_kelvin_helmholtz(m, seed=1), rd.Mesh3(m)
+        g.set_state(W)
+        g.step_cfl(1, 0.3, rd.B, rd.RK2)
+    W = g.get_state()
+    nv = m["nv"]
+    for first, k, x in ((nv - 1, 0, 0.0), (nv // 2, 0, -1.0), (77, -1, np.nan), (3, -1, np.inf), (1, 1, 1e6)):
+        bad = W.copy()
+        bad[k, [first, nv - 1]] = x
+        with pytest.raises(rd.RDError, match=f"vertex {first}\\b") as e:
+            g.set_state(bad)
+        assert e.value.status == rd.RD_ENONPHYS
+        assert np.array_equal(g.get_state(), W)
+    g.set_state(W)
+    assert np.array_equal(g.get_state(), W)
+    g.close()
