@@ -27,9 +27,10 @@ struct TilePlan3 {
 };
 
 // tet: [4 nt] corners; xyz: coordinates; target: tetrahedra per tile, at most
-// kTileTets. Returns an error message, empty when built.
+// kTileTets; renumber: vertices as first met, else the caller's. Returns an
+// error message, empty when built.
 inline std::string build_tiles3(int64_t nv, int64_t nt, const int32_t* tet, const double* const xyz[3],
-                                const double per[3], int target, int threads, TilePlan3& P) {
+                                const double per[3], int target, bool renumber, int threads, TilePlan3& P) {
   struct Item {
     float c[3];
     int32_t id;
@@ -177,12 +178,12 @@ inline std::string build_tiles3(int64_t nv, int64_t nt, const int32_t* tet, cons
   }
   P.torder.resize(nt);
   for (int64_t t = 0; t < nt; ++t) P.torder[t] = it[t].id;
-  // vertices as first met, records of a vertex by ascending tile
+  // vertex numbers, records of a vertex by ascending tile
   P.inv.assign(nv, -1);
   P.rbeg.assign(nv + 1, 0);
   int32_t next = 0;
   for (int32_t& v : P.lv) {
-    if (P.inv[v] < 0) P.inv[v] = next++;
+    if (P.inv[v] < 0) P.inv[v] = renumber ? next++ : v;
     v = P.inv[v];
     ++P.rbeg[v + 1];
   }

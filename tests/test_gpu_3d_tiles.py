@@ -83,3 +83,29 @@ def test_tiles_match_the_oracle(rd, O, name, scheme):
         g.step_cfl(1, 0.2, scheme, time)
         assert rel_err(g.get_state(), ref) <= 1e-12, time
     g.close()
+
+
+@pytest.mark.parametrize("N", [25, 26])
+@pytest.mark.parametrize("scramble", [False, True])
+def test_numbering_kept_or_not(rd, O, N, scramble):
+    """Meshes of up to 16384 vertices keep the caller's numbering on the device,
+    larger ones do not: a state comes back as it was set, and steps match the
+    oracle, in either."""
+    import torch
+    m = box(N, scramble)
+    W = I.ic3_kelvin_helmholtz(m, seed=5)
+    om = O.OracleMesh3(m)
+    g = rd.Mesh3(m)
+    g.set_state(W)
+    assert np.array_equal(g.get_state(), W)
+    ref = W
+    for _ in range(2):
+        dt = om.max_dt(ref, 0.4)
+        assert abs(g.max_dt(0.4) - dt) <= 1e-12 * dt
+        g.step_cfl(1, 0.4, rd.B, rd.RK2)
+        ref = om.step(ref, dt, rd.B, rd.RK2)
+        assert rel_err(g.get_state(), ref) <= 2e-12
+    out = torch.empty((5, m["nv"]), dtype=torch.float64, device="cuda")
+    rd._check(rd.lib().rd3_get_state(g.h, out.data_ptr(), 1))
+    assert np.array_equal(out.cpu().numpy(), g.get_state())
+    g.close()
