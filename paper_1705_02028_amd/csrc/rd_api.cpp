@@ -1885,26 +1885,33 @@ namespace {
 
 // Buffers of one mesh-generation call, freed together: device memory, cut
 // from few allocations, and the host's report, which the device writes.
+// Allocations of up to 1 MiB take 1 us with their release, larger ones 25 (beyond
+// 64 MiB 250), so a small mesh's arrays come from pieces of 1 MiB, a larger one's
+// from 16.
+constexpr int64_t kSmallDl = 80000;  // triangles whose arrays take less than 1 MiB each
 struct DlBuffers {
   std::vector<void*> p;
   char* at = nullptr;
-  size_t left = 0;
+  size_t left = 0, piece = size_t(16) << 20;
   rd::dl::Control* control = nullptr;
   int exact_blocks = 0;  // workgroups the exact pass has scratch for
-  rd::dl::Report* report = nullptr;
+  // the report, in pinned memory that the device writes (`mapped`, 24 us to
+  // take and give back) or in `own`, the control words copied at each wait
+  rd::dl::Report own;
+  rd::dl::Report* mapped = nullptr;
   DlBuffers() = default;
   DlBuffers(const DlBuffers&) = delete;
   DlBuffers& operator=(const DlBuffers&) = delete;
   ~DlBuffers() {
     for (void* q : p) (void)hipFree(q);
-    if (report) (void)hipHostFree(report);
+    if (mapped) (void)hipHostFree(mapped);
   }
   template <class T>
   bool get(T** out, size_t n) {
     const size_t bytes = (std::max<size_t>(n, 1) * sizeof(T) + 255) & ~size_t(255);
     if (bytes > left) {
       void* q = nullptr;
-      const size_t take = std::max<size_t>(bytes, size_t(16) << 20);
+      const size_t take = std::max<size_t>(bytes, piece);
       if (hipMalloc(&q, take) != hipSuccess) return false;
       p.push_back(q);
       at = static_cast<char*>(q);
@@ -1915,11 +1922,18 @@ struct DlBuffers {
     left -= bytes;
     return true;
   }
-  bool get_control() {
+  bool get_report() {
     void* q = nullptr;
-    if (!get(&control, 1) || hipHostMalloc(&q, sizeof(rd::dl::Report), hipHostMallocDefault) != hipSuccess) return false;
-    report = static_cast<rd::dl::Report*>(q);
+    if (hipHostMalloc(&q, sizeof(rd::dl::Report), hipHostMallocDefault) != hipSuccess) return false;
+    mapped = static_cast<rd::dl::Report*>(q);
     return true;
+  }
+  const volatile rd::dl::Report* report() const { return mapped ? mapped : &own; }
+  // Waits for the stream and for the report.
+  bool read_report(const rd::dl::Mesh& m, const rd::dl::Refine& r, hipStream_t s) {
+    const hipError_t e = mapped ? rd::dl::launch_report(m, r, control, mapped, s)
+                                : hipMemcpyAsync(&own.c, control, sizeof(own.c), hipMemcpyDeviceToHost, s);
+    return e == hipSuccess && hipStreamSynchronize(s) == hipSuccess;
   }
 };
 
@@ -1961,17 +1975,16 @@ rd_status dl_flip_all(rd::dl::Mesh& m, const rd::dl::Refine& r, DlBuffers& b, hi
                       int32_t* round, int32_t* pass, int* ahead, const More& more) {
   constexpr int32_t kMaxRounds = 1000000;
   const int32_t round0 = *round, pass0 = *pass;
-  volatile rd::dl::Report* h = b.report;
+  const volatile rd::dl::Report* h = b.report();
   int start = rd::dl::kFresh;
   for (int32_t n = 0;;) {
     for (int k = 0; k < *ahead; ++k, ++n, start = rd::dl::kGoOn)
       if (!hip_ok(rd::dl::launch_round(m, b.control, start, round0 + 1 + n, pass0 + n, r.count, b.exact_blocks, s)))
         return fail(RD_EDEVICE, "flip pass failed");
-    if (!more() || !hip_ok(rd::dl::launch_report(m, r, b.control, b.report, s)) || !hip_ok(hipStreamSynchronize(s)))
-      return fail(RD_EDEVICE, "flip pass failed");
+    if (!more() || !b.read_report(m, r, s)) return fail(RD_EDEVICE, "flip pass failed");
     if (h->c.stuck) return fail(RD_EDEVICE, "a round flipped no edge");
-    // scratch for the exact pass: 41 KB a thread, a few times the edges seen at most
-    const int want = (int)std::min<int64_t>(16, (h->c.need + 63) / 64);
+    // scratch for the exact pass: 41 KB a thread, one for every edge seen up to 4096
+    const int want = (int)std::min<int64_t>(64, (h->c.need + 63) / 64);
     if (h->c.starved || want > 4 * b.exact_blocks) {
       if (want > b.exact_blocks) {
         if (!b.get(&m.work, rd::dl::exact_scratch(want))) return fail(RD_ENOMEM, "device allocation failed");
@@ -2055,7 +2068,8 @@ RD_API rd_status rd_delaunay_flip(int64_t n_vertices, const double* x, const dou
   m.ts = nt;
   m.px = period_x;
   m.py = period_y;
-  if (!b.get(&m.x, nv) || !b.get(&m.y, nv) || !dl_flip_arrays(m, b, nt) || !b.get_control())
+  if (nt <= kSmallDl) b.piece = size_t(1) << 20;
+  if (!b.get(&m.x, nv) || !b.get(&m.y, nv) || !dl_flip_arrays(m, b, nt) || !b.get(&b.control, 1))
     return fail(RD_ENOMEM, "device allocation failed");
   if (hipStreamCreate(&g.s) != hipSuccess) return fail(RD_EDEVICE, "hipStreamCreate failed");
   const hipStream_t s = g.s;
@@ -2068,7 +2082,7 @@ RD_API rd_status rd_delaunay_flip(int64_t n_vertices, const double* x, const dou
     return fail(RD_EDEVICE, "upload failed");
   int64_t flips = 0;
   int32_t round = 0, pass = 0;  // every mark is 0: the first pass tests every edge
-  int ahead = 6;
+  int ahead = 2;  // a jittered lattice takes one round that flips and one that finds nothing
   if ((st = dl_flip_all(m, rd::dl::Refine(), b, s, &flips, &round, &pass, &ahead, [] { return true; })) != RD_OK)
     return st;
   if (!hip_ok(hipMemcpyAsync(tsoa.data(), m.tri, sizeof(int32_t) * 3 * nt, hipMemcpyDeviceToHost, s)) ||
@@ -2140,10 +2154,12 @@ RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, i
     size_t scan_bytes = 0, sort_bytes = 0;
   };
   DlBuffers b;
+  b.piece = size_t(1) << 20;
   std::unique_ptr<Arrays> A(new Arrays());
   StreamGuard g;  // declared after the buffers: the stream is drained before they are freed
   auto allocate = [&](Arrays& a, int64_t vs, int64_t ts) {
     a.m.ts = ts;
+    if (ts <= kSmallDl) a.b.piece = size_t(1) << 20;
     rd::dl::Refine& r = a.r;
     a.scan_bytes = rd::dl::scan_tmp_bytes(ts);
     if (!a.b.get(&a.m.x, vs) || !a.b.get(&a.m.y, vs) || !dl_flip_arrays(a.m, a.b, ts) || !a.b.get(&r.prio, ts) ||
@@ -2166,7 +2182,7 @@ RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, i
   A->r.nv = nv0;
   A->r.r2 = max_radius * max_radius;
   A->r.b2 = max_ratio * max_ratio;
-  if (!allocate(*A, std::min(max_vertices, nv0 + ts0 - nt0), ts0) || !b.get_control())
+  if (!allocate(*A, std::min(max_vertices, nv0 + ts0 - nt0), ts0) || !b.get(&b.control, 1) || !b.get_report())
     return fail(RD_ENOMEM, "device allocation failed");
   if (size_grid) {
     // grid frame: the period on a periodic axis (nodes wrap), else the input's extent
@@ -2238,7 +2254,7 @@ RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, i
     if (n_flips) *n_flips = flips;
     return result;
   };
-  int ahead = 6;
+  int ahead = 2;  // as rd_delaunay_flip
   // the same arrays with room for the next iteration
   auto grow = [&]() -> rd_status {
     const int64_t ts = std::min<int64_t>(max_triangles, std::max(4 * nt, 2 * A->m.ts));
@@ -2281,11 +2297,10 @@ RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, i
     if (renumber) {
       if ((st = dl_reorder(m, o, nv, A->sort_tmp, A->sort_bytes, s)) != RD_OK) return st;
       nt_ordered = nt;
-      if (!candidates() || !hip_ok(rd::dl::launch_report(m, r, b.control, b.report, s)) ||
-          !hip_ok(hipStreamSynchronize(s)))
+      if (!candidates() || !b.read_report(m, r, s))
         return fail(RD_EDEVICE, "insertion-set passes failed");
     }
-    const volatile rd::dl::Report* h = b.report;
+    const volatile rd::dl::Report* h = b.report();
     if (h->count[0] == 0) {
       if (h->count[1] > 0)
         return download(fail(RD_EUNSUPPORTED, "a circumcentre lies more than a quarter period from its triangle"));

@@ -31,7 +31,7 @@
 namespace rd {
 namespace dl {
 
-constexpr int kBlock = 256;
+constexpr int kBlock = 256, kExactBlock = 64;
 
 // Rounds are enqueued several at a time without the host looking in between:
 // whether an edge was illegal, and what the round did, is kept on the device
@@ -63,8 +63,11 @@ __global__ __launch_bounds__(kBlock) void k_mark(Mesh m, const Control* c, int32
 }
 
 // Without scratch memory, and with something to do, ends the run unfinished.
-__global__ __launch_bounds__(kBlock) void k_exact(Mesh m, Control* c) {
-  const int64_t n = m.count[2], id = (int64_t)blockIdx.x * kBlock + threadIdx.x, all = (int64_t)gridDim.x * kBlock;
+// Workgroups of one wave: a few hundred edges spread over the compute units, and
+// the scratch (41 KB a thread) is no more than they need.
+__global__ __launch_bounds__(kExactBlock) void k_exact(Mesh m, Control* c) {
+  const int64_t n = m.count[2], id = (int64_t)blockIdx.x * kExactBlock + threadIdx.x;
+  const int64_t all = (int64_t)gridDim.x * kExactBlock;
   if (!m.work) {  // one workgroup
     if (id == 0 && !c->done && n > 0) {
       c->done = c->starved = 1;
@@ -181,14 +184,14 @@ __global__ __launch_bounds__(kBlock) void k_tapply(Mesh m, Order o) {
 
 static unsigned nblocks(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-int64_t exact_scratch(int blocks) { return blocks * kBlock * (int64_t)pred::kIncircleScratch; }
+int64_t exact_scratch(int blocks) { return blocks * kExactBlock * (int64_t)pred::kIncircleScratch; }
 
 hipError_t launch_round(const Mesh& m, Control* c, int start, int32_t round, int32_t pass, int* also, int exact_blocks,
                         hipStream_t s) {
   const dim3 g(nblocks(m.nt)), b(kBlock);
   hipLaunchKernelGGL(k_reset, dim3(nblocks(m.nt > 3 ? m.nt : 3)), b, 0, s, m, c, start, also);
   hipLaunchKernelGGL(k_mark, g, b, 0, s, m, c, pass);
-  hipLaunchKernelGGL(k_exact, dim3(m.work ? exact_blocks : 1), b, 0, s, m, c);
+  hipLaunchKernelGGL(k_exact, dim3(m.work ? exact_blocks : 1), dim3(kExactBlock), 0, s, m, c);
   hipLaunchKernelGGL(k_flip, g, b, 0, s, m, c, round, pass);
   hipLaunchKernelGGL(k_fix, g, b, 0, s, m, c, round);
   return hipGetLastError();
