@@ -1567,9 +1567,7 @@ void destroy_graphs(rd_batch* b) {
 
 }  // namespace
 
-RD_API rd_status rd_batch_create(rd_mesh* const* meshes, int n, void* stream, rd_batch** out) {
-  if (!out) return fail(RD_EINVAL, "null output pointer");
-  *out = nullptr;
+static rd_status batch_create(rd_mesh* const* meshes, int n, void* stream, rd_batch** out) {
   if (!meshes || n <= 0) return fail(RD_EINVAL, "empty batch");
   const double gamma = meshes[0] ? meshes[0]->gamma : 0.0;
   // The batch unwraps triangles with one period per axis: the members that
@@ -1640,6 +1638,21 @@ RD_API rd_status rd_batch_create(rd_mesh* const* meshes, int n, void* stream, rd
   desc.n_wall_edges = (int64_t)wall.size() / 2;
   desc.wall_edges = wall.empty() ? nullptr : wall.data();
   desc.gamma = gamma;
+  // blocks of the member copies
+  std::vector<int32_t> mb, vb;
+  for (int k = 0; k < n; ++k)
+    for (int64_t v = 0; v < meshes[k]->p.nv; v += rd::kBlock) {
+      mb.push_back(k);
+      vb.push_back((int32_t)v);
+    }
+  std::unique_ptr<rd_batch> owner(new rd_batch());
+  rd_batch* b = owner.get();
+  b->versions.assign(n, -1);
+  b->members.assign(meshes, meshes + n);
+  b->voff = voff;
+  b->toff = toff;
+  std::vector<double> Ldom(n);
+  for (int k = 0; k < n; ++k) Ldom[k] = meshes[k]->Ldom;  // each member's own domain size
   DeviceGuard g(meshes[0]->device);
   hipStream_t own = nullptr;
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
@@ -1650,24 +1663,13 @@ RD_API rd_status rd_batch_create(rd_mesh* const* meshes, int n, void* stream, rd
     return fail(RD_EDEVICE, "hipEventCreate failed");
   }
   rd_mesh* flat = nullptr;
-  std::vector<double> Ldom(n);
-  for (int k = 0; k < n; ++k) Ldom[k] = meshes[k]->Ldom;  // each member's own domain size
-  rd_status st = create_mesh(&desc, own, voff, toff, Ldom, &flat);
+  rd_status st = guarded([&] { return create_mesh(&desc, own, voff, toff, Ldom, &flat); });
   if (st != RD_OK) {
     (void)hipEventDestroy(ev_in);
     (void)hipEventDestroy(ev_out);
     (void)hipStreamDestroy(own);
     return st;
   }
-  // blocks of the member copies
-  std::vector<int32_t> mb, vb;
-  for (int k = 0; k < n; ++k)
-    for (int64_t v = 0; v < meshes[k]->p.nv; v += rd::kBlock) {
-      mb.push_back(k);
-      vb.push_back((int32_t)v);
-    }
-  std::unique_ptr<rd_batch> owner(new rd_batch());
-  rd_batch* b = owner.get();
   if ((st = dalloc(flat, &b->mem, n)) || (st = upload(flat, &b->mb, mb)) || (st = upload(flat, &b->vb, vb))) {
     rd_mesh_destroy(flat);
     (void)hipEventDestroy(ev_in);
@@ -1676,11 +1678,7 @@ RD_API rd_status rd_batch_create(rd_mesh* const* meshes, int n, void* stream, rd
     return st;
   }
   b->nblocks = (int)mb.size();
-  b->versions.assign(n, -1);
   b->flat = flat;
-  b->members.assign(meshes, meshes + n);
-  b->voff = voff;
-  b->toff = toff;
   b->stream = static_cast<hipStream_t>(stream);
   b->own = own;
   b->ev_in = ev_in;
@@ -1688,6 +1686,12 @@ RD_API rd_status rd_batch_create(rd_mesh* const* meshes, int n, void* stream, rd
   (void)owner.release();
   *out = b;
   return RD_OK;
+}
+
+RD_API rd_status rd_batch_create(rd_mesh* const* meshes, int n, void* stream, rd_batch** out) {
+  if (!out) return fail(RD_EINVAL, "null output pointer");
+  *out = nullptr;
+  return guarded([&] { return batch_create(meshes, n, stream, out); });
 }
 
 namespace {
@@ -2043,9 +2047,8 @@ struct StreamGuard {
 
 }  // namespace
 
-RD_API rd_status rd_delaunay_flip(int64_t n_vertices, const double* x, const double* y, double period_x,
-                                  double period_y, int64_t n_triangles, int32_t* tri, int64_t* n_flips,
-                                  int32_t* n_rounds) {
+static rd_status delaunay_flip(int64_t n_vertices, const double* x, const double* y, double period_x, double period_y,
+                               int64_t n_triangles, int32_t* tri, int64_t* n_flips, int32_t* n_rounds) {
   rd_mesh_desc desc{};
   desc.n_vertices = n_vertices;
   desc.n_triangles = n_triangles;
@@ -2095,12 +2098,17 @@ RD_API rd_status rd_delaunay_flip(int64_t n_vertices, const double* x, const dou
   return RD_OK;
 }
 
-RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, int64_t max_vertices,
-                                    double period_x, double period_y, int64_t* n_triangles, int32_t* tri,
-                                    int64_t max_triangles, double max_radius, double max_ratio,
-                                    const double* size_grid, int32_t grid_nx, int32_t grid_ny,
-                                    int32_t max_iterations, int32_t morton, int32_t* n_iterations,
-                                    int64_t* n_flips) {
+RD_API rd_status rd_delaunay_flip(int64_t n_vertices, const double* x, const double* y, double period_x,
+                                  double period_y, int64_t n_triangles, int32_t* tri, int64_t* n_flips,
+                                  int32_t* n_rounds) {
+  return guarded([&] { return delaunay_flip(n_vertices, x, y, period_x, period_y, n_triangles, tri, n_flips, n_rounds); });
+}
+
+static rd_status delaunay_refine(int64_t* n_vertices, double* x, double* y, int64_t max_vertices, double period_x,
+                                 double period_y, int64_t* n_triangles, int32_t* tri, int64_t max_triangles,
+                                 double max_radius, double max_ratio, const double* size_grid, int32_t grid_nx,
+                                 int32_t grid_ny, int32_t max_iterations, int32_t morton, int32_t* n_iterations,
+                                 int64_t* n_flips) {
   if (!n_vertices || !n_triangles) return fail(RD_EINVAL, "null count pointer");
   const int64_t nv0 = *n_vertices, nt0 = *n_triangles;
   if (max_vertices < nv0 || max_triangles < nt0) return fail(RD_EINVAL, "capacity below the current size");
@@ -2323,6 +2331,19 @@ RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, i
     nt += nadd;
     m.nt = nt;
   }
+}
+
+RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, int64_t max_vertices,
+                                    double period_x, double period_y, int64_t* n_triangles, int32_t* tri,
+                                    int64_t max_triangles, double max_radius, double max_ratio,
+                                    const double* size_grid, int32_t grid_nx, int32_t grid_ny,
+                                    int32_t max_iterations, int32_t morton, int32_t* n_iterations,
+                                    int64_t* n_flips) {
+  return guarded([&] {
+    return delaunay_refine(n_vertices, x, y, max_vertices, period_x, period_y, n_triangles, tri, max_triangles,
+                           max_radius, max_ratio, size_grid, grid_nx, grid_ny, max_iterations, morton, n_iterations,
+                           n_flips);
+  });
 }
 
 // --------------------------------------------------------- three dimensions --
