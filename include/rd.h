@@ -200,8 +200,9 @@ rd_status rd_mesh_tile_info(const rd_mesh* mesh, int64_t info[4]);
  * returns it in *best; candidates are taken in the given order and a later
  * one replaces the size kept so far only when it is more than 2% faster
  * (about the spread of one timing), so the first candidate (the two-pass
- * form by default) wins near-ties. The mesh's state is restored afterwards.
- * Waits. */
+ * form by default) wins near-ties. The FP64 step has one form: it is timed
+ * once, with the first usable size, which is kept, and that time is reported
+ * for every size in range. The mesh's state is restored afterwards. Waits. */
 rd_status rd_tune(rd_mesh* mesh, double cfl, int scheme, int time, int precision, int n_steps,
                   const int* candidates, int n_candidates, double* ms_per_step, int* best);
 

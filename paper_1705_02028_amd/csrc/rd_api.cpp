@@ -871,9 +871,11 @@ rd_status build_patches(rd_mesh* m) {
 // whose size the library chooses: cut to half the triangles of a 512-triangle
 // tile they left the last of a workgroup's eight wavefronts empty, 2.36
 // against 1.53 ms for two steps at 2048^2, state in and out.)
+bool tile_in_range(int tt) { return tt == 0 || (tt >= 32 && tt <= 1024); }
+
 rd_status set_tile(rd_mesh* m, int tt) {
   if (tt == m->tile) return RD_OK;
-  if (tt != 0 && (tt < 32 || tt > 1024)) return fail(RD_EINVAL, "tile size must be 0 or in [32, 1024]");
+  if (!tile_in_range(tt)) return fail(RD_EINVAL, "tile size must be 0 or in [32, 1024]");
   DeviceGuard g(m->device);
   HIPCHK(hipStreamSynchronize(m->stream));
   return guarded([&] { return build_tiles(m, tt); });
@@ -1313,6 +1315,10 @@ RD_API rd_status rd_tune(rd_mesh* m, double cfl, int scheme, int time, int preci
   float pick_ms = 0.0f;
   for (int i = 0; i < n_candidates; ++i) {
     if (ms_per_step) ms_per_step[i] = -1.0;
+    if (!fp32 && pick >= 0) {  // the FP64 step has one form: its time stands for every size
+      if (ms_per_step && tile_in_range(candidates[i])) ms_per_step[i] = pick_ms / n_steps;
+      continue;
+    }
     st = set_tile(m, candidates[i]);
     if (st == RD_EUNSUPPORTED || st == RD_EINVAL) continue;
     if (st != RD_OK) break;
@@ -1822,6 +1828,10 @@ RD_API rd_status rd_batch_tune(rd_batch* b, double cfl, int scheme, int time, in
   std::vector<hipStream_t> outer;
   for (int i = 0; i < n_candidates; ++i) {
     if (ms_per_step) ms_per_step[i] = -1.0;
+    if (!fp32 && pick >= 0) {  // as rd_tune
+      if (ms_per_step && tile_in_range(candidates[i])) ms_per_step[i] = pick_ms / n_steps;
+      continue;
+    }
     st = batch_set_tile(b, candidates[i]);
     if (st == RD_EUNSUPPORTED || st == RD_EINVAL) continue;
     if (st != RD_OK) break;
