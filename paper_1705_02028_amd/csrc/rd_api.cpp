@@ -85,15 +85,6 @@ int host_threads() {
   return (int)std::min(8u, std::max(1u, n));
 }
 
-// f(i) for i = 0 .. n - 1, on a few threads when there is enough to do.
-template <class F>
-void parallel_for(int64_t n, const F& f, int64_t enough = 100000) {
-  const int w = n < enough ? 1 : host_threads();
-  rd::run_workers(w, [&](int q) {
-    for (int64_t i = n * q / w; i < n * (q + 1) / w; ++i) f(i);
-  });
-}
-
 // The host side of a call may run out of memory (or of threads): no C++
 // exception crosses the ABI.
 template <class F>
@@ -114,10 +105,14 @@ struct HostGeom {
   rd::UVec<double> V;
 };
 
-// The checks of rd_mesh_validate. Several threads share large meshes: each
-// takes a range of triangles, then a range of vertices, whose corners it finds
-// by reading the whole triangle list.
-rd_status check_desc(const rd_mesh_desc* d, HostGeom* out) {
+// Workers for the host side of a mesh of n triangles: small ones are done
+// sooner than the threads would start.
+int workers_for(int64_t nt) { return nt < 30000 ? 1 : host_threads(); }
+
+// The checks of rd_mesh_validate, and (out) the lists. Each worker takes a
+// range of triangles, then a range of vertices, whose corners it finds by
+// reading the triangles in blocks, those blocks that have none left out.
+rd_status check_desc(const rd_mesh_desc* d, HostGeom* out, rd::Workers& pool) {
   if (!d) return fail(RD_EINVAL, "null mesh description");
   if (d->n_vertices <= 0 || d->n_triangles <= 0) return fail(RD_EINVAL, "empty mesh");
   if (d->n_vertices >= (int64_t(1) << 31) || 3 * d->n_triangles >= (int64_t(1) << 31))
@@ -128,24 +123,44 @@ rd_status check_desc(const rd_mesh_desc* d, HostGeom* out) {
   if (d->n_wall_edges < 0 || (d->n_wall_edges > 0 && !d->wall_edges))
     return fail(RD_EINVAL, "bad wall edge list");
   const int64_t nv = d->n_vertices, nt = d->n_triangles;
-  const int w = nt < 30000 ? 1 : host_threads();
-  rd::UVec<double> area(nt);
-  std::vector<int64_t> bad(w, nt);  // first bad triangle of each range
-  rd::run_workers(w, [&](int q) {
-    for (int64_t t = nt * q / w; t < nt * (q + 1) / w; ++t) {
-      const int32_t v[3] = {d->tri[3 * t], d->tri[3 * t + 1], d->tri[3 * t + 2]};
-      bool ok = true;
-      for (int k = 0; k < 3; ++k) ok = ok && v[k] >= 0 && v[k] < nv;
-      double px[3] = {0.0, 0.0, 0.0}, py[3] = {0.0, 0.0, 0.0};
-      for (int k = 1; ok && k < 3; ++k) {
-        px[k] = unwrap_h(d->x[v[k]] - d->x[v[0]], d->period_x);
-        py[k] = unwrap_h(d->y[v[k]] - d->y[v[0]], d->period_y);
+  const int w = pool.size();
+  constexpr int64_t kBlockTri = 1024;
+  const int64_t nb = (nt + kBlockTri - 1) / kBlockTri;
+  struct Span {
+    int32_t lo, hi;  // vertices of a block's corners
+  };
+  rd::UVec<Span> span(nb);
+  rd::UVec<double> third(out ? nt : 0);  // a third of each triangle's area
+  std::vector<int64_t> bad(w, nt);       // first bad triangle of each worker
+  pool.run([&](int q) {
+    for (int64_t k = nb * q / w; k < nb * (q + 1) / w; ++k) {
+      int32_t lo = INT32_MAX, hi = -1;
+      for (int64_t t = k * kBlockTri; t < std::min(nt, (k + 1) * kBlockTri); ++t) {
+        const int32_t* v = d->tri + 3 * t;
+        if (t + 16 < nt)  // the coordinates of one ahead: without locality each is a miss
+          for (int c = 0; c < 3; ++c) {
+            __builtin_prefetch(d->x + v[48 + c]);
+            __builtin_prefetch(d->y + v[48 + c]);
+          }
+        const int32_t v0 = std::min(v[0], std::min(v[1], v[2])), v1 = std::max(v[0], std::max(v[1], v[2]));
+        lo = std::min(lo, v0);
+        hi = std::max(hi, v1);
+        double area = 0.0;
+        if (v0 >= 0 && v1 < nv) {
+          double px[3] = {0.0, 0.0, 0.0}, py[3] = {0.0, 0.0, 0.0};
+          for (int c = 1; c < 3; ++c) {
+            px[c] = unwrap_h(d->x[v[c]] - d->x[v[0]], d->period_x);
+            py[c] = unwrap_h(d->y[v[c]] - d->y[v[0]], d->period_y);
+          }
+          area = 0.5 * (px[1] * py[2] - py[1] * px[2]);
+        }
+        if (!(area > 0.0)) {
+          bad[q] = t;
+          return;
+        }
+        if (out) third[t] = area / 3.0;
       }
-      area[t] = 0.5 * (px[1] * py[2] - py[1] * px[2]);
-      if (!ok || !(area[t] > 0.0)) {
-        bad[q] = t;
-        return;
-      }
+      span[k] = Span{lo, hi};
     }
   });
   for (int64_t t : bad)
@@ -155,45 +170,71 @@ rd_status check_desc(const rd_mesh_desc* d, HostGeom* out) {
           return fail(RD_EINVAL, "triangle " + std::to_string(t) + " has a vertex index out of range");
       return fail(RD_EINVAL, "triangle " + std::to_string(t) + " is not counter-clockwise with positive area");
     }
+  // f(s, v) for the corners s of the vertices v in [a, b), ascending; collected
+  // block by block first, without a branch on each
+  auto corners = [&](int64_t a, int64_t b, const auto& f) {
+    int32_t mine[3 * kBlockTri];
+    for (int64_t k = 0; k < nb; ++k) {
+      if (span[k].hi < a || span[k].lo >= b) continue;
+      const int64_t s0 = 3 * k * kBlockTri, s1 = 3 * std::min(nt, (k + 1) * kBlockTri);
+      int32_t n = 0;
+      for (int64_t s = s0; s < s1; ++s) {
+        mine[n] = (int32_t)s;
+        n += (uint64_t)(d->tri[s] - a) < (uint64_t)(b - a);
+      }
+      for (int32_t i = 0; i < n; ++i) f(mine[i], d->tri[mine[i]]);
+    }
+  };
+  auto share = [&](int q) { return nv * q / w; };
   HostGeom geo;
   rd::UVec<int32_t>&row = geo.row, &slot = geo.slot;
   row.resize(nv + 1);
-  slot.resize(3 * nt);
-  geo.V.resize(nv);
-  auto share = [&](int q) { return nv * q / w; };
-  row[0] = 0;
-  rd::run_workers(w, [&](int q) {
+  std::vector<int64_t> first(w + 1, 0), lost(w, nv);  // corners before each worker's vertices; first bad vertex
+  pool.run([&](int q) {
     const int64_t a = share(q), b = share(q + 1);
     std::fill(row.begin() + a + 1, row.begin() + b + 1, 0);
-    for (int64_t s = 0; s < 3 * nt; ++s)
-      if (d->tri[s] >= a && d->tri[s] < b) ++row[d->tri[s] + 1];
+    corners(a, b, [&](int64_t, int32_t v) { ++row[v + 1]; });
+    int64_t n = 0;
+    for (int64_t i = b; i-- > a;) {
+      n += row[i + 1];
+      if (row[i + 1] == 0 || row[i + 1] > kMaxDegree) lost[q] = i;
+    }
+    first[q + 1] = n;
   });
-  for (int64_t i = 0; i < nv; ++i) {
-    const int32_t deg = row[i + 1];
-    if (deg == 0) return fail(RD_EINVAL, "vertex " + std::to_string(i) + " belongs to no triangle");
-    // a triangle's rank among the triangles of each corner vertex is packed in 10 bits
-    if (deg > kMaxDegree)
+  for (int64_t i : lost)
+    if (i < nv) {
+      const int32_t deg = row[i + 1];
+      if (deg == 0) return fail(RD_EINVAL, "vertex " + std::to_string(i) + " belongs to no triangle");
+      // a triangle's rank among the triangles of each corner vertex is packed in 10 bits
       return fail(RD_EINVAL, "vertex " + std::to_string(i) + " belongs to " + std::to_string(deg) +
                                  " triangles; at most " + std::to_string(kMaxDegree) + " are supported");
-    row[i + 1] += row[i];
-  }
-  rd::run_workers(w, [&](int q) {
-    const int64_t a = share(q), b = share(q + 1);
-    std::vector<int32_t> fill(row.begin() + a, row.begin() + b);
-    for (int64_t s = 0; s < 3 * nt; ++s)
-      if (d->tri[s] >= a && d->tri[s] < b) slot[fill[d->tri[s] - a]++] = (int32_t)s;
-    for (int64_t i = a; i < b; ++i) {
-      double V = 0.0;
-      for (int32_t j = row[i]; j < row[i + 1]; ++j) V += area[slot[j] / 3] / 3.0;
-      geo.V[i] = V;
     }
-  });
   for (int64_t e = 0; e < d->n_wall_edges; ++e) {
     const int32_t a = d->wall_edges[2 * e], b = d->wall_edges[2 * e + 1];
     if (a < 0 || a >= nv || b < 0 || b >= nv || a == b)
       return fail(RD_EINVAL, "wall edge " + std::to_string(e) + " is invalid");
   }
-  if (out) *out = std::move(geo);
+  if (!out) return RD_OK;
+  for (int q = 0; q < w; ++q) first[q + 1] += first[q];
+  slot.resize(3 * nt);
+  geo.V.resize(nv);
+  row[0] = 0;
+  pool.run([&](int q) {
+    const int64_t a = share(q), b = share(q + 1);
+    rd::UVec<int32_t> next(b - a);  // where each vertex's next corner goes
+    int32_t at = (int32_t)first[q];
+    for (int64_t i = a; i < b; ++i) {
+      next[i - a] = at;
+      at += row[i + 1];
+      row[i + 1] = at;
+      geo.V[i] = 0.0;
+    }
+    corners(a, b, [&](int64_t s, int32_t v) {
+      slot[next[v - a]++] = (int32_t)s;
+      geo.V[v] += third[s / 3];
+    });
+  });
+  *out = std::move(geo);
   return RD_OK;
 }
 
@@ -223,15 +264,23 @@ struct rd_mesh {
   // host copies, kept for batches, for other patches and for the second view
   rd::UVec<double> x, y, V;
   rd::UVec<int32_t> tri, row, slot;
-  std::vector<int32_t> wall, bc, wv, wptr;
-  std::vector<uint8_t> ghost;
+  rd::UVec<int32_t> bc;
+  std::vector<int32_t> wall, wv, wptr;
+  rd::UVec<uint8_t> ghost;
   std::vector<rd::WallEnt> went;
   double px = 0.0, py = 0.0, gamma = 1.4;
   double Ldom = 0.0;  // domain size of the Bx sensor
   // device buffers
   std::vector<void*> allocs;
-  char* slab = nullptr;  // the newest shared allocation, and its bytes that are free
-  size_t slab_left = 0;
+  // the newest shared allocations (of buffers, and of tables from the host), and
+  // their bytes that are free
+  struct Slab {
+    char* at = nullptr;
+    size_t left = 0;
+  } slab, tables;
+  // during creation: what goes to the tables, in one copy
+  rd::UVec<char> stage;
+  bool staging = false;
   double* scratch = nullptr;      // [4 nv] host states pass through it
   int* bad = nullptr;             // first vertex of a host state that is not physical
   unsigned* done = nullptr;       // workgroups of the CFL pass that have finished
@@ -269,19 +318,29 @@ rd_status dalloc_in(std::vector<void*>& list, T** p, size_t n) {
   return RD_OK;
 }
 
+// Brings what is staged to the device.
+rd_status flush_stage(rd_mesh* m) {
+  const size_t n = kSlab - m->tables.left;
+  if (m->staging && m->tables.at) HIPCHK(hipMemcpy(m->tables.at, m->stage.data(), n, hipMemcpyHostToDevice));
+  return RD_OK;
+}
+
 // Buffers that live as long as the mesh: small ones (a small mesh has some
 // sixty) share allocations of half a megabyte, at 256-byte boundaries.
 template <class T>
-rd_status dalloc(rd_mesh* m, T** p, size_t n) {
+rd_status dalloc(rd_mesh* m, T** p, size_t n, rd_mesh::Slab rd_mesh::*from = &rd_mesh::slab) {
+  rd_mesh::Slab& s = m->*from;
   const size_t bytes = (std::max<size_t>(n, 1) * sizeof(T) + 255) & ~size_t(255);
   if (bytes > kSlab / 4) return dalloc_in(m->allocs, p, n);
-  if (bytes > m->slab_left) {
-    rd_status st = dalloc_in(m->allocs, &m->slab, kSlab);
-    if (st != RD_OK) return st;
-    m->slab_left = kSlab;
+  if (bytes > s.left) {
+    const bool tables = &s == &m->tables;
+    rd_status st = tables ? flush_stage(m) : RD_OK;
+    if (st != RD_OK || (st = dalloc_in(m->allocs, &s.at, kSlab)) != RD_OK) return st;
+    s.left = kSlab;
+    if (tables && m->staging) m->stage.resize(kSlab);
   }
-  *p = reinterpret_cast<T*>(m->slab + (kSlab - m->slab_left));
-  m->slab_left -= bytes;
+  *p = reinterpret_cast<T*>(s.at + (kSlab - s.left));
+  s.left -= bytes;
   return RD_OK;
 }
 
@@ -295,9 +354,12 @@ rd_status upload_in(std::vector<void*>& list, T** p, const std::vector<T, A>& h)
 
 template <class T, class A>
 rd_status upload(rd_mesh* m, T** p, const std::vector<T, A>& h) {
-  rd_status st = dalloc(m, p, h.size());
-  if (st != RD_OK) return st;
-  if (!h.empty()) HIPCHK(hipMemcpy(*p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
+  rd_status st = dalloc(m, p, h.size(), &rd_mesh::tables);
+  if (st != RD_OK || h.empty()) return st;
+  const ptrdiff_t at = m->tables.at ? reinterpret_cast<char*>(*p) - m->tables.at : -1;
+  const size_t bytes = h.size() * sizeof(T);
+  if (m->staging && at >= 0 && at + bytes <= kSlab) std::memcpy(&m->stage[at], h.data(), bytes);
+  else HIPCHK(hipMemcpy(*p, h.data(), bytes, hipMemcpyHostToDevice));
   return RD_OK;
 }
 
@@ -478,7 +540,7 @@ rd::State state_of(const rd_mesh* m) {
 
 // The tables of the second view of the mesh and the blocks of its vertex
 // reductions.
-rd_status build_view(rd_mesh* m) {
+rd_status build_view(rd_mesh* m, rd::Workers& pool) {
   rd::Dev& d = m->d;
   rd::CflPlan& c = m->cfl;
   const int64_t nv = m->d.nv, nt = m->d.nt;
@@ -510,7 +572,7 @@ rd_status build_view(rd_mesh* m) {
   std::vector<int32_t> vmesh, tmesh;
   rd::UVec<uint32_t> rk(nt);
   // the triangle of every part slot (none: -1)
-  parallel_for((int64_t)sbase.size(), [&](int64_t g) {
+  pool.each((int64_t)sbase.size(), [&](int64_t g) {
     const int64_t end = g + 1 < (int64_t)sbase.size() ? sbase[g + 1] : base;
     for (int64_t l = 0; l < 64; ++l) {
       const int64_t v = 64 * g + l;
@@ -519,11 +581,15 @@ rd_status build_view(rd_mesh* m) {
       for (int64_t j = 0; sbase[g] + 64 * j < end; ++j)
         vtri[sbase[g] + l + 64 * j] = j < n ? m->slot[m->row[v] + j] / 3 : -1;
     }
-  }, 2000);
+  });
   // corners, and the rank of each triangle among the triangles of each of its
   // corner vertices (10 bits per corner)
-  parallel_for(nt, [&](int64_t t) {
+  pool.each(nt, [&](int64_t t) {
     uint32_t r = 0;
+    for (int k = 0; k < 3; ++k) {  // the lists ahead: without locality each is two misses
+      if (t + 24 < nt) __builtin_prefetch(&m->row[m->tri[3 * (t + 24) + k]]);
+      if (t + 12 < nt) __builtin_prefetch(&m->slot[m->row[m->tri[3 * (t + 12) + k]]]);
+    }
     for (int k = 0; k < 3; ++k) {
       const int32_t v = m->tri[3 * t + k];
       tv[k * nt + t] = v;
@@ -734,7 +800,7 @@ int patch_own(int64_t nv, int ncu) {
 
 constexpr int kPatchVertexBytes = 112;  // of LDS in the second stage
 
-rd_status build_patches(rd_mesh* m) {
+rd_status build_patches(rd_mesh* m, rd::Workers& pool) {
   rd::Patches& q = m->p;
   const int64_t nv = q.nv, nt = m->d.nt;
   rd::PatchPlan P;
@@ -751,7 +817,7 @@ rd_status build_patches(rd_mesh* m) {
   in.voff = &m->voff;
   in.toff = &m->toff;
   in.own = patch_own(nv, m->ncu);
-  in.threads = nv < 15000 ? 1 : host_threads();  // a thread costs about 30 us
+  in.workers = &pool;
   std::string why = rd::build_patch_plan(in, P);
   // a vertex in more triangles than a workgroup has threads: its patch keeps
   // vertex records and parts apart in LDS, so the other patches are kept small
@@ -787,12 +853,11 @@ rd_status build_patches(rd_mesh* m) {
   if (need > (size_t)m->lds_max)
     return fail(RD_EUNSUPPORTED, "patches of this mesh need " + std::to_string(need) + " bytes of LDS");
   // descriptors, geometry and boundary lists in internal order
-  rd::UVec<int32_t> inv(nv);
-  parallel_for(nv, [&](int64_t i) { inv[P.order[i]] = (int32_t)i; });
+  const rd::UVec<int32_t>& inv = P.inv;
   std::vector<rd::PatchDesc> desc(P.npatch);
   rd::UVec<double2> xy(nv + P.halo.size());
   rd::UVec<double> V(nv);
-  parallel_for(P.npatch, [&](int64_t k) {
+  pool.each(P.npatch, [&](int64_t k) {
     int64_t at = (int64_t)P.vbeg[k] + P.hbeg[k];
     rd::PatchDesc& d = desc[k];
     d = rd::PatchDesc();
@@ -811,8 +876,8 @@ rd_status build_patches(rd_mesh* m) {
       const int32_t v = P.order[l < d.own ? d.v0 + l : P.halo[d.h0 + l - d.own]];
       xy[at++] = make_double2(m->x[v], m->y[v]);
     }
-  }, 400);
-  parallel_for(nv, [&](int64_t i) { V[i] = m->ghost[P.order[i]] ? -m->V[P.order[i]] : m->V[P.order[i]]; });
+  });
+  pool.each(nv, [&](int64_t i) { V[i] = m->ghost[P.order[i]] ? -m->V[P.order[i]] : m->V[P.order[i]]; });
   std::vector<int32_t> wb;
   std::vector<rd::WallEnt> went = m->went;
   if (!m->wv.empty()) {
@@ -891,7 +956,10 @@ rd_status check_step_args(int scheme, int time, int precision) {
 }  // namespace
 
 RD_API rd_status rd_mesh_validate(const rd_mesh_desc* desc) {
-  return guarded([&] { return check_desc(desc, nullptr); });
+  return guarded([&] {
+    rd::Workers pool(desc ? workers_for(desc->n_triangles) : 1);
+    return check_desc(desc, nullptr, pool);
+  });
 }
 
 namespace {
@@ -902,7 +970,8 @@ namespace {
 rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::vector<int64_t>& voff,
                       const std::vector<int64_t>& toff, const std::vector<double>& Ldom, rd_mesh** out) {
   HostGeom geo;
-  rd_status st = check_desc(desc, &geo);
+  rd::Workers pool(desc ? workers_for(desc->n_triangles) : 1);
+  rd_status st = check_desc(desc, &geo, pool);
   if (st != RD_OK) return st;
   struct Drop {
     void operator()(rd_mesh* m) const {
@@ -922,14 +991,36 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   m->x.resize(nv);
   m->y.resize(nv);
   m->tri.resize(3 * nt);
-  parallel_for(nv, [&](int64_t i) {
-    m->x[i] = desc->x[i];
-    m->y[i] = desc->y[i];
+  m->ghost.resize(nv);
+  // copies of the description, its extent, and whether it has ghosts
+  struct Seen {
+    double x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
+    bool ghosts = false;
+  };
+  std::vector<Seen> seen(pool.size());
+  pool.run([&](int q) {
+    Seen s;
+    const int64_t w = pool.size();
+    for (int64_t i = nv * q / w; i < nv * (q + 1) / w; ++i) {
+      const double x = m->x[i] = desc->x[i], y = m->y[i] = desc->y[i];
+      s.x0 = std::min(s.x0, x);
+      s.x1 = std::max(s.x1, x);
+      s.y0 = std::min(s.y0, y);
+      s.y1 = std::max(s.y1, y);
+      m->ghost[i] = desc->ghost && desc->ghost[i] ? 1 : 0;
+      s.ghosts = s.ghosts || m->ghost[i];
+    }
+    std::copy(desc->tri + 3 * (nt * q / w), desc->tri + 3 * (nt * (q + 1) / w), m->tri.begin() + 3 * (nt * q / w));
+    seen[q] = s;
   });
-  parallel_for(3 * nt, [&](int64_t i) { m->tri[i] = desc->tri[i]; });
-  m->ghost.assign(nv, 0);
-  if (desc->ghost)
-    for (int64_t i = 0; i < nv; ++i) m->ghost[i] = desc->ghost[i] ? 1 : 0;
+  Seen all;
+  for (const Seen& s : seen) {
+    all.x0 = std::min(all.x0, s.x0);
+    all.x1 = std::max(all.x1, s.x1);
+    all.y0 = std::min(all.y0, s.y0);
+    all.y1 = std::max(all.y1, s.y1);
+    all.ghosts = all.ghosts || s.ghosts;
+  }
   if (desc->n_wall_edges > 0) m->wall.assign(desc->wall_edges, desc->wall_edges + 2 * desc->n_wall_edges);
   m->px = desc->period_x;
   m->py = desc->period_y;
@@ -941,11 +1032,12 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   m->row.swap(geo.row);
   m->slot.swap(geo.slot);
   // boundary kinds and wall incidences (ascending edge id per vertex)
-  bool has_bc = false;
-  for (int64_t i = 0; i < nv; ++i) has_bc |= m->ghost[i] != 0;
-  has_bc |= !m->wall.empty();
-  if (has_bc) {
-    m->bc.assign(nv, -1);
+  if (m->wall.empty() && all.ghosts) {
+    m->bc.resize(nv);
+    pool.each(nv, [&](int64_t i) { m->bc[i] = m->ghost[i] ? -2 : -1; });
+    m->wptr.push_back(0);
+  } else if (!m->wall.empty()) {
+    m->bc.resize(nv);
     // incidences per vertex, ascending edge id
     const int64_t nw = (int64_t)m->wall.size() / 2;
     std::vector<int32_t> wrow(nv + 1, 0);
@@ -988,10 +1080,8 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   p.hpy = m->py > 0.0 ? 0.5 * m->py : HUGE_VAL;
   // domain size L of the Bx sensor: the period on a periodic axis, else the coordinate extent
   {
-    const auto xr = std::minmax_element(m->x.begin(), m->x.end());
-    const auto yr = std::minmax_element(m->y.begin(), m->y.end());
-    const double lx = m->px > 0.0 ? m->px : *xr.second - *xr.first;
-    const double ly = m->py > 0.0 ? m->py : *yr.second - *yr.first;
+    const double lx = m->px > 0.0 ? m->px : all.x1 - all.x0;
+    const double ly = m->py > 0.0 ? m->py : all.y1 - all.y0;
     m->Ldom = std::max(lx, ly);
   }
   const size_t nmesh = m->voff.size() - 1;
@@ -1002,9 +1092,10 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   rd::D4 *W0, *W1, *D;
   int *cur, *flag;
   double *dt, *vr;
+  m->staging = true;
   if ((st = dalloc(m, &W0, nv)) || (st = dalloc(m, &W1, nv)) || (st = dalloc(m, &D, nv)) ||
-      (st = upload(m, &cur, std::vector<int>{0, 0})) || (st = upload(m, &m->done, std::vector<unsigned>{0})) || (st = dalloc(m, &m->bad, 1)) || (st = upload(m, &flag, std::vector<int>(nmesh, 0))) ||
-      (st = dalloc(m, &dt, nmesh)) || (st = upload(m, &vr, vr0)) || (st = dalloc(m, &m->scratch, 4 * nv)))
+      (st = upload(m, &cur, std::vector<int>{0, 0})) || (st = upload(m, &m->done, std::vector<unsigned>{0})) ||
+      (st = dalloc(m, &m->bad, 1)) || (st = upload(m, &flag, std::vector<int>(nmesh, 0))) || (st = dalloc(m, &dt, nmesh)) || (st = upload(m, &vr, vr0)) || (st = dalloc(m, &m->scratch, 4 * nv)))
     return st;
   p.W[0] = W0;
   p.W[1] = W1;
@@ -1013,7 +1104,7 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   p.flag = d.flag = flag;
   p.dt = d.dt = dt;
   p.vr = d.vr = vr;
-  if ((st = build_view(m)) != RD_OK) return st;
+  if ((st = build_view(m, pool)) != RD_OK) return st;
   rd::D4 *W, *Ws, *Z, *C, *kN, *kT, *wcn, *wcs;
   if ((st = dalloc(m, &W, nv)) || (st = dalloc(m, &Ws, nv)) || (st = dalloc(m, &Z, nv)) ||
       (st = dalloc(m, &C, d.ns)) || (st = dalloc(m, &kN, 2 * nt)) || (st = dalloc(m, &kT, nt)) ||
@@ -1027,7 +1118,9 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   d.keepT = kT;
   d.WCn = wcn;
   d.WCs = wcs;
-  if ((st = build_patches(m)) != RD_OK) return st;
+  if ((st = build_patches(m, pool)) != RD_OK || (st = flush_stage(m)) != RD_OK) return st;
+  m->staging = false;
+  rd::UVec<char>().swap(m->stage);
   hipError_t e = hipMemset(W0, 0, sizeof(rd::D4) * nv);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) return fail(RD_EDEVICE, std::string("initialising buffers: ") + hipGetErrorString(e));
@@ -1954,12 +2047,12 @@ struct DlBuffers {
 // Corner and neighbour tables [3][nt] of nt triangles (tri: [nt][3]): the
 // triangle across an edge is the other one at its first vertex that has the
 // second.
-rd_status dl_tables(int64_t nt, const int32_t* tri, const HostGeom& geo, rd::UVec<int32_t>& tsoa,
+rd_status dl_tables(int64_t nt, const int32_t* tri, const HostGeom& geo, rd::Workers& pool, rd::UVec<int32_t>& tsoa,
                     rd::UVec<int32_t>& nbr) {
   tsoa.resize(3 * nt);
   nbr.resize(3 * nt);
   std::atomic<bool> many{false};
-  parallel_for(nt, [&](int64_t t) {
+  pool.each(nt, [&](int64_t t) {
     for (int i = 0; i < 3; ++i) {
       const int32_t b = tri[3 * t + (i + 1) % 3], c = tri[3 * t + (i + 2) % 3];
       int32_t u = -1;
@@ -1972,7 +2065,7 @@ rd_status dl_tables(int64_t nt, const int32_t* tri, const HostGeom& geo, rd::UVe
       tsoa[i * nt + t] = tri[3 * t + i];
       nbr[i * nt + t] = u;
     }
-  }, 20000);
+  });
   return many ? fail(RD_EINVAL, "an edge belongs to more than two triangles") : RD_OK;
 }
 
@@ -2069,11 +2162,12 @@ static rd_status delaunay_flip(int64_t n_vertices, const double* x, const double
   desc.period_y = period_y;
   desc.gamma = 1.4;  // not used; the check requires a valid value
   HostGeom geo;
-  rd_status st = check_desc(&desc, &geo);
+  rd::Workers pool(workers_for(n_triangles));
+  rd_status st = check_desc(&desc, &geo, pool);
   if (st != RD_OK) return st;
   const int64_t nt = n_triangles, nv = n_vertices;
   rd::UVec<int32_t> nbr, tsoa;
-  if ((st = dl_tables(nt, tri, geo, tsoa, nbr)) != RD_OK) return st;
+  if ((st = dl_tables(nt, tri, geo, pool, tsoa, nbr)) != RD_OK) return st;
   DlBuffers b;
   StreamGuard g;  // declared after the buffers: the stream is drained before they are freed
   rd::dl::Mesh m;
@@ -2146,13 +2240,14 @@ static rd_status delaunay_refine(int64_t* n_vertices, double* x, double* y, int6
   desc.period_y = period_y;
   desc.gamma = 1.4;  // not used; the check requires a valid value
   HostGeom geo;
-  rd_status st = check_desc(&desc, &geo);
+  rd::Workers pool(workers_for(nt0));
+  rd_status st = check_desc(&desc, &geo, pool);
   if (st != RD_OK) return st;
   for (int64_t v = 0; v < nv0; ++v)
     if ((period_x > 0.0 && !(x[v] >= 0.0 && x[v] < period_x)) || (period_y > 0.0 && !(y[v] >= 0.0 && y[v] < period_y)))
       return fail(RD_EINVAL, "a coordinate on a periodic axis is outside [0, period)");
   rd::UVec<int32_t> nbr, tsoa;
-  if ((st = dl_tables(nt0, tri, geo, tsoa, nbr)) != RD_OK) return st;
+  if ((st = dl_tables(nt0, tri, geo, pool, tsoa, nbr)) != RD_OK) return st;
   for (int64_t t = 0; t < nt0; ++t)
     for (int i = 0; i < 3; ++i) {
       if (nbr[i * nt0 + t] >= 0) continue;

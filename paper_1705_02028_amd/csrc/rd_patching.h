@@ -13,11 +13,13 @@
 #pragma once
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstdint>
-#include <new>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <string>
 #include <thread>
@@ -43,11 +45,13 @@ struct NoInit : std::allocator<T> {
 template <class T>
 using UVec = std::vector<T, NoInit<T>>;
 
+class Workers;
+
 struct PatchPlan {
   int32_t npatch = 0;
   int32_t max_tri = 0;                 // triangles of the largest patch
   int32_t max_lv = 0, max_slots = 0;   // local vertices and part slots of the largest patches
-  UVec<int32_t> order;                 // [nv] internal vertex -> caller's vertex
+  UVec<int32_t> order, inv;            // [nv] internal vertex -> caller's vertex, and back
   std::vector<int32_t> vbeg;           // [npatch + 1] owned internal vertices of each patch
   std::vector<int32_t> hbeg, halo;     // halo (internal ids) of each patch, ascending
   std::vector<int32_t> tbeg;           // [npatch + 1] patch triangles
@@ -73,6 +77,7 @@ struct PatchInput {
   int32_t max_tri = 512;  // a patch with more triangles is cut again (one vertex at least)
   int32_t own = 0;        // wanted owned vertices per patch
   int threads = 1;
+  Workers* workers = nullptr;  // these instead, where given
 };
 
 // f(q) for q = 0 .. w - 1, each on a thread of its own where one can be
@@ -101,16 +106,117 @@ void run_workers(int w, const F& f) {
   if (failed) throw std::bad_alloc();
 }
 
+// A few threads that run one function after another: f(q) for q = 0 .. size() -
+// 1, the caller's thread among them. They are started by the first run and
+// live as long as the object (starting eight costs about as much as building
+// the plan of a small mesh); between runs that follow each other at once they
+// spin, then sleep. One run at a time, none from within another.
+class Workers {
+ public:
+  explicit Workers(int n) : n_(std::max(1, n)) {}
+  Workers(const Workers&) = delete;
+  Workers& operator=(const Workers&) = delete;
+  ~Workers() {
+    if (t_.empty()) return;
+    {
+      std::lock_guard<std::mutex> g(m_);
+      stop_ = true;
+      gen_.fetch_add(1);
+    }
+    cv_.notify_all();
+    for (auto& x : t_) x.join();
+  }
+  int size() const { return n_; }
+
+  // What a worker throws (memory) is thrown again here.
+  template <class F>
+  void run(const F& f) {
+    if (n_ == 1) {
+      f(0);
+      return;
+    }
+    start();
+    failed_ = false;
+    arg_ = &f;
+    call_ = [](const void* p, int q) { (*static_cast<const F*>(p))(q); };
+    left_.store((int)t_.size());
+    {
+      std::lock_guard<std::mutex> g(m_);
+      gen_.fetch_add(1);
+    }
+    cv_.notify_all();
+    one(0);
+    for (int q = (int)t_.size() + 1; q < n_; ++q) one(q);  // threads that could not be had
+    for (int k = 0; left_.load() > 0; ++k)
+      if (k > kSpin) std::this_thread::yield();
+    if (failed_) throw std::bad_alloc();
+  }
+
+  // f(i) for i = 0 .. n - 1, in equal shares
+  template <class F>
+  void each(int64_t n, const F& f) {
+    run([&](int q) {
+      for (int64_t i = n * q / n_; i < n * (q + 1) / n_; ++i) f(i);
+    });
+  }
+
+ private:
+  static constexpr int kSpin = 2000;
+  const int n_;
+  std::vector<std::thread> t_;
+  std::mutex m_;
+  std::condition_variable cv_;
+  std::atomic<uint32_t> gen_{0};
+  std::atomic<int> left_{0};
+  std::atomic<bool> failed_{false};
+  bool stop_ = false, started_ = false;
+  const void* arg_ = nullptr;
+  void (*call_)(const void*, int) = nullptr;
+
+  void one(int q) {
+    try {
+      call_(arg_, q);
+    } catch (...) {
+      failed_ = true;
+    }
+  }
+  void start() {
+    if (started_) return;
+    started_ = true;
+    t_.reserve(n_ - 1);
+    for (int q = 1; q < n_; ++q) {
+      try {
+        t_.emplace_back([this, q] { loop(q); });
+      } catch (...) {
+        break;
+      }
+    }
+  }
+  void loop(int q) {
+    for (uint32_t seen = 0;;) {
+      for (int k = 0; k < kSpin && gen_.load() == seen; ++k) std::this_thread::yield();
+      if (gen_.load() == seen) {
+        std::unique_lock<std::mutex> g(m_);
+        cv_.wait(g, [&] { return gen_.load() != seen; });
+      }
+      seen = gen_.load();
+      if (stop_) return;
+      one(q);
+      left_.fetch_sub(1);
+    }
+  }
+};
+
 class PatchBuilder {
  public:
-  PatchBuilder(const PatchInput& in, PatchPlan& P) : in_(in), P_(P) {}
+  PatchBuilder(const PatchInput& in, PatchPlan& P) : in_(in), P_(P), own_(in.threads), w_(in.workers ? *in.workers : own_) {}
 
   std::string build() {
     const size_t nmesh = in_.voff->size() - 1;
     P_ = PatchPlan();
     P_.order.resize(in_.nv);
     pts_.resize(in_.nv);
-    parallel(in_.nv, [&](int64_t i) { pts_[i] = Point{in_.x[i], in_.y[i], (int32_t)i}; });
+    swap_.resize(in_.nv);
     // groups: per mesh a list of group bounds, found by bisection in parallel
     std::vector<int64_t> cuts;  // group starts
     std::vector<int32_t> mesh_groups(nmesh + 1, 0);
@@ -121,44 +227,35 @@ class PatchBuilder {
     const int64_t ngroups = mesh_groups[nmesh];
     cuts.assign(ngroups + 1, in_.nv);
     if (nmesh == 1) {
-      if (in_.threads > 1) swap_.resize(in_.nv);
-      bisect(0, in_.nv, 0, ngroups, cuts, in_.threads);
-      UVec<Point>().swap(swap_);
+      points(0, in_.nv, w_.size() > 1);
+      bisect_all(ngroups, cuts);
     } else {
-      parallel((int64_t)nmesh, [&](int64_t k) {
-        bisect((*in_.voff)[k], (*in_.voff)[k + 1], mesh_groups[k], mesh_groups[k + 1], cuts, 1);
+      tasks((int64_t)nmesh, [&](int64_t k) {
+        points((*in_.voff)[k], (*in_.voff)[k + 1], false);
+        bisect((*in_.voff)[k], (*in_.voff)[k + 1], mesh_groups[k], mesh_groups[k + 1], cuts);
       });
     }
-    // groups whose triangles exceed the limit are cut again; every piece is ordered by degree and caller's id
-    gof_.resize(in_.nv);
-    parallel(ngroups, [&](int64_t g) {
-      for (int64_t i = cuts[g]; i < cuts[g + 1]; ++i) gof_[pts_[i].id] = (int32_t)g;
+    // triangles of every group, counted in the order of the triangles; groups
+    // with more than the limit are cut again
+    where_.resize(in_.nv);
+    w_.each(ngroups, [&](int64_t g) {
+      for (int64_t i = cuts[g]; i < cuts[g + 1]; ++i) where_[pts_[i].id].patch = (int32_t)g;
     });
+    count_triangles(ngroups);
     std::vector<std::vector<int64_t>> pieces(ngroups);
-    std::vector<std::vector<int32_t>> tris(ngroups);  // of the groups left whole
-    parallel(ngroups, [&](int64_t g) {
-      group_triangles((int32_t)g, cuts[g], cuts[g + 1], tris[g]);
-      if ((int64_t)tris[g].size() <= in_.max_tri || cuts[g + 1] - cuts[g] == 1) {
+    std::atomic<bool> split{false};
+    tasks(ngroups, [&](int64_t g) {
+      if (total(g) <= in_.max_tri || cuts[g + 1] - cuts[g] == 1) {
         pieces[g] = {cuts[g]};
       } else {
         pieces[g] = split_to_fit(cuts[g], cuts[g + 1]);
-        tris[g].clear();
-      }
-      for (int64_t i = cuts[g]; i < cuts[g + 1]; ++i) P_.order[i] = pts_[i].id;
-      for (size_t q = 0; q < pieces[g].size(); ++q) {
-        const int64_t b = pieces[g][q], e = q + 1 < pieces[g].size() ? pieces[g][q + 1] : cuts[g + 1];
-        std::sort(P_.order.begin() + b, P_.order.begin() + e, [&](int32_t p, int32_t r) {
-          const int32_t dp = in_.row[p + 1] - in_.row[p], dr = in_.row[r + 1] - in_.row[r];
-          return dp > dr || (dp == dr && p < r);
-        });
+        if (pieces[g].size() > 1) split = true;
       }
     });
     P_.mbeg.push_back(0);
     for (size_t k = 0; k < nmesh; ++k) {
       for (int32_t g = mesh_groups[k]; g < mesh_groups[k + 1]; ++g)
         for (int64_t b : pieces[g]) {
-          tris_.emplace_back();
-          if (pieces[g].size() == 1) tris_.back().swap(tris[g]);
           P_.vbeg.push_back((int32_t)b);
           P_.pmesh.push_back((int32_t)k);
         }
@@ -166,43 +263,116 @@ class PatchBuilder {
     }
     P_.npatch = (int32_t)P_.vbeg.size();
     P_.vbeg.push_back((int32_t)in_.nv);
+    // every patch by descending degree, then the caller's id
+    P_.deg.resize(in_.nv);
+    w_.run([&](int q) {
+      std::vector<uint64_t> key;
+      for (int64_t k = share(P_.npatch, q); k < share(P_.npatch, q + 1); ++k) {
+        const int32_t v0 = P_.vbeg[k], v1 = P_.vbeg[k + 1];
+        key.clear();
+        for (int32_t i = v0; i < v1; ++i) {
+          const int32_t v = pts_[i].id;
+          key.push_back((uint64_t)(uint32_t)(INT32_MAX - (in_.row[v + 1] - in_.row[v])) << 32 | (uint32_t)v);
+        }
+        std::sort(key.begin(), key.end());
+        for (int32_t i = v0; i < v1; ++i) {
+          const int32_t v = (int32_t)(uint32_t)key[i - v0];
+          P_.order[i] = v;
+          P_.deg[i] = (uint16_t)(INT32_MAX - (int32_t)(key[i - v0] >> 32));
+          where_[v] = Where{i, (int32_t)k};
+        }
+      }
+    });
     UVec<Point>().swap(pts_);
-    UVec<int32_t>().swap(gof_);
+    UVec<Point>().swap(swap_);
+    if (split) count_triangles(P_.npatch);
     return fill();
   }
 
  private:
   const PatchInput& in_;
   PatchPlan& P_;
+  Workers own_;
+  Workers& w_;
+  // A vertex, its coordinates in units of the longer side of its mesh's box
+  // (single precision is enough to cut by).
   struct Point {
-    double x, y;
+    float x, y;
     int32_t id;
   };
-  UVec<Point> pts_, swap_;  // vertices, partitioned as the order is found; room for parallel cuts
-  std::vector<std::vector<int32_t>> tris_;  // triangles of each patch (empty: still to be found)
-  UVec<int32_t> gof_;       // group of each of the caller's vertices
+  UVec<Point> pts_, swap_;  // vertices, partitioned as the order is found; room for the cuts
+  struct Where {
+    int32_t at, patch;  // internal id; patch (its group, before the patches are final)
+  };
+  UVec<Where> where_;                         // of each of the caller's vertices
+  std::vector<std::vector<int32_t>> counts_;  // [worker][patch] triangles of the worker's share that belong to it
 
+  int64_t share(int64_t n, int q) const { return n * q / w_.size(); }
+
+  // f(i) for i = 0 .. n - 1, each by the next free worker
   template <class F>
-  void parallel(int64_t n, const F& f) {
-    const int w = (int)std::max<int64_t>(1, std::min<int64_t>(in_.threads, n));
-    run_workers(w, [&](int q) {
-      for (int64_t i = n * q / w; i < n * (q + 1) / w; ++i) f(i);
+  void tasks(int64_t n, const F& f) {
+    std::atomic<int64_t> next{0};
+    w_.run([&](int) {
+      for (int64_t i; (i = next.fetch_add(1)) < n;) f(i);
     });
   }
 
-  // Position in [b, e) of the cut that leaves about `want` vertices before
-  // it, pts[b, e) partitioned around it along the longer side; on several
-  // threads by a histogram of the coordinate first.
-  int64_t cut(int64_t b, int64_t e, int64_t want, int64_t lo, int64_t hi, int threads = 1) {
+  // Points of the vertices [b, e) of one mesh.
+  void points(int64_t b, int64_t e, bool parallel) {
     struct Box {
       double x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
     };
-    const int w = threads > 1 && e - b > 100000 ? threads : 1;
-    std::vector<Box> box(w);
-    auto share = [&](int q) { return b + (e - b) * q / w; };
-    run_workers(w, [&](int q) {
+    const int n = parallel ? w_.size() : 1;
+    std::vector<Box> box(n);
+    auto part = [&](int q) { return b + (e - b) * q / n; };
+    auto bounds = [&](int q) {
       Box B;
-      for (int64_t i = share(q); i < share(q + 1); ++i) {
+      for (int64_t i = part(q); i < part(q + 1); ++i) {
+        B.x0 = std::min(B.x0, in_.x[i]);
+        B.x1 = std::max(B.x1, in_.x[i]);
+        B.y0 = std::min(B.y0, in_.y[i]);
+        B.y1 = std::max(B.y1, in_.y[i]);
+      }
+      box[q] = B;
+    };
+    if (parallel) w_.run(bounds);
+    else bounds(0);
+    Box B;
+    for (const Box& o : box) {
+      B.x0 = std::min(B.x0, o.x0);
+      B.x1 = std::max(B.x1, o.x1);
+      B.y0 = std::min(B.y0, o.y0);
+      B.y1 = std::max(B.y1, o.y1);
+    }
+    const double len = std::max(B.x1 - B.x0, B.y1 - B.y0);
+    const double f = len > 1e-300 && len < INFINITY ? 1.0 / len : 0.0;
+    auto put = [&](int q) {
+      for (int64_t i = part(q); i < part(q + 1); ++i)
+        pts_[i] = Point{(float)((in_.x[i] - B.x0) * f), (float)((in_.y[i] - B.y0) * f), (int32_t)i};
+    };
+    if (parallel) w_.run(put);
+    else put(0);
+  }
+
+  // Position in [b, e) of the cut that leaves about `want` vertices before
+  // it, pts[b, e) partitioned around it along the longer side (into the bins of
+  // a histogram below, at and above the cut first); by all workers, or
+  // (parallel: false) the caller.
+  int64_t cut(int64_t b, int64_t e, int64_t want, int64_t lo, int64_t hi, bool parallel = false) {
+    struct Box {
+      float x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
+    };
+    const int w = parallel ? w_.size() : 1;
+    std::vector<Box> box(w);
+    auto part = [&](int q) { return b + (e - b) * q / w; };
+    auto all = [&](const auto& f) {
+      if (parallel) w_.run(f);
+      else f(0);
+    };
+    all([&](int q) {
+      Box B;
+      for (int64_t i = part(q); i < part(q + 1); ++i) {
         B.x0 = std::min(B.x0, pts_[i].x);
         B.x1 = std::max(B.x1, pts_[i].x);
         B.y0 = std::min(B.y0, pts_[i].y);
@@ -222,20 +392,21 @@ class PatchBuilder {
     auto less = [&](const Point& p, const Point& q) { return co(p) < co(q) || (co(p) == co(q) && p.id < q.id); };
     int64_t u = b, v = e;  // the cut lies in [u, v), in place around it
     const int64_t m = b + want;
-    if (w > 1) {
-      constexpr int kBins = 4096;
-      const double c0 = ax ? B.x0 : B.y0, len = (ax ? B.x1 : B.y1) - c0, f = len > 0.0 ? kBins / len : 0.0;
-      auto bin = [&](const Point& p) { return std::min(kBins - 1, (int)((co(p) - c0) * f)); };
-      std::vector<std::vector<int64_t>> count(w);
-      run_workers(w, [&](int q) {
-        count[q].assign(kBins, 0);
-        for (int64_t i = share(q); i < share(q + 1); ++i) ++count[q][bin(pts_[i])];
+    if (e - b > 256) {
+      const int bins = (int)std::min<int64_t>(4096, (e - b) / 16);
+      const float c0 = ax ? B.x0 : B.y0, len = (ax ? B.x1 : B.y1) - c0;
+      const float f = len > 0.0f ? bins / len : 0.0f;
+      auto bin = [&](const Point& p) { return std::min(bins - 1, (int)((co(p) - c0) * f)); };
+      std::vector<int32_t> count((size_t)w * bins, 0);
+      all([&](int q) {
+        int32_t* c = &count[(size_t)q * bins];
+        for (int64_t i = part(q); i < part(q + 1); ++i) ++c[bin(pts_[i])];
       });
       int64_t before = b;
       int at = 0;
       for (;; ++at) {
         int64_t n = 0;
-        for (int q = 0; q < w; ++q) n += count[q][at];
+        for (int q = 0; q < w; ++q) n += count[(size_t)q * bins + at];
         if (before + n > m) {
           u = before;
           v = before + n;
@@ -244,33 +415,31 @@ class PatchBuilder {
         before += n;
       }
       // three runs: bins below, the bin of the cut, bins above
-      std::vector<int64_t> p0(w), p1(w), p2(w);
-      int64_t a0 = b, a1 = u, a2 = v;
+      std::vector<std::array<int64_t, 3>> to(w);
+      int64_t next[3] = {b, u, v};
       for (int q = 0; q < w; ++q) {
-        int64_t below = 0;
-        for (int k = 0; k < at; ++k) below += count[q][k];
-        p0[q] = a0;
-        p1[q] = a1;
-        p2[q] = a2;
-        a0 += below;
-        a1 += count[q][at];
-        a2 += share(q + 1) - share(q) - below - count[q][at];
+        const int32_t* c = &count[(size_t)q * bins];
+        int64_t n[3] = {0, c[at], part(q + 1) - part(q) - c[at]};
+        for (int k = 0; k < at; ++k) n[0] += c[k];
+        n[2] -= n[0];
+        for (int k = 0; k < 3; ++k) {
+          to[q][k] = next[k];
+          next[k] += n[k];
+        }
       }
-      run_workers(w, [&](int q) {
-        int64_t x = p0[q], y = p1[q], z = p2[q];
-        for (int64_t i = share(q); i < share(q + 1); ++i) {
+      all([&](int q) {
+        std::array<int64_t, 3> x = to[q];
+        for (int64_t i = part(q); i < part(q + 1); ++i) {
           const int k = bin(pts_[i]);
-          swap_[k < at ? x++ : (k == at ? y++ : z++)] = pts_[i];
+          swap_[x[(k >= at) + (k > at)]++] = pts_[i];
         }
       });
-      run_workers(w, [&](int q) {
-        std::copy(swap_.begin() + share(q), swap_.begin() + share(q + 1), pts_.begin() + share(q));
-      });
+      all([&](int q) { std::copy(swap_.begin() + part(q), swap_.begin() + part(q + 1), pts_.begin() + part(q)); });
     }
     auto o = pts_.begin();
     std::nth_element(o + u, o + m, o + v, less);
     // the run of vertices with the coordinate of the cut: move the cut to its nearer end
-    const double at = co(pts_[m]);
+    const float at = co(pts_[m]);
     int64_t below = u - b, same = 0;
     for (int64_t i = u; i < v; ++i) {
       below += co(pts_[i]) < at;
@@ -285,44 +454,83 @@ class PatchBuilder {
     return k;
   }
 
-  // Cuts order[b, e) into groups g0 .. g1 - 1; cuts[g] receives their starts.
-  void bisect(int64_t b, int64_t e, int64_t g0, int64_t g1, std::vector<int64_t>& cuts, int threads) {
-    const int64_t n = g1 - g0;
-    if (n == 1) {
+  struct Range {
+    int64_t b, e, g0, g1;  // vertices, groups they are to become
+  };
+  // The cut of a range in two, returned as the first vertex and group of its second part.
+  Range halves(const Range& r, bool parallel) {
+    const int64_t n = r.g1 - r.g0, na = n / 2, nb = n - na;
+    // a snapped cut may move by at most an eighth of the smaller side's vertices
+    const int64_t len = r.e - r.b, want = len * na / n;
+    const int64_t slack = std::min(want, len - want) / 8;
+    const int64_t lo = std::max(na, want - slack), hi = std::min(len - nb, want + slack);
+    const int64_t k = cut(r.b, r.e, std::min(std::max(want, na), len - nb), lo, hi, parallel);
+    return Range{k, r.e, r.g0 + na, r.g1};
+  }
+
+  // Cuts pts[b, e) into groups g0 .. g1 - 1; cuts[g] receives their starts.
+  void bisect(int64_t b, int64_t e, int64_t g0, int64_t g1, std::vector<int64_t>& cuts) {
+    if (g1 - g0 == 1) {
       cuts[g0] = b;
       return;
     }
-    const int64_t na = n / 2, nb = n - na;
-    // a snapped cut may move by at most an eighth of the smaller side's vertices
-    const int64_t len = e - b, want = len * na / n;
-    const int64_t slack = std::min(want, len - want) / 8;
-    const int64_t lo = std::max(na, want - slack), hi = std::min(len - nb, want + slack);
-    const int64_t k = cut(b, e, std::min(std::max(want, na), len - nb), lo, hi, threads);
-    run_workers(threads > 1 ? 2 : 1, [&](int q) {
-      if (threads > 1) {
-        if (q == 0) bisect(b, k, g0, g0 + na, cuts, threads / 2);
-        else bisect(k, e, g0 + na, g1, cuts, threads - threads / 2);
-      } else {
-        bisect(b, k, g0, g0 + na, cuts, 1);
-        bisect(k, e, g0 + na, g1, cuts, 1);
-      }
-    });
+    const Range s = halves(Range{b, e, g0, g1}, false);
+    bisect(b, s.b, g0, s.g0, cuts);
+    bisect(s.b, e, s.g0, g1, cuts);
   }
 
-  // Triangles of a whole group: each taken at its corner of least id in it.
-  void group_triangles(int32_t g, int64_t b, int64_t e, std::vector<int32_t>& T) const {
-    T.reserve(2 * (e - b) + 2 * in_.own / 7 + 16);
-    for (int64_t i = b; i < e; ++i) {
-      const int32_t v = pts_[i].id;
-      for (int32_t j = in_.row[v]; j < in_.row[v + 1]; ++j) {
-        const int32_t t = in_.slot[j] / 3;
-        const int32_t* c = in_.tri + 3 * (int64_t)t;
-        bool first = true;
-        for (int q = 0; q < 3; ++q) first = first && !(c[q] < v && gof_[c[q]] == g);
-        if (first) T.push_back(t);
-      }
+  // The same for one mesh: the largest ranges cut by all workers together, then
+  // each range by whichever worker is free.
+  void bisect_all(int64_t ngroups, std::vector<int64_t>& cuts) {
+    std::vector<Range> todo{{0, in_.nv, 0, ngroups}};
+    auto take = [&](Range& r, bool parallel) {  // r keeps its first part
+      const Range s = halves(r, parallel);
+      r.e = s.b;
+      r.g1 = s.g0;
+      return s;
+    };
+    for (size_t k = 0; w_.size() > 1 && k < todo.size();) {
+      if (todo[k].e - todo[k].b < 50000 || todo[k].g1 - todo[k].g0 == 1) ++k;
+      else todo.push_back(take(todo[k], true));
     }
-    std::sort(T.begin(), T.end());
+    std::mutex m;
+    int busy = 0;  // workers that may still add ranges
+    bool failed = false;
+    auto work = [&] {
+      for (bool mine = false;;) {
+        Range r{0, 0, 0, 0};
+        {
+          std::lock_guard<std::mutex> g(m);
+          busy -= mine;
+          mine = !todo.empty();
+          if (mine) {
+            r = todo.back();
+            todo.pop_back();
+            ++busy;
+          }
+          if (failed || (!mine && busy == 0)) return;
+        }
+        if (!mine) {
+          std::this_thread::yield();
+          continue;
+        }
+        while (w_.size() > 1 && r.e - r.b > 4000 && r.g1 - r.g0 > 1) {
+          const Range s = take(r, false);
+          std::lock_guard<std::mutex> g(m);
+          todo.push_back(s);
+        }
+        bisect(r.b, r.e, r.g0, r.g1, cuts);
+      }
+    };
+    w_.run([&](int) {
+      try {
+        work();
+      } catch (...) {  // out of memory: nobody waits for this worker's ranges
+        std::lock_guard<std::mutex> g(m);
+        failed = true;
+        throw;
+      }
+    });
   }
 
   std::vector<int64_t> split_to_fit(int64_t b, int64_t e) {
@@ -339,106 +547,171 @@ class PatchBuilder {
     return out;
   }
 
+  // Calls f(k) for every patch k that triangle t belongs to.
+  template <class F>
+  void patches_of(const Where a[3], const F& f) const {
+    f(a[0].patch);
+    if (a[1].patch != a[0].patch) f(a[1].patch);
+    if (a[2].patch != a[0].patch && a[2].patch != a[1].patch) f(a[2].patch);
+  }
+  void corners_of(int64_t t, Where a[3]) const {
+    for (int c = 0; c < 3; ++c) a[c] = where_[in_.tri[3 * t + c]];
+  }
+
+  void count_triangles(int64_t n) {
+    counts_.resize(w_.size());
+    w_.run([&](int q) {
+      std::vector<int32_t>& c = counts_[q];
+      c.assign(n, 0);
+      Where a[3];
+      for (int64_t t = share(in_.nt, q); t < share(in_.nt, q + 1); ++t) {
+        corners_of(t, a);
+        patches_of(a, [&](int32_t k) { ++c[k]; });
+      }
+    });
+  }
+  int64_t total(int64_t k) const {
+    int64_t n = 0;
+    for (const auto& c : counts_) n += c[k];
+    return n;
+  }
+
   // Triangles, halo and part slots of every patch.
   std::string fill() {
     const int32_t np = P_.npatch;
-    UVec<int32_t> inv(in_.nv);
-    parallel(in_.threads, [&](int64_t q) {
-      for (int64_t i = in_.nv * q / in_.threads; i < in_.nv * (q + 1) / in_.threads; ++i) inv[P_.order[i]] = (int32_t)i;
-    });
-    UVec<int32_t> pof(in_.nv);  // patch of each internal vertex
-    parallel(np, [&](int64_t k) {
-      for (int32_t i = P_.vbeg[k]; i < P_.vbeg[k + 1]; ++i) pof[i] = (int32_t)k;
-    });
-    // counts, then contents: a triangle is taken at its first owned corner
+    P_.inv.resize(in_.nv);
+    w_.each(in_.nv, [&](int64_t v) { P_.inv[v] = where_[v].at; });
+    // each worker's triangles go to every patch behind those of the workers
+    // before it, so a patch's are ascending
     P_.tbeg.assign(np + 1, 0);
-    P_.hbeg.assign(np + 1, 0);
-    P_.deg.resize(in_.nv);
-    std::vector<std::vector<int32_t>>&tris = tris_, halos(np);
-    std::vector<int32_t> slots(np);
-    parallel(np, [&](int64_t k) {
-      std::vector<int32_t>&T = tris[k], &H = halos[k];
-      const int32_t v0 = P_.vbeg[k], v1 = P_.vbeg[k + 1];
-      int32_t s = 0;
-      const bool known = !T.empty();
-      for (int32_t i = v0; i < v1; ++i) {
-        const int32_t v = P_.order[i];
-        P_.deg[i] = (uint16_t)(in_.row[v + 1] - in_.row[v]);
-        s += in_.row[v + 1] - in_.row[v];
-        if (!known)
-          for (int32_t j = in_.row[v]; j < in_.row[v + 1]; ++j) T.push_back(in_.slot[j] / 3);
-      }
-      if (!known) {
-        std::sort(T.begin(), T.end());
-        T.erase(std::unique(T.begin(), T.end()), T.end());
-      }
-      for (int32_t t : T)
-        for (int c = 0; c < 3; ++c) {
-          const int32_t w = inv[in_.tri[3 * (int64_t)t + c]];
-          if (w < v0 || w >= v1) H.push_back(w);
-        }
-      slots[k] = s;
-      std::sort(H.begin(), H.end());
-      H.erase(std::unique(H.begin(), H.end()), H.end());
-    });
-    int64_t nt = 0, nh = 0;
+    int64_t nt = 0;
     for (int32_t k = 0; k < np; ++k) {
-      nt += (int64_t)tris[k].size();
-      nh += (int64_t)halos[k].size();
-      if (nt >= (int64_t(1) << 31) || nh >= (int64_t(1) << 31)) return "too many patch triangles";
-      const int32_t lv = P_.vbeg[k + 1] - P_.vbeg[k] + (int32_t)halos[k].size();
-      if (lv >= 65535 || slots[k] >= 65535) return "a patch has too many vertices";
-      P_.tbeg[k + 1] = (int32_t)nt;
-      P_.hbeg[k + 1] = (int32_t)nh;
-      P_.max_tri = std::max(P_.max_tri, (int32_t)tris[k].size());
-      P_.max_lv = std::max(P_.max_lv, lv);
-      P_.max_slots = std::max(P_.max_slots, slots[k]);
-    }
-    P_.jbeg.assign(np + 1, 0);
-    for (int32_t k = 0; k < np; ++k) {  // the first owned vertex has the largest degree
-      int32_t base = 0;
-      int32_t n = P_.vbeg[k + 1] - P_.vbeg[k];
-      for (int32_t j = 0; j < P_.deg[P_.vbeg[k]]; ++j) {
-        while (n > 0 && P_.deg[P_.vbeg[k] + n - 1] <= j) --n;
-        P_.jb.push_back(base);
-        base += n;
+      P_.tbeg[k] = (int32_t)nt;
+      for (auto& c : counts_) {
+        const int32_t n = c[k];
+        c[k] = (int32_t)nt;  // now where its first one goes
+        nt += n;
       }
-      P_.jbeg[k + 1] = (int32_t)P_.jb.size();
+      if (nt >= (int64_t(1) << 31)) return "too many patch triangles";
+      P_.max_tri = std::max(P_.max_tri, (int32_t)(nt - P_.tbeg[k]));
     }
+    P_.tbeg[np] = (int32_t)nt;
     P_.tri.resize(3 * nt);
     P_.tid.resize(nt);
-    P_.seam.assign(np, 0);
-    P_.halo.resize(nh);
-    parallel(np, [&](int64_t k) {
-      const std::vector<int32_t>&T = tris[k], &H = halos[k];
-      const int32_t v0 = P_.vbeg[k], v1 = P_.vbeg[k + 1], own = v1 - v0;
-      std::copy(H.begin(), H.end(), P_.halo.begin() + P_.hbeg[k]);
-      const int32_t* jb = P_.jb.data() + P_.jbeg[k];
-      std::vector<uint16_t> next(own, 0);  // triangles are ascending: ranks in order of appearance
-      for (size_t j = 0; j < T.size(); ++j) {
-        const int64_t at = P_.tbeg[k] + (int64_t)j;
-        int32_t owner = INT32_MAX;
-        for (int c = 0; c < 3; ++c) {
-          const int32_t w = inv[in_.tri[3 * (int64_t)T[j] + c]];
-          owner = std::min(owner, pof[w]);
-          uint16_t lv, dst;
-          if (w >= v0 && w < v1) {
-            lv = (uint16_t)(w - v0);
-            dst = (uint16_t)(jb[next[w - v0]++] + lv);
-          } else {
-            lv = (uint16_t)(own + (std::lower_bound(H.begin(), H.end(), w) - H.begin()));
-            dst = 0xffff;
-          }
-          P_.tri[c * nt + at] = lv | (uint32_t)dst << 16;
-        }
-        P_.tid[at] = owner == k ? T[j] : -1 - T[j];
-        const int32_t* c = in_.tri + 3 * (int64_t)T[j];
-        for (int i = 1; i < 3; ++i)
-          if (std::fabs(in_.x[c[i]] - in_.x[c[0]]) > in_.hpx || std::fabs(in_.y[c[i]] - in_.y[c[0]]) > in_.hpy)
-            P_.seam[k] = 1;
+    w_.run([&](int q) {
+      std::vector<int32_t>& next = counts_[q];
+      Where a[3];
+      for (int64_t t = share(in_.nt, q); t < share(in_.nt, q + 1); ++t) {
+        corners_of(t, a);
+        const int32_t owner = std::min(a[0].patch, std::min(a[1].patch, a[2].patch));
+        patches_of(a, [&](int32_t k) {
+          const int64_t at = next[k]++;
+          P_.tid[at] = (int32_t)(owner == k ? t : -1 - t);
+          for (int c = 0; c < 3; ++c) P_.tri[c * nt + at] = (uint32_t)a[c].at;  // internal id for now
+        });
       }
-      std::vector<int32_t>().swap(tris[k]);
     });
+    UVec<Where>().swap(where_);
+    counts_.clear();
+    // patch by patch: halo, part slots, local ids
+    P_.hbeg.assign(np + 1, 0);
+    P_.jbeg.assign(np + 1, 0);
+    P_.seam.assign(np, 0);
+    struct Part {
+      std::vector<int32_t> halo, jb;
+      int32_t max_lv = 0, max_slots = 0;
+      bool large = false;
+    };
+    std::vector<Part> part(w_.size());
+    const bool periodic = in_.hpx < INFINITY || in_.hpy < INFINITY;
+    w_.run([&](int q) {
+      Part& o = part[q];
+      UVec<int32_t> loc(in_.nv);  // of a vertex met in this patch its place in H; checked there, so never cleared
+      std::vector<int32_t> H;
+      std::vector<uint16_t> next;
+      std::vector<double> x, y;
+      for (int64_t k = share(np, q); k < share(np, q + 1); ++k) {
+        const int32_t v0 = P_.vbeg[k], v1 = P_.vbeg[k + 1], own = v1 - v0;
+        const int64_t t0 = P_.tbeg[k], t1 = P_.tbeg[k + 1];
+        H.clear();
+        for (int c = 0; c < 3; ++c)
+          for (int64_t at = t0; at < t1; ++at) {
+            const int32_t w = (int32_t)P_.tri[c * nt + at];
+            if (w >= v0 && w < v1) continue;
+            const uint32_t l = (uint32_t)loc[w];
+            if (l < H.size() && H[l] == w) continue;
+            loc[w] = (int32_t)H.size();
+            H.push_back(w);
+          }
+        std::sort(H.begin(), H.end());
+        for (size_t i = 0; i < H.size(); ++i) loc[H[i]] = (int32_t)i;
+        // part slots: the first owned vertex has the largest degree
+        const size_t j0 = o.jb.size();
+        int32_t slots = 0;
+        for (int32_t j = 0, n = own; j < P_.deg[v0]; ++j) {
+          while (n > 0 && P_.deg[v0 + n - 1] <= j) --n;
+          o.jb.push_back(slots);
+          slots += n;
+        }
+        P_.jbeg[k + 1] = (int32_t)(o.jb.size() - j0);
+        P_.hbeg[k + 1] = (int32_t)H.size();
+        o.halo.insert(o.halo.end(), H.begin(), H.end());
+        const int64_t lv = own + (int64_t)H.size();
+        if (lv >= 65535 || slots >= 65535) {
+          o.large = true;
+          return;
+        }
+        o.max_lv = std::max(o.max_lv, (int32_t)lv);
+        o.max_slots = std::max(o.max_slots, slots);
+        if (periodic) {
+          x.resize(lv);
+          y.resize(lv);
+          for (int64_t l = 0; l < lv; ++l) {
+            const int32_t v = P_.order[l < own ? v0 + l : H[l - own]];
+            x[l] = in_.x[v];
+            y[l] = in_.y[v];
+          }
+        }
+        next.assign(own, 0);  // triangles are ascending: ranks in order of appearance
+        for (int64_t at = t0; at < t1; ++at) {
+          int32_t l[3];
+          for (int c = 0; c < 3; ++c) {
+            uint32_t& p = P_.tri[c * nt + at];
+            const int32_t w = (int32_t)p;
+            uint32_t dst = 0xffff;
+            if (w >= v0 && w < v1) {
+              l[c] = w - v0;
+              dst = (uint32_t)(o.jb[j0 + next[l[c]]++] + l[c]);
+            } else {
+              l[c] = own + loc[w];
+            }
+            p = (uint32_t)l[c] | dst << 16;
+          }
+          if (periodic)
+            for (int i = 1; i < 3; ++i)
+              if (std::fabs(x[l[i]] - x[l[0]]) > in_.hpx || std::fabs(y[l[i]] - y[l[0]]) > in_.hpy) P_.seam[k] = 1;
+        }
+      }
+    });
+    int64_t nh = 0, nj = 0;
+    for (const Part& o : part) {
+      if (o.large) return "a patch has too many vertices";
+      nh += (int64_t)o.halo.size();
+      nj += (int64_t)o.jb.size();
+      P_.max_lv = std::max(P_.max_lv, o.max_lv);
+      P_.max_slots = std::max(P_.max_slots, o.max_slots);
+    }
+    if (nh >= (int64_t(1) << 31) || nj >= (int64_t(1) << 31)) return "too many patch triangles";
+    P_.halo.reserve(nh);
+    P_.jb.reserve(nj);
+    for (const Part& o : part) {
+      P_.halo.insert(P_.halo.end(), o.halo.begin(), o.halo.end());
+      P_.jb.insert(P_.jb.end(), o.jb.begin(), o.jb.end());
+    }
+    for (int32_t k = 0; k < np; ++k) {
+      P_.hbeg[k + 1] += P_.hbeg[k];
+      P_.jbeg[k + 1] += P_.jbeg[k];
+    }
     return std::string();
   }
 };
