@@ -246,9 +246,8 @@ struct rd_mesh {
   rd::Patches p;             // the step's view, vertices in internal order (patch by patch)
   rd::Dev d;                 // the second view (the caller's order): residual, adjoint
   rd::CflPlan cfl;           // its vertex reductions
-  // the FP32 step: buffers allocated on first use, and its tiles
+  // the FP32 step (its state is d.W): buffers allocated on first use, and its tiles
   rd::Dev32 d32;
-  rd::D4* W32 = nullptr;     // its state
   rd::Tiles tiles;
   std::vector<void*> tile_allocs;
   // Where the state is by the host's account: in the FP32 form after FP32
@@ -298,7 +297,6 @@ struct rd_mesh {
   int32_t max_mesh_patches = 0;     // patches of the mesh (of a batch: the member) that has most
   int64_t tile_info[4] = {0, 0, 0, 0};
   const int32_t* inv = nullptr;     // [nv] device: internal vertex of each of the caller's
-  int version = 0;                  // counts the changes of what state_of() gives (a batch holds it)
   std::vector<int64_t> voff, toff;  // vertex / triangle ranges of the meshes laid end to end
 };
 
@@ -460,18 +458,12 @@ rd_status run_steps(rd_mesh* m, int n, int scheme, int time, int fp32, double cf
   return RD_OK;
 }
 
-rd::Dev view32(const rd_mesh* m) {
-  rd::Dev d = m->d;
-  d.W = m->W32;
-  return d;
-}
-
 // The tiled form of the FP32 step: the tile pass finishes interior vertices
 // (stage 1: their residual R1 and CFL bound; stage 2: their new state), the
 // shared pass the rest. Stage 1 stores R1 only; W* is rebuilt from it where
 // needed, after dt is known.
 rd_status run_step32_tiled(rd_mesh* m, int scheme, int time, double cfl, double dt, hipEvent_t* ev) {
-  const rd::Dev d = view32(m);
+  const rd::Dev d = m->d;
   const rd::Tiles& tl = m->tiles;
   rd::Dev32 h = m->d32;
   h.slump = m->p.slump;
@@ -504,7 +496,7 @@ rd_status run_step32_tiled(rd_mesh* m, int scheme, int time, double cfl, double 
 // The step with FP32 distribution, two passes over the second view.
 rd_status run_step32(rd_mesh* m, int scheme, int time, double cfl, double dt, hipEvent_t* ev) {
   if (m->tiles.ntiles > 0) return run_step32_tiled(m, scheme, time, cfl, dt, ev);
-  const rd::Dev d = view32(m);
+  const rd::Dev d = m->d;
   rd::Dev32 h = m->d32;
   h.slump = m->p.slump;
   hipStream_t s = m->stream;
@@ -535,7 +527,7 @@ rd_status run_step32(rd_mesh* m, int scheme, int time, double cfl, double dt, hi
 }
 
 rd::State state_of(const rd_mesh* m) {
-  return rd::State{{m->p.W[0], m->p.W[1]}, m->p.cur, m->inv, m->W32};
+  return rd::State{{m->p.W[0], m->p.W[1]}, m->p.cur, m->inv, m->d.W};
 }
 
 // The tables of the second view of the mesh and the blocks of its vertex
@@ -740,7 +732,8 @@ rd_status build_tiles(rd_mesh* m, int tt) {
   return RD_OK;
 }
 
-// The FP32 step's buffers, on first use.
+// The FP32 step's own buffers, on first use (its state, signal speeds and CFL
+// terms are the second view's, there from creation).
 rd_status buffers32(rd_mesh* m) {
   rd::Dev32& h = m->d32;
   const int64_t nv = m->d.nv, nt = m->d.nt;
@@ -748,21 +741,13 @@ rd_status buffers32(rd_mesh* m) {
   if (!h.Zf) {
     rd::Dev32 n = h;  // the tiled form's buffers may be there
     rd::F4 *c, *kn, *kt;
-    rd::D4* W;
-    float* lam;
-    double* sig;
     if ((st = dalloc(m, &n.Zf, nv)) || (st = dalloc(m, &n.dW, nv)) || (st = dalloc(m, &kn, 2 * nt)) ||
-        (st = dalloc(m, &kt, nt)) || (st = dalloc(m, &lam, nt)) || (st = dalloc(m, &sig, nv)) ||
-        (st = dalloc(m, &W, nv)) || (st = dalloc(m, &c, m->d.ns)))
+        (st = dalloc(m, &kt, nt)) || (st = dalloc(m, &c, m->d.ns)))
       return st;
     n.C = c;
     n.keepN = kn;
     n.keepT = kt;
-    m->d.lam = lam;
-    m->d.sig = sig;
-    m->W32 = W;
     h = n;
-    ++m->version;
   }
   return RD_OK;
 }
@@ -777,7 +762,7 @@ rd_status enter(rd_mesh* m, int fp32) {
   if (!m->captured && (fp32 != 0) == m->form32) return RD_OK;
   hipStream_t s = m->stream;
   if (fp32) {
-    HIPCHK(rd::launch_enter32(view32(m), m->d32, state_of(m), s));
+    HIPCHK(rd::launch_enter32(m->d, m->d32, state_of(m), s));
     HIPCHK(rd::launch_set_int(m->p.cur, rd::kForm32, s));
   } else {
     HIPCHK(rd::launch_patch_enter(m->p, state_of(m), s));
@@ -1106,11 +1091,14 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   p.vr = d.vr = vr;
   if ((st = build_view(m, pool)) != RD_OK) return st;
   rd::D4 *W, *Ws, *Z, *C, *kN, *kT, *wcn, *wcs;
+  float* lam;
   if ((st = dalloc(m, &W, nv)) || (st = dalloc(m, &Ws, nv)) || (st = dalloc(m, &Z, nv)) ||
+      (st = dalloc(m, &d.sig, nv)) || (st = dalloc(m, &lam, nt)) ||
       (st = dalloc(m, &C, d.ns)) || (st = dalloc(m, &kN, 2 * nt)) || (st = dalloc(m, &kT, nt)) ||
       (st = dalloc(m, &wcn, m->wv.size())) || (st = dalloc(m, &wcs, m->wv.size())))
     return st;
   d.W = W;
+  d.lam = lam;
   d.Ws = Ws;
   d.Z = Z;
   d.C = C;
@@ -1212,7 +1200,7 @@ RD_API rd_status rd_set_state(rd_mesh* m, const double* W, int on_device) {
   }
   // into the form of the last steps
   note_capture(m);
-  if (m->form32) HIPCHK(rd::launch_set32(view32(m), m->d32, m->p.cur, src, bad, s));
+  if (m->form32) HIPCHK(rd::launch_set32(m->d, m->d32, m->p.cur, src, bad, s));
   else HIPCHK(rd::launch_patch_set(m->p, m->inv, src, bad, s));
   if (on_device) return RD_OK;
   // a host state is in place when the call returns
@@ -1641,7 +1629,6 @@ struct rd_batch {
   rd::PatchMember* mem = nullptr;
   int32_t *mb = nullptr, *vb = nullptr;
   int nblocks = 0;
-  std::vector<int> versions;     // of the members' internal orders, as in mem
   hipStream_t stream = nullptr;  // the caller's stream
   hipStream_t own = nullptr;     // the batch's own stream (a null stream cannot be captured)
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
@@ -1746,7 +1733,6 @@ static rd_status batch_create(rd_mesh* const* meshes, int n, void* stream, rd_ba
     }
   std::unique_ptr<rd_batch> owner(new rd_batch());
   rd_batch* b = owner.get();
-  b->versions.assign(n, -1);
   b->members.assign(meshes, meshes + n);
   b->voff = voff;
   b->toff = toff;
@@ -1769,7 +1755,12 @@ static rd_status batch_create(rd_mesh* const* meshes, int n, void* stream, rd_ba
     (void)hipStreamDestroy(own);
     return st;
   }
-  if ((st = dalloc(flat, &b->mem, n)) || (st = upload(flat, &b->mb, mb)) || (st = upload(flat, &b->vb, vb))) {
+  std::vector<rd::PatchMember> mem;
+  for (int k = 0; k < n; ++k) {
+    const rd_mesh* m = meshes[k];
+    mem.push_back(rd::PatchMember{state_of(m), m->p.cur, m->p.flag, (int32_t)m->p.nv, (int32_t)voff[k]});
+  }
+  if ((st = upload(flat, &b->mem, mem)) || (st = upload(flat, &b->mb, mb)) || (st = upload(flat, &b->vb, vb))) {
     rd_mesh_destroy(flat);
     (void)hipEventDestroy(ev_in);
     (void)hipEventDestroy(ev_out);
@@ -1811,18 +1802,6 @@ rd_status batch_begin(rd_batch* b, int fp32, std::vector<hipStream_t>& outer) {
   for (hipStream_t o : outer) {
     HIPCHK(hipEventRecord(b->ev_in, o));
     HIPCHK(hipStreamWaitEvent(s, b->ev_in, 0));
-  }
-  // a member whose state has moved to other buffers since the last run is described anew
-  bool same = true;
-  for (size_t k = 0; k < b->members.size(); ++k) same = same && b->versions[k] == b->members[k]->version;
-  if (!same) {
-    std::vector<rd::PatchMember> mem;
-    for (size_t k = 0; k < b->members.size(); ++k) {
-      const rd_mesh* m = b->members[k];
-      mem.push_back(rd::PatchMember{state_of(m), m->p.cur, m->p.flag, (int32_t)m->p.nv, (int32_t)b->voff[k]});
-      b->versions[k] = m->version;
-    }
-    HIPCHK(rd::launch_put_members(b->mem, mem.data(), (int)mem.size(), s));
   }
   HIPCHK(rd::launch_patch_members(state_of(f), f->p.cur, f->p.flag, f->p.nv, b->mem, b->mb, b->vb, b->nblocks, false,
                                   s));

@@ -501,25 +501,7 @@ __global__ __launch_bounds__(kBlock) void k_patch_members(State st, int* cur, in
   else st.W[0][st.inv[u]] = *q.st.at(v);
 }
 
-constexpr int kPutMembers = 32;  // a launch: 2 KiB of arguments
-struct PutMembers {
-  PatchMember m[kPutMembers];
-};
-__global__ __launch_bounds__(kPutMembers) void k_put_members(PatchMember* dst, PutMembers src, int n) {
-  if ((int)threadIdx.x < n) dst[threadIdx.x] = src.m[threadIdx.x];
-}
-
 // ------------------------------------------------------------- launchers --
-
-hipError_t launch_put_members(PatchMember* dst, const PatchMember* src, int n, hipStream_t s) {
-  for (int i = 0; i < n; i += kPutMembers) {
-    PutMembers c;
-    const int k = n - i < kPutMembers ? n - i : kPutMembers;
-    for (int j = 0; j < k; ++j) c.m[j] = src[i + j];
-    hipLaunchKernelGGL(k_put_members, dim3(1), dim3(kPutMembers), 0, s, dst + i, c, k);
-  }
-  return hipGetLastError();
-}
 
 size_t patch_lds_bytes(const Patches& p, int stage, bool cfl, bool wide) {
   const int32_t lv = p.max_lv + (p.max_lv & 1);

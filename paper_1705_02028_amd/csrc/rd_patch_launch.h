@@ -15,9 +15,6 @@ struct PatchMember {
   int32_t nv, v0;      // vertices; the member's first vertex in the batch (caller's order)
 };
 
-// Descriptions of n members into device memory, by value: nothing is waited for.
-hipError_t launch_put_members(PatchMember* dst, const PatchMember* src, int n, hipStream_t s);
-
 // Dynamic LDS bytes of a patch workgroup.
 size_t patch_lds_bytes(const Patches& p, int stage, bool cfl, bool wide = false);
 // stage 1 (also Euler): p.D and, with cfl, the patch bounds p.pmin; stage 2:
