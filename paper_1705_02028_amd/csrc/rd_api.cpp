@@ -288,7 +288,6 @@ struct rd_mesh {
   // adjoint buffers, allocated on first use
   rd::AdjDev adj;
   rd::D4* adjW = nullptr;     // W^n of the step being reversed
-  double* adjSig = nullptr;   // [nv] signal speeds of the recomputation (the mesh's stay with its state)
   double* adjIn = nullptr;    // [4 nv] host staging: W^n in, then dL/dW^n out
   double* adjOut = nullptr;   // [4 nv] host staging: dL/dW^{n+1} in
   hipEvent_t events[RD_NKERNELS + 1] = {};
@@ -341,6 +340,30 @@ rd_status dalloc(rd_mesh* m, T** p, size_t n, rd_mesh::Slab rd_mesh::*from = &rd
   s.left -= bytes;
   return RD_OK;
 }
+
+// Several buffers of a mesh in one allocation: the runtime keeps about 64 MB of
+// freed blocks, and an allocation that makes it give one of them back takes 250
+// us, so a dozen of a first call's own could take milliseconds.
+class Block {
+ public:
+  template <class T>
+  Block& add(T** p, size_t n) {
+    at_[n_++] = {reinterpret_cast<void**>(p), bytes_};
+    bytes_ += (std::max<size_t>(n, 1) * sizeof(T) + 255) & ~size_t(255);
+    return *this;
+  }
+  rd_status take(rd_mesh* m) {
+    char* q;
+    rd_status st = dalloc(m, &q, bytes_);
+    for (int k = 0; st == RD_OK && k < n_; ++k) *at_[k].first = q + at_[k].second;
+    return st;
+  }
+
+ private:
+  std::pair<void**, size_t> at_[16];
+  int n_ = 0;
+  size_t bytes_ = 0;
+};
 
 template <class T, class A>
 rd_status upload_in(std::vector<void*>& list, T** p, const std::vector<T, A>& h) {
@@ -741,9 +764,8 @@ rd_status buffers32(rd_mesh* m) {
   if (!h.Zf) {
     rd::Dev32 n = h;  // the tiled form's buffers may be there
     rd::F4 *c, *kn, *kt;
-    if ((st = dalloc(m, &n.Zf, nv)) || (st = dalloc(m, &n.dW, nv)) || (st = dalloc(m, &kn, 2 * nt)) ||
-        (st = dalloc(m, &kt, nt)) || (st = dalloc(m, &c, m->d.ns)))
-      return st;
+    st = Block().add(&n.Zf, nv).add(&n.dW, nv).add(&kn, 2 * nt).add(&kt, nt).add(&c, m->d.ns).take(m);
+    if (st != RD_OK) return st;
     n.C = c;
     n.keepN = kn;
     n.keepT = kt;
@@ -1078,9 +1100,9 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   int *cur, *flag;
   double *dt, *vr;
   m->staging = true;
-  if ((st = dalloc(m, &W0, nv)) || (st = dalloc(m, &W1, nv)) || (st = dalloc(m, &D, nv)) ||
+  if ((st = Block().add(&W0, nv).add(&W1, nv).add(&D, nv).add(&m->scratch, 4 * nv).take(m)) ||
       (st = upload(m, &cur, std::vector<int>{0, 0})) || (st = upload(m, &m->done, std::vector<unsigned>{0})) ||
-      (st = dalloc(m, &m->bad, 1)) || (st = upload(m, &flag, std::vector<int>(nmesh, 0))) || (st = dalloc(m, &dt, nmesh)) || (st = upload(m, &vr, vr0)) || (st = dalloc(m, &m->scratch, 4 * nv)))
+      (st = dalloc(m, &m->bad, 1)) || (st = upload(m, &flag, std::vector<int>(nmesh, 0))) || (st = dalloc(m, &dt, nmesh)) || (st = upload(m, &vr, vr0)))
     return st;
   p.W[0] = W0;
   p.W[1] = W1;
@@ -1092,11 +1114,9 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
   if ((st = build_view(m, pool)) != RD_OK) return st;
   rd::D4 *W, *Ws, *Z, *C, *kN, *kT, *wcn, *wcs;
   float* lam;
-  if ((st = dalloc(m, &W, nv)) || (st = dalloc(m, &Ws, nv)) || (st = dalloc(m, &Z, nv)) ||
-      (st = dalloc(m, &d.sig, nv)) || (st = dalloc(m, &lam, nt)) ||
-      (st = dalloc(m, &C, d.ns)) || (st = dalloc(m, &kN, 2 * nt)) || (st = dalloc(m, &kT, nt)) ||
-      (st = dalloc(m, &wcn, m->wv.size())) || (st = dalloc(m, &wcs, m->wv.size())))
-    return st;
+  st = Block().add(&W, nv).add(&Ws, nv).add(&Z, nv).add(&d.sig, nv).add(&lam, nt).add(&C, d.ns).add(&kN, 2 * nt)
+           .add(&kT, nt).add(&wcn, m->wv.size()).add(&wcs, m->wv.size()).take(m);
+  if (st != RD_OK) return st;
   d.W = W;
   d.lam = lam;
   d.Ws = Ws;
@@ -1120,7 +1140,7 @@ rd_status create_mesh(const rd_mesh_desc* desc, hipStream_t stream, const std::v
 // boundary.
 struct NoallocLayout {
   size_t bytes = 0;
-  size_t R2, R1, LamS, LamN, Zn, Wa, Sig, CZ, CZW, KN, KT;
+  size_t R2, R1, LamS, LamN, Zn, Wa, CZ, CZW, KN, KT;
   NoallocLayout(int64_t nv, int64_t nt, int64_t ns) {
     auto take = [&](size_t n) {
       const size_t at = bytes;
@@ -1133,7 +1153,6 @@ struct NoallocLayout {
     LamN = take(sizeof(rd::D4) * nv);
     Zn = take(sizeof(rd::D4) * nv);
     Wa = take(sizeof(rd::D4) * nv);
-    Sig = take(sizeof(double) * nv);
     CZ = take(sizeof(rd::D4) * ns);
     CZW = take(sizeof(rd::ZW) * ns);
     KN = take(sizeof(rd::D4) * 2 * nt);
@@ -1488,14 +1507,13 @@ rd_status adjoint_args(rd_mesh* m, double dt, int scheme, int time) {
 
 // Enqueues the reverse of one step on the mesh's stream, all pointers on the
 // device: the step from W_n is recomputed on the buffers of `a` (W^n copy Wa,
-// signal speeds sig, latches a.flag) and the mesh's stage buffers; the mesh's
-// own state, signal speeds and latch are not touched.
-rd_status adjoint_enqueue(rd_mesh* m, const rd::AdjDev& a, rd::D4* Wa, double* sig, const double* W_n,
-                          double dt, int scheme, int time, const double* lam_np1, double* lam_n) {
+// latches a.flag) and the mesh's stage buffers; the mesh's own state, signal
+// speeds and latch are not touched.
+rd_status adjoint_enqueue(rd_mesh* m, const rd::AdjDev& a, rd::D4* Wa, const double* W_n, double dt, int scheme,
+                          int time, const double* lam_np1, double* lam_n) {
   hipStream_t s = m->stream;
   rd::Dev d = m->d;
   d.W = Wa;
-  d.sig = sig;
   d.flag = a.flag;
   // parameter vectors at W^n go straight to Zn (read by the stage-1 passes and
   // the adjoint); the first-stage vertex pass writes W* and the stage-2
@@ -1532,19 +1550,15 @@ RD_API rd_status rd_adjoint_step(rd_mesh* m, const double* W_n, double dt, int s
     rd::ZW* cZW;
     rd::AdjRec2* r2;
     rd::AdjRec1* r1;
-    double *in, *out, *sig;
+    double *in, *out;
     int* flag;
-    if ((st = dalloc(m, &lamS, nv)) || (st = dalloc(m, &lamN, nv)) || (st = dalloc(m, &r2, nv)) ||
-        (st = dalloc(m, &r1, nv)) ||
-        (st = dalloc(m, &Zn, nv)) || (st = dalloc(m, &cZ, m->d.ns)) || (st = dalloc(m, &cZW, m->d.ns)) ||
-        (st = dalloc(m, &kN, 2 * nt)) || (st = dalloc(m, &kT, nt)) || (st = dalloc(m, &Wa, nv)) ||
-        (st = dalloc(m, &in, 4 * nv)) || (st = dalloc(m, &out, 4 * nv)) || (st = dalloc(m, &sig, nv)) ||
-        (st = dalloc(m, &flag, 2)))
-      return st;
+    st = Block().add(&lamS, nv).add(&lamN, nv).add(&r2, nv).add(&r1, nv).add(&Zn, nv).add(&cZ, m->d.ns)
+             .add(&cZW, m->d.ns).add(&kN, 2 * nt).add(&kT, nt).add(&Wa, nv).add(&in, 4 * nv).add(&out, 4 * nv)
+             .add(&flag, 2).take(m);
+    if (st != RD_OK) return st;
     HIPCHK(rd::launch_set_int(flag, 0, m->stream));
     HIPCHK(rd::launch_set_int(flag + 1, 0, m->stream));
     a.flag = flag;
-    m->adjSig = sig;
     a.lamS = lamS;
     a.lamN = lamN;
     a.r2 = r2;
@@ -1572,7 +1586,7 @@ RD_API rd_status rd_adjoint_step(rd_mesh* m, const double* W_n, double dt, int s
     lsrc = m->adjOut;
   }
   double* out = on_device ? lam_n : m->adjIn;
-  if ((st = adjoint_enqueue(m, m->adj, m->adjW, m->adjSig, src, dt, scheme, time, lsrc, out)) != RD_OK) return st;
+  if ((st = adjoint_enqueue(m, m->adj, m->adjW, src, dt, scheme, time, lsrc, out)) != RD_OK) return st;
   if (!on_device) {
     HIPCHK(hipMemcpyAsync(lam_n, m->adjIn, sizeof(double) * 4 * nv, hipMemcpyDeviceToHost, s));
     return adjoint_status(m);
@@ -1608,7 +1622,7 @@ RD_API rd_status rd_adjoint_step_noalloc(rd_mesh* m, const double* W_n, double d
   a.flag = flags;
   // the latches start cleared on every call (a fill kernel, so the call can be captured)
   HIPCHK(rd::launch_fill_int(flags, 0, 2, m->stream));
-  return adjoint_enqueue(m, a, reinterpret_cast<rd::D4*>(p + o.Wa), reinterpret_cast<double*>(p + o.Sig), W_n, dt,
+  return adjoint_enqueue(m, a, reinterpret_cast<rd::D4*>(p + o.Wa), W_n, dt,
                          scheme, time, lam_np1, lam_n);
 }
 
