@@ -317,9 +317,11 @@ rd_status rd_delaunay_flip(int64_t n_vertices, const double* x, const double* y,
  * returned) or device allocation fails; RD_EUNSUPPORTED when no proposed
  * point can be inserted, or a circumcentre lies more than a quarter period
  * away on a periodic axis (mesh so far returned); RD_EDEVICE. Allocates
- * about 140 bytes of device memory per triangle of capacity (about 100 more
- * with morton = 1), uses a stream
- * of its own and waits for it. */
+ * about 140 bytes of device memory per triangle (about 100 more with
+ * morton = 1), at first for four times the input's triangles (at least 65536),
+ * then for more as the mesh grows, never for more than the capacity; while the
+ * mesh moves to larger arrays both are held. Uses a stream of its own and
+ * waits for it. */
 rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, int64_t max_vertices, double period_x,
                              double period_y, int64_t* n_triangles, int32_t* tri, int64_t max_triangles,
                              double max_radius, double max_ratio, const double* size_grid, int32_t grid_nx,

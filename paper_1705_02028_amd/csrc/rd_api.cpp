@@ -1977,9 +1977,10 @@ RD_API const char* rd_last_error(void) { return g_last_error.c_str(); }
 //
 // A triangulation is checked as a mesh is (indices, counter-clockwise
 // triangles after unwrapping); the neighbour table is built on the host from
-// sorted vertex pairs; the flip rounds and refinement iterations run on the
-// current device (rd_delaunay.hip), the host reading a few counters per
-// round.
+// the triangles around each vertex; the flip rounds and refinement iterations
+// run on the current device (rd_delaunay.hip), which keeps their account
+// (Control): the host enqueues rounds ahead, and an iteration's candidates
+// behind them, and waits once for all.
 
 namespace {
 
@@ -2446,9 +2447,9 @@ RD_API rd_status rd_delaunay_refine(int64_t* n_vertices, double* x, double* y, i
 
 // --------------------------------------------------------- three dimensions --
 //
-// Host side of the tetrahedral path: validation and geometry (face normals,
-// volumes, vertex volumes), the sliced-ELL slot order of the vertex sums,
-// buffers and the launch order of a step (kernels in rd3_kernels.hip).
+// Host side of the tetrahedral path: validation and geometry (volumes, vertex
+// volumes), the tiles (rd3_tiling.h), buffers and the launch order of a step
+// (kernels in rd3_kernels.hip, which form the face normals themselves).
 
 struct rd3_mesh {
   rd3::Dev3 d;
@@ -2475,20 +2476,49 @@ double unwrap3(double d, double period) {
   return d;
 }
 
-template <class T>
-bool dev_get(rd3_mesh* m, T** out, size_t n) {
-  void* q = nullptr;
-  if (hipMalloc(&q, std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) return false;
-  m->bufs.push_back(q);
-  *out = static_cast<T*>(q);
-  return true;
-}
+// The buffers of a mesh, in one allocation, tables from the host first: those
+// of a small mesh go up in one copy (a copy takes 12 us, and there are ten).
+class Buffers3 {
+ public:
+  template <class T, class A>
+  Buffers3& put(T** p, const std::vector<T, A>& h) {
+    return add(p, h.data(), sizeof(T) * h.size());
+  }
+  template <class T>
+  Buffers3& get(T** p, size_t n) {
+    return add(p, nullptr, sizeof(T) * n);
+  }
+  rd_status take(rd3_mesh* m) {
+    void* q = nullptr;
+    if (hipMalloc(&q, bytes_) != hipSuccess) return fail(RD_ENOMEM, "device allocation failed");
+    m->bufs.push_back(q);
+    char* const base = static_cast<char*>(q);
+    std::vector<char> stage(tables_ <= kSlab ? tables_ : 0);
+    for (const Entry& e : list_) {
+      *e.p = base + e.at;
+      if (!e.from || e.size == 0) continue;
+      if (!stage.empty()) std::memcpy(&stage[e.at], e.from, e.size);
+      else HIPCHK(hipMemcpy(base + e.at, e.from, e.size, hipMemcpyHostToDevice));
+    }
+    if (!stage.empty()) HIPCHK(hipMemcpy(base, stage.data(), tables_, hipMemcpyHostToDevice));
+    return RD_OK;
+  }
 
-template <class T>
-bool dev_put(rd3_mesh* m, T** out, const std::vector<T>& h) {
-  return dev_get(m, out, h.size()) &&
-         hipMemcpy(*out, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice) == hipSuccess;
-}
+ private:
+  struct Entry {
+    void** p;
+    const void* from;
+    size_t at, size;
+  };
+  std::vector<Entry> list_;
+  size_t bytes_ = 0, tables_ = 0;
+  Buffers3& add(void* p, const void* from, size_t size) {
+    list_.push_back({static_cast<void**>(p), from, bytes_, size});
+    bytes_ += (std::max<size_t>(size, 1) + 255) & ~size_t(255);
+    if (from) tables_ = bytes_;
+    return *this;
+  }
+};
 
 rd_status rd3_check_step(int scheme, int time) {
   if (scheme < RD_N || scheme > RD_BMIN) return fail(RD_EINVAL, "unknown scheme for three dimensions");
@@ -2573,8 +2603,9 @@ static rd_status rd3_create(const rd3_mesh_desc* desc, rd3_mesh** out) {
   while (target > 64 && nt < (int64_t)target * 2 * ncu) target /= 2;
   rd3::TilePlan3 P;
   m->renumbered = nv > kRenumber3;
-  const std::string why = rd3::build_tiles3(nv, nt, desc->tet, xyz, per, target, m->renumbered,
-                                           nt < 5000 ? 1 : host_threads(), P);
+  // 12^3 cells: 1.8 ms by one worker, 1.0 by four, 1.3 by eight; 8^3: 0.36, 0.28, 0.46
+  rd::Workers pool(nt < 5000 ? 1 : nt < 30000 ? std::min(4, host_threads()) : host_threads());
+  const std::string why = rd3::build_tiles3(nv, nt, desc->tet, xyz, per, target, m->renumbered, pool, P);
   if (!why.empty()) return fail(RD_EINVAL, why);
   d.nv = nv;
   d.ntiles = (int32_t)P.tile.size();
@@ -2591,26 +2622,27 @@ static rd_status rd3_create(const rd3_mesh_desc* desc, rd3_mesh** out) {
     d.half[k] = per[k] > 0.0 ? 0.5 * per[k] : HUGE_VAL;
   }
   std::vector<double> Vi(nv);
-  std::vector<double2> r1(5 * nv, make_double2(0.0, 0.0));
-  for (int64_t v = 0; v < nv; ++v) {
+  rd::UVec<double2> r1(5 * nv);
+  pool.each(nv, [&](int64_t v) {
     const int64_t i = P.inv[v];
     Vi[i] = V[v];
+    for (int k = 0; k < 3; ++k) r1[5 * i + k] = make_double2(0.0, 0.0);
     r1[5 * i + 3] = make_double2(xyz[0][v], xyz[1][v]);
     r1[5 * i + 4] = make_double2(xyz[2][v], 0.0);
-  }
+  });
   rd3::Tile3* dtile;
   uint32_t* dtet;
   int32_t *dlv, *drpos, *djb, *drbeg, *dinv;
   uint16_t* ddeg;
   double* dV;
   const int nb = rd3::cfl_blocks(nv);
-  if (!dev_put(m.get(), &dtile, P.tile) || !dev_put(m.get(), &dtet, P.tet) || !dev_put(m.get(), &dlv, P.lv) ||
-      !dev_put(m.get(), &drpos, P.rpos) || !dev_put(m.get(), &ddeg, P.deg) || !dev_put(m.get(), &djb, P.jb) ||
-      !dev_put(m.get(), &drbeg, P.rbeg) || !dev_put(m.get(), &dinv, P.inv) || !dev_put(m.get(), &dV, Vi) ||
-      !dev_put(m.get(), &d.r1, r1) || !dev_get(m.get(), &d.W, 5 * nv) || !dev_get(m.get(), &d.Ws, 5 * nv) ||
-      !dev_get(m.get(), &d.r2, 5 * nv) || !dev_get(m.get(), &d.rec, 6 * P.lv.size()) || !dev_get(m.get(), &d.dt, 1) ||
-      !dev_get(m.get(), &d.bmin, nb) || !dev_get(m.get(), &d.flag, 1) || !dev_get(m.get(), &m->bad, 1))
-    return fail(RD_ENOMEM, "device allocation failed");
+  Buffers3 buffers;
+  buffers.put(&dtile, P.tile).put(&dtet, P.tet).put(&dlv, P.lv).put(&drpos, P.rpos).put(&ddeg, P.deg).put(&djb, P.jb);
+  buffers.put(&drbeg, P.rbeg).put(&dinv, P.inv).put(&dV, Vi).put(&d.r1, r1);
+  buffers.get(&d.W, 5 * nv).get(&d.Ws, 5 * nv).get(&d.r2, 5 * nv).get(&d.rec, 6 * P.lv.size()).get(&d.dt, 1);
+  buffers.get(&d.bmin, nb).get(&d.flag, 1).get(&m->bad, 1);
+  rd_status st = buffers.take(m.get());
+  if (st != RD_OK) return st;
   HIPCHK(hipStreamCreate(&m->stream));
   HIPCHK(hipMemsetAsync(d.W, 0, sizeof(double) * 5 * nv, m->stream));
   HIPCHK(hipMemsetAsync(d.flag, 0, sizeof(int), m->stream));

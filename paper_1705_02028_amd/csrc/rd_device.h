@@ -17,8 +17,10 @@
 // each into one word, so a triangle pass reads 4 bytes of slot data per
 // triangle instead of three 32-bit slot positions.
 //
-// Algebra of the adjoint's forward recomputation (equal in exact arithmetic to Appendix A's explicit
-// entries): with unit normal n, Roe state (u, v, h, c), w = u n_x + v n_y,
+// Algebra of the FP32 step and of the adjoint's reverse passes (equal in exact
+// arithmetic to Appendix A's explicit entries; the adjoint's stage-1
+// recomputation uses rd_sym.h): with unit normal n, Roe state (u, v, h, c),
+// w = u n_x + v n_y,
 //   E = (1, u, v, h), N = (0, n_x, n_y, w),
 //   g(y) = alpha/c y0 - (gamma-1)(u/c y1 + v/c y2 - y3/c),
 //   d(y) = -w y0 + n_x y1 + n_y y2,
