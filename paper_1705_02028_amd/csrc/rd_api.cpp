@@ -1987,15 +1987,20 @@ namespace {
 // Buffers of one mesh-generation call, freed together: device memory, cut
 // from few allocations, and the host's report, which the device writes.
 // Allocations of up to 1 MiB take 1 us with their release, larger ones 25 (beyond
-// 64 MiB 250), so a small mesh's arrays come from pieces of 1 MiB, a larger one's
-// from 16.
+// 64 MiB 250), so the arrays of a small mesh's flips come from pieces of 1 MiB,
+// others from 16: a refinement's passes take 5 to 9 % longer in many small pieces
+// (12 x 12 points to 3e-2 3.4 ms against 3.1, 32 x 32 to 4e-3 14.9 against 14.2).
 constexpr int64_t kSmallDl = 80000;  // triangles whose arrays take less than 1 MiB each
 struct DlBuffers {
   std::vector<void*> p;
   char* at = nullptr;
   size_t left = 0, piece = size_t(16) << 20;
   rd::dl::Control* control = nullptr;
-  int exact_blocks = 0;  // workgroups the exact pass has scratch for
+  // Workgroups the exact pass has scratch for, and how many times those that a
+  // run had use for a new block gives: a refinement's runs come to have use for
+  // more of them, and a thread that takes a second edge doubles the pass (32 x 32
+  // points to 4e-3 14.2 ms without the spare, 13.6 with it).
+  int exact_blocks = 0, exact_spare = 1;
   // the report, in pinned memory that the device writes (`mapped`, 24 us to
   // take and give back) or in `own`, the control words copied at each wait
   rd::dl::Report own;
@@ -2085,7 +2090,7 @@ rd_status dl_flip_all(rd::dl::Mesh& m, const rd::dl::Refine& r, DlBuffers& b, hi
     if (!more() || !b.read_report(m, r, s)) return fail(RD_EDEVICE, "flip pass failed");
     if (h->c.stuck) return fail(RD_EDEVICE, "a round flipped no edge");
     // scratch for the exact pass: 41 KB a thread, one for every edge seen up to 4096
-    const int want = (int)std::min<int64_t>(64, (h->c.need + 63) / 64);
+    const int want = b.exact_spare * (int)std::min<int64_t>(64 / b.exact_spare, (h->c.need + 63) / 64);
     if (h->c.starved || want > 4 * b.exact_blocks) {
       if (want > b.exact_blocks) {
         if (!b.get(&m.work, rd::dl::exact_scratch(want))) return fail(RD_ENOMEM, "device allocation failed");
@@ -2262,11 +2267,11 @@ static rd_status delaunay_refine(int64_t* n_vertices, double* x, double* y, int6
   };
   DlBuffers b;
   b.piece = size_t(1) << 20;
+  b.exact_spare = 4;
   std::unique_ptr<Arrays> A(new Arrays());
   StreamGuard g;  // declared after the buffers: the stream is drained before they are freed
   auto allocate = [&](Arrays& a, int64_t vs, int64_t ts) {
     a.m.ts = ts;
-    if (ts <= kSmallDl) a.b.piece = size_t(1) << 20;
     rd::dl::Refine& r = a.r;
     a.scan_bytes = rd::dl::scan_tmp_bytes(ts);
     if (!a.b.get(&a.m.x, vs) || !a.b.get(&a.m.y, vs) || !dl_flip_arrays(a.m, a.b, ts) || !a.b.get(&r.prio, ts) ||
