@@ -106,8 +106,10 @@ struct HostGeom {
 };
 
 // Workers for the host side of a mesh of n triangles: small ones are done
-// sooner than the threads would start.
-int workers_for(int64_t nt) { return nt < 30000 ? 1 : host_threads(); }
+// sooner than the threads would start, medium ones before eight would (mesh
+// creation, us, by one / four / eight: 620 / 590 / 700 at 64^2, 1400 / 900 /
+// 1000 at 93^2, 2800 / 1600 / 1500 at 144^2).
+int workers_for(int64_t nt) { return nt < 10000 ? 1 : nt < 30000 ? std::min(4, host_threads()) : host_threads(); }
 
 // The checks of rd_mesh_validate, and (out) the lists. Each worker takes a
 // range of triangles, then a range of vertices, whose corners it finds by
