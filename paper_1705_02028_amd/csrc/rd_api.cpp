@@ -285,7 +285,8 @@ struct rd_mesh {
   double* scratch = nullptr;      // [4 nv] host states pass through it
   int* bad = nullptr;             // first vertex of a host state that is not physical
   unsigned* done = nullptr;       // workgroups of the CFL pass that have finished
-  double* host_dt = nullptr;      // host memory it writes its result to, from the first rd_max_dt on
+  double* host_dt = nullptr;      // host memory it writes its result to, from the second rd_max_dt on
+  bool asked = false;             // rd_max_dt has been called
   double* phi_scratch = nullptr;  // [4 nt] triangle residuals to a host caller
   // adjoint buffers, allocated on first use
   rd::AdjDev adj;
@@ -1258,19 +1259,23 @@ RD_API rd_status rd_max_dt(rd_mesh* m, double cfl, double* dt_out) {
   note_capture(m);
   if (m->form32 || m->captured) HIPCHK(rd::launch_patch_copy(m->p, state_of(m), m->stream));
   // The device writes the result into host memory: a wait then gives it, where
-  // a copy behind the kernels cost 10 us more at 49^2. Up to kDirectPatches
+  // a copy behind the kernels costs 10 us more at 49^2. A mesh's first call takes
+  // the copy, since to allocate that memory costs 30 us. Up to kDirectPatches
   // patches the last workgroup takes the minimum itself (their count goes
   // through one word, which many more would queue for).
-  if (!m->host_dt) {
+  if (m->asked && !m->host_dt) {
     void* q = nullptr;
     HIPCHK(hipHostMalloc(&q, sizeof(double), hipHostMallocDefault));
     m->host_dt = static_cast<double*>(q);
   }
+  m->asked = true;
+  double* const to = m->host_dt ? m->host_dt : m->scratch;
   const bool one = m->p.npatch <= kDirectPatches;
-  HIPCHK(rd::launch_patch_cfl(m->p, cfl, one ? m->done : nullptr, m->host_dt, m->stream));
-  if (!one) HIPCHK(rd::launch_patch_dt(m->p, cfl, m->stream, m->host_dt));
+  HIPCHK(rd::launch_patch_cfl(m->p, cfl, one ? m->done : nullptr, to, m->stream));
+  if (!one) HIPCHK(rd::launch_patch_dt(m->p, cfl, m->stream, to));
+  if (!m->host_dt) HIPCHK(hipMemcpyAsync(dt_out, to, sizeof(double), hipMemcpyDeviceToHost, m->stream));
   HIPCHK(hipStreamSynchronize(m->stream));
-  *dt_out = *const_cast<volatile double*>(m->host_dt);
+  if (m->host_dt) *dt_out = *const_cast<volatile double*>(m->host_dt);
   return RD_OK;
 }
 

@@ -80,3 +80,22 @@ def test_max_dt_after_replays(orc, rd, prec):
         g.step_cfl(1, 0.3, rd.B, rd.RK2, 1 - prec)
         assert g.max_dt(0.3) == pytest.approx(om.max_dt(g.get_state(), 0.3), rel=1e-14, abs=0.0), k
     g.close()
+
+
+@pytest.mark.parametrize("N", [9, 350])  # the last workgroup's minimum; a kernel of its own above 512 patches
+def test_every_call_the_same(rd, N):
+    """The first call of a mesh brings the result back by a copy, later ones
+    read what the device wrote to host memory."""
+    m = I.split_square(N, jitter=0.2, seed=7)
+    W = I.random_smooth_state(m, seed=8)
+    g = rd.Mesh(m)
+    g.set_state(W)
+    dt = [g.max_dt(0.4) for _ in range(4)]
+    g.step_cfl(1, 0.4, rd.B, rd.RK2)
+    after = [g.max_dt(0.4) for _ in range(2)]
+    g.set_state(g.get_state())
+    h = rd.Mesh(m)
+    h.set_state(g.get_state())
+    assert dt == dt[:1] * 4 and after == [h.max_dt(0.4)] * 2 and after[0] != dt[0]
+    g.close()
+    h.close()
