@@ -60,8 +60,9 @@ constexpr int32_t kMaxDegree = 1023;
 // on the device (launch_check_state), whose two launches and copy take 16 us
 // whatever the size (rd_set_state, us, host / device: 20 / 36 at 64 vertices,
 // 39 / 41 at 6400, 48 / 44 at 10000; rd3_set_state: 22 / 36 at 125, 40 / 51 at
-// 8000, 52 / 56 at 13824, 72 / 65 at 21952).
-constexpr int64_t kHostCheck2 = 8192, kHostCheck3 = 16384;
+// 8000, 52 / 56 at 13824, 72 / 65 at 21952, but with an RK2 step and the state
+// out after it 164 / 192 at 19683 and 233 / 260 at 27000, 388 / 385 at 54872).
+constexpr int64_t kHostCheck2 = 8192, kHostCheck3 = 32768;
 
 // First vertex of a state [2 + momenta][nv] that is not physical, nv if none:
 // the check of launch_check_state.
@@ -2565,8 +2566,10 @@ rd_status rd3_stages(rd3_mesh* m, double cfl, int scheme, int time, hipEvent_t* 
 // then goes out as it stands, without a launch to reorder it first
 // (rd3_get_state, us, without / with: 11 / 23 at 512 vertices, 36 / 49 at
 // 13824), and it is in the caches in any order (a step with its state set: 71 /
-// 71 at 2744 vertices, 80 / 78 at 8000, 88 / 87 at 13824).
-constexpr int64_t kRenumber3 = 16384;
+// 71 at 2744 vertices, 80 / 78 at 8000, 88 / 87 at 13824; state in, an Euler step,
+// state out 142 / 168 at 19683 and 195 / 233 at 27000; ten RK2 steps 608 / 599 and
+// 745 / 732, in random order 622 / 608 and 758 / 732, 901 / 858 at 39304).
+constexpr int64_t kRenumber3 = 32768;
 
 static rd_status rd3_create(const rd3_mesh_desc* desc, rd3_mesh** out) {
   if (!desc || !out) return fail(RD_EINVAL, "null argument");

@@ -38,11 +38,11 @@ def test_host_state_then_another_stream(N, prec):
     g.close()
 
 
-@pytest.mark.parametrize("dim,N", [(2, 89), (2, 90), (3, 25), (3, 26)])
+@pytest.mark.parametrize("dim,N", [(2, 89), (2, 90), (3, 25), (3, 32), (3, 33)])
 @pytest.mark.parametrize("prec", [0, 1])
 def test_either_check_names_the_first_vertex(dim, N, prec):
     """Small host states are checked on the host, those of more than 8192
-    vertices (16384 in three dimensions) on the device: the same vertex, and
+    vertices (32768 in three dimensions) on the device: the same vertex, and
     the state that was there stays."""
     from paper_1705_02028_amd import rd
     if dim == 2:
